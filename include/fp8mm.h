@@ -220,7 +220,7 @@ int fp8_quantize_rows(const void* x, int64_t rows, int64_t cols, int in_dtype, i
  * and activation gradients all feed GEMMs, and the backward pass consumes them transposed):
  *   q_out   device, rows x cols bytes, q[r][c] = FP8(fl32(x[r][c] * scale)); may be NULL
  *   qt_out  device, cols x rows bytes, qt[c][r] = q[r][c]
- * Any shape; rows and cols multiples of 16 with 16-byte aligned pointers take the tiled kernel.
+ * Any shape and alignment; whole lines are written where rows is a multiple of 128.
  */
 int fp8_quantize_transpose(const void* x, int64_t rows, int64_t cols, int in_dtype, int fmt,
                            const float* scale_dev, uint8_t* q_out, uint8_t* qt_out, void* stream);

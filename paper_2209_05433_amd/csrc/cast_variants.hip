@@ -15,6 +15,8 @@
 // (fp8_encode.hpp).
 #include "cast_common.hpp"
 
+#include <type_traits>
+
 namespace fp8mm {
 namespace {
 
@@ -164,12 +166,46 @@ __global__ __launch_bounds__(kThreads) void quantize_rows_kernel(const void* __r
 // the diagonal walk and the 256-column tile, 18432 x 16384 5.1 -> 5.4, 12288 x 49152 4.8 -> 5.0;
 // with q^T written to the places of q (no scatter) the same
 // kernel reaches 5.4, the plain cast 5.9 (cold).
+//
+// Any shape and alignment: vectors are loaded and stored at whatever address they have, and tiles that
+// reach over an edge do their tests in a second copy of the code.  (One element per lane, with q^T
+// scattered byte by byte, took 5000 x 6144 in 304 us; this takes 27.)
 // ------------------------------------------------------------------------------------------
 constexpr int TT = 128;                       // tile rows; also the tile columns of the fp32 form
 constexpr int QT_PITCH = TT + 16;             // LDS row pitch of the q^T tile (16-byte pad spreads the rows over the banks)
 
 typedef int v2i __attribute__((ext_vector_type(2)));
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
+
+// Vectors at any address: the target's global loads and stores take them as one instruction.
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+typedef u32x2 u32x2_any __attribute__((aligned(1)));
+typedef unsigned u32_any __attribute__((aligned(1)));
+
+// A vector without its first k elements (0 <= k < per_vec): the rest moves to the front.
+template <int DT>
+__device__ __forceinline__ u32x4 drop_elements(u32x4 v, int k)
+{
+    const int words = DT == FP8_F32 ? k : k >> 1;
+    if (words & 2) v = (u32x4){v.z, v.w, v.w, v.w};
+    if (words & 1) v = (u32x4){v.y, v.z, v.w, v.w};
+    if (DT == FP8_BF16 && (k & 1))
+        v = (u32x4){(v.x >> 16) | (v.y << 16), (v.y >> 16) | (v.z << 16), (v.z >> 16) | (v.w << 16), v.w >> 16};
+    return v;
+}
+
+// The `count` (1 .. per_vec - 1) elements of a row too short for a vector, one by one.
+template <int DT>
+__device__ __forceinline__ u32x4 load_elements(const void* src, int count)
+{
+    u32x4 v = {0u, 0u, 0u, 0u};
+    for (int e = 0; e < count; ++e) {
+        const unsigned x = DT == FP8_F32 ? ((const unsigned*)src)[e] : (unsigned)((const unsigned short*)src)[e] << (16 * (e & 1));
+        const int d = DT == FP8_F32 ? e : e >> 1;
+        v = (u32x4){v.x | (d == 0 ? x : 0u), v.y | (d == 1 ? x : 0u), v.z | (d == 2 ? x : 0u), v.w | (d == 3 ? x : 0u)};
+    }
+    return v;
+}
 
 template <int DT> struct TransposeTile { static constexpr int cols = DT == FP8_BF16 ? 256 : 128; };
 
@@ -196,36 +232,66 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const void
     const int tid = threadIdx.x;
     const int lr = tid / LPR, lc = (tid % LPR) * EPL;    // lane's row within a pass, first column
 
-    // load everything first (PASSES 16-byte loads in flight per lane), then convert
-    u32x4 v[PASSES];
+    // load everything first (PASSES 16-byte loads in flight per lane), then convert; rows beyond the
+    // edge are read from the last one and not stored.  The lane in which the row ends reads the last
+    // vector of the row and drops what belongs to the lane before it.
+    const int64_t c = c0 + lc;
+    const int left = cols - c < EPL ? (int)(cols - c) : EPL;          // elements of the lane that exist (<= 0: none)
+    const int below = rows - 1 - (r0 + lr) < TT ? (int)(rows - 1 - (r0 + lr)) : TT;      // rows of x under the lane's first one
+    // WHOLE: the tile lies inside the matrix, no tests (with them every tile was 1 % slower)
+    auto convert_tile = [&](auto whole_tag) {
+        constexpr bool WHOLE = decltype(whole_tag)::value;
+        const char* first = (const char*)x + (size_t)(r0 + lr) * (size_t)cols * Elem<DT>::size;
+        const int64_t pitch = cols * Elem<DT>::size;
+        auto row_at = [&](int p, int64_t col) {
+            return first + (WHOLE || p * RPP < below ? p * RPP : below) * pitch + col * Elem<DT>::size;
+        };
+        u32x4 v[PASSES];
+        if (WHOLE) {
 #pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-        const int64_t r = r0 + p * RPP + lr, c = c0 + lc;
-        v[p] = (u32x4){0u, 0u, 0u, 0u};
-        if (r < rows && c < cols)
-            v[p] = __builtin_nontemporal_load((const u32x4*)((const char*)x + ((size_t)r * (size_t)cols + (size_t)c) * Elem<DT>::size));
-    }
-#pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-        const int tr = p * RPP + lr;
-        unsigned b0, b1 = 0;
-        if (DT == FP8_BF16) {
-            b0 = encode4<FMT>(as_f32(v[p].x << 16) * s, as_f32(v[p].x & 0xffff0000u) * s,
-                              as_f32(v[p].y << 16) * s, as_f32(v[p].y & 0xffff0000u) * s);
-            b1 = encode4<FMT>(as_f32(v[p].z << 16) * s, as_f32(v[p].z & 0xffff0000u) * s,
-                              as_f32(v[p].w << 16) * s, as_f32(v[p].w & 0xffff0000u) * s);
-            *LDS_PTR(v2i, tile + tr * PITCH + lc) = (v2i){(int)b0, (int)b1};
+            for (int p = 0; p < PASSES; ++p) v[p] = __builtin_nontemporal_load((const u32x4_any*)row_at(p, c));
         } else {
-            b0 = encode4<FMT>(as_f32(v[p].x) * s, as_f32(v[p].y) * s, as_f32(v[p].z) * s, as_f32(v[p].w) * s);
-            *LDS_PTR(unsigned, tile + tr * PITCH + lc) = b0;
+#pragma unroll
+            for (int p = 0; p < PASSES; ++p) v[p] = (u32x4){0u, 0u, 0u, 0u};
+            if (left > 0 && cols >= EPL) {
+                const int64_t from = left == EPL ? c : cols - EPL;
+#pragma unroll
+                for (int p = 0; p < PASSES; ++p) v[p] = __builtin_nontemporal_load((const u32x4_any*)row_at(p, from));
+                if (left < EPL) {
+#pragma unroll
+                    for (int p = 0; p < PASSES; ++p) v[p] = drop_elements<DT>(v[p], EPL - left);
+                }
+            } else if (left > 0) {
+#pragma unroll
+                for (int p = 0; p < PASSES; ++p) v[p] = load_elements<DT>(row_at(p, c), left);
+            }
         }
-        // q straight from the registers: the lanes of one tile row cover its bytes
-        const int64_t r = r0 + tr, c = c0 + lc;
-        if (q && r < rows && c < cols) {
-            uint8_t* dst = q + (size_t)r * (size_t)cols + (size_t)c;
-            if (DT == FP8_BF16) *(u32x2*)dst = (u32x2){b0, b1}; else *(unsigned*)dst = b0;
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int tr = p * RPP + lr;
+            unsigned b0, b1 = 0;
+            if (DT == FP8_BF16) {
+                b0 = encode4<FMT>(as_f32(v[p].x << 16) * s, as_f32(v[p].x & 0xffff0000u) * s,
+                                  as_f32(v[p].y << 16) * s, as_f32(v[p].y & 0xffff0000u) * s);
+                b1 = encode4<FMT>(as_f32(v[p].z << 16) * s, as_f32(v[p].z & 0xffff0000u) * s,
+                                  as_f32(v[p].w << 16) * s, as_f32(v[p].w & 0xffff0000u) * s);
+                *LDS_PTR(v2i, tile + tr * PITCH + lc) = (v2i){(int)b0, (int)b1};
+            } else {
+                b0 = encode4<FMT>(as_f32(v[p].x) * s, as_f32(v[p].y) * s, as_f32(v[p].z) * s, as_f32(v[p].w) * s);
+                *LDS_PTR(unsigned, tile + tr * PITCH + lc) = b0;
+            }
+            // q straight from the registers: the lanes of one tile row cover its bytes
+            if (!q) continue;
+            uint8_t* dst = q + (size_t)(r0 + tr) * (size_t)cols + (size_t)c;
+            if (WHOLE || (p * RPP <= below && left == EPL)) {
+                if (DT == FP8_BF16) *(u32x2_any*)dst = (u32x2){b0, b1}; else *(u32_any*)dst = b0;
+            } else if (p * RPP <= below) {
+                for (int e = 0; e < left; ++e) dst[e] = (uint8_t)((e < 4 ? b0 : b1) >> (8 * (e & 3)));
+            }
         }
-    }
+    };
+    const bool whole = r0 + TT <= rows && c0 + TC <= cols;
+    if (whole) convert_tile(std::true_type{}); else convert_tile(std::false_type{});
     __syncthreads();
     // q^T: the transposing reads hand a lane 16 consecutive tile rows of one tile column = 16 bytes of
     // a row of q^T; a wave instruction covers 16 columns x 64 rows, wave w owns the columns
@@ -259,23 +325,12 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const void
     for (int p = 0; p < TC / 32; ++p) {
         const int tc = p * 32 + (tid >> 3), trc = (tid & 7) * 16;         // row of the q^T tile, first byte in it
         const int64_t orow = c0 + tc, ocol = r0 + trc;                    // position in q^T (cols x rows)
-        if (orow < cols && ocol < rows)
-            *(u32x4*)(qt + (size_t)orow * (size_t)rows + (size_t)ocol) = *LDS_PTR(u32x4, tile + tc * QT_PITCH + trc);
-    }
-}
-
-// Any shape and alignment: one element per lane, both outputs written directly.
-template <int DT, int FMT>
-__global__ __launch_bounds__(kThreads) void quantize_transpose_scalar_kernel(const void* __restrict__ x, int64_t rows, int64_t cols,
-                                                                            const float* __restrict__ scale_dev,
-                                                                            uint8_t* __restrict__ q, uint8_t* __restrict__ qt)
-{
-    const float s = *scale_dev;
-    const size_t n = (size_t)rows * (size_t)cols, stride = (size_t)gridDim.x * kThreads;
-    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) {
-        const uint8_t b = (uint8_t)encode_bits<FMT>(load_scalar<DT>(x, i) * s);
-        if (q) q[i] = b;
-        qt[(i % (size_t)cols) * (size_t)rows + i / (size_t)cols] = b;
+        uint8_t* dst = qt + (size_t)orow * (size_t)rows + (size_t)ocol;
+        if (whole || (orow < cols && ocol + 16 <= rows)) {
+            *(u32x4_any*)dst = *LDS_PTR(u32x4, tile + tc * QT_PITCH + trc);
+        } else if (orow < cols) {
+            for (int e = 0; e < rows - ocol; ++e) dst[e] = *LDS_PTR(uint8_t, tile + tc * QT_PITCH + trc + e);
+        }
     }
 }
 
@@ -513,16 +568,11 @@ int launch_quantize_transpose(const void* x, int64_t rows, int64_t cols, int in_
     if (rows == 0 || cols == 0) return FP8_OK;
     const int tcols = in_dtype == FP8_BF16 ? TransposeTile<FP8_BF16>::cols : TransposeTile<FP8_F32>::cols;
     const int64_t tiles_r = (rows + TT - 1) / TT, tiles_c = (cols + tcols - 1) / tcols;
-    const bool vec = aligned16(x) && aligned16(qt_out) && (!q_out || aligned16(q_out)) && rows % 16 == 0 && cols % 16 == 0 &&
-                     tiles_r * tiles_c < (1ll << 31);
-    if (vec) {
-        const dim3 grid((unsigned)(tiles_r * tiles_c));
-        const bool diagonal = rows >= 4096 && (rows & (rows - 1)) == 0;      // see "Tile order" at the kernel
-        FP8MM_DISPATCH_DT_FMT(quantize_transpose_kernel, grid, x, rows, cols, scale_dev, q_out, qt_out, (int)tiles_r, (int)tiles_c, diagonal);
-    } else {
-        const dim3 grid(grid_for((size_t)rows * (size_t)cols, 4096));
-        FP8MM_DISPATCH_DT_FMT(quantize_transpose_scalar_kernel, grid, x, rows, cols, scale_dev, q_out, qt_out);
-    }
+    if (tiles_r * tiles_c >= (1ll << 31))
+        return fail(FP8_ERR_UNSUPPORTED, "quantize_transpose: %lld x %lld tiles exceed the grid limit", (long long)tiles_r, (long long)tiles_c);
+    const dim3 grid((unsigned)(tiles_r * tiles_c));
+    const bool diagonal = rows >= 4096 && (rows & (rows - 1)) == 0;      // see "Tile order" at the kernel
+    FP8MM_DISPATCH_DT_FMT(quantize_transpose_kernel, grid, x, rows, cols, scale_dev, q_out, qt_out, (int)tiles_r, (int)tiles_c, diagonal);
     return check_launch("quantize_transpose");
 }
 
