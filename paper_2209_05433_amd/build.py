@@ -1,5 +1,5 @@
 """Builds libfp8mm.so (the HIP kernels and their C ABI) and libfp8probes.so (the measurement probes
-of bench.py) for gfx950 with hipcc, in-tree.
+of bench.py) for gfx950 with hipcc, and the Python binding _native.so with g++, in-tree.
 
 Every translation unit is compiled to an object of its own, in parallel; the tiled GEMM source is
 compiled eight times, once per pair of operand storage orders (-DFP8MM_LAYOUT=0..3) and
@@ -17,6 +17,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libfp8mm.so")
 PROBES_LIB = os.path.join(PKG, "libfp8probes.so")     # measurement probes for bench.py, not part of the product library
+BINDING = os.path.join(PKG, "_native.so")              # the Python binding (host code on torch's C++ interface)
 
 # (source, extra defines, object name)
 UNITS = [("gemm_tiled.hip", ["-DFP8MM_LAYOUT=%d" % k, "-DFP8MM_ACC=%d" % a], "gemm_tiled_l%d_a%d.o" % (k, a))
@@ -53,6 +54,20 @@ def _run(cmd, verbose):
         print(out)
 
 
+def binding_command(out: str = BINDING) -> list:
+    """The compiler command of the Python binding: plain host C++, linked to libfp8mm.so beside it and to torch."""
+    import sysconfig
+
+    import torch
+    root = os.path.join(os.path.dirname(torch.__file__))
+    inc = [os.path.join(ROOT, "include"), os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(hipcc()))), "include"), sysconfig.get_paths()["include"]]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, *[x for i in inc for x in ("-isystem", i)],
+            os.path.join(CSRC, "native_binding.cpp"), "-o", out, "-L", PKG, "-lfp8mm", "-L", os.path.join(root, "lib"),
+            "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + os.path.join(root, "lib")]
+
+
 def build(verbose: bool = False) -> str:
     """Compile every source every time it is called; returns the path of the library."""
     os.makedirs(OBJ, exist_ok=True)
@@ -64,6 +79,7 @@ def build(verbose: bool = False) -> str:
         list(ex.map(lambda c: _run(c, verbose), jobs))
     _run([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB,
           *[os.path.join(OBJ, obj) for _, _, obj in UNITS]], verbose)
+    _run(binding_command(), verbose)
     return LIB
 
 
