@@ -412,7 +412,10 @@ int fp8_scaled_gemm(const void* a, const void* b, int in_dtype, int transA, int 
  * FP8_PLAN_ELEMENTWISE_STORES where the rows of the output do not start on 16-byte boundaries, and
  * with FP8_PLAN_PERSISTENT where the 256 x 128 kernel runs in its persistent form (answered for
  * per-tensor factors, an fp32 output and the default accumulation mode; with a bf16 output or
- * FP8_GEMM_MFMA8 the form is used over a narrower range of K, see FP8_KNOB_PERSIST).
+ * FP8_GEMM_MFMA8 the form is used over a narrower range of K, see FP8_KNOB_PERSIST).  Problems of few
+ * tiles run on a kernel of smaller ones (32 x 32 to 64 x 64, the waves of a workgroup sharing K; the same
+ * instructions, accumulation mode and bound); the answer is then still the one above that describes
+ * their shape and alignment.
  * A negative value is minus an fp8_status_t (bad arguments).  Section 2 fixes the arithmetic,
  * not the kernel: every plan computes the same product within the stated bounds.
  */

@@ -22,7 +22,9 @@ BINDING = os.path.join(PKG, "_native.so")              # the Python binding (hos
 # (source, extra defines, object name)
 UNITS = [("gemm_tiled.hip", ["-DFP8MM_LAYOUT=%d" % k, "-DFP8MM_ACC=%d" % a], "gemm_tiled_l%d_a%d.o" % (k, a))
          for k in range(4) for a in range(2)] + \
-        [("gemm_dispatch.hip", [], "gemm_dispatch.o"), ("gemm_splitk.hip", [], "gemm_splitk.o"), ("gemm_mfma_any.hip", [], "gemm_mfma_any.o"),
+        [("gemm_mfma_any.hip", ["-DFP8MM_LAYOUT=%d" % k], "gemm_mfma_any_l%d.o" % k) for k in range(4)] + \
+        [("gemm_small.hip", ["-DFP8MM_LAYOUT=%d" % k], "gemm_small_l%d.o" % k) for k in range(4)] + \
+        [("gemm_dispatch.hip", [], "gemm_dispatch.o"), ("gemm_splitk.hip", [], "gemm_splitk.o"),
          ("cast_kernels.hip", [], "cast_kernels.o"),
          ("cast_variants.hip", [], "cast_variants.o"),
          ("api.hip", [], "api.o")]

@@ -79,11 +79,27 @@ int launch_gemm(const GemmArgs& g);
 bool mfma_any_takes(const GemmArgs& g);
 bool mfma_any_wide(const GemmArgs& g);
 int launch_mfma_any(const GemmArgs& g);
+#define FP8MM_ANY_NAME_(l) launch_mfma_any_l##l
+#define FP8MM_ANY_NAME(l) FP8MM_ANY_NAME_(l)
+int FP8MM_ANY_NAME(0)(const GemmArgs& g, bool wide);         // one translation unit per pair of storage orders
+int FP8MM_ANY_NAME(1)(const GemmArgs& g, bool wide);
+int FP8MM_ANY_NAME(2)(const GemmArgs& g, bool wide);
+int FP8MM_ANY_NAME(3)(const GemmArgs& g, bool wide);
 
 // The tiled kernel instance for g's storage orders and accumulation mode, with g.tile_n, g.splits,
 // g.pairs_per_split and g.ep.ragged_n as given (the caller has checked that the tiled kernel takes
 // the problem).
 int launch_tiled(const GemmArgs& g);
+
+// The kernel for small problems (gemm_small.hip), one translation unit per pair of storage orders;
+// its forms are named by their output tile.
+enum { SMALL_NONE = -1, SMALL_32x32 = 0, SMALL_32x64 = 1, SMALL_64x64 = 2 };
+#define FP8MM_SMALL_NAME_(l) launch_small_l##l
+#define FP8MM_SMALL_NAME(l) FP8MM_SMALL_NAME_(l)
+int FP8MM_SMALL_NAME(0)(const GemmArgs& g, int form);
+int FP8MM_SMALL_NAME(1)(const GemmArgs& g, int form);
+int FP8MM_SMALL_NAME(2)(const GemmArgs& g, int form);
+int FP8MM_SMALL_NAME(3)(const GemmArgs& g, int form);
 
 // Split-K (gemm_splitk.hip): K cut into `splits` slices of pairs_per_split stage pairs.
 constexpr int kMaxSplitK = 64;
@@ -100,7 +116,8 @@ int fill_gemm_args(const char* who, GemmArgs& g, const uint8_t* A, int fmtA, int
 
 // The dispatcher's decision for a problem with M, N, K > 0 (what launch_gemm acts on).
 enum { GEMM_GENERIC = 1, GEMM_TILED_256 = 2, GEMM_TILED_128 = 3, GEMM_MFMA_ANY = 4, GEMM_TILED_MIXED = 5 };
-struct GemmPlan { int kernel; bool elementwise_stores; bool persistent; int wide_cols; };
+// small: the form of the small-tile kernel that takes the problem instead (SMALL_*).
+struct GemmPlan { int kernel; bool elementwise_stores; bool persistent; int wide_cols; int small; };
 GemmPlan plan_gemm(const GemmArgs& g);
 
 // ---- small device helpers used by the kernels -------------------------------------------------

@@ -9,6 +9,7 @@
 #include "gemm_common.hpp"
 
 #include <algorithm>
+#include <cmath>
 
 namespace fp8mm {
 namespace {
@@ -117,11 +118,55 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 }  // namespace
 
+namespace {
+
+// Microseconds for one tile of the tiled kernel, S stages of 64 along K (fitted to one-round and
+// three-round problems, 4096 x 4096 and 4096 x 6144 over K = 512 .. 8192).
+struct TileTimes { double wide, narrow; };
+TileTimes tile_times(int acc, double S)
+{
+    return acc == ACC_FP8 ? TileTimes{0.65 * S + 8.6, 0.37 * S + 4.7} : TileTimes{1.30 * S + 9.4, 0.70 * S + 5.8};
+}
+
+// The form of the small-tile kernel (gemm_small.hip) that beats the kernel the problem would otherwise
+// take, or SMALL_NONE.  Times in microseconds, fitted to 25 shapes from 8 x 1104 x 768 to 2048 x 2048 x
+// 2048 in all storage orders (within 20 %): a launch and the ends of a workgroup, then per workgroup and
+// compute unit a time that grows with K.  A workgroup alone on its unit takes as long as one of a full
+// unit in the 4-wave forms; the 8-wave form overlaps two, and pays for 32-byte rows of an operand
+// that is not contiguous along K.  The tiled kernel: rounds of 256 workgroups.  The any-shape kernel:
+// 0.03 us per K for a round, 0.7 PFLOP/s at best where the small tiles are in question.
+int choose_small(const GemmArgs& g, bool tiled)
+{
+    const double M = (double)g.M, N = (double)g.N, K = (double)g.K;
+    auto units = [&](double tm, double tn) { return std::ceil(M / tm) * std::ceil(N / tn) / 256.0; };
+    const double u64 = units(64, 64);
+    if (u64 > 32) return SMALL_NONE;
+    double other;
+    if (tiled) {
+        const TileTimes t = tile_times(g.acc, 2.0 * std::ceil(K / (2 * TILE_K)));
+        other = std::min(std::ceil(units(256, 256)) * t.wide, std::ceil(units(256, 128)) * t.narrow);
+        if (g.acc == ACC_FP8) other += 1.5;                  // (the fit is that much too short below S = 16)
+    } else {
+        other = 5.0 + std::max(0.03 * K, 2.0 * M * N * K / 0.7e9);
+    }
+    const bool lines = !g.transA && g.transB;                // both operands contiguous along K
+    const double t32 = 3.4 + std::max(0.001 * K, units(32, 32) * (0.3 + (lines ? 0.0014 : 0.0025) * K));
+    const double t3264 = 4.0 + std::max(1.0, units(32, 64)) * (0.6 + 0.0018 * K);
+    const double t64 = 4.0 + std::max(1.0, u64) * (1.2 + 0.0026 * K);
+    const double best = std::min(t32, std::min(t3264, t64));
+    if (best >= 0.95 * other) return SMALL_NONE;
+    return best == t32 ? SMALL_32x32 : best == t3264 ? SMALL_32x64 : SMALL_64x64;
+}
+
+}  // namespace
+
 // Which kernel a (non-empty, K > 0) problem takes.
 GemmPlan plan_gemm(const GemmArgs& g)
 {
     const int64_t M = g.M, N = g.N, K = g.K;
-    GemmPlan plan{!force_generic() && mfma_any_takes(g) ? GEMM_MFMA_ANY : GEMM_GENERIC, false, false, 0};
+    GemmPlan plan{!force_generic() && mfma_any_takes(g) ? GEMM_MFMA_ANY : GEMM_GENERIC, false, false, 0, SMALL_NONE};
+    // a knob that asks for another form of the kernels keeps the small one out
+    const bool small_allowed = g.splits <= 1 && !knob(FP8_KNOB_TILE_N) && !knob(FP8_KNOB_GEMM_KERNEL) && !knob(FP8_KNOB_MIXED) && !knob(FP8_KNOB_PERSIST);
     const uint64_t ldmax = (uint64_t)(M > N ? (M > K ? M : K) : (N > K ? N : K));
     const bool fits32 = 256 * ldmax < (1ull << 32) && M < (1ll << 31) - TILE_M && N < (1ll << 31) - TILE_N &&
                         K < (1ll << 31) &&
@@ -138,6 +183,7 @@ GemmPlan plan_gemm(const GemmArgs& g)
     const bool c_lines = N % 16 == 0 && aligned16(g.C) && (!g.ep.b_per_col || aligned16(g.ep.sB_dev));
     const bool fast = !force_generic() && !force_mfma_any() && aligned16(g.A) && aligned16(g.B) && fits32 && K % 16 == 0 &&
                       (g.transB || N % 16 == 0) && (!g.transA || M % 16 == 0);
+    if (small_allowed) plan.small = choose_small(g, fast);
     if (!fast) return plan;
     // Tile width.  One workgroup per compute unit (256 of them) runs at a time.  The 256 x 128
     // tile sustains about 0.88 of the rate of the 256 x 256 tile (measured on 8192 x 49152 x
@@ -155,9 +201,7 @@ GemmPlan plan_gemm(const GemmArgs& g)
     // Both widths in one launch (gemm_mixed_kernel): the first c tile columns of 256, the rest of N in
     // tiles of 128.  Chosen where a model of the run time says it beats the better single width by 3 %:
     // workgroups are handed to the 256 compute units in order, the wide ones first; a tile takes
-    // a S + b microseconds, S = stages of 64 along K (fitted to one-round and three-round problems,
-    // 4096 x 4096 and 4096 x 6144 over K = 512 .. 8192: fp16 mode 1.30 S + 9.4 wide, 0.70 S + 5.8
-    // narrow; FP8 mode 0.65 S + 8.6 and 0.37 S + 4.7), and the change of width costs 3 + 32 / S
+    // what tile_times() says, and the change of width costs 3 + 32 / S
     // microseconds (measured: the mixed launch is that much slower than its two parts).  With these
     // figures it pays for long K (4096 x 6144 x 8192: 4 % in the fp16 mode, 7 % in the FP8 mode) and
     // not for short K, where the narrow tile is nearly as efficient as the wide one.  Problems of
@@ -165,10 +209,9 @@ GemmPlan plan_gemm(const GemmArgs& g)
     // Knob FP8_KNOB_MIXED: 0 = by the model, 1 = never, 2 = wherever it is possible.
     const int mk = knob(FP8_KNOB_MIXED);
     const int64_t tiles_m = (M + TILE_M - 1) / TILE_M, wide_cols_all = (N + TILE_N - 1) / TILE_N;
-    if (!tn && mk != 1 && g.splits <= 1 && N > TILE_N && tiles_m * wide_cols_all <= 64 * 256) {
+    if (!tn && mk != 1 && plan.small == SMALL_NONE && g.splits <= 1 && N > TILE_N && tiles_m * wide_cols_all <= 64 * 256) {
         const double S = 2.0 * (double)((K + 2 * TILE_K - 1) / (2 * TILE_K));
-        const double tw = g.acc == ACC_FP8 ? 0.65 * S + 8.6 : 1.30 * S + 9.4;
-        const double tnar = g.acc == ACC_FP8 ? 0.37 * S + 4.7 : 0.70 * S + 5.8;
+        const double tw = tile_times(g.acc, S).wide, tnar = tile_times(g.acc, S).narrow;
         const double change = 3.0 + 32.0 / S;
         // time until the last of Tw wide and then Tn narrow tiles ends on 256 units
         auto makespan = [&](int64_t Tw, int64_t Tn) {
@@ -217,6 +260,35 @@ GemmPlan plan_gemm(const GemmArgs& g)
     return plan;
 }
 
+// ---- the matrix-core kernel for any shape (gemm_mfma_any.hip) ------------------------------------
+static int64_t tile_count(const GemmArgs& g, int64_t edge) { return ((g.M + edge - 1) / edge) * ((g.N + edge - 1) / edge); }
+
+bool mfma_any_takes(const GemmArgs& g)
+{
+    return g.M > 0 && g.N > 0 && g.K > 0 && tile_count(g, 128) <= 0x7fffffffll;
+}
+
+// The wide form where its 256 x 256 tiles fill the rounds of one workgroup per compute unit to
+// 80 % at least and K is long enough for the two-stage pipeline to pay; FP8_KNOB_TILE_N forces
+// either form (128 / 256).
+bool mfma_any_wide(const GemmArgs& g)
+{
+    const int forced = knob(FP8_KNOB_TILE_N);
+    const int64_t tiles = tile_count(g, 256), units = 256;
+    const int64_t rounds = (tiles + units - 1) / units;
+    // 32-bit offsets within a tile's stage: 255 rows of K bytes, or 63 K-rows of M / N bytes
+    if (g.K >= (1 << 24) || g.M >= (1 << 26) || g.N >= (1 << 26)) return false;
+    if (forced) return forced == 256;
+    return g.K >= 512 && 5 * tiles >= 4 * rounds * units;
+}
+
+int launch_mfma_any(const GemmArgs& g)
+{
+    typedef int (*any_fn)(const GemmArgs&, bool);
+    static const any_fn table[4] = {FP8MM_ANY_NAME(0), FP8MM_ANY_NAME(1), FP8MM_ANY_NAME(2), FP8MM_ANY_NAME(3)};
+    return table[(g.transA ? 2 : 0) + (g.transB ? 1 : 0)](g, mfma_any_wide(g));
+}
+
 int launch_tiled(const GemmArgs& g)
 {
     typedef int (*tiled_fn)(const GemmArgs&);
@@ -240,6 +312,13 @@ int launch_gemm(const GemmArgs& g)
         return check_launch("gemm (K = 0 fill)");
     }
     const GemmPlan plan = plan_gemm(g);
+    if (plan.small != SMALL_NONE) {
+        typedef int (*small_fn)(const GemmArgs&, int);
+        static const small_fn table[4] = {FP8MM_SMALL_NAME(0), FP8MM_SMALL_NAME(1), FP8MM_SMALL_NAME(2), FP8MM_SMALL_NAME(3)};
+        GemmArgs gs = g;
+        if (plan.kernel == GEMM_MFMA_ANY) gs.acc = ACC_F16;  // as the any-shape kernel computes these problems
+        return table[(g.transA ? 2 : 0) + (g.transB ? 1 : 0)](gs, plan.small);
+    }
     if (plan.kernel == GEMM_MFMA_ANY) return launch_mfma_any(g);
     if (plan.kernel != GEMM_GENERIC) {
         GemmArgs gt = g;

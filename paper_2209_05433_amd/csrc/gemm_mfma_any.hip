@@ -538,41 +538,20 @@ int launch_one(const GemmArgs& g, bool wide)
     return check_launch("gemm (matrix-core kernel for any shape, wide form)");
 }
 
-template <int FA, int FB>
-int launch_layout(const GemmArgs& g, bool wide)
-{
-    // A stored M x K is K-contiguous; B stored N x K (transB) is K-contiguous
-    if (!g.transA) return g.transB ? launch_one<FA, FB, true, true>(g, wide) : launch_one<FA, FB, true, false>(g, wide);
-    return g.transB ? launch_one<FA, FB, false, true>(g, wide) : launch_one<FA, FB, false, false>(g, wide);
-}
-
 }  // namespace
 
-bool mfma_any_takes(const GemmArgs& g)
-{
-    return g.M > 0 && g.N > 0 && g.K > 0 && tile_count(g, FT) <= 0x7fffffffll;
-}
+#if !defined(FP8MM_LAYOUT)
+#error "compile with -DFP8MM_LAYOUT=0..3 (2 * transA + transB)"
+#endif
 
-// The wide form where its 256 x 256 tiles fill the rounds of one workgroup per compute unit to
-// 80 % at least and K is long enough for the two-stage pipeline to pay; FP8_KNOB_TILE_N forces
-// either form (128 / 256).
-bool mfma_any_wide(const GemmArgs& g)
+// This file is compiled once per pair of storage orders (-DFP8MM_LAYOUT): A stored M x K is
+// K-contiguous, B stored N x K (transB) is K-contiguous.
+int FP8MM_ANY_NAME(FP8MM_LAYOUT)(const GemmArgs& g, bool wide)
 {
-    const int forced = knob(FP8_KNOB_TILE_N);
-    const int64_t tiles = tile_count(g, WT), units = 256;
-    const int64_t rounds = (tiles + units - 1) / units;
-    // 32-bit offsets within a tile's stage: 255 rows of K bytes, or 63 K-rows of M / N bytes
-    if (g.K >= (1 << 24) || g.M >= (1 << 26) || g.N >= (1 << 26)) return false;
-    if (forced) return forced == 256;
-    return g.K >= 8 * FK && 5 * tiles >= 4 * rounds * units;
-}
-
-int launch_mfma_any(const GemmArgs& g)
-{
-    const bool wide = mfma_any_wide(g);
+    constexpr bool A_KC = (FP8MM_LAYOUT & 2) == 0, B_KC = (FP8MM_LAYOUT & 1) != 0;
     if (g.fmtA == FP8_E4M3)
-        return g.fmtB == FP8_E4M3 ? launch_layout<FP8_E4M3, FP8_E4M3>(g, wide) : launch_layout<FP8_E4M3, FP8_E5M2>(g, wide);
-    return g.fmtB == FP8_E4M3 ? launch_layout<FP8_E5M2, FP8_E4M3>(g, wide) : launch_layout<FP8_E5M2, FP8_E5M2>(g, wide);
+        return g.fmtB == FP8_E4M3 ? launch_one<FP8_E4M3, FP8_E4M3, A_KC, B_KC>(g, wide) : launch_one<FP8_E4M3, FP8_E5M2, A_KC, B_KC>(g, wide);
+    return g.fmtB == FP8_E4M3 ? launch_one<FP8_E5M2, FP8_E4M3, A_KC, B_KC>(g, wide) : launch_one<FP8_E5M2, FP8_E5M2, A_KC, B_KC>(g, wide);
 }
 
 }  // namespace fp8mm

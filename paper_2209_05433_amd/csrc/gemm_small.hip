@@ -1,0 +1,386 @@
+// Matrix-core GEMM for small problems, any shape and any alignment, for gfx950 (MI355X).
+//
+//   c[M x N] = (op(A)[M x K] x op(B)[K x N]) / (sA sB),   D = cast_out(c)
+//
+// The tiled kernel wants hundreds of 256-wide output tiles; a batch of a few tokens, or a 256 x 256
+// product, gives it a handful of workgroups that each walk all of K behind 160 KB of LDS.  Here the
+// output tile is 32 x 32, 32 x 64 or 64 x 64, and the waves of a workgroup share its K: wave w takes
+// the chunks w, w + NW, ... of 64 or 128, so that
+//   - a few hundred workgroups exist where the tiled kernel has ten, and K is walked NW times faster;
+//   - every byte is read once per workgroup, by the one wave that multiplies it: nothing is shared
+//     between waves until the end, and there is no barrier in the K loop;
+//   - D chunks of both operands are in flight per wave, in registers.
+// A chunk is fetched as it lies in memory, neighbouring lanes on neighbouring 16 bytes of a row (loads
+// at any address; pieces that reach over an edge load the last 16 bytes of their row and shift), and
+// goes into a slab of LDS that belongs to the wave, out of which the fragments of the matrix
+// instruction are read: 16-byte reads for an operand that is contiguous along K, transposing reads for
+// the other kind.  (Loading the K-contiguous kind straight into the fragment layout, a row per lane,
+// needs no LDS but touches 64 lines per instruction, which the vector cache looks up one per clock:
+// 16 x 12288 x 12288 took 51 us, this form 34 us = 4.4 TB/s.)  At the end the waves' sums meet in LDS, are
+// added in wave order and leave through the same steps as in the tiled kernel (arXiv 2209.05433,
+// Section 2: factors taken out once per output; for the products see the ACC_* constants).
+//
+// Bound by latency where a form has less than a workgroup per compute unit (256 x 256 x 256: 8.6 us on
+// the tiled kernel, 3.9 here), by the stream of the weight for few tokens (16 x 6144 x 2048: 25 -> 5.7 us;
+// 16 x 12288 x 12288: 107 -> 34), by LDS and vector instructions per product beyond that (64 x 64 tiles
+// reach 0.8 PFLOP/s; 1024 x 1024 x 1024: 17.8 -> 8.5 us; 1000 x 3000 x 1000: 53 -> 18).
+//
+// This file is compiled once per pair of storage orders: -DFP8MM_LAYOUT.
+#include "gemm_common.hpp"
+
+#include <atomic>
+
+namespace fp8mm {
+namespace {
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef u32x4 u32x4_any __attribute__((aligned(1)));     // 16 bytes at any address: one load on this target
+
+#define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
+
+constexpr int SK = 64;                                    // K per sub-chunk; a chunk has S of them
+
+// The vector without its first k bytes (0 <= k < 16), zeros behind the rest.
+__device__ __forceinline__ u32x4 drop_bytes(u32x4 v, int k)
+{
+    if (k & 8) v = (u32x4){v.z, v.w, 0u, 0u};
+    if (k & 4) v = (u32x4){v.y, v.z, v.w, 0u};
+    const int b = k & 3;
+    return (u32x4){__builtin_amdgcn_alignbyte(v.y, v.x, b), __builtin_amdgcn_alignbyte(v.z, v.y, b),
+                   __builtin_amdgcn_alignbyte(v.w, v.z, b), __builtin_amdgcn_alignbyte(0u, v.w, b)};
+}
+
+// A whole row of fewer than 16 bytes, at the end of the vector.
+__device__ __forceinline__ u32x4 load_short(const uint8_t* row, int len)
+{
+    u32x4 v = {0u, 0u, 0u, 0u};
+    for (int j = 0; j < len; ++j) {
+        const int at = 16 - len + j;
+        const unsigned b = (unsigned)row[j] << (8 * (at & 3));
+        v = (u32x4){v.x | (at >> 2 == 0 ? b : 0u), v.y | (at >> 2 == 1 ? b : 0u), v.z | (at >> 2 == 2 ? b : 0u), v.w | (at >> 2 == 3 ? b : 0u)};
+    }
+    return v;
+}
+
+// 16 bytes of a row of `len` bytes, from byte `at` on; zeros beyond the row's end (nothing outside the
+// row is read).
+__device__ __forceinline__ u32x4 load_guarded(const uint8_t* row, int64_t at, int64_t len)
+{
+    const int64_t count = len - at;
+    if (count >= 16) return *(const u32x4_any*)(row + at);
+    if (count <= 0) return (u32x4){0u, 0u, 0u, 0u};
+    return drop_bytes(len >= 16 ? *(const u32x4_any*)(row + len - 16) : load_short(row, (int)len), (int)(16 - count));
+}
+
+// One operand of the tile: R blocks of 32 rows of op(A) / columns of op(B) from t0 on, `ext` of them in
+// all; chunks of CK = 64 S along K.  KC: element (r, k) at base[r K + k]; else at base[k ext + r].
+template <bool KC, int R, int S>
+struct Operand {
+    static constexpr int CK = S * SK;
+    static constexpr int PIECES = 2 * R * S;              // 16-byte loads per lane and chunk
+    static constexpr int ROWB = KC ? CK : 32 * R;         // bytes of a row of the chunk as it lies in memory
+    static constexpr int ROWS = KC ? 32 * R : CK;
+    static constexpr int PITCH = ROWB + 16;               // ... and in LDS (16 bytes spread the rows over the banks)
+    static constexpr int SLAB = ROWS * PITCH;
+    static constexpr int LPR = ROWB / 16;                 // lanes per row of a load
+    static constexpr int RPL = 64 / LPR;                  // rows per load
+    const uint8_t* base;                                  // KC: of the lane's first piece; MC: of its column
+    int64_t ext, K;
+    int last;                                             // KC: rows of the operand under the lane's first one
+    int shift;                                            // MC: how far the lane's column lies in front of where its columns begin
+    bool edge;                                            // MC: the tile reaches over the edge (same for all lanes)
+
+    __device__ __forceinline__ void setup(const uint8_t* p, int64_t ext_, int64_t K_, int64_t t0, int l)
+    {
+        ext = ext_; K = K_;
+        const int row = l / LPR, at = 16 * (l % LPR);
+        if (KC) {
+            const int64_t r = t0 + row < ext ? t0 + row : ext - 1;
+            base = p + r * K + at;
+            last = ext - 1 - r < 32 * R ? (int)(ext - 1 - r) : 32 * R;
+            shift = 0; edge = false;
+        } else {
+            edge = t0 + 32 * R > ext;
+            const int64_t own = t0 + at, col = own + 16 <= ext ? own : ext - 16;
+            base = p + col;
+            shift = own - col < 15 ? (int)(own - col) : 15;      // a lane wholly outside: any bytes do
+            last = row;
+        }
+    }
+    // chunk c, which lies wholly inside K
+    __device__ __forceinline__ void fetch(u32x4 (&x)[PIECES], int64_t c) const
+    {
+#pragma unroll
+        for (int q = 0; q < PIECES; ++q) {
+            if (KC) x[q] = *(const u32x4_any*)(base + c * CK + (int64_t)(q * RPL < last ? q * RPL : last) * K);
+            else x[q] = *(const u32x4_any*)(base + (c * CK + q * RPL + last) * ext);
+        }
+    }
+    __device__ __forceinline__ void fetch_guarded(u32x4 (&x)[PIECES], int64_t c, int l) const
+    {
+#pragma unroll
+        for (int q = 0; q < PIECES; ++q) {
+            if (KC) {
+                const int at = 16 * (l % LPR);
+                x[q] = load_guarded(base - at + (int64_t)(q * RPL < last ? q * RPL : last) * K, c * CK + at, K);
+            } else {
+                const int64_t k = c * CK + q * RPL + last;
+                x[q] = k >= K ? (u32x4){0u, 0u, 0u, 0u} : ext >= 16 ? *(const u32x4_any*)(base + k * ext) : load_short(base + (16 - ext) + k * ext, (int)ext);
+            }
+        }
+    }
+    // the chunk into the wave's slab, as it lies in memory
+    __device__ __forceinline__ void store(const u32x4 (&x)[PIECES], uint8_t* slab, int l) const
+    {
+#pragma unroll
+        for (int q = 0; q < PIECES; ++q)
+            *LDS_PTR(u32x4, slab + (q * RPL + l / LPR) * PITCH + 16 * (l % LPR)) = !KC && edge ? drop_bytes(x[q], shift) : x[q];
+    }
+    // the fragments of sub-chunk s: lane (r, h) = (l % 32, l / 32) gets the K bytes 32 (S h + s) .. + 31 of
+    // row r of each block
+    __device__ __forceinline__ void fragments(const uint8_t* slab, int s, int l, v8i (&f)[R]) const
+    {
+        const int t16 = l & 15;
+        const uint8_t* p = KC ? slab + (l & 31) * PITCH + 32 * (S * (l >> 5) + s)
+                              : slab + (32 * (S * (l >> 5) + s) + (t16 >> 1)) * PITCH + 16 * ((l >> 4) & 1) + 8 * (t16 & 1);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            if (KC) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const u32x4 v = *LDS_PTR(u32x4, p + 32 * i * PITCH + 16 * j);
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) f[i][4 * j + d] = (int)v[d];
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const v2i t = __builtin_amdgcn_ds_read_tr8_b64_v2i32(LDS_PTR(v2i, p + 32 * i + 8 * j * PITCH));
+                    f[i][2 * j] = t.x; f[i][2 * j + 1] = t.y;
+                }
+            }
+        }
+    }
+};
+
+constexpr int RED_PITCH = 36;                             // floats per row of a wave's 32 RM x 32 block of sums
+
+template <bool A_KC, bool B_KC, int RM, int RN, int S>
+constexpr int small_lds_per_wave()
+{
+    const int red = 32 * RM * RED_PITCH * 4, slabs = Operand<A_KC, RM, S>::SLAB + Operand<B_KC, RN, S>::SLAB;
+    return red > slabs ? red : slabs;
+}
+
+// Tile of 32 RM x 32 RN outputs, NW waves, D chunks in flight per wave.
+template <int FMT_A, int FMT_B, int ACC, bool A_KC, bool B_KC, int RM, int RN, int S, int NW, int D>
+__global__ __launch_bounds__(64 * NW) void gemm_small_kernel(
+    const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __restrict__ C,
+    int64_t M, int64_t N, int64_t K, EpilogueArgs ep)
+{
+    typedef Operand<A_KC, RM, S> OpA;
+    typedef Operand<B_KC, RN, S> OpB;
+    constexpr int CK = S * SK;
+    constexpr int PER_WAVE = small_lds_per_wave<A_KC, B_KC, RM, RN, S>();
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];       // NW * PER_WAVE
+    const int tid = threadIdx.x, l = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // Tiles down the rows of C first; every XCD (workgroup ids go round-robin over the 8 of them) gets one
+    // contiguous run, so that the tiles of one column strip share their B in one L2.
+    const int64_t tiles_m = (M + 32 * RM - 1) / (32 * RM), total = gridDim.x;
+    const int64_t x = blockIdx.x % 8, idx = blockIdx.x / 8, share = total / 8, rem = total % 8;
+    const int64_t p = x * share + (x < rem ? x : rem) + idx;
+    const int64_t m0 = (p % tiles_m) * (32 * RM), n0 = (p / tiles_m) * (32 * RN);
+
+    OpA a; OpB b;
+    a.setup(A, M, K, m0, l);
+    b.setup(B, N, K, n0, l);
+    uint8_t* slab_a = lds + w * PER_WAVE;
+    uint8_t* slab_b = slab_a + OpA::SLAB;
+
+    v16f acc[RN][RM];
+#pragma unroll
+    for (int i = 0; i < RN; ++i)
+#pragma unroll
+        for (int j = 0; j < RM; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+
+    auto multiply = [&](const u32x4 (&xa)[OpA::PIECES], const u32x4 (&xb)[OpB::PIECES]) __attribute__((always_inline)) {
+        a.store(xa, slab_a, l);
+        b.store(xb, slab_b, l);
+#pragma unroll
+        for (int sub = 0; sub < S; ++sub) {
+            v8i fa[RM], fb[RN];
+            a.fragments(slab_a, sub, l, fa);
+            b.fragments(slab_b, sub, l, fb);
+            if (ACC == ACC_FP8) {
+#pragma unroll
+                for (int i = 0; i < RN; ++i)
+#pragma unroll
+                    for (int j = 0; j < RM; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[i], fa[j], acc[i][j], FMT_B, FMT_A, 0, 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    v8h ha[RM], hb[RN];
+#pragma unroll
+                    for (int j = 0; j < RM; ++j) ha[j] = widen8<FMT_A>(fa[j][2 * s], fa[j][2 * s + 1]);
+#pragma unroll
+                    for (int i = 0; i < RN; ++i) hb[i] = widen8<FMT_B>(fb[i][2 * s], fb[i][2 * s + 1]);
+#pragma unroll
+                    for (int i = 0; i < RN; ++i)
+#pragma unroll
+                        for (int j = 0; j < RM; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hb[i], ha[j], acc[i][j], 0, 0, 0);
+                }
+            }
+        }
+    };
+
+    // Chunks that lie inside K: no tests, and a load for every step (the last ones repeat the wave's
+    // last chunk), so that the waits leave D - 1 chunks in flight.
+    const int64_t chunks = (K + CK - 1) / CK;
+    const int64_t plain = (A_KC || M >= 16) && (B_KC || N >= 16) ? K / CK : 0;
+    const int64_t mine = plain > w ? (plain - w + NW - 1) / NW : 0;      // of this wave
+    if (mine > 0) {
+        u32x4 xa[D][OpA::PIECES], xb[D][OpB::PIECES];
+        auto fetch = [&](int d, int64_t i) __attribute__((always_inline)) {
+            const int64_t c = w + NW * (i < mine ? i : mine - 1);
+            a.fetch(xa[d], c);
+            b.fetch(xb[d], c);
+        };
+#pragma unroll
+        for (int d = 0; d < D; ++d) fetch(d, d);
+        int64_t i = 0;
+        for (; i + D <= mine; i += D)
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                multiply(xa[d], xb[d]);
+                fetch(d, i + d + D);
+            }
+#pragma unroll
+        for (int d = 0; d < D - 1; ++d)
+            if (i + d < mine) multiply(xa[d], xb[d]);
+    }
+    for (int64_t c = plain + (w + NW - plain % NW) % NW; c < chunks; c += NW) {
+        u32x4 xa[OpA::PIECES], xb[OpB::PIECES];
+        a.fetch_guarded(xa, c, l);
+        b.fetch_guarded(xb, c, l);
+        multiply(xa, xb);
+    }
+
+    // The waves' sums meet in LDS, 32 columns at a time; a thread adds 4 consecutive columns of a row.
+    const float sA_host = ep.sA, sB_host = ep.sB;         // by value: a choice between two memory locations would cost scratch
+    const float sD = ep.out_kind >= OUT_E4M3 ? scale_value(ep.sD_dev, 1.0f) : 1.0f;
+    const double b_all = ep.b_per_col ? 1.0 : (double)scale_value(ep.sB_dev, sB_host);
+    const int esz = ep.out_kind == OUT_F32 ? 4 : ep.out_kind == OUT_BF16 ? 2 : 1;
+    unsigned amax_bits = 0;
+#pragma unroll
+    for (int i = 0; i < RN; ++i) {
+        __syncthreads();                                  // the slabs, or the block before, are done with
+        float* mine_red = (float*)(lds + w * PER_WAVE);
+#pragma unroll
+        for (int j = 0; j < RM; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *LDS_PTR(v4f, mine_red + (32 * j + (l & 31)) * RED_PITCH + 8 * q + 4 * (l >> 5)) =
+                    (v4f){acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+        __syncthreads();
+        for (int u = tid; u < 32 * RM * 8; u += 64 * NW) {
+            const int64_t gm = m0 + (u >> 3), gn = n0 + 32 * i + 4 * (u & 7);
+            if (gm >= M || gn >= N) continue;
+            const float* red = (const float*)lds + (u >> 3) * RED_PITCH + 4 * (u & 7);
+            v4f s = *LDS_PTR(v4f, red);
+#pragma unroll
+            for (int v = 1; v < NW; ++v) s += *LDS_PTR(v4f, red + v * (PER_WAVE / 4));
+            const float sa = ep.a_per_row ? ep.sA_dev[gm] : scale_value(ep.sA_dev, sA_host);
+            const float ra = (float)(1.0 / ((double)sa * b_all));
+            const int left = N - gn < 4 ? (int)(N - gn) : 4;
+            float c[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                c[e] = s[e] * ra;
+                if (ep.b_per_col) c[e] *= 1.0f / ep.sB_dev[gn + (e < left ? e : left - 1)];
+                if (e < left) amax_bits = max(amax_bits, as_u32(c[e]) & 0x7fffffffu);
+            }
+            uint8_t* out = (uint8_t*)C + (size_t)(gm * N + gn) * esz;
+            const bool vec = left == 4 && ((uintptr_t)out & (4 * esz - 1)) == 0;
+            if (ep.out_kind == OUT_F32) {
+                if (vec) *(v4f*)out = (v4f){c[0], c[1], c[2], c[3]};
+                else for (int e = 0; e < left; ++e) ((float*)out)[e] = e == 0 ? c[0] : e == 1 ? c[1] : e == 2 ? c[2] : c[3];
+            } else if (ep.out_kind == OUT_BF16) {
+                const unsigned lo = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){c[0], c[1]}, v2bf));
+                const unsigned hi = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){c[2], c[3]}, v2bf));
+                if (vec) *(v2i*)out = (v2i){(int)lo, (int)hi};
+                else for (int e = 0; e < left; ++e) ((unsigned short*)out)[e] = (unsigned short)((e < 2 ? lo : hi) >> (16 * (e & 1)));
+            } else {
+                const unsigned o = ep.out_kind == OUT_E4M3 ? encode4<FP8_E4M3>(c[0] * sD, c[1] * sD, c[2] * sD, c[3] * sD)
+                                                           : encode4<FP8_E5M2>(c[0] * sD, c[1] * sD, c[2] * sD, c[3] * sD);
+                if (vec) *(unsigned*)out = o;
+                else for (int e = 0; e < left; ++e) out[e] = (uint8_t)(o >> (8 * e));
+            }
+        }
+    }
+    if (ep.amax_out) wave_amax_commit(amax_bits, ep.amax_out);
+}
+
+template <int FA, int FB, int ACC, bool A_KC, bool B_KC, int RM, int RN, int S, int NW, int D>
+int launch_form(const GemmArgs& g)
+{
+    constexpr int LDS = NW * small_lds_per_wave<A_KC, B_KC, RM, RN, S>();
+    auto kern = gemm_small_kernel<FA, FB, ACC, A_KC, B_KC, RM, RN, S, NW, D>;
+    if (LDS > 65536) {
+        // more dynamic LDS than the default limit: raised once per device
+        static std::atomic<unsigned long long> attr_set{0ull};
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return fail(FP8_ERR_DEVICE, "hipGetDevice failed");
+        const unsigned long long bit = 1ull << (dev & 63);
+        if (dev >= 64 || !(attr_set.load(std::memory_order_relaxed) & bit)) {
+            hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+            if (e != hipSuccess) return fail(FP8_ERR_DEVICE, "hipFuncSetAttribute(LDS=%d): %s", LDS, hipGetErrorString(e));
+            if (dev < 64) attr_set.fetch_or(bit, std::memory_order_relaxed);
+        }
+    }
+    const int64_t tiles = ((g.M + 32 * RM - 1) / (32 * RM)) * ((g.N + 32 * RN - 1) / (32 * RN));
+    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(64 * NW), LDS, g.stream, g.A, g.B, g.C, g.M, g.N, g.K, g.ep);
+    return check_launch("gemm (small tiles)");
+}
+
+template <int FA, int FB, int ACC>
+int launch_acc(const GemmArgs& g, int form)
+{
+    constexpr bool A_KC = (FP8MM_LAYOUT & 2) == 0, B_KC = (FP8MM_LAYOUT & 1) != 0;
+    // (waves, chunks of 64 or 128 and chunks in flight measured best of about twenty combinations)
+    switch (form) {
+        case SMALL_32x32: return launch_form<FA, FB, ACC, A_KC, B_KC, 1, 1, 2, 8, 2>(g);
+        case SMALL_32x64: return launch_form<FA, FB, ACC, A_KC, B_KC, 1, 2, 2, 4, 2>(g);
+        default: return launch_form<FA, FB, ACC, A_KC, B_KC, 2, 2, 1, 4, 1>(g);
+    }
+}
+
+}  // namespace
+
+#if !defined(FP8MM_LAYOUT)
+#error "compile with -DFP8MM_LAYOUT=0..3 (2 * transA + transB)"
+#endif
+
+template <int FA, int FB>
+static int launch_formats(const GemmArgs& g, int form)
+{
+    return g.acc == ACC_FP8 ? launch_acc<FA, FB, ACC_FP8>(g, form) : launch_acc<FA, FB, ACC_F16>(g, form);
+}
+
+int FP8MM_SMALL_NAME(FP8MM_LAYOUT)(const GemmArgs& g, int form)
+{
+    if (g.fmtA == FP8_E4M3)
+        return g.fmtB == FP8_E4M3 ? launch_formats<FP8_E4M3, FP8_E4M3>(g, form) : launch_formats<FP8_E4M3, FP8_E5M2>(g, form);
+    return g.fmtB == FP8_E4M3 ? launch_formats<FP8_E5M2, FP8_E4M3>(g, form) : launch_formats<FP8_E5M2, FP8_E5M2>(g, form);
+}
+
+}  // namespace fp8mm

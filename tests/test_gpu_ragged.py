@@ -47,3 +47,43 @@ def test_transposing_cast_at_the_edges_of_its_tiles(rows, cols, off, dtype):
     assert np.array_equal(q.view(rows, cols).cpu().numpy(), want)
     assert np.array_equal(qt.view(cols, rows).cpu().numpy(), want.T)
     assert guards_hold(bq, n, off) and guards_hold(bt, n, off)
+
+
+# (M, N, K, offset of both operands in bytes): each form of the small-tile kernel, at one and several tiles, with
+# rows shorter than a vector, K shorter than a chunk, K ends inside a chunk, and operands that start anywhere
+SMALL = [(1, 1, 1, 0), (5, 15, 17, 0), (31, 33, 63, 1), (32, 32, 64, 0), (33, 63, 65, 3), (16, 320, 2048, 0), (17, 97, 1030, 5), (64, 130, 129, 0),
+         (65, 1025, 127, 0), (100, 260, 1100, 7), (300, 1030, 200, 0), (257, 400, 2500, 1), (700, 900, 513, 0)]
+
+
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K,off", SMALL)
+def test_small_tiles_at_their_edges(M, N, K, off, transA, transB):
+    """Small integers, so that every sum is exact in every order: all four outputs kinds and both
+    instruction modes against the oracle, with guard words around the output."""
+    rng = np.random.default_rng(M * 31 + N * 7 + K)
+    A = oracle.quantize(rng.integers(-3, 4, (M, K)).astype(np.float32), E4M3, np.float32(1.0))
+    B = oracle.quantize(rng.integers(-3, 4, (K, N)).astype(np.float32), E5M2, np.float32(1.0))
+    S, _ = oracle.gemm_rows(A, E4M3, B, E5M2)
+
+    def operand(x):
+        buf, view = inside(x.size, off)
+        view.copy_(torch.from_numpy(np.ascontiguousarray(x).reshape(-1)))
+        return view.view(*x.shape)
+
+    dA, dB = operand(A.T if transA else A), operand(B.T if transB else B)
+    sA, sB, sD = torch.full((M,), 2.0, device="cuda"), torch.full((N,), 0.5, device="cuda"), torch.full((1,), 0.25, device="cuda")
+    sA[M // 2] = 4.0
+    c_ref = S / (sA.cpu().numpy().astype(np.float64)[:, None] * 0.5)
+    amax = torch.full((1,), -1.0, device="cuda")
+    for flags in (0, fp8.FP8_GEMM_MFMA8):
+        for kind, dtype in ((fp8.FP8_OUT_F32, torch.float32), (fp8.FP8_OUT_BF16, torch.bfloat16), (fp8.FP8_OUT_E4M3, torch.uint8)):
+            buf = torch.full((M * N + 16,), 9, dtype=dtype, device="cuda")
+            D = buf[8:8 + M * N].view(M, N)
+            fp8.fp8_gemm_fused(dA, E4M3, transA, dB, E5M2, transB, D, kind, sA, sB, sD if dtype == torch.uint8 else None, amax, flags)
+            torch.cuda.synchronize()
+            if dtype == torch.uint8:
+                assert np.array_equal(D.cpu().numpy(), oracle.quantize(c_ref.astype(np.float32), E4M3, np.float32(0.25)))
+            else:
+                assert np.array_equal(D.double().cpu().numpy(), torch.from_numpy(c_ref).to(dtype).double().numpy())
+            assert bool((buf[:8] == 9).all()) and bool((buf[8 + M * N:] == 9).all())
+            assert float(amax.item()) == float(np.max(np.abs(c_ref)))
