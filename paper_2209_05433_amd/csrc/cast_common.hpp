@@ -18,6 +18,10 @@ constexpr int kMultiMax = FP8_MULTI_MAX;  // tensors per launch of the multi-ten
 constexpr size_t kStreamingStoreBytes = (size_t)384 << 20;   // outputs from this size on are stored non-temporally
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+// Vectors at any address: the target's global loads and stores take them as one instruction.
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+typedef u32x2 u32x2_any __attribute__((aligned(1)));
+typedef unsigned u32_any __attribute__((aligned(1)));
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 // ------------------------------------------------------------------------------------------
@@ -58,9 +62,10 @@ __device__ __forceinline__ unsigned scalar_mag(const void* x, size_t i)
     return ((unsigned)(((const unsigned short*)x)[i] & 0x7fffu)) << 16;
 }
 
+template <int THREADS = kThreads>
 __device__ __forceinline__ unsigned block_max_u32(unsigned v)
 {
-    __shared__ unsigned part[kThreads / 64];
+    __shared__ unsigned part[THREADS / 64];
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         unsigned o = __shfl_xor(v, off, 64);
@@ -70,7 +75,7 @@ __device__ __forceinline__ unsigned block_max_u32(unsigned v)
     __syncthreads();
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int w = 1; w < kThreads / 64; ++w) v = v > part[w] ? v : part[w];
+        for (int w = 1; w < THREADS / 64; ++w) v = v > part[w] ? v : part[w];
     }
     return v;   // valid in thread 0
 }
@@ -128,11 +133,11 @@ __device__ __forceinline__ void scale_item(const u32x4 (&v)[DT == FP8_BF16 ? 2 :
 // fp32 4.25 -> 6.2 TB/s.
 template <int DT> struct Piece;
 template <> struct Piece<FP8_BF16> {
-    typedef u32x2 type;
+    typedef u32x2_any type;
     static __device__ __forceinline__ type of(const u32x4& o, int k) { return (u32x2){o[2 * k], o[2 * k + 1]}; }
 };
 template <> struct Piece<FP8_F32> {
-    typedef unsigned type;
+    typedef u32_any type;
     static __device__ __forceinline__ type of(const u32x4& o, int k) { return o[k]; }
 };
 
@@ -165,7 +170,7 @@ __device__ __forceinline__ void cast_group(const u32x4* in, typename Piece<DT>::
 // A lane's walk over the vectors [vlo, vhi) of its workgroup: 8 vectors per step, all loads of a
 // step issued before the first conversion; then the remainder, group by group.
 template <int DT, int FMT, int PATH, bool NTS, bool AMAX>
-__device__ __forceinline__ void cast_run(const u32x4* __restrict__ xv, typename Piece<DT>::type* __restrict__ qp,
+__device__ __forceinline__ void cast_run(const u32x4_any* __restrict__ xv, typename Piece<DT>::type* __restrict__ qp,
                                          size_t vlo, size_t vhi, float s, unsigned& run)
 {
     constexpr int VPI = DT == FP8_BF16 ? 2 : 4;

@@ -13,11 +13,14 @@
 namespace fp8mm {
 namespace {
 
-// Vector path: x is 16-byte aligned.  nvec full vectors, then n - nvec*per_vec tail elements.
-// Every workgroup takes whole chunks of 32 KB (8 vectors per lane, all loaded before the first
-// compare), four workgroups per compute unit; one atomic per workgroup at the end (with one chunk
-// per workgroup the thousands of atomics on one cell cost a quarter of the run time).
-constexpr int kAmaxChunkVecs = kThreads * 8;
+// nvec whole vectors, at any address, then n - nvec*per_vec tail elements.  Every workgroup takes
+// chunks of 32 KB (8 vectors per lane, all loaded before the first compare), four workgroups per
+// compute unit; one atomic per workgroup at the end (with one chunk per workgroup the thousands of
+// atomics on one cell cost a quarter of the run time).  Tensors that give fewer than 512 chunks are cut
+// into chunks of 8 KB: their time is the latency of a few loads, not bandwidth.
+constexpr int kAmaxVecs = 8;                                         // per lane and chunk
+constexpr int kAmaxVecsSmall = 2;
+constexpr size_t kAmaxSmallBelow = (size_t)512 * kThreads * kAmaxVecs;   // vectors
 
 // Last step of the amax kernels in their one-launch form (fp8_amax_scale): no cell has to be
 // cleared beforehand and the scale comes out of the same launch.  Every workgroup leaves its
@@ -46,6 +49,13 @@ __device__ __forceinline__ void amax_finish_ticket(unsigned r, unsigned* __restr
                                                    float* __restrict__ amax_out, float* __restrict__ scale_out,
                                                    unsigned bid, unsigned grid)
 {
+    if (grid == 1) {
+        if (threadIdx.x == 0) {
+            *amax_out = as_f32(r);
+            if (scale_out) *scale_out = scale_rule(as_f32(r), fmt);
+        }
+        return;
+    }
     __shared__ bool last;
     if (threadIdx.x == 0) {
         __hip_atomic_store(&ws[kTicketPartials + bid], r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -57,7 +67,7 @@ __device__ __forceinline__ void amax_finish_ticket(unsigned r, unsigned* __restr
         bool l = false;
         if (draw_ticket(&ws[32 * (1 + g)]) == members - 1) {
             __hip_atomic_store(&ws[32 * (1 + g)], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            l = draw_ticket(&ws[0]) == groups - 1;
+            l = groups == 1 || draw_ticket(&ws[0]) == groups - 1;
         }
         last = l;
     }
@@ -77,6 +87,42 @@ __device__ __forceinline__ void amax_finish_ticket(unsigned r, unsigned* __restr
     }
 }
 
+// The maximum over the chunks (of kThreads VECS vectors) that workgroup `bid` of `grid` takes, into run.
+// The whole chunks first (a loop without tests: with the partial one in it the compiler shared loads
+// between the two cases and waited for all of them, 83 -> 109 us on 2^28 elements); in the partial one
+// the lanes beyond the end read the last vector again.
+template <int DT, int VECS>
+__device__ __forceinline__ void amax_chunks(const u32x4_any* xv, size_t nvec, unsigned bid, unsigned grid, unsigned (&run)[4])
+{
+    constexpr size_t CHUNK = (size_t)kThreads * VECS;
+    const size_t whole = nvec / CHUNK;
+    for (size_t c = bid; c < whole; c += grid) {
+        const u32x4_any* p = xv + c * CHUNK + threadIdx.x;
+        u32x4 v[VECS];
+#pragma unroll
+        for (int j = 0; j < VECS; ++j) v[j] = __builtin_nontemporal_load(p + j * kThreads);
+#pragma unroll
+        for (int j = 0; j < VECS; ++j) run[j & 3] = vec_mag_max<DT>(v[j], run[j & 3]);
+    }
+    if (whole * CHUNK < nvec && whole % grid == bid) {
+        u32x4 v[VECS];
+#pragma unroll
+        for (int j = 0; j < VECS; ++j) {
+            const size_t i = whole * CHUNK + threadIdx.x + j * kThreads;
+            v[j] = xv[i < nvec ? i : nvec - 1];
+        }
+#pragma unroll
+        for (int j = 0; j < VECS; ++j) run[j & 3] = vec_mag_max<DT>(v[j], run[j & 3]);
+    }
+}
+
+// Workgroups for a tensor of nvec vectors.
+inline unsigned amax_grid(size_t nvec)
+{
+    const size_t chunk = (size_t)kThreads * (nvec < kAmaxSmallBelow ? kAmaxVecsSmall : kAmaxVecs), chunks = (nvec + chunk - 1) / chunk;
+    return (unsigned)(chunks < 1 ? 1 : chunks > (size_t)kAmaxBlocks ? (size_t)kAmaxBlocks : chunks);
+}
+
 // The work of workgroup `bid` of `grid` on one tensor.
 template <int DT, bool TICKET>
 __device__ __forceinline__ void amax_vec_body(const void* __restrict__ x, size_t n, unsigned* __restrict__ out_bits,
@@ -84,23 +130,11 @@ __device__ __forceinline__ void amax_vec_body(const void* __restrict__ x, size_t
                                               unsigned bid, unsigned grid)
 {
     constexpr int PV = Elem<DT>::per_vec;
-    const u32x4* xv = (const u32x4*)x;
+    const u32x4_any* xv = (const u32x4_any*)x;
     const size_t nvec = n / PV;
-    const size_t nchunk = nvec / kAmaxChunkVecs;
     unsigned run[4] = {0u, 0u, 0u, 0u};
-    for (size_t c = bid; c < nchunk; c += grid) {
-        const u32x4* p = xv + c * kAmaxChunkVecs + threadIdx.x;
-        u32x4 v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = __builtin_nontemporal_load(p + j * kThreads);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) run[j & 3] = vec_mag_max<DT>(v[j], run[j & 3]);
-    }
-    // vectors after the last whole chunk, then the tail elements: workgroup 0
-    if (bid == 0) {
-        for (size_t i = nchunk * kAmaxChunkVecs + threadIdx.x; i < nvec; i += kThreads)
-            run[0] = vec_mag_max<DT>(__builtin_nontemporal_load(&xv[i]), run[0]);
-    }
+    if (nvec < kAmaxSmallBelow) amax_chunks<DT, kAmaxVecsSmall>(xv, nvec, bid, grid, run);
+    else amax_chunks<DT, kAmaxVecs>(xv, nvec, bid, grid, run);
     unsigned r;
     if (DT == FP8_F32) {
         const unsigned a = run[0] > run[1] ? run[0] : run[1], b = run[2] > run[3] ? run[2] : run[3];
@@ -167,27 +201,6 @@ __global__ __launch_bounds__(kThreads) void amax_multi_kernel(MultiTensors m, fl
                             scale_out ? scale_out + t : nullptr, blockIdx.x - m.first[t], m.first[t + 1] - m.first[t]);
 }
 
-// Any alignment the element type allows: one element per lane per step.
-template <int DT, bool TICKET>
-__global__ __launch_bounds__(kThreads) void amax_scalar_kernel(const void* __restrict__ x, size_t n,
-                                                              unsigned* __restrict__ out_bits, unsigned* __restrict__ ws,
-                                                              int fmt, float* __restrict__ scale_out)
-{
-    const size_t stride = (size_t)gridDim.x * kThreads;
-    unsigned r = 0;
-    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) {
-        unsigned m = scalar_mag<DT>(x, i);
-        r = r > m ? r : m;
-    }
-    r = block_max_u32(r);
-    if (TICKET) {
-        __syncthreads();
-        amax_finish_ticket(r, ws, fmt, (float*)out_bits, scale_out, blockIdx.x, gridDim.x);
-        return;
-    }
-    if (threadIdx.x == 0) atomicMax(out_bits, r);
-}
-
 // n == 0 in the one-launch form: amax 0, scale by the degenerate rule.
 __global__ void amax_empty_kernel(int fmt, float* __restrict__ amax_out, float* __restrict__ scale_out)
 {
@@ -206,7 +219,7 @@ __global__ void scale_kernel(const float* __restrict__ amax, int fmt, float* __r
 // largest finite value (Section 2), NaN -> NaN, inf -> NaN (E4M3) or inf (E5M2).
 // ------------------------------------------------------------------------------------------
 
-// Vector path: x and q are 16-byte aligned.  Every workgroup owns one contiguous run of the
+// x and q at any address.  Every workgroup owns one contiguous run of the
 // tensor (see cast_run / cast_group for how its lanes share the work).  Stores are ordinary up to
 // kStreamingStoreBytes of output, where they win 5 % because part of the output stays in the
 // 256 MB memory-side cache, and non-temporal beyond (5-8 % better there).
@@ -221,7 +234,7 @@ __device__ __forceinline__ void quantize_vec_body(const void* __restrict__ x, si
     const size_t hi = lo + per < nitem ? lo + per : nitem;
     unsigned unused = 0;
     if (lo < hi)
-        cast_run<DT, FMT, PATH, NTS, false>((const u32x4*)x, (typename Piece<DT>::type*)q, VPI * lo, VPI * hi, s, unused);
+        cast_run<DT, FMT, PATH, NTS, false>((const u32x4_any*)x, (typename Piece<DT>::type*)q, VPI * lo, VPI * hi, s, unused);
     if (bid == 0) {                                 // fewer than 16 tail elements
         const size_t t = nitem * 16 + threadIdx.x;
         if (t < n) q[t] = (uint8_t)encode_bits<FMT, PATH != kCastBitsStrict>(load_scalar<DT>(x, t) * s);
@@ -248,19 +261,6 @@ __global__ __launch_bounds__(kThreads) void quantize_multi_kernel(MultiTensors m
     else quantize_vec_body<DT, FP8_E5M2, PATH, false>(m.x[t], m.n[t], scale_dev[t], m.q[t], bid, grid);
 }
 
-// Any alignment: one element per lane per step, always the integer rounding.
-template <int DT, int FMT, bool SAT>
-__global__ __launch_bounds__(kThreads) void quantize_scalar_kernel(const void* __restrict__ x, size_t n,
-                                                                  float scale,
-                                                                  const float* __restrict__ scale_dev,
-                                                                  uint8_t* __restrict__ q)
-{
-    const float s = scale_dev ? *scale_dev : scale;
-    const size_t stride = (size_t)gridDim.x * kThreads;
-    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride)
-        q[i] = (uint8_t)encode_bits<FMT, SAT>(load_scalar<DT>(x, i) * s);
-}
-
 }  // namespace
 
 namespace {
@@ -270,21 +270,11 @@ template <bool TICKET>
 void launch_amax_kernels(const void* x, size_t n, int in_dtype, unsigned* out, unsigned* ws, int fmt, float* scale_out,
                          hipStream_t stream)
 {
-    if (aligned16(x)) {
-        const size_t per_vec = in_dtype == FP8_F32 ? 4 : 8;
-        const size_t nchunk = n / per_vec / kAmaxChunkVecs;
-        const int grid = (int)(nchunk < 1 ? 1 : nchunk > (size_t)kAmaxBlocks ? (size_t)kAmaxBlocks : nchunk);
-        if (in_dtype == FP8_F32)
-            hipLaunchKernelGGL((amax_vec_kernel<FP8_F32, TICKET>), dim3(grid), dim3(kThreads), 0, stream, x, n, out, ws, fmt, scale_out);
-        else
-            hipLaunchKernelGGL((amax_vec_kernel<FP8_BF16, TICKET>), dim3(grid), dim3(kThreads), 0, stream, x, n, out, ws, fmt, scale_out);
-    } else {
-        const int grid = grid_for(n, kAmaxBlocks);
-        if (in_dtype == FP8_F32)
-            hipLaunchKernelGGL((amax_scalar_kernel<FP8_F32, TICKET>), dim3(grid), dim3(kThreads), 0, stream, x, n, out, ws, fmt, scale_out);
-        else
-            hipLaunchKernelGGL((amax_scalar_kernel<FP8_BF16, TICKET>), dim3(grid), dim3(kThreads), 0, stream, x, n, out, ws, fmt, scale_out);
-    }
+    const unsigned grid = amax_grid(n / (in_dtype == FP8_F32 ? 4 : 8));
+    if (in_dtype == FP8_F32)
+        hipLaunchKernelGGL((amax_vec_kernel<FP8_F32, TICKET>), dim3(grid), dim3(kThreads), 0, stream, x, n, out, ws, fmt, scale_out);
+    else
+        hipLaunchKernelGGL((amax_vec_kernel<FP8_BF16, TICKET>), dim3(grid), dim3(kThreads), 0, stream, x, n, out, ws, fmt, scale_out);
 }
 }  // namespace
 
@@ -306,13 +296,12 @@ int launch_amax_scale(const void* x, size_t n, int in_dtype, int fmt, float* ama
     return check_launch("amax_scale");
 }
 
-// One launch where every tensor takes the vector path (non-empty, 16-byte aligned); tensor by tensor
-// otherwise.  Results are those of the single-tensor launches either way.
+// One launch where no tensor is empty; tensor by tensor otherwise.  Results are those of the single-tensor launches either way.
 int launch_amax_scale_multi(int count, const void* const* x, const size_t* n, int in_dtype, const int* fmt, float* amax_out,
                             float* scale_out, void* workspace, hipStream_t stream)
 {
     bool one = count > 1;
-    for (int i = 0; i < count; ++i) one = one && n[i] > 0 && aligned16(x[i]);
+    for (int i = 0; i < count; ++i) one = one && n[i] > 0;
     if (!one) {
         for (int i = 0; i < count; ++i)
             if (int e = launch_amax_scale(x[i], n[i], in_dtype, fmt[i], amax_out + i, scale_out ? scale_out + i : nullptr,
@@ -325,9 +314,8 @@ int launch_amax_scale_multi(int count, const void* const* x, const size_t* n, in
     unsigned total = 0;
     const size_t per_vec = in_dtype == FP8_F32 ? 4 : 8;
     for (int i = 0; i < count; ++i) {
-        const size_t nchunk = n[i] / per_vec / kAmaxChunkVecs;
         m.x[i] = x[i]; m.n[i] = n[i]; m.fmt[i] = fmt[i]; m.first[i] = total;
-        total += (unsigned)(nchunk < 1 ? 1 : nchunk > (size_t)kAmaxBlocks ? (size_t)kAmaxBlocks : nchunk);
+        total += amax_grid(n[i] / per_vec);
     }
     for (int i = count; i <= kMultiMax; ++i) m.first[i] = total;
     if (in_dtype == FP8_F32)
@@ -346,15 +334,23 @@ int launch_scale_from_amax(const float* amax, int fmt, float* scale_out, hipStre
 }
 
 namespace {
+// Workgroups of the cast kernels: runs of 4 items of 16 elements per lane (the knob FP8_KNOB_CAST_RUN
+// overrides), shorter ones where that would leave the chip with fewer than 512 workgroups (1024 for
+// fp32, whose items are twice as long: 8.4 10^6 elements 27.9 -> 24.6 us with the other steps of a cast).
+int cast_grid(size_t n, int in_dtype)
+{
+    const size_t items = n / 16, spread = items / ((size_t)kThreads * (in_dtype == FP8_F32 ? 1024 : 512));
+    const size_t per_lane = knob(FP8_KNOB_CAST_RUN) ? (size_t)knob(FP8_KNOB_CAST_RUN) : spread < 1 ? 1 : spread > 4 ? 4 : spread;
+    return grid_for((items + per_lane - 1) / per_lane, kCastBlocks);
+}
+
 template <int DT, int FMT>
 void launch_quantize_typed(const void* x, size_t n, float scale, const float* scale_dev,
                            uint8_t* q, bool saturate, hipStream_t stream)
 {
-    if (aligned16(x) && aligned16(q)) {
-        const size_t per_lane = knob(FP8_KNOB_CAST_RUN) ? (size_t)knob(FP8_KNOB_CAST_RUN) : 4;    // items of 16 elements per lane
-        const int grid = grid_for((n / 16 + per_lane - 1) / per_lane, kCastBlocks);
-        // An output that does not fit the memory-side cache (256 MB) is written past it.
-        const bool nts = n >= kStreamingStoreBytes;
+    const int grid = cast_grid(n, DT);
+    // An output that does not fit the memory-side cache (256 MB) is written past it.
+    const bool nts = n >= kStreamingStoreBytes;
 #define FP8MM_LAUNCH_QV(PATH)                                                                                      \
     do {                                                                                                           \
         if (nts) hipLaunchKernelGGL((quantize_vec_kernel<DT, FMT, PATH, true>), dim3(grid), dim3(kThreads), 0,     \
@@ -362,17 +358,10 @@ void launch_quantize_typed(const void* x, size_t n, float scale, const float* sc
         else hipLaunchKernelGGL((quantize_vec_kernel<DT, FMT, PATH, false>), dim3(grid), dim3(kThreads), 0,        \
                                 stream, x, n, scale, scale_dev, q);                                                \
     } while (0)
-        if (!saturate) FP8MM_LAUNCH_QV(kCastBitsStrict);
-        else if (cast_path() == kCastCvt) FP8MM_LAUNCH_QV(kCastCvt);
-        else FP8MM_LAUNCH_QV(kCastBits);
+    if (!saturate) FP8MM_LAUNCH_QV(kCastBitsStrict);
+    else if (cast_path() == kCastCvt) FP8MM_LAUNCH_QV(kCastCvt);
+    else FP8MM_LAUNCH_QV(kCastBits);
 #undef FP8MM_LAUNCH_QV
-    } else if (saturate) {
-        hipLaunchKernelGGL((quantize_scalar_kernel<DT, FMT, true>), dim3(grid_for(n, 2048)), dim3(kThreads), 0,
-                           stream, x, n, scale, scale_dev, q);
-    } else {
-        hipLaunchKernelGGL((quantize_scalar_kernel<DT, FMT, false>), dim3(grid_for(n, 2048)), dim3(kThreads), 0,
-                           stream, x, n, scale, scale_dev, q);
-    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -390,7 +379,7 @@ __device__ __forceinline__ unsigned to_bf16_bits(float f)
 template <int FMT, int OUT>
 __global__ __launch_bounds__(kThreads) void dequantize_kernel(const uint8_t* __restrict__ q, size_t n, float scale,
                                                              const float* __restrict__ scale_dev,
-                                                             void* __restrict__ out, bool vec)
+                                                             void* __restrict__ out)
 {
     // The result depends on the byte alone: every workgroup first tabulates the 256 results (one
     // decode, one IEEE division and, for bf16, one rounding per thread) in LDS, then streams.  With
@@ -407,10 +396,10 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const uint8_t* __r
     }
     __syncthreads();
     const size_t stride = (size_t)gridDim.x * kThreads;
-    const size_t nvec = vec ? n / EPV : 0;
+    const size_t nvec = n / EPV;
     auto load_piece = [&](size_t i) {
-        if (OUT == FP8_F32) return (u32x2){__builtin_nontemporal_load(&((const unsigned*)q)[i]), 0u};
-        return __builtin_nontemporal_load(&((const u32x2*)q)[i]);
+        if (OUT == FP8_F32) return (u32x2){__builtin_nontemporal_load(&((const u32_any*)q)[i]), 0u};
+        return (u32x2)__builtin_nontemporal_load(&((const u32x2_any*)q)[i]);
     };
     auto emit = [&](size_t i, u32x2 p) {
         unsigned r[EPV];
@@ -423,7 +412,7 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const uint8_t* __r
 #pragma unroll
             for (int d = 0; d < 4; ++d) o[d] = r[2 * d] | (r[2 * d + 1] << 16);
         }
-        ((u32x4*)out)[i] = o;
+        ((u32x4_any*)out)[i] = o;
     };
     // every workgroup owns one contiguous run of the vectors
     const size_t per = (nvec + gridDim.x - 1) / gridDim.x;
@@ -463,14 +452,13 @@ int launch_dequantize(const uint8_t* q, size_t n, int fmt, float scale, const fl
                       int out_dtype, void* out, hipStream_t stream)
 {
     if (n == 0) return FP8_OK;
-    const bool vec = aligned16(q) && aligned16(out);
-    const int grid = grid_for(vec ? n / 16 + 1 : n, 256 * 256);     // many short runs measured best (write-heavy stream)
+    const int grid = grid_for(n / 16 + 1, 256 * 256);     // many short runs measured best (write-heavy stream)
     if (fmt == FP8_E4M3) {
-        if (out_dtype == FP8_F32) hipLaunchKernelGGL((dequantize_kernel<FP8_E4M3, FP8_F32>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out, vec);
-        else hipLaunchKernelGGL((dequantize_kernel<FP8_E4M3, FP8_BF16>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out, vec);
+        if (out_dtype == FP8_F32) hipLaunchKernelGGL((dequantize_kernel<FP8_E4M3, FP8_F32>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out);
+        else hipLaunchKernelGGL((dequantize_kernel<FP8_E4M3, FP8_BF16>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out);
     } else {
-        if (out_dtype == FP8_F32) hipLaunchKernelGGL((dequantize_kernel<FP8_E5M2, FP8_F32>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out, vec);
-        else hipLaunchKernelGGL((dequantize_kernel<FP8_E5M2, FP8_BF16>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out, vec);
+        if (out_dtype == FP8_F32) hipLaunchKernelGGL((dequantize_kernel<FP8_E5M2, FP8_F32>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out);
+        else hipLaunchKernelGGL((dequantize_kernel<FP8_E5M2, FP8_BF16>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out);
     }
     return check_launch("dequantize");
 }
@@ -478,9 +466,9 @@ int launch_dequantize(const uint8_t* q, size_t n, int fmt, float scale, const fl
 int launch_quantize_multi(int count, const void* const* x, const size_t* n, int in_dtype, const int* fmt,
                           const float* scale_dev, uint8_t* const* q_out, hipStream_t stream)
 {
-    // one launch where every tensor takes the vector path with ordinary stores; else tensor by tensor
+    // one launch where no tensor is empty and all take ordinary stores; else tensor by tensor
     bool one = count > 1;
-    for (int i = 0; i < count; ++i) one = one && n[i] > 0 && n[i] < kStreamingStoreBytes && aligned16(x[i]) && aligned16(q_out[i]);
+    for (int i = 0; i < count; ++i) one = one && n[i] > 0 && n[i] < kStreamingStoreBytes;
     if (!one) {
         for (int i = 0; i < count; ++i)
             if (int e = launch_quantize(x[i], n[i], in_dtype, fmt[i], 0.0f, scale_dev + i, true, q_out[i], stream)) return e;
@@ -489,10 +477,9 @@ int launch_quantize_multi(int count, const void* const* x, const size_t* n, int 
     MultiTensors m{};
     m.count = count;
     unsigned total = 0;
-    const size_t per_lane = knob(FP8_KNOB_CAST_RUN) ? (size_t)knob(FP8_KNOB_CAST_RUN) : 4;
     for (int i = 0; i < count; ++i) {
         m.x[i] = x[i]; m.q[i] = q_out[i]; m.n[i] = n[i]; m.fmt[i] = fmt[i]; m.first[i] = total;
-        total += (unsigned)grid_for((n[i] / 16 + per_lane - 1) / per_lane, kCastBlocks);
+        total += (unsigned)cast_grid(n[i], in_dtype);
     }
     for (int i = count; i <= kMultiMax; ++i) m.first[i] = total;
     const bool cvt = cast_path() == kCastCvt;

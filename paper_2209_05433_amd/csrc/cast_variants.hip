@@ -39,34 +39,34 @@ __device__ __forceinline__ void raise_cell(unsigned* cell, unsigned bits)
 // ------------------------------------------------------------------------------------------
 // cast + amax in one pass
 // ------------------------------------------------------------------------------------------
+constexpr size_t kAloneItems = 8 * kThreads;        // items of 16 elements that one workgroup casts alone
+
 template <int DT, int FMT, bool NTS>
 __global__ __launch_bounds__(kThreads) void quantize_amax_kernel(const void* __restrict__ x, size_t n,
                                                                 const float* __restrict__ scale_dev,
                                                                 uint8_t* __restrict__ q,
-                                                                unsigned* __restrict__ amax_bits, bool vec)
+                                                                unsigned* __restrict__ amax_bits)
 {
     constexpr int VPI = DT == FP8_BF16 ? 2 : 4;     // 16-byte vectors per 16 elements
     const float s = *scale_dev;
     unsigned run = 0;
-    size_t done = 0;
-    if (vec) {
-        const size_t nitem = n / 16;
-        const size_t per = (nitem + gridDim.x - 1) / gridDim.x;
-        const size_t lo = (size_t)blockIdx.x * per;
-        const size_t hi = lo + per < nitem ? lo + per : nitem;
-        if (lo < hi)
-            cast_run<DT, FMT, kCastCvt, NTS, true>((const u32x4*)x, (typename Piece<DT>::type*)q, VPI * lo, VPI * hi, s, run);
-        done = nitem * 16;
-    }
+    const size_t nitem = n / 16;
+    const size_t per = (nitem + gridDim.x - 1) / gridDim.x;
+    const size_t lo = (size_t)blockIdx.x * per;
+    const size_t hi = lo + per < nitem ? lo + per : nitem;
+    if (lo < hi)
+        cast_run<DT, FMT, kCastCvt, NTS, true>((const u32x4_any*)x, (typename Piece<DT>::type*)q, VPI * lo, VPI * hi, s, run);
     unsigned r = run_to_bits<DT>(run);
-    const size_t stride = (size_t)gridDim.x * kThreads;
-    for (size_t t = done + (size_t)blockIdx.x * kThreads + threadIdx.x; t < n; t += stride) {
+    const size_t t = nitem * 16 + threadIdx.x;      // fewer than 16 tail elements
+    if (blockIdx.x == 0 && t < n) {
         const unsigned m = scalar_mag<DT>(x, t);
         r = r > m ? r : m;
         q[t] = (uint8_t)encode_bits<FMT>(load_scalar<DT>(x, t) * s);
     }
     r = block_max_u32(r);
-    if (threadIdx.x == 0) raise_cell(amax_bits, r);
+    if (threadIdx.x != 0) return;
+    if (gridDim.x == 1) *amax_bits = r;             // a single workgroup: the cell was not cleared
+    else raise_cell(amax_bits, r);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kThreads) void quantize_rows_kernel(const void* __r
         if (vec) {                              // cols is a multiple of 16: whole groups of vectors
             const int64_t nitem = cols / 16;
             unsigned unused = 0;
-            cast_run<DT, FMT, kCastCvt, false, false>((const u32x4*)xr, (typename Piece<DT>::type*)qr, 0, (size_t)(VPI * nitem), s, unused);
+            cast_run<DT, FMT, kCastCvt, false, false>((const u32x4_any*)xr, (typename Piece<DT>::type*)qr, 0, (size_t)(VPI * nitem), s, unused);
             done = nitem * 16;
         }
         for (int64_t t = done + threadIdx.x; t < cols; t += kThreads)
@@ -176,11 +176,6 @@ constexpr int QT_PITCH = TT + 16;             // LDS row pitch of the q^T tile (
 
 typedef int v2i __attribute__((ext_vector_type(2)));
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
-
-// Vectors at any address: the target's global loads and stores take them as one instruction.
-typedef u32x4 u32x4_any __attribute__((aligned(1)));
-typedef u32x2 u32x2_any __attribute__((aligned(1)));
-typedef unsigned u32_any __attribute__((aligned(1)));
 
 // A vector without its first k elements (0 <= k < per_vec): the rest moves to the front.
 template <int DT>
@@ -425,15 +420,15 @@ template <int DT, int FMT>
 __global__ __launch_bounds__(kThreads) void quantize_sr_kernel(const void* __restrict__ x, size_t n, float scale,
                                                               const float* __restrict__ scale_dev,
                                                               unsigned seed_lo, unsigned seed_hi,
-                                                              uint8_t* __restrict__ q, bool vec)
+                                                              uint8_t* __restrict__ q)
 {
     constexpr int V = DT == FP8_BF16 ? 1 : 2;       // 16-byte vectors per block
     constexpr int U = 4;
     const float s = scale_dev ? *scale_dev : scale;
     size_t done = 0;
-    if (vec) {
-        const u32x4* xv = (const u32x4*)x;
-        u32x2* qp = (u32x2*)q;
+    {
+        const u32x4_any* xv = (const u32x4_any*)x;
+        u32x2_any* qp = (u32x2_any*)q;
         const size_t nblock = n / 8;
         const size_t per = (nblock + gridDim.x - 1) / gridDim.x;
         const size_t lo = (size_t)blockIdx.x * per;
@@ -498,19 +493,21 @@ int launch_quantize_amax(const void* x, size_t n, int in_dtype, int fmt, const f
                          float* amax_out, hipStream_t stream)
 {
     unsigned* bits = (unsigned*)amax_out;
-    hipLaunchKernelGGL(store_u32_kernel, dim3(1), dim3(1), 0, stream, bits, 0u);
-    if (n == 0) return check_launch("quantize_amax init");
-    const bool vec = aligned16(x) && aligned16(q_out);
     // Measured (bf16, E4M3): up to a few hundred MB of output 512 workgroups (one atomic each) and
     // ordinary stores are best (2^28 elements: 134 us, against 142 with 16384 workgroups and 148 with
     // non-temporal stores); an output beyond the memory-side cache goes out non-temporally from many
-    // short runs (6.04 10^8 elements: 329 us against 367).
+    // short runs (6.04 10^8 elements: 329 us against 367).  Up to kAloneItems a single workgroup
+    // casts the tensor, which needs no cleared cell: one launch instead of two.
     const bool nts = n >= kStreamingStoreBytes;
-    const dim3 grid(vec ? grid_for((n / 16 + 3) / 4, nts ? kCastBlocks : 512) : grid_for(n, 2048));
+    const size_t items = n / 16;
+    const size_t per_lane = items < (size_t)kThreads * 512 ? 1 : items < (size_t)kThreads * 1024 ? 2 : 4;
+    const dim3 grid(items <= kAloneItems ? 1 : grid_for((items + per_lane - 1) / per_lane, nts ? kCastBlocks : 512));
+    if (grid.x > 1 || n == 0) hipLaunchKernelGGL(store_u32_kernel, dim3(1), dim3(1), 0, stream, bits, 0u);
+    if (n == 0) return check_launch("quantize_amax init");
 #define FP8MM_QA(DT, FMT)                                                                                                   \
     do {                                                                                                                    \
-        if (nts) hipLaunchKernelGGL((quantize_amax_kernel<DT, FMT, true>), grid, dim3(kThreads), 0, stream, x, n, scale_dev, q_out, bits, vec); \
-        else hipLaunchKernelGGL((quantize_amax_kernel<DT, FMT, false>), grid, dim3(kThreads), 0, stream, x, n, scale_dev, q_out, bits, vec);    \
+        if (nts) hipLaunchKernelGGL((quantize_amax_kernel<DT, FMT, true>), grid, dim3(kThreads), 0, stream, x, n, scale_dev, q_out, bits); \
+        else hipLaunchKernelGGL((quantize_amax_kernel<DT, FMT, false>), grid, dim3(kThreads), 0, stream, x, n, scale_dev, q_out, bits);    \
     } while (0)
     if (in_dtype == FP8_F32) { if (fmt == FP8_E4M3) FP8MM_QA(FP8_F32, FP8_E4M3); else FP8MM_QA(FP8_F32, FP8_E5M2); }
     else { if (fmt == FP8_E4M3) FP8MM_QA(FP8_BF16, FP8_E4M3); else FP8MM_QA(FP8_BF16, FP8_E5M2); }
@@ -522,9 +519,8 @@ int launch_quantize_sr(const void* x, size_t n, int in_dtype, int fmt, float sca
                        uint64_t seed, uint8_t* q_out, hipStream_t stream)
 {
     if (n == 0) return FP8_OK;
-    const bool vec = aligned16(x) && aligned16(q_out);
-    const dim3 grid(vec ? grid_for((n / 8 + 3) / 4, kCastBlocks) : grid_for(n, 2048));     // 4 blocks of 8 elements per lane
-    FP8MM_DISPATCH_DT_FMT(quantize_sr_kernel, grid, x, n, scale, scale_dev, (unsigned)seed, (unsigned)(seed >> 32), q_out, vec);
+    const dim3 grid(grid_for((n / 8 + 3) / 4, kCastBlocks));     // 4 blocks of 8 elements per lane
+    FP8MM_DISPATCH_DT_FMT(quantize_sr_kernel, grid, x, n, scale, scale_dev, (unsigned)seed, (unsigned)(seed >> 32), q_out);
     return check_launch("quantize_sr");
 }
 

@@ -87,3 +87,31 @@ def test_small_tiles_at_their_edges(M, N, K, off, transA, transB):
                 assert np.array_equal(D.double().cpu().numpy(), torch.from_numpy(c_ref).to(dtype).double().numpy())
             assert bool((buf[:8] == 9).all()) and bool((buf[8 + M * N:] == 9).all())
             assert float(amax.item()) == float(np.max(np.abs(c_ref)))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,off", [(1, 0), (7, 1), (15, 1), (16, 0), (4095, 3), (16 * 2048, 0), (16 * 2048 + 1, 1), (32 * 1024 + 5, 1), (262144 + 9, 0), (1048576 * 4 + 3, 1)])
+def test_flat_casts_at_any_length_and_address(n, off, dtype):
+    """amax and factor, plain cast, cast + amax, stochastic cast and back, on tensors that start
+    anywhere and end inside a vector, an item or a chunk."""
+    x, host = source(n, dtype, off, seed=n)
+    ws = torch.zeros(fp8.FP8_AMAX_WORKSPACE_BYTES // 4, dtype=torch.int32, device="cuda")
+    amax, scale, amax2 = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda"), torch.full((1,), -1.0, device="cuda")
+    for _ in range(2):
+        fp8.fp8_amax_scale(x, E5M2, amax, scale, ws)
+    a_ref = oracle.amax(host)
+    s_ref = oracle.scale_from_amax(a_ref, E5M2)
+    bufs = [inside(n, off) for _ in range(3)]
+    fp8.fp8_quantize_dscale(x, E5M2, scale, bufs[0][1])
+    fp8.fp8_quantize_amax(x, E5M2, scale, bufs[1][1], amax2)
+    fp8.fp8_quantize_sr(x, E5M2, scale, 77, bufs[2][1])
+    back = torch.full((n + 2,), 5.0, device="cuda")
+    fp8.fp8_dequantize(bufs[0][1], E5M2, scale, back[1:1 + n])
+    torch.cuda.synchronize()
+    assert np.float32(amax.item()) == a_ref and np.float32(scale.item()) == s_ref and np.float32(amax2.item()) == a_ref
+    want = oracle.quantize(host, E5M2, s_ref)
+    assert np.array_equal(bufs[0][1].cpu().numpy(), want) and np.array_equal(bufs[1][1].cpu().numpy(), want)
+    assert np.array_equal(bufs[2][1].cpu().numpy(), oracle.quantize_sr(host, E5M2, s_ref, 77))
+    assert np.array_equal(back[1:1 + n].cpu().numpy(), oracle.dequantize(want, E5M2, s_ref).astype(np.float32))
+    assert back[0].item() == 5.0 and back[n + 1].item() == 5.0
+    assert all(guards_hold(b, n, off) for b, _ in bufs)
