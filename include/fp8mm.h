@@ -373,12 +373,11 @@ int fp8_gemm_fused(const uint8_t* A, int fmtA, int transA, const uint8_t* B, int
 /*
  * fp8_scaled_gemm -- the whole of Section 2's scheme for one product in ONE call: per-tensor amax and
  * factor of both operands (fmt_max / amax), their casts to FP8, the FP8 x FP8 product with
- * single-precision accumulation, and the factors taken out once per output.  It issues exactly the
- * launches of fp8_amax_scale_multi, fp8_quantize_multi and fp8_gemm_ex (factors read from scale_out)
- * in that order on `stream`, so every result is theirs bit for bit; what it saves is the host time
- * between three short dependent launches (4096 x 6144 x 2048: 0.147 - 0.155 -> 0.128 - 0.142 ms per step
- * over hosts; replaying the launches from a captured HIP graph, which a caller can do with either
- * form, gives 0.118).
+ * single-precision accumulation, and the factors taken out once per output.  It does on `stream` what
+ * fp8_amax_scale_multi, fp8_quantize_multi and fp8_gemm_ex (factors read from scale_out) do in that
+ * order, and every result is theirs bit for bit; what it saves is the host time between short dependent
+ * launches, and for operands of up to 2.5 MB together one of the launches (amax and cast read them once:
+ * 256 x 256 x 256 from fp32 18 -> 9.2 us a call).
  *   a, b        the operands in the wide type in_dtype, stored as fp8_gemm_ex stores A and B
  *               (a: M x K, or K x M if transA; b: K x N, or N x K if transB); alignment as for fp8_amax
  *   fmtA, fmtB  FP8 formats the operands are cast to

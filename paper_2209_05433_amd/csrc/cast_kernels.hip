@@ -10,6 +10,8 @@
 #include "fp8_encode.hpp"
 #include "cast_common.hpp"
 
+#include <algorithm>
+
 namespace fp8mm {
 namespace {
 
@@ -261,6 +263,134 @@ __global__ __launch_bounds__(kThreads) void quantize_multi_kernel(MultiTensors m
     else quantize_vec_body<DT, FP8_E5M2, PATH, false>(m.x[t], m.n[t], scale_dev[t], m.q[t], bid, grid);
 }
 
+// ------------------------------------------------------------------------------------------
+// amax, factor and cast of small tensors (up to kMultiMax of them) in ONE launch that reads them once
+// (fp8_scaled_gemm).  Two launches on operands of this size cost what launches cost, on the host and
+// between the kernels; here a workgroup keeps its chunk of 64 KB in registers while the maxima of all
+// chunks of the tensor meet in the workspace, and casts it from there:
+//   - workgroup b leaves its maximum in slot b and reads the others until all are there.  A slot holds
+//     the maximum with bit 31 set (maxima have it clear), so the value is its own flag: one store and
+//     one load per lane of a wave, agent-scope atomics both, no other data is exchanged through memory;
+//   - nobody has to be resident for anybody else to finish: a workgroup that has waited kPatience
+//     computes the maxima that are missing itself, from the tensor;
+//   - the last workgroup to have read the slots clears them for the next call.
+// Measured, amax + cast of both operands, two launches -> one: 0.5 MB of fp32 6.9 -> 3.8 us, 1 MB of bf16 7.4
+// -> 5.0.  The exchange takes longer the more workgroups take part (4 MB: 7.9 -> 9.1; 42 MB: 20.4 -> 22 - 25 with
+// chunks of 32 ... 256 KB), where two launches are the better form: their second read comes out of the
+// memory-side cache.
+// ------------------------------------------------------------------------------------------
+constexpr int kCastThreads = 512, kCastVecs = 8;                     // a chunk: 8 vectors per lane
+constexpr size_t kCastChunk = (size_t)kCastThreads * kCastVecs;      // vectors
+constexpr size_t kOneLaunchBytes = (size_t)5 << 19;                  // input up to which one launch is the better form: 2.5 MB
+constexpr unsigned kCastDone = kTicketPartials + kAmaxBlocks;        // workspace word: workgroups that have read all slots
+constexpr unsigned kCastSlots = kCastDone + 32;                      // ... and the slots (nothing else uses these words)
+constexpr unsigned long long kPatience = 20000;                      // ticks of the 100 MHz clock: 200 us
+static_assert(kOneLaunchBytes / (16 * kCastChunk) + 1 <= 64 && (kCastSlots + 64) * sizeof(unsigned) <= FP8_AMAX_WORKSPACE_BYTES, "a slot per lane");
+
+// Packed running maximum of vectors (vec_mag_max) -> fp32 bits.
+template <int DT>
+__device__ __forceinline__ unsigned packed_to_bits(unsigned run)
+{
+    if (DT == FP8_F32) return run;
+    const u16x2 p = __builtin_bit_cast(u16x2, run);
+    return (unsigned)(p.x > p.y ? p.x : p.y) << 16;
+}
+
+// The vectors of chunk b that the thread holds (zeros where there are none), and its tail element if it has one
+// (the elements behind the last whole vector belong to the last chunk): their largest magnitude.
+template <int DT>
+__device__ __forceinline__ unsigned load_chunk(const void* x, size_t n, size_t b, bool tail, u32x4 (&v)[kCastVecs])
+{
+    const u32x4_any* xv = (const u32x4_any*)x;
+    const size_t nvec = n / Elem<DT>::per_vec;
+    unsigned run = 0;
+#pragma unroll
+    for (int k = 0; k < kCastVecs; ++k) {
+        const size_t i = b * kCastChunk + threadIdx.x + (size_t)k * kCastThreads;
+        v[k] = (u32x4){0u, 0u, 0u, 0u};
+        if (i < nvec) v[k] = xv[i];
+    }
+#pragma unroll
+    for (int k = 0; k < kCastVecs; ++k) run = vec_mag_max<DT>(v[k], run);
+    const size_t t = nvec * Elem<DT>::per_vec + threadIdx.x;
+    const unsigned r = packed_to_bits<DT>(run);
+    return tail && t < n ? max(r, scalar_mag<DT>(x, t)) : r;
+}
+
+template <int DT, int FMT>
+__device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_t n, uint8_t* __restrict__ q, float* __restrict__ amax_out,
+                                               float* __restrict__ scale_out, unsigned* __restrict__ ws, unsigned bid, unsigned grid)
+{
+    constexpr int VPI = DT == FP8_BF16 ? 2 : 4;              // vectors that make 16 elements
+    u32x4 v[kCastVecs];
+    const unsigned own = block_max_u32<kCastThreads>(load_chunk<DT>(x, n, bid, bid == grid - 1, v));
+    __shared__ unsigned largest;
+    __shared__ unsigned long long absent;                    // chunks whose maximum has not come
+    __shared__ bool last;
+    if (threadIdx.x < 64) {
+        const unsigned l = threadIdx.x;
+        if (l == 0 && grid > 1) __hip_atomic_store(&ws[kCastSlots + bid], own | 0x80000000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long began = wall_clock64();
+        unsigned p = l == 0 && grid == 1 ? own | 0x80000000u : l < grid ? 0u : 0x80000000u;
+        while (!(p >> 31)) {
+            p = __hip_atomic_load(&ws[kCastSlots + l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (wall_clock64() - began > kPatience) break;
+        }
+        const unsigned long long here = __ballot(p >> 31);
+        unsigned m = p & 0x7fffffffu;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, d, 64));
+        if (l == 0) {
+            largest = m;
+            absent = ~here;
+            last = grid > 1 && __hip_atomic_fetch_add(&ws[kCastDone], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == grid - 1;
+        }
+    }
+    __syncthreads();
+    for (unsigned long long left = absent; left; left &= left - 1) {       // (never, unless the chip was busy for kPatience)
+        const unsigned b = (unsigned)__builtin_ctzll(left);
+        u32x4 other[kCastVecs];
+        const unsigned m = block_max_u32<kCastThreads>(load_chunk<DT>(x, n, b, b == grid - 1, other));
+        if (threadIdx.x == 0) largest = max(largest, m);
+        __syncthreads();
+    }
+    const float a = as_f32(largest), s = scale_rule(a, FMT);
+    if (bid == 0 && threadIdx.x == 0) { *amax_out = a; *scale_out = s; }
+    const size_t nvec = n / Elem<DT>::per_vec, first = bid * kCastChunk + threadIdx.x;
+    typename Piece<DT>::type* qp = (typename Piece<DT>::type*)q;
+#pragma unroll
+    for (int g = 0; g < kCastVecs / VPI; ++g) {
+        u32x4 item[VPI];
+        float y[16];
+#pragma unroll
+        for (int k = 0; k < VPI; ++k) item[k] = v[g * VPI + k];
+        scale_item<DT>(item, s, y);
+        const u32x4 o = encode16<FMT, kCastCvt>(y);
+#pragma unroll
+        for (int k = 0; k < VPI; ++k) {
+            const size_t i = first + (size_t)(g * VPI + k) * kCastThreads;
+            if (i < nvec) qp[i] = Piece<DT>::of(o, k);
+        }
+    }
+    const size_t t = nvec * Elem<DT>::per_vec + threadIdx.x;
+    if (bid == grid - 1 && t < n) q[t] = (uint8_t)encode_bits<FMT>(load_scalar<DT>(x, t) * s);
+    if (last && threadIdx.x < 64) {
+        if (threadIdx.x < grid) __hip_atomic_store(&ws[kCastSlots + threadIdx.x], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) __hip_atomic_store(&ws[kCastDone], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+template <int DT>
+__global__ __launch_bounds__(kCastThreads) void amax_cast_kernel(MultiTensors m, float* __restrict__ amax_out, float* __restrict__ scale_out,
+                                                                unsigned* __restrict__ ws)
+{
+    const int t = multi_find(m, blockIdx.x);
+    const unsigned bid = blockIdx.x - m.first[t], grid = m.first[t + 1] - m.first[t];
+    unsigned* w = ws + (size_t)t * (FP8_AMAX_WORKSPACE_BYTES / 4);
+    if (m.fmt[t] == FP8_E4M3) amax_cast_body<DT, FP8_E4M3>(m.x[t], m.n[t], m.q[t], amax_out + t, scale_out + t, w, bid, grid);
+    else amax_cast_body<DT, FP8_E5M2>(m.x[t], m.n[t], m.q[t], amax_out + t, scale_out + t, w, bid, grid);
+}
+
 }  // namespace
 
 namespace {
@@ -491,6 +621,37 @@ int launch_quantize_multi(int count, const void* const* x, const size_t* n, int 
         else hipLaunchKernelGGL((quantize_multi_kernel<FP8_BF16, kCastBits>), dim3(total), dim3(kThreads), 0, stream, m, scale_dev);
     }
     return check_launch("quantize_multi");
+}
+
+// amax, factors and casts of `count` tensors: one launch where the tensors are small (see amax_cast_kernel), else
+// the two launches of the multi-tensor forms.
+int launch_amax_cast(int count, const void* const* x, const size_t* n, int in_dtype, const int* fmt, float* amax_out, float* scale_out,
+                     void* workspace, uint8_t* const* q_out, hipStream_t stream)
+{
+    const size_t esz = in_dtype == FP8_F32 ? 4 : 2;
+    size_t bytes = 0;
+    bool one = cast_path() == kCastCvt;
+    for (int i = 0; i < count; ++i) {
+        one = one && n[i] > 0;
+        bytes += n[i] * esz;
+    }
+    if (!one || bytes > kOneLaunchBytes) {
+        if (int e = launch_amax_scale_multi(count, x, n, in_dtype, fmt, amax_out, scale_out, workspace, stream)) return e;
+        return launch_quantize_multi(count, x, n, in_dtype, fmt, scale_out, q_out, stream);
+    }
+    MultiTensors m{};
+    m.count = count;
+    unsigned total = 0;
+    for (int i = 0; i < count; ++i) {
+        m.x[i] = x[i]; m.q[i] = q_out[i]; m.n[i] = n[i]; m.fmt[i] = fmt[i]; m.first[i] = total;
+        total += (unsigned)std::max<size_t>(1, (n[i] * esz / 16 + kCastChunk - 1) / kCastChunk);
+    }
+    for (int i = count; i <= kMultiMax; ++i) m.first[i] = total;
+    if (in_dtype == FP8_F32)
+        hipLaunchKernelGGL(amax_cast_kernel<FP8_F32>, dim3(total), dim3(kCastThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace);
+    else
+        hipLaunchKernelGGL(amax_cast_kernel<FP8_BF16>, dim3(total), dim3(kCastThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace);
+    return check_launch("amax_cast");
 }
 
 }  // namespace fp8mm

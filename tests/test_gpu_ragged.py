@@ -115,3 +115,29 @@ def test_flat_casts_at_any_length_and_address(n, off, dtype):
     assert np.array_equal(back[1:1 + n].cpu().numpy(), oracle.dequantize(want, E5M2, s_ref).astype(np.float32))
     assert back[0].item() == 5.0 and back[n + 1].item() == 5.0
     assert all(guards_hold(b, n, off) for b, _ in bufs)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 3), (33, 65, 127), (256, 256, 256), (1, 100000, 7), (300, 5000, 300), (2049, 3000, 1025), (4096, 6144, 2048)])
+def test_one_call_equals_the_separate_calls_at_every_size_of_its_casts(M, N, K, dtype):
+    """fp8_scaled_gemm keeps operands of up to a chip's registers between amax and cast: every chunk
+    size, one and several workgroups per tensor, ends inside a vector, twice on one workspace (the first call
+    has to leave it as it found it), and a workspace the separate calls have used."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    a = torch.randn((M, K), device="cuda", generator=g).mul_(7.0).to(DTYPES[dtype])
+    b = torch.randn((K, N), device="cuda", generator=g).to(DTYPES[dtype])
+    a.view(-1)[-1] = 900.0                                # the largest values are the last ones
+    b.view(-1)[-1] = -300.0
+    new = lambda *shape, dt=torch.float32: torch.zeros(shape, dtype=dt, device="cuda")
+    ws = new(2 * fp8.FP8_AMAX_WORKSPACE_BYTES // 4, dt=torch.int32)
+    amax, scale, qa, qb, c = new(2), new(2), new(M, K, dt=torch.uint8), new(K, N, dt=torch.uint8), new(M, N)
+    fp8.fp8_amax_scale_multi((a, b), (E4M3, E5M2), amax, scale, ws)
+    fp8.fp8_quantize_multi((a, b), (E4M3, E5M2), scale, (qa, qb))
+    fp8.fp8_gemm_ex(qa, E4M3, False, qb, E5M2, False, c, scale[0:1], scale[1:2])
+    for _ in range(3):
+        amax1, scale1, qa1, qb1, c1 = new(2), new(2), new(M, K, dt=torch.uint8), new(K, N, dt=torch.uint8), new(M, N)
+        fp8.fp8_scaled_gemm(a, E4M3, False, b, E5M2, False, qa1, qb1, amax1, scale1, ws, c1)
+        torch.cuda.synchronize()
+        assert torch.equal(amax, amax1) and torch.equal(scale, scale1)
+        assert torch.equal(qa, qa1) and torch.equal(qb, qb1) and torch.equal(c, c1)
+    assert amax1.tolist() == [900.0, 300.0]
