@@ -141,3 +141,25 @@ def test_one_call_equals_the_separate_calls_at_every_size_of_its_casts(M, N, K, 
         assert torch.equal(amax, amax1) and torch.equal(scale, scale1)
         assert torch.equal(qa, qa1) and torch.equal(qb, qb1) and torch.equal(c, c1)
     assert amax1.tolist() == [900.0, 300.0]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows,cols,off", [(1, 1, 1), (37, 3, 0), (5, 8, 1), (18, 121, 0), (70, 515, 1), (9, 2053, 0), (6, 3001, 3), (3, 4099, 0), (2, 20001, 1), (4, 8192, 0), (65, 256, 0)])
+def test_rows_of_every_length(rows, cols, off, dtype):
+    """Row maxima, factors and cast in each form (lanes per row), rows that start anywhere and end inside a
+    vector; the largest value of a row is its last one."""
+    n = rows * cols
+    x, host = source(n, dtype, off, seed=rows)
+    x = x.view(rows, cols)
+    x[:, -1] = -500.0
+    host = (bf16_to_bits(x) if dtype == "bf16" else x.cpu().numpy()).reshape(rows, cols)
+    amax, scale = torch.full((rows,), -1.0, device="cuda"), torch.zeros(rows, device="cuda")
+    buf, q = inside(n, off)
+    fp8.fp8_amax_rows(x, amax)
+    fp8.fp8_scale_from_amax_n(amax, E4M3, scale)
+    fp8.fp8_quantize_rows(x, E4M3, scale, q.view(rows, cols))
+    torch.cuda.synchronize()
+    a_ref = oracle.amax_rows(host)
+    assert np.array_equal(amax.cpu().numpy(), a_ref)
+    assert np.array_equal(q.view(rows, cols).cpu().numpy(), oracle.quantize_rows(host, E4M3, oracle.scale_from_amax_n(a_ref, E4M3)))
+    assert guards_hold(buf, n, off)
