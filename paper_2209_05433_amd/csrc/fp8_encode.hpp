@@ -86,6 +86,14 @@ __device__ __forceinline__ unsigned encode4(float y0, float y1, float y2, float 
     return cvt_pair<FMT, true>(y2, y3, w);
 }
 
+// The same for values whose magnitudes are known to be at most the format's maximum.
+template <int FMT>
+__device__ __forceinline__ unsigned encode4_inside(float y0, float y1, float y2, float y3)
+{
+    if (FMT == FP8_E4M3) return (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(y2, y3, __builtin_amdgcn_cvt_pk_fp8_f32(y0, y1, 0, false), true);
+    return (unsigned)__builtin_amdgcn_cvt_pk_bf8_f32(y2, y3, __builtin_amdgcn_cvt_pk_bf8_f32(y0, y1, 0, false), true);
+}
+
 // Sixteen scaled values -> four dwords.  Converter path: one test for NaN/inf over all sixteen
 // (a single, almost never taken branch per item), then eight packed conversions.
 template <int FMT, int PATH>

@@ -35,8 +35,6 @@ struct EpilogueArgs {
     float* amax_out;              // null or one cell, zeroed by the launcher, raised with atomicMax
     int out_kind;
     int a_per_row, b_per_col;
-    int ragged_n;                 // set by the dispatcher for the tiled kernel: rows of C or the per-column
-                                  // factors do not start on 16-byte boundaries, outputs are stored one by one
 };
 
 struct GemmArgs {
@@ -87,7 +85,7 @@ int FP8MM_ANY_NAME(2)(const GemmArgs& g, bool wide);
 int FP8MM_ANY_NAME(3)(const GemmArgs& g, bool wide);
 
 // The tiled kernel instance for g's storage orders and accumulation mode, with g.tile_n, g.splits,
-// g.pairs_per_split and g.ep.ragged_n as given (the caller has checked that the tiled kernel takes
+// g.pairs_per_split as given (the caller has checked that the tiled kernel takes
 // the problem).
 int launch_tiled(const GemmArgs& g);
 

@@ -120,13 +120,21 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 namespace {
 
-// Microseconds for one tile of the tiled kernel, S stages of 64 along K (fitted to one-round and
-// three-round problems, 4096 x 4096 and 4096 x 6144 over K = 512 .. 8192).
+// Microseconds for one tile of the tiled kernel, S stages of 64 along K, as one of several rounds of 256 that
+// run at a time (fitted to 4096 x 6144 over K = 512 .. 2048 and to 3294 x 11648 x 4288; within 5 %).
 struct TileTimes { double wide, narrow; };
 TileTimes tile_times(int acc, double S)
 {
-    return acc == ACC_FP8 ? TileTimes{0.65 * S + 8.6, 0.37 * S + 4.7} : TileTimes{1.30 * S + 9.4, 0.70 * S + 5.8};
+    return acc == ACC_FP8 ? TileTimes{0.62 * S + 8.9, 0.46 * S + 5.2} : TileTimes{1.21 * S + 10.0, 0.79 * S + 6.4};
 }
+
+// The same for a 256 x 256 tile of the any-shape kernel, and the time of its 128 x 128 form, of which several
+// workgroups share a compute unit (4096 x 50257 x 2048, 6000 x 3000 x 1500; 2048 x 6144 x 2048, 1000 x 3000 x 1000).
+double any_wide_us(double M, double N, double K)
+{
+    return std::ceil(std::ceil(M / 256) * std::ceil(N / 256) / 256.0) * (5.0 + 1.95 * std::ceil(K / 64));
+}
+double any_128_us(double M, double N, double K) { return 5.0 + std::max(0.03 * K, 2.0 * M * N * K / 0.62e9); }
 
 // The form of the small-tile kernel (gemm_small.hip) that beats the kernel the problem would otherwise
 // take, or SMALL_NONE.  Times in microseconds, fitted to 25 shapes from 8 x 1104 x 768 to 2048 x 2048 x
@@ -147,7 +155,7 @@ int choose_small(const GemmArgs& g, bool tiled)
         other = std::min(std::ceil(units(256, 256)) * t.wide, std::ceil(units(256, 128)) * t.narrow);
         if (g.acc == ACC_FP8) other += 1.5;                  // (the fit is that much too short below S = 16)
     } else {
-        other = 5.0 + std::max(0.03 * K, 2.0 * M * N * K / 0.7e9);
+        other = std::min(any_128_us(M, N, K), any_wide_us(M, N, K));
     }
     const bool lines = !g.transA && g.transB;                // both operands contiguous along K
     const double t32 = 3.4 + std::max(0.001 * K, units(32, 32) * (0.3 + (lines ? 0.0014 : 0.0025) * K));
@@ -185,34 +193,29 @@ GemmPlan plan_gemm(const GemmArgs& g)
                       (g.transB || N % 16 == 0) && (!g.transA || M % 16 == 0);
     if (small_allowed) plan.small = choose_small(g, fast);
     if (!fast) return plan;
-    // Tile width.  One workgroup per compute unit (256 of them) runs at a time.  The 256 x 128
-    // tile sustains about 0.88 of the rate of the 256 x 256 tile (measured on 8192 x 49152 x
-    // 12288: 0.80-0.92 over the layouts and modes), so it is chosen when it fills the rounds of
-    // workgroups that much better (4096 x 6144: 384 wide tiles = 1.5 rounds, 768 narrow ones = 3).
-    // The knob FP8_KNOB_TILE_N = 128 | 256 overrides the choice.
-    auto fill = [&](int64_t bn) {
-        const int64_t tiles = ((M + TILE_M - 1) / TILE_M) * ((N + bn - 1) / bn);
-        return (double)tiles / (double)(((tiles + 255) / 256) * 256);
-    };
+    // Tile width.  One workgroup per compute unit (256 of them) runs at a time: the width whose rounds
+    // of workgroups take less time (4096 x 6144: 384 wide tiles = two rounds, the second half empty, 768
+    // narrow ones = three).  The knob FP8_KNOB_TILE_N = 128 | 256 overrides the choice.
+    const TileTimes tile = tile_times(g.acc, 2.0 * (double)((K + 2 * TILE_K - 1) / (2 * TILE_K)));
+    const int64_t tiles_m = (M + TILE_M - 1) / TILE_M, wide_cols_all = (N + TILE_N - 1) / TILE_N;
+    auto rounds = [&](int64_t tiles) { return (double)((tiles + 255) / 256); };
     const int tn = knob(FP8_KNOB_TILE_N);
-    const bool narrow = tn ? tn == 128 : 0.88 * fill(128) > fill(256);
+    const bool narrow = tn ? tn == 128 : rounds(tiles_m * ((N + 127) / 128)) * tile.narrow < rounds(tiles_m * wide_cols_all) * tile.wide;
     plan.kernel = narrow ? GEMM_TILED_128 : GEMM_TILED_256;
     plan.elementwise_stores = !c_lines;
     // Both widths in one launch (gemm_mixed_kernel): the first c tile columns of 256, the rest of N in
     // tiles of 128.  Chosen where a model of the run time says it beats the better single width by 3 %:
     // workgroups are handed to the 256 compute units in order, the wide ones first; a tile takes
-    // what tile_times() says, and the change of width costs 3 + 32 / S
-    // microseconds (measured: the mixed launch is that much slower than its two parts).  With these
-    // figures it pays for long K (4096 x 6144 x 8192: 4 % in the fp16 mode, 7 % in the FP8 mode) and
-    // not for short K, where the narrow tile is nearly as efficient as the wide one.  Problems of
+    // what tile_times() says, and the change of width costs 3 us and up to 350 / S more, the more the
+    // fuller the narrow tiles' last round is (4096 x 6144 over K = 2048 .. 8192, 3001 x 6144 x 2048).  With these
+    // figures it pays for long K (4096 x 6144 x 8192: 4 % in the fp16 mode, 7 % in the FP8 mode) and where
+    // the wide tiles fill little of their last round (3001 x 6144 x 2048: 3 - 7 %).  Problems of
     // more than 64 rounds are left alone (the last round is then under 2 %).
     // Knob FP8_KNOB_MIXED: 0 = by the model, 1 = never, 2 = wherever it is possible.
     const int mk = knob(FP8_KNOB_MIXED);
-    const int64_t tiles_m = (M + TILE_M - 1) / TILE_M, wide_cols_all = (N + TILE_N - 1) / TILE_N;
     if (!tn && mk != 1 && plan.small == SMALL_NONE && g.splits <= 1 && N > TILE_N && tiles_m * wide_cols_all <= 64 * 256) {
         const double S = 2.0 * (double)((K + 2 * TILE_K - 1) / (2 * TILE_K));
-        const double tw = tile_times(g.acc, S).wide, tnar = tile_times(g.acc, S).narrow;
-        const double change = 3.0 + 32.0 / S;
+        const double tw = tile.wide, tnar = tile.narrow;
         // time until the last of Tw wide and then Tn narrow tiles ends on 256 units
         auto makespan = [&](int64_t Tw, int64_t Tn) {
             const int64_t q = Tw / 256, k = Tw % 256;          // k units get q + 1 wide tiles, the others q
@@ -220,7 +223,7 @@ GemmPlan plan_gemm(const GemmArgs& g)
             double best = 1e300;
             for (int64_t r = 0; r <= Tn; ++r) {                // r narrow tiles on the units that are free first
                 const int64_t late = r * tnar >= tw ? (int64_t)((r * tnar - tw) / tnar) : 0;     // and as many as fit on the others
-                if ((256 - k) * r + k * late >= Tn) { best = (double)q * tw + (double)r * tnar; break; }
+                if ((256 - k) * r + k * late >= Tn) { best = std::max((double)(q + (k > 0)) * tw, (double)q * tw + (double)r * tnar); break; }
             }
             for (int64_t r = 1; r <= Tn; ++r) {                // or the last one ends on a unit that had q + 1 wide tiles
                 const int64_t early = (int64_t)((tw + r * tnar) / tnar);
@@ -233,7 +236,9 @@ GemmPlan plan_gemm(const GemmArgs& g)
         double best = 1e300;
         int64_t best_c = 0;
         for (int64_t c = 1; c * TILE_N < N; ++c) {
-            const double t = makespan(tiles_m * c, tiles_m * ((N - c * TILE_N + 127) / 128)) + change;
+            const int64_t Tn = tiles_m * ((N - c * TILE_N + 127) / 128);
+            const double change = 3.0 + 350.0 / S * (double)(Tn % 256 ? Tn % 256 : 256) / 256.0;
+            const double t = makespan(tiles_m * c, Tn) + change;
             if (t < best) { best = t; best_c = c; }
         }
         if (best_c > 0 && (mk == 2 || best < 0.97 * uniform)) {
@@ -268,18 +273,16 @@ bool mfma_any_takes(const GemmArgs& g)
     return g.M > 0 && g.N > 0 && g.K > 0 && tile_count(g, 128) <= 0x7fffffffll;
 }
 
-// The wide form where its 256 x 256 tiles fill the rounds of one workgroup per compute unit to
-// 80 % at least and K is long enough for the two-stage pipeline to pay; FP8_KNOB_TILE_N forces
+// The wide form where its 256 x 256 tiles take less time than the other's (from a fill of their rounds of
+// about 60 % on) and K is long enough for the two-stage pipeline to pay; FP8_KNOB_TILE_N forces
 // either form (128 / 256).
 bool mfma_any_wide(const GemmArgs& g)
 {
     const int forced = knob(FP8_KNOB_TILE_N);
-    const int64_t tiles = tile_count(g, 256), units = 256;
-    const int64_t rounds = (tiles + units - 1) / units;
     // 32-bit offsets within a tile's stage: 255 rows of K bytes, or 63 K-rows of M / N bytes
     if (g.K >= (1 << 24) || g.M >= (1 << 26) || g.N >= (1 << 26)) return false;
     if (forced) return forced == 256;
-    return g.K >= 512 && 5 * tiles >= 4 * rounds * units;
+    return g.K >= 512 && any_wide_us((double)g.M, (double)g.N, (double)g.K) < any_128_us((double)g.M, (double)g.N, (double)g.K);
 }
 
 int launch_mfma_any(const GemmArgs& g)
@@ -322,7 +325,6 @@ int launch_gemm(const GemmArgs& g)
     if (plan.kernel == GEMM_MFMA_ANY) return launch_mfma_any(g);
     if (plan.kernel != GEMM_GENERIC) {
         GemmArgs gt = g;
-        gt.ep.ragged_n = plan.elementwise_stores ? 1 : 0;
         gt.tile_n = plan.kernel == GEMM_TILED_128 ? 128 : 256;
         gt.wide_cols = plan.kernel == GEMM_TILED_MIXED ? plan.wide_cols : 0;
         gt.persist = plan.persistent;

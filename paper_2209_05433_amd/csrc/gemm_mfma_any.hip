@@ -23,7 +23,7 @@
 // 32 KB of LDS and about 100 registers per lane: several workgroups share a compute unit and hide
 // each other's barriers and load latencies; nothing in this form is pipelined by hand.  Problems of
 // many tiles take the wide form further down (256 x 256 tiles, one workgroup per compute unit).
-#include "gemm_common.hpp"
+#include "gemm_epilogue.hpp"
 
 #include <atomic>
 #include <type_traits>
@@ -31,11 +31,7 @@
 namespace fp8mm {
 namespace {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
-
-#define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 
 constexpr int FT = 128;                 // tile edge
 constexpr int FK = 64;                  // K per stage
@@ -368,7 +364,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_any_wide_kernel(
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];     // [stage parity][A image, B image]
     const int tid = threadIdx.x;
-    const int w = tid >> 6, l = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
     const int wm = w >> 1, wn = w & 1, r = l & 31, h = l >> 5;
     const int64_t tiles_m = (M + WT - 1) / WT, tiles_n = (N + WT - 1) / WT;
     int64_t tm, tn;
@@ -511,7 +507,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_any_wide_kernel(
     }
     if (st < stages) stage(std::false_type{}, 0, a0, b0);
 
-    store_outputs<4>(acc, C, M, N, m0 + wm * 128, n0 + wn * 128, r, h, ep);
+    __syncthreads();                                  // every wave is done with the images
+    store_tile<4>(acc, lds, ep, C, (int)M, (int)N, (int)m0, (int)n0, w);
 }
 
 template <int FA, int FB, bool A_KC, bool B_KC>

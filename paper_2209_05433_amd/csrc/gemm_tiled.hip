@@ -10,8 +10,7 @@
 // of 16 if B is stored K x N, M a multiple of 16 if A is stored K x M.  K is walked in pairs of
 // stages (128 bytes); where K is not a multiple of 128 the last pair is filled up with zero bytes.  M and N need not be
 // multiples of the tile: loads of rows / columns beyond the edge are redirected to existing ones,
-// their outputs are not stored.  Where the rows of C (or a per-column factor vector) do not start
-// on 16-byte boundaries the epilogue stores element by element (EpilogueArgs::ragged_n).
+// their outputs are not stored.
 //
 //   - one workgroup of 4 waves per 256 x 256 output tile, each wave owns 128 x 128 of it as
 //     4 x 4 blocks of v_mfma_f32_32x32x64_f8f6f4 (K = 64 per instruction, operand formats
@@ -44,7 +43,7 @@
 //     default): see the note at the ACC_* constants for why both exist.
 //
 // This file is compiled once per (storage orders, accumulation mode): -DFP8MM_LAYOUT, -DFP8MM_ACC.
-#include "gemm_common.hpp"
+#include "gemm_epilogue.hpp"
 
 #include <atomic>
 #include <type_traits>
@@ -54,13 +53,6 @@ namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-
-#define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 
 // ------------------------------------------------------------------------------------------
 // Fast kernel
@@ -237,122 +229,6 @@ __device__ __forceinline__ void read_part(const uint8_t* smem, const Operand& op
             f[blk][2 * s] = p.x; f[blk][2 * s + 1] = p.y;
         }
     }
-}
-
-// The epilogue of one wave: its 128 x 32 NB sub-tile of accumulators -> memory.
-//   c = acc * ra(row) [* cb(column)]: the reciprocal scales, applied once per output;
-//   amax of |c| (if asked for); conversion to the output kind; whole-line stores.
-// A lane holds 4 consecutive N of one C row per accumulator quad; written straight out that would
-// be small pieces scattered over 32 rows per instruction.  Instead the wave turns each 32 x 32 NB
-// block around through its own piece of the (now idle) LDS and stores it with 16 bytes per lane
-// along N: whole 128-byte lines (64-byte halves for FP8 outputs of the narrow tile).  Every output kind is
-// converted before the turn (FP8: multiplied by the output scale and rounded four at a time by the
-// routine of the cast kernels), so the turn moves 4, 2 or 1 bytes per output.
-template <int OUT, bool BVEC, int NB>
-__device__ __forceinline__ void epilogue(v16f (&acc)[NB][4], uint8_t* smem, const EpilogueArgs& ep, void* C, int M, int N,
-                                         int wave_m0, int wave_n0, int w, int l)
-{
-    constexpr bool FP8OUT = OUT == OUT_E4M3 || OUT == OUT_E5M2;
-    constexpr int ESZ = OUT == OUT_F32 ? 4 : OUT == OUT_BF16 ? 2 : 1;     // bytes per output in memory
-    constexpr int LSZ = ESZ;                                              // bytes per output in LDS
-    constexpr int WN = 32 * NB;                                           // columns of the wave's sub-tile
-    constexpr int ROWB = WN * LSZ + 16;                                   // padded LDS row of the wave's block
-    constexpr int ROWS_PER_ST = 1024 / (WN * ESZ);                        // C rows covered by one store instruction
-    const int h = l >> 5;
-
-    // reciprocal scales: per row in ra (with the per-tensor sB folded in), per column in cb
-    // (the by-value factors are copied out of the argument block first: a choice between two
-    // memory locations would force the block into scratch memory)
-    const float sA_host = ep.sA, sB_host = ep.sB;
-    float ra[4];
-    {
-        const double b = BVEC ? 1.0 : (double)scale_value(ep.sB_dev, sB_host);
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-            const float a = ep.a_per_row ? ep.sA_dev[min(wave_m0 + mb * 32 + (l & 31), M - 1)] : scale_value(ep.sA_dev, sA_host);
-            ra[mb] = (float)(1.0 / ((double)a * b));
-        }
-    }
-    v4f cb[BVEC ? NB : 1][BVEC ? 4 : 1];
-    if (BVEC) {
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int col = wave_n0 + nb * 32 + 8 * q + 4 * h;
-                v4f s;
-                if (ep.ragged_n) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) s[i] = ep.sB_dev[min(col + i, N - 1)];
-                } else {
-                    s = *(const v4f*)(ep.sB_dev + min(col, N - 4));
-                }
-                cb[BVEC ? nb : 0][BVEC ? q : 0] = (v4f){1.0f / s.x, 1.0f / s.y, 1.0f / s.z, 1.0f / s.w};
-            }
-    }
-    const float sD = FP8OUT ? scale_value(ep.sD_dev, 1.0f) : 1.0f;
-    unsigned amax_bits = 0;
-
-    uint8_t* blk = smem + w * (32 * ROWB);
-    uint8_t* c_wave = (uint8_t*)C + ((size_t)wave_m0 * N + wave_n0) * ESZ;
-    const int st_row = l / (64 / ROWS_PER_ST), st_col = (l % (64 / ROWS_PER_ST)) * 16;   // byte column in memory
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float c0 = acc[nb][mb][4 * q + 0] * ra[mb], c1 = acc[nb][mb][4 * q + 1] * ra[mb];
-                float c2 = acc[nb][mb][4 * q + 2] * ra[mb], c3 = acc[nb][mb][4 * q + 3] * ra[mb];
-                if (BVEC) {
-                    const v4f s = cb[BVEC ? nb : 0][BVEC ? q : 0];
-                    c0 *= s.x; c1 *= s.y; c2 *= s.z; c3 *= s.w;
-                }
-                if (ep.amax_out) {
-                    // outputs beyond the edges of C hold products of redirected loads: not counted
-                    // (unless N is ragged, the four columns are inside or outside together)
-                    const int col = wave_n0 + nb * 32 + 8 * q + 4 * h;
-                    const bool row_in = wave_m0 + mb * 32 + (l & 31) < M;
-                    const unsigned k0 = row_in && col < N ? 0x7fffffffu : 0u, k1 = row_in && col + 1 < N ? 0x7fffffffu : 0u;
-                    const unsigned k2 = row_in && col + 2 < N ? 0x7fffffffu : 0u, k3 = row_in && col + 3 < N ? 0x7fffffffu : 0u;
-                    const unsigned m01 = max(as_u32(c0) & k0, as_u32(c1) & k1);
-                    const unsigned m23 = max(as_u32(c2) & k2, as_u32(c3) & k3);
-                    amax_bits = max(amax_bits, max(m01, m23));
-                }
-                uint8_t* dst = blk + (l & 31) * ROWB + (nb * 32 + 8 * q + 4 * h) * LSZ;
-                if (OUT == OUT_F32) {
-                    *LDS_PTR(v4f, dst) = (v4f){c0, c1, c2, c3};
-                } else if (OUT == OUT_BF16) {
-                    v2i o;
-                    o.x = (int)__builtin_bit_cast(unsigned, __builtin_convertvector((v2f){c0, c1}, v2bf));
-                    o.y = (int)__builtin_bit_cast(unsigned, __builtin_convertvector((v2f){c2, c3}, v2bf));
-                    *LDS_PTR(v2i, dst) = o;
-                } else {
-                    *LDS_PTR(unsigned, dst) = encode4<OUT == OUT_E4M3 ? FP8_E4M3 : FP8_E5M2>(c0 * sD, c1 * sD, c2 * sD, c3 * sD);
-                }
-            }
-#pragma unroll
-        for (int i = 0; i < 32 / ROWS_PER_ST; ++i) {
-            const int row = i * ROWS_PER_ST + st_row;
-            uint8_t* out = c_wave + (size_t)(mb * 32 + row) * N * ESZ + st_col;
-            if (wave_m0 + mb * 32 + row >= M || wave_n0 + st_col / ESZ >= N) continue;   // beyond the edges of C
-            const u32x4 o = *LDS_PTR(u32x4, blk + row * ROWB + st_col);
-            if (!ep.ragged_n) {
-                *(u32x4*)out = o;                        // (non-temporal stores measured the same, 8 shapes)
-            } else {                                    // rows of C start anywhere: element by element
-                const int left = N - (wave_n0 + st_col / ESZ);          // columns from the lane's first one to the edge
-#pragma unroll
-                for (int e = 0; e < 16 / ESZ; ++e) {
-                    if (e < left) {
-                        if (ESZ == 4) ((unsigned*)out)[e] = o[e];
-                        else if (ESZ == 2) ((unsigned short*)out)[e] = (unsigned short)(o[e >> 1] >> (16 * (e & 1)));
-                        else out[e] = (uint8_t)(o[e >> 2] >> (8 * (e & 3)));
-                    }
-                }
-            }
-        }
-    }
-    if (ep.amax_out) wave_amax_commit(amax_bits, ep.amax_out);
 }
 
 // A_KC / B_KC: how the operand lies in memory (see Operand); NB: width of the tile in blocks of 32
@@ -844,28 +720,9 @@ __device__ __forceinline__ void gemm_tile_body(
         return;
     }
 
-    // ---- epilogue (wave-uniform choice of the output kind and of the scale granularity) --------
     __builtin_amdgcn_s_waitcnt(0xC07F);
     __builtin_amdgcn_s_barrier();                           // every wave is done with the operand slabs
-    const int wave_m0 = m0 + wm * 128, wave_n0 = n0 + wn * (32 * NB);
-    // The lane index is taken afresh from the execution mask count: values derived from the one
-    // computed before the K loop would have to stay in registers (or be spilled) all through it.
-    const int le = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    if (ep.b_per_col) {
-        switch (ep.out_kind) {
-            case OUT_F32: epilogue<OUT_F32, true, NB>(acc, smem, ep, C, M, N, wave_m0, wave_n0, w, le); break;
-            case OUT_BF16: epilogue<OUT_BF16, true, NB>(acc, smem, ep, C, M, N, wave_m0, wave_n0, w, le); break;
-            case OUT_E4M3: epilogue<OUT_E4M3, true, NB>(acc, smem, ep, C, M, N, wave_m0, wave_n0, w, le); break;
-            default: epilogue<OUT_E5M2, true, NB>(acc, smem, ep, C, M, N, wave_m0, wave_n0, w, le); break;
-        }
-    } else {
-        switch (ep.out_kind) {
-            case OUT_F32: epilogue<OUT_F32, false, NB>(acc, smem, ep, C, M, N, wave_m0, wave_n0, w, le); break;
-            case OUT_BF16: epilogue<OUT_BF16, false, NB>(acc, smem, ep, C, M, N, wave_m0, wave_n0, w, le); break;
-            case OUT_E4M3: epilogue<OUT_E4M3, false, NB>(acc, smem, ep, C, M, N, wave_m0, wave_n0, w, le); break;
-            default: epilogue<OUT_E5M2, false, NB>(acc, smem, ep, C, M, N, wave_m0, wave_n0, w, le); break;
-        }
-    }
+    store_tile<NB>(acc, smem, ep, C, M, N, m0, n0, w);
 }
 
 template <int FMT_A, int FMT_B, int ACC, bool A_KC, bool B_KC, int NB, bool PERSIST>
