@@ -185,9 +185,8 @@ GemmPlan plan_gemm(const GemmArgs& g)
     // needs: K a multiple of 16 (it walks K in pairs of stages of 64 and fills a last, partial pair
     // up with zeros; rows of a K-contiguous operand start every K bytes); 16-byte aligned operands;
     // rows of an N-contiguous B and of an M-contiguous A that start on 16-byte boundaries (N % 16, M % 16).  Rows of C (and a
-    // per-column factor vector) that do not start on 16-byte boundaries are served by the
-    // element-wise stores of the epilogue: with B stored N x K any N goes (a vocabulary-sized
-    // output layer, weights stored [out, in]).
+    // per-column factor vector) may start anywhere (the epilogue's stores go to any address): with
+    // B stored N x K any N goes (a vocabulary-sized output layer, weights stored [out, in]).
     const bool c_lines = N % 16 == 0 && aligned16(g.C) && (!g.ep.b_per_col || aligned16(g.ep.sB_dev));
     const bool fast = !force_generic() && !force_mfma_any() && aligned16(g.A) && aligned16(g.B) && fits32 && K % 16 == 0 &&
                       (g.transB || N % 16 == 0) && (!g.transA || M % 16 == 0);

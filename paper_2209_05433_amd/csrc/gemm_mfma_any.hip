@@ -22,7 +22,8 @@
 //   - the epilogue is that of the generic kernel, element by element (any N, any output alignment).
 // 32 KB of LDS and about 100 registers per lane: several workgroups share a compute unit and hide
 // each other's barriers and load latencies; nothing in this form is pipelined by hand.  Problems of
-// many tiles take the wide form further down (256 x 256 tiles, one workgroup per compute unit).
+// many tiles take the wide form further down (256 x 256 tiles, one workgroup per compute unit, the tiled
+// kernel's epilogue).
 #include "gemm_epilogue.hpp"
 
 #include <atomic>
@@ -125,7 +126,7 @@ __device__ __forceinline__ void tile_of(int64_t bid, int64_t tiles_m, int64_t ti
     tn = q / rows;
 }
 
-// Epilogue of both kernels: c = acc / (sA sB) element by element, as in the generic kernel (any N,
+// Epilogue of the 128 x 128 form: c = acc / (sA sB) element by element, as in the generic kernel (any N,
 // any output alignment).  acc[nb][mb] is the wave's block of 32 columns nb x 32 rows mb; wave_m /
 // wave_n = first row / column of the wave's part of C; lane (r, h) holds, per accumulator quad, 4
 // consecutive columns of row r of a block.
