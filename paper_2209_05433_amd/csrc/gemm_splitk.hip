@@ -105,7 +105,6 @@ int launch_gemm_splitk(const GemmArgs& g, const SplitPlan& sp, void* ws)
     part.ep = EpilogueArgs{};
     part.ep.sA = 1.0f; part.ep.sB = 1.0f;                   // the slices carry plain sums
     part.ep.out_kind = OUT_F32;
-    part.ep.ragged_n = (g.N % 4 != 0 || !aligned_to(ws, 16)) ? 1 : 0;
     part.tile_n = sp.tile_n;
     part.persist = false;
     part.splits = sp.splits;
