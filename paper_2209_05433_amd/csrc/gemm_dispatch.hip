@@ -115,6 +115,7 @@ bool force_generic() { return knob(FP8_KNOB_GEMM_KERNEL) == 1; }
 bool force_mfma_any() { return knob(FP8_KNOB_GEMM_KERNEL) == 2; }
 
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
+inline int64_t tile_count(const GemmArgs& g, int64_t edge) { return ((g.M + edge - 1) / edge) * ((g.N + edge - 1) / edge); }
 
 }  // namespace
 
@@ -173,8 +174,9 @@ GemmPlan plan_gemm(const GemmArgs& g)
 {
     const int64_t M = g.M, N = g.N, K = g.K;
     GemmPlan plan{!force_generic() && mfma_any_takes(g) ? GEMM_MFMA_ANY : GEMM_GENERIC, false, false, 0, SMALL_NONE};
-    // a knob that asks for another form of the kernels keeps the small one out
-    const bool small_allowed = g.splits <= 1 && !knob(FP8_KNOB_TILE_N) && !knob(FP8_KNOB_GEMM_KERNEL) && !knob(FP8_KNOB_MIXED) && !knob(FP8_KNOB_PERSIST);
+    // a knob that asks for another form of the kernels keeps the small one out, unless FP8_KNOB_SMALL names a form of it
+    const int small = g.splits <= 1 && !force_generic() ? knob(FP8_KNOB_SMALL) : 1;
+    const bool small_allowed = small == 0 && !knob(FP8_KNOB_TILE_N) && !knob(FP8_KNOB_GEMM_KERNEL) && !knob(FP8_KNOB_MIXED) && !knob(FP8_KNOB_PERSIST);
     const uint64_t ldmax = (uint64_t)(M > N ? (M > K ? M : K) : (N > K ? N : K));
     const bool fits32 = 256 * ldmax < (1ull << 32) && M < (1ll << 31) - TILE_M && N < (1ll << 31) - TILE_N &&
                         K < (1ll << 31) &&
@@ -191,6 +193,7 @@ GemmPlan plan_gemm(const GemmArgs& g)
     const bool fast = !force_generic() && !force_mfma_any() && aligned16(g.A) && aligned16(g.B) && fits32 && K % 16 == 0 &&
                       (g.transB || N % 16 == 0) && (!g.transA || M % 16 == 0);
     if (small_allowed) plan.small = choose_small(g, fast);
+    else if (small >= 2 && tile_count(g, 32) <= 0x7fffffffll) plan.small = SMALL_32x32 + small - 2;
     if (!fast) return plan;
     // Tile width.  One workgroup per compute unit (256 of them) runs at a time: the width whose rounds
     // of workgroups take less time (4096 x 6144: 384 wide tiles = two rounds, the second half empty, 768
@@ -260,13 +263,11 @@ GemmPlan plan_gemm(const GemmArgs& g)
                           !g.ep.a_per_row && !g.ep.b_per_col && g.ep.out_kind <= OUT_BF16 && !g.ep.amax_out && g.splits <= 1;
     const bool pays = tiles > 256 && (g.ep.out_kind == OUT_F32 ? K <= 64 * TILE_K
                                                                : g.acc == ACC_F16 && K >= 16 * TILE_K && K <= 32 * TILE_K);
-    plan.persistent = possible && pk != 1 && (pk == 2 || pays);
+    plan.persistent = possible && plan.small == SMALL_NONE && pk != 1 && (pk == 2 || pays);
     return plan;
 }
 
 // ---- the matrix-core kernel for any shape (gemm_mfma_any.hip) ------------------------------------
-static int64_t tile_count(const GemmArgs& g, int64_t edge) { return ((g.M + edge - 1) / edge) * ((g.N + edge - 1) / edge); }
-
 bool mfma_any_takes(const GemmArgs& g)
 {
     return g.M > 0 && g.N > 0 && g.K > 0 && tile_count(g, 128) <= 0x7fffffffll;

@@ -221,3 +221,20 @@ def test_bench_refuses_more_than_one_gpu():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode == 2 and "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_knob_of_the_small_tiles():
+    """FP8_KNOB_SMALL takes its five values; a plan does not name the persistent form for a call that runs small tiles."""
+    assert fp8.fp8_get_knob(fp8.FP8_KNOB_SMALL) == 0
+    for bad in (-1, 5):
+        with pytest.raises(fp8.Fp8Error):
+            fp8.fp8_set_knob(fp8.FP8_KNOB_SMALL, bad)
+    A, B, C = 1 << 20, 1 << 30, 1 << 34
+    plan = lambda: fp8.lib().fp8_gemm_plan(A, 0, B, 0, C, 4096, 6144, 2048, None)
+    try:
+        for value, persistent in ((0, True), (1, True), (2, False), (3, False), (4, False)):
+            fp8.fp8_set_knob(fp8.FP8_KNOB_SMALL, value)
+            assert fp8.fp8_get_knob(fp8.FP8_KNOB_SMALL) == value
+            assert plan() == fp8.FP8_PLAN_TILED_256x128 | (fp8.FP8_PLAN_PERSISTENT if persistent else 0)
+    finally:
+        fp8.fp8_set_knob(fp8.FP8_KNOB_SMALL, 0)

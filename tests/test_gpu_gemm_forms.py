@@ -1,0 +1,63 @@
+"""Every form of the matrix-core kernels through the products that the dispatcher would send to one of
+them: each form is pinned by knobs, so that a later change of the dispatcher's rules leaves it covered.
+The checks are those of the tests that run at default knobs (test_gpu_gemm, test_gpu_gemm_fused,
+test_gpu_ragged), against the oracle."""
+import contextlib
+
+import pytest
+
+import paper_2209_05433_amd as fp8
+import test_gpu_gemm as gemm
+import test_gpu_gemm_fused as fused
+import test_gpu_ragged as ragged
+from gpu_util import knob
+
+pytestmark = pytest.mark.gpu
+
+TILE_N, KERNEL, SMALL = fp8.FP8_KNOB_TILE_N, fp8.FP8_KNOB_GEMM_KERNEL, fp8.FP8_KNOB_SMALL
+SMALL_FORMS = {"32x32": {SMALL: 2}, "32x64": {SMALL: 3}, "64x64": {SMALL: 4}}
+# (a problem that the tiled kernel does not take runs on the any-shape form of the same width)
+FORMS = {"tiled 256": {TILE_N: 256}, "tiled 128": {TILE_N: 128}, "any 256": {KERNEL: 2, TILE_N: 256}, "any 128": {KERNEL: 2, TILE_N: 128}, **SMALL_FORMS}
+
+
+@contextlib.contextmanager
+def pinned(knobs):
+    with contextlib.ExitStack() as stack:
+        for which, value in knobs.items():
+            stack.enter_context(knob(which, value))
+        yield
+
+
+# Beside the sizes of the default test: several trips of every wave along K and a remainder, and a
+# row-contiguous operand whose rows are shorter than a vector
+EDGES = ragged.SMALL + [(9, 70, 5000, 0), (130, 12, 4133, 3), (12, 200, 4133, 2), (200, 330, 6200, 1), (64, 64, 256, 1)]
+
+
+@pytest.mark.parametrize("form", sorted(SMALL_FORMS))
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K,off", EDGES)
+def test_small_forms_at_their_edges(M, N, K, off, transA, transB, form):
+    with pinned(SMALL_FORMS[form]):
+        ragged.test_small_tiles_at_their_edges(M, N, K, off, transA, transB)
+
+
+@pytest.mark.parametrize("form", sorted(FORMS))
+@pytest.mark.parametrize("mode", fused.MODES)
+def test_outputs_of_every_form(mode, form):
+    """Special values and output maxima with NaN, FP8 outputs below and beyond the format's maximum, factors per
+    row and column, sums that are exact."""
+    with pinned(FORMS[form]):
+        fused.test_fp8_output_special_values_and_amax_nan(mode)
+        for kind in (fp8.FP8_OUT_E4M3, fp8.FP8_OUT_E5M2):
+            fused.test_fp8_output_with_output_scale_and_amax(kind, mode)
+            fused.test_fp8_output_is_the_oracle_byte_where_sums_are_exact(kind, mode)
+        for a_vec in (0, 1):
+            for b_vec in (0, 1):
+                fused.test_per_channel_scales(a_vec, b_vec, mode)
+        gemm.test_one_hot_probes_over_a_multi_tile_problem(mode)
+        gemm.test_non_finite_operands_keep_their_class(mode)
+        for fmtA, fmtB in gemm.MIXES:
+            gemm.test_random_codes_all_format_mixes(fmtA, fmtB, fp8.FP8_F32, mode)
+    if mode == "f16":
+        with pinned(FORMS[form]):
+            fused.test_per_channel_scales_are_not_swapped_or_shifted()
