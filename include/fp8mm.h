@@ -451,10 +451,13 @@ int fp8_gemm_plan(const uint8_t* A, int transA, const uint8_t* B, int transB, co
  *                         (and no knob asks for another kernel, tile width or form), 1 never (fp8_gemm_plan
  *                         then names the kernel that runs), 2 / 3 / 4 always, with tiles of 32 x 32 /
  *                         32 x 64 / 64 x 64 (FP8MM_SMALL)
+ *   FP8_KNOB_PATIENCE     the one-launch amax + cast of fp8_scaled_gemm: 0 a workgroup waits 200 us for the other
+ *                         workgroups' maxima before it computes the missing ones itself, 1 it does not wait
+ *                         (FP8MM_PATIENCE)
  */
 typedef enum { FP8_KNOB_CAST_PATH = 0, FP8_KNOB_TILE_N = 1, FP8_KNOB_GROUP_M = 2, FP8_KNOB_GEMM_KERNEL = 3,
                FP8_KNOB_SPLIT_K = 4, FP8_KNOB_CAST_RUN = 5, FP8_KNOB_PERSIST = 6, FP8_KNOB_MIXED = 7,
-               FP8_KNOB_SMALL = 8, FP8_KNOB_COUNT = 9 } fp8_knob_t;
+               FP8_KNOB_SMALL = 8, FP8_KNOB_PATIENCE = 9, FP8_KNOB_COUNT = 10 } fp8_knob_t;
 int fp8_set_knob(int knob, int value);
 int fp8_get_knob(int knob);
 

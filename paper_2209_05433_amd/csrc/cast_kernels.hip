@@ -273,7 +273,9 @@ __global__ __launch_bounds__(kThreads) void quantize_multi_kernel(MultiTensors m
 //     one load per lane of a wave, agent-scope atomics both, no other data is exchanged through memory;
 //   - nobody has to be resident for anybody else to finish: a workgroup that has waited kPatience
 //     computes the maxima that are missing itself, from the tensor;
-//   - the last workgroup to have read the slots clears them for the next call.
+//   - the last workgroup to have read the slots clears them for the next call.  A workgroup that gave up has
+//     not seen its own maximum arrive: it is waited for before the workgroup counts itself among the readers, or it
+//     could land behind the clearing.
 // Measured, amax + cast of both operands, two launches -> one: 0.5 MB of fp32 6.9 -> 3.8 us, 1 MB of bf16 7.4
 // -> 5.0.  The exchange takes longer the more workgroups take part (4 MB: 7.9 -> 9.1; 42 MB: 20.4 -> 22 - 25 with
 // chunks of 32 ... 256 KB), where two launches are the better form: their second read comes out of the
@@ -284,7 +286,7 @@ constexpr size_t kCastChunk = (size_t)kCastThreads * kCastVecs;      // vectors
 constexpr size_t kOneLaunchBytes = (size_t)5 << 19;                  // input up to which one launch is the better form: 2.5 MB
 constexpr unsigned kCastDone = kTicketPartials + kAmaxBlocks;        // workspace word: workgroups that have read all slots
 constexpr unsigned kCastSlots = kCastDone + 32;                      // ... and the slots (nothing else uses these words)
-constexpr unsigned long long kPatience = 20000;                      // ticks of the 100 MHz clock: 200 us
+constexpr unsigned kPatience = 20000;                                // ticks of the 100 MHz clock: 200 us
 static_assert(kOneLaunchBytes / (16 * kCastChunk) + 1 <= 64 && (kCastSlots + 64) * sizeof(unsigned) <= FP8_AMAX_WORKSPACE_BYTES, "a slot per lane");
 
 // Packed running maximum of vectors (vec_mag_max) -> fp32 bits.
@@ -319,7 +321,7 @@ __device__ __forceinline__ unsigned load_chunk(const void* x, size_t n, size_t b
 
 template <int DT, int FMT>
 __device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_t n, uint8_t* __restrict__ q, float* __restrict__ amax_out,
-                                               float* __restrict__ scale_out, unsigned* __restrict__ ws, unsigned bid, unsigned grid)
+                                               float* __restrict__ scale_out, unsigned* __restrict__ ws, unsigned bid, unsigned grid, unsigned patience)
 {
     constexpr int VPI = DT == FP8_BF16 ? 2 : 4;              // vectors that make 16 elements
     u32x4 v[kCastVecs];
@@ -334,8 +336,11 @@ __device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_
         unsigned p = l == 0 && grid == 1 ? own | 0x80000000u : l < grid ? 0u : 0x80000000u;
         while (!(p >> 31)) {
             p = __hip_atomic_load(&ws[kCastSlots + l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (wall_clock64() - began > kPatience) break;
+            if (wall_clock64() - began > patience) break;
         }
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_s_waitcnt(0x0070);                  // vmcnt(0): the own maximum has been acknowledged
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
         const unsigned long long here = __ballot(p >> 31);
         unsigned m = p & 0x7fffffffu;
 #pragma unroll
@@ -382,13 +387,13 @@ __device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_
 
 template <int DT>
 __global__ __launch_bounds__(kCastThreads) void amax_cast_kernel(MultiTensors m, float* __restrict__ amax_out, float* __restrict__ scale_out,
-                                                                unsigned* __restrict__ ws)
+                                                                unsigned* __restrict__ ws, unsigned patience)
 {
     const int t = multi_find(m, blockIdx.x);
     const unsigned bid = blockIdx.x - m.first[t], grid = m.first[t + 1] - m.first[t];
     unsigned* w = ws + (size_t)t * (FP8_AMAX_WORKSPACE_BYTES / 4);
-    if (m.fmt[t] == FP8_E4M3) amax_cast_body<DT, FP8_E4M3>(m.x[t], m.n[t], m.q[t], amax_out + t, scale_out + t, w, bid, grid);
-    else amax_cast_body<DT, FP8_E5M2>(m.x[t], m.n[t], m.q[t], amax_out + t, scale_out + t, w, bid, grid);
+    if (m.fmt[t] == FP8_E4M3) amax_cast_body<DT, FP8_E4M3>(m.x[t], m.n[t], m.q[t], amax_out + t, scale_out + t, w, bid, grid, patience);
+    else amax_cast_body<DT, FP8_E5M2>(m.x[t], m.n[t], m.q[t], amax_out + t, scale_out + t, w, bid, grid, patience);
 }
 
 }  // namespace
@@ -647,10 +652,11 @@ int launch_amax_cast(int count, const void* const* x, const size_t* n, int in_dt
         total += (unsigned)std::max<size_t>(1, (n[i] * esz / 16 + kCastChunk - 1) / kCastChunk);
     }
     for (int i = count; i <= kMultiMax; ++i) m.first[i] = total;
+    const unsigned patience = knob(FP8_KNOB_PATIENCE) ? 0 : kPatience;
     if (in_dtype == FP8_F32)
-        hipLaunchKernelGGL(amax_cast_kernel<FP8_F32>, dim3(total), dim3(kCastThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace);
+        hipLaunchKernelGGL(amax_cast_kernel<FP8_F32>, dim3(total), dim3(kCastThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace, patience);
     else
-        hipLaunchKernelGGL(amax_cast_kernel<FP8_BF16>, dim3(total), dim3(kCastThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace);
+        hipLaunchKernelGGL(amax_cast_kernel<FP8_BF16>, dim3(total), dim3(kCastThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace, patience);
     return check_launch("amax_cast");
 }
 

@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import paper_2209_05433_amd as fp8
-from gpu_util import bf16_to_bits
+from gpu_util import bf16_to_bits, knob
 
 pytestmark = pytest.mark.gpu
 
@@ -120,8 +120,7 @@ def test_flat_casts_at_any_length_and_address(n, off, dtype):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 3), (33, 65, 127), (256, 256, 256), (1, 100000, 7), (300, 5000, 300), (2049, 3000, 1025), (4096, 6144, 2048)])
 def test_one_call_equals_the_separate_calls_at_every_size_of_its_casts(M, N, K, dtype):
-    """fp8_scaled_gemm keeps operands of up to a chip's registers between amax and cast: every chunk
-    size, one and several workgroups per tensor, ends inside a vector, twice on one workspace (the first call
+    """fp8_scaled_gemm keeps operands of up to 2.5 MB together in registers between amax and cast: one and several workgroups per tensor, ends inside a vector, twice on one workspace (the first call
     has to leave it as it found it), and a workspace the separate calls have used."""
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
     a = torch.randn((M, K), device="cuda", generator=g).mul_(7.0).to(DTYPES[dtype])
@@ -141,6 +140,31 @@ def test_one_call_equals_the_separate_calls_at_every_size_of_its_casts(M, N, K, 
         assert torch.equal(amax, amax1) and torch.equal(scale, scale1)
         assert torch.equal(qa, qa1) and torch.equal(qb, qb1) and torch.equal(c, c1)
     assert amax1.tolist() == [900.0, 300.0]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("M,N,K", [(300, 1000, 300), (515, 129, 513), (1, 40000, 7)])
+def test_one_launch_casts_without_waiting(M, N, K, dtype):
+    """A workgroup of the one-launch amax and cast that stops waiting takes the missing maxima from the tensor: with no
+    wait at all, several workgroups per tensor and ends inside a vector, on one workspace again and again;
+    maxima, factors and bytes are the oracle's and the workspace is left cleared."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    a = torch.randn((M, K), device="cuda", generator=g).to(DTYPES[dtype])
+    b = torch.randn((K, N), device="cuda", generator=g).to(DTYPES[dtype])
+    a.view(-1)[-1], b.view(-1)[0] = 900.0, -300.0
+    hosts = [bf16_to_bits(t).reshape(t.shape) if dtype == "bf16" else t.cpu().numpy() for t in (a, b)]
+    ws = torch.zeros(2 * fp8.FP8_AMAX_WORKSPACE_BYTES // 4, dtype=torch.int32, device="cuda")
+    amax, scale, c = torch.zeros(2, device="cuda"), torch.zeros(2, device="cuda"), torch.zeros((M, N), device="cuda")
+    want = [(oracle.amax(h), oracle.scale_from_amax(oracle.amax(h), f)) for h, f in zip(hosts, (E4M3, E5M2))]
+    with knob(fp8.FP8_KNOB_PATIENCE, 1):
+        for _ in range(20):
+            qa, qb = (torch.zeros(t.shape, dtype=torch.uint8, device="cuda") for t in (a, b))
+            fp8.fp8_scaled_gemm(a, E4M3, False, b, E5M2, False, qa, qb, amax, scale, ws, c)
+            torch.cuda.synchronize()
+            assert not bool(ws.any())
+            assert [(np.float32(x), np.float32(s)) for x, s in zip(amax.tolist(), scale.tolist())] == want
+            for q, h, f, w in ((qa, hosts[0], E4M3, want[0]), (qb, hosts[1], E5M2, want[1])):
+                assert np.array_equal(q.cpu().numpy(), oracle.quantize(h, f, w[1]))
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
