@@ -4,6 +4,8 @@
 
 #include "gemm_common.hpp"
 
+#include <type_traits>
+
 namespace fp8mm {
 namespace {
 
@@ -17,11 +19,13 @@ typedef u32x4 u32x4_any __attribute__((aligned(1)));     // 16 bytes at any addr
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 
 // LDS of the epilogue: the waves' blocks (at most 4 x 32 rows of 528 bytes), then these.
-constexpr int EP_COLUMNS = 72 * 1024;       // reciprocals of the per-column factors, 256 floats
+constexpr int EP_COLUMNS = 72 * 1024;       // reciprocals of the per-column factors, 256 floats or doubles
 constexpr int EP_AMAX = 74 * 1024;          // one word per wave
 
 // The accumulators of one wave -> memory.
-//   c = acc * ra(row) [* cb(column)]: the reciprocal scales, applied once per output;
+//   c = acc * ra(row) [* cb(column)]: the reciprocal scales, applied once per output.  With per-column
+//   factors F64 keeps both reciprocals and their product in 64 bits, rounded once: as accurate as dividing by
+//   the product, and finite wherever that is (1 / sA alone may lie beyond the 32-bit range);
 //   amax of |c| (if asked for); conversion to the output kind; whole-line stores.
 // A lane holds 4 consecutive N of one C row per accumulator quad; written straight out that would
 // be small pieces scattered over 32 rows per instruction.  Instead the wave turns each 32 x 32 NB
@@ -32,7 +36,7 @@ constexpr int EP_AMAX = 74 * 1024;          // one word per wave
 // Every output kind is converted before the turn (FP8: multiplied by the output scale and rounded sixteen at
 // a time by the routine of the cast kernels), so the turn moves 4, 2 or 1 bytes per output.
 // All four waves call it (barriers inside where there are per-column factors or an output maximum).
-template <int OUT, bool BVEC, int NB>
+template <int OUT, bool BVEC, int NB, bool F64>
 __device__ __forceinline__ void epilogue(v16f (&acc)[NB][4], uint8_t* smem, const EpilogueArgs& ep, void* C, int M, int N,
                                          int m0, int n0, int w, int l)
 {
@@ -51,21 +55,25 @@ __device__ __forceinline__ void epilogue(v16f (&acc)[NB][4], uint8_t* smem, cons
     // memory locations would force the block into scratch memory)
     const float sA_host = ep.sA, sB_host = ep.sB;
     float ra[4];
+    double ra64[4];
     {
         const double b = BVEC ? 1.0 : (double)scale_value(ep.sB_dev, sB_host);
 #pragma unroll
         for (int mb = 0; mb < 4; ++mb) {
             const float a = ep.a_per_row ? ep.sA_dev[min(wave_m0 + mb * 32 + (l & 31), M - 1)] : scale_value(ep.sA_dev, sA_host);
-            ra[mb] = (float)(1.0 / ((double)a * b));
+            ra64[mb] = 1.0 / ((double)a * b);
+            ra[mb] = (float)ra64[mb];
         }
     }
-    float* columns = (float*)(smem + EP_COLUMNS);
+    typedef typename std::conditional<F64, double, float>::type factor_t;
+    typedef factor_t v4factor __attribute__((ext_vector_type(4)));
+    factor_t* columns = (factor_t*)(smem + EP_COLUMNS);
     if (BVEC) {
         const int t = w * 64 + l;
-        if (t < 64 * NB) *LDS_PTR(float, columns + t) = 1.0f / ep.sB_dev[min(n0 + t, N - 1)];
+        if (t < 64 * NB) *LDS_PTR(factor_t, columns + t) = (factor_t)1 / (factor_t)ep.sB_dev[min(n0 + t, N - 1)];
         __syncthreads();
     }
-    auto column_factors = [&](int nb, int q) { return *LDS_PTR(v4f, columns + wn * WN + nb * 32 + 8 * q + 4 * h); };
+    auto column_factors = [&](int nb, int q) { return *LDS_PTR(v4factor, columns + wn * WN + nb * 32 + 8 * q + 4 * h); };
     const float sD = FP8OUT ? scale_value(ep.sD_dev, 1.0f) : 1.0f;
 
     // Output maximum: outputs beyond the edges of C hold products of redirected loads and do not count.
@@ -84,13 +92,14 @@ __device__ __forceinline__ void epilogue(v16f (&acc)[NB][4], uint8_t* smem, cons
             float y[16];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                v4f f = {1.0f, 1.0f, 1.0f, 1.0f};
+                v4factor f = {1, 1, 1, 1};
                 if (BVEC) f = column_factors(nb, q);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    float c = acc[nb][mb][4 * q + i] * ra[mb];
-                    if (BVEC) c *= f[i];
-                    y[4 * q + i] = c;
+                    const float a = acc[nb][mb][4 * q + i];
+                    if (!BVEC) y[4 * q + i] = a * ra[mb];
+                    else if (F64) y[4 * q + i] = a * (float)(ra64[mb] * f[i]);
+                    else y[4 * q + i] = a * ra[mb] * (float)f[i];
                 }
             }
             unsigned quad_max = 0;                       // over the 16 outputs (FP8 outputs: also tells how to convert)
@@ -175,7 +184,7 @@ __device__ __forceinline__ void epilogue(v16f (&acc)[NB][4], uint8_t* smem, cons
 
 // The workgroup's tile, with the output kind and the scale granularity chosen for the whole wave.  The LDS holds
 // nothing any more that somebody needs.
-template <int NB>
+template <int NB, bool F64>
 __device__ __forceinline__ void store_tile(v16f (&acc)[NB][4], uint8_t* smem, const EpilogueArgs& ep, void* C, int M, int N, int m0, int n0, int w)
 {
     // The lane index is taken afresh from the execution mask count: values derived from the one
@@ -183,17 +192,17 @@ __device__ __forceinline__ void store_tile(v16f (&acc)[NB][4], uint8_t* smem, co
     const int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     if (ep.b_per_col) {
         switch (ep.out_kind) {
-            case OUT_F32: epilogue<OUT_F32, true, NB>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
-            case OUT_BF16: epilogue<OUT_BF16, true, NB>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
-            case OUT_E4M3: epilogue<OUT_E4M3, true, NB>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
-            default: epilogue<OUT_E5M2, true, NB>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
+            case OUT_F32: epilogue<OUT_F32, true, NB, F64>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
+            case OUT_BF16: epilogue<OUT_BF16, true, NB, F64>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
+            case OUT_E4M3: epilogue<OUT_E4M3, true, NB, F64>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
+            default: epilogue<OUT_E5M2, true, NB, F64>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
         }
     } else {
         switch (ep.out_kind) {
-            case OUT_F32: epilogue<OUT_F32, false, NB>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
-            case OUT_BF16: epilogue<OUT_BF16, false, NB>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
-            case OUT_E4M3: epilogue<OUT_E4M3, false, NB>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
-            default: epilogue<OUT_E5M2, false, NB>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
+            case OUT_F32: epilogue<OUT_F32, false, NB, F64>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
+            case OUT_BF16: epilogue<OUT_BF16, false, NB, F64>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
+            case OUT_E4M3: epilogue<OUT_E4M3, false, NB, F64>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
+            default: epilogue<OUT_E5M2, false, NB, F64>(acc, smem, ep, C, M, N, m0, n0, w, l); break;
         }
     }
 }

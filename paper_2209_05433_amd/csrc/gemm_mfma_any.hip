@@ -509,7 +509,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_any_wide_kernel(
     if (st < stages) stage(std::false_type{}, 0, a0, b0);
 
     __syncthreads();                                  // every wave is done with the images
-    store_tile<4>(acc, lds, ep, C, (int)M, (int)N, (int)m0, (int)n0, w);
+    store_tile<4, true>(acc, lds, ep, C, (int)M, (int)N, (int)m0, (int)n0, w);
 }
 
 template <int FA, int FB, bool A_KC, bool B_KC>

@@ -187,6 +187,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(
     typedef Operand<B_KC, RN, S> OpB;
     constexpr int CK = S * SK;
     constexpr int PER_WAVE = small_lds_per_wave<A_KC, B_KC, RM, RN, S>();
+    constexpr int RED = 32 * RM * RED_PITCH * 4;          // bytes of a wave's sums
+    static_assert(PER_WAVE - RED >= 32 * (RM + RN) * 8, "the reciprocals of the factors lie behind the first wave's sums");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];       // NW * PER_WAVE
     const int tid = threadIdx.x, l = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -197,6 +199,19 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(
     const int64_t x = blockIdx.x % 8, idx = blockIdx.x / 8, share = total / 8, rem = total % 8;
     const int64_t p = x * share + (x < rem ? x : rem) + idx;
     const int64_t m0 = (p % tiles_m) * (32 * RM), n0 = (p / tiles_m) * (32 * RN);
+
+    // the factor that the thread will take the reciprocal of, loaded while the products run
+    double factor = 1.0;
+    {
+        const float sA_host = ep.sA, sB_host = ep.sB;     // by value: a choice between two memory locations would cost scratch
+        if (tid < 32 * RM) {
+            const int64_t gm = m0 + tid < M ? m0 + tid : M - 1;
+            factor = (double)(ep.a_per_row ? ep.sA_dev[gm] : scale_value(ep.sA_dev, sA_host)) * (ep.b_per_col ? 1.0 : (double)scale_value(ep.sB_dev, sB_host));
+        } else if (ep.b_per_col && tid < 32 * (RM + RN)) {
+            const int64_t gn = n0 + tid - 32 * RM;
+            factor = ep.sB_dev[gn < N ? gn : N - 1];
+        }
+    }
 
     OpA a; OpB b;
     a.setup(A, M, K, m0, l);
@@ -275,15 +290,19 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(
         multiply(xa, xb);
     }
 
-    // The waves' sums meet in LDS, 32 columns at a time; a thread adds 4 consecutive columns of a row.
-    const float sA_host = ep.sA, sB_host = ep.sB;         // by value: a choice between two memory locations would cost scratch
+    // The waves' sums meet in LDS, 32 columns at a time; a thread adds 4 consecutive columns of a row.  The
+    // reciprocals of the factors of the tile's rows (per-tensor ones: sA sB in all of them) and columns lie
+    // behind the first wave's sums, in 64 bits: their product, rounded once, is as accurate as dividing by the
+    // product of the factors, and finite wherever that is (1 / sA alone may lie beyond the 32-bit range).
     const float sD = ep.out_kind >= OUT_E4M3 ? scale_value(ep.sD_dev, 1.0f) : 1.0f;
-    const double b_all = ep.b_per_col ? 1.0 : (double)scale_value(ep.sB_dev, sB_host);
+    double* row_factors = (double*)(lds + RED);
+    double* col_factors = row_factors + 32 * RM;
     const int esz = ep.out_kind == OUT_F32 ? 4 : ep.out_kind == OUT_BF16 ? 2 : 1;
     unsigned amax_bits = 0;
 #pragma unroll
     for (int i = 0; i < RN; ++i) {
         __syncthreads();                                  // the slabs, or the block before, are done with
+        if (i == 0 && tid < 32 * (RM + RN)) *LDS_PTR(double, row_factors + tid) = 1.0 / factor;
         float* mine_red = (float*)(lds + w * PER_WAVE);
 #pragma unroll
         for (int j = 0; j < RM; ++j)
@@ -299,14 +318,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(
             v4f s = *LDS_PTR(v4f, red);
 #pragma unroll
             for (int v = 1; v < NW; ++v) s += *LDS_PTR(v4f, red + v * (PER_WAVE / 4));
-            const float sa = ep.a_per_row ? ep.sA_dev[gm] : scale_value(ep.sA_dev, sA_host);
-            const float ra = (float)(1.0 / ((double)sa * b_all));
+            const double ra = *LDS_PTR(double, row_factors + (u >> 3));
             const int left = N - gn < 4 ? (int)(N - gn) : 4;
             float c[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                c[e] = s[e] * ra;
-                if (ep.b_per_col) c[e] *= 1.0f / ep.sB_dev[gn + (e < left ? e : left - 1)];
+                c[e] = s[e] * (float)(ep.b_per_col ? ra * *LDS_PTR(double, col_factors + 32 * i + 4 * (u & 7) + e) : ra);
                 if (e < left) amax_bits = max(amax_bits, as_u32(c[e]) & 0x7fffffffu);
             }
             uint8_t* out = (uint8_t*)C + (size_t)(gm * N + gn) * esz;

@@ -722,7 +722,7 @@ __device__ __forceinline__ void gemm_tile_body(
 
     __builtin_amdgcn_s_waitcnt(0xC07F);
     __builtin_amdgcn_s_barrier();                           // every wave is done with the operand slabs
-    store_tile<NB>(acc, smem, ep, C, M, N, m0, n0, w);
+    store_tile<NB, false>(acc, smem, ep, C, M, N, m0, n0, w);
 }
 
 template <int FMT_A, int FMT_B, int ACC, bool A_KC, bool B_KC, int NB, bool PERSIST>

@@ -4,6 +4,7 @@ The checks are those of the tests that run at default knobs (test_gpu_gemm, test
 test_gpu_ragged), against the oracle."""
 import contextlib
 
+import numpy as np
 import pytest
 
 import paper_2209_05433_amd as fp8
@@ -61,3 +62,22 @@ def test_outputs_of_every_form(mode, form):
     if mode == "f16":
         with pinned(FORMS[form]):
             fused.test_per_channel_scales_are_not_swapped_or_shifted()
+
+
+@pytest.mark.parametrize("form", ["any 128", "any 256", *sorted(SMALL_FORMS)])
+def test_factors_per_column_are_rounded_once(form):
+    """Off the tiled kernel an output is acc * fl32(1 / (sA sB)), the reciprocal formed in 64 bits and rounded once: the
+    bits of that expression where the sums are exact, and a finite product of factors whose own reciprocals leave the
+    32-bit range (1 / 1e-39 = inf, 1 / (1e-39 * 1e5) = 1e34)."""
+    rng = np.random.default_rng(71)
+    M, N, K = 300, 333, 530                      # (rows of B and of the output start at odd places: not the tiled kernel's)
+    A, B = fused.int_codes(rng, (M, K)), fused.int_codes(rng, (K, N))
+    S = fused.oracle.gemm_rows(A, fused.E4M3, B, fused.E4M3)[0].astype(np.float32)
+    sB = rng.uniform(0.5, 4.0, N).astype(np.float32)
+    with pinned(FORMS[form]):
+        for sA, col in ((rng.uniform(0.5, 4.0, M).astype(np.float32), sB), (np.float32(1.7), sB), (np.full(M, 1e-39, np.float32), sB * np.float32(1e5))):
+            a = np.broadcast_to(np.asarray(sA, np.float64), (M,))[:, None]
+            want = S * (1.0 / (a * col.astype(np.float64))).astype(np.float32)
+            assert np.all(np.isfinite(want))
+            got = fused.run_fused(A, fused.E4M3, B, fused.E4M3, fp8.FP8_OUT_F32, sA, col)[0].cpu().numpy()
+            assert np.array_equal(got, want), "%d of %d outputs differ" % (np.count_nonzero(got != want), want.size)
