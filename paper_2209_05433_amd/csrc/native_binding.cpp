@@ -102,15 +102,23 @@ void* stream_of(PyObject* o)
     return p;
 }
 
-void* device(const at::Tensor& t, const char* what)
+void check_device(const at::Tensor& t, const char* what)
 {
     if (!t.is_cuda()) raise(PyExc_ValueError, "%s must live in device memory", what);
     if (!t.is_contiguous()) raise(PyExc_ValueError, "%s must be contiguous", what);
-    return const_cast<void*>(t.const_data_ptr());
 }
-void* device(PyObject* o, const char* what) { return device(tensor(o, what), what); }
-void* device_or_null(const at::Tensor& t, const char* what) { return t.numel() ? device(t, what) : nullptr; }
-void* device_or_none(PyObject* o, const char* what) { return is_none(o) ? nullptr : device(o, what); }
+
+// A tensor that is read ...
+const void* device(const at::Tensor& t, const char* what) { check_device(t, what); return t.const_data_ptr(); }
+const void* device(PyObject* o, const char* what) { return device(tensor(o, what), what); }
+const void* device_or_null(const at::Tensor& t, const char* what) { return t.numel() ? device(t, what) : nullptr; }
+const void* device_or_none(PyObject* o, const char* what) { return is_none(o) ? nullptr : device(o, what); }
+
+// ... and one that is written: a lazy clone gets memory of its own first.
+void* written(const at::Tensor& t, const char* what) { check_device(t, what); return t.mutable_data_ptr(); }
+void* written(PyObject* o, const char* what) { return written(tensor(o, what), what); }
+void* written_or_null(const at::Tensor& t, const char* what) { return t.numel() ? written(t, what) : nullptr; }
+void* written_or_none(PyObject* o, const char* what) { return is_none(o) ? nullptr : written(o, what); }
 
 int dtype_of(const at::Tensor& t)
 {
@@ -120,7 +128,7 @@ int dtype_of(const at::Tensor& t)
 }
 
 // fp32 cells on the device: `count` of them (-1: any number).
-float* cells(PyObject* o, const char* what, int64_t count)
+const at::Tensor& cells_tensor(PyObject* o, const char* what, int64_t count)
 {
     const at::Tensor& t = tensor(o, what);
     if (t.scalar_type() != at::kFloat || (count >= 0 && t.numel() != count)) {
@@ -128,8 +136,10 @@ float* cells(PyObject* o, const char* what, int64_t count)
         PyErr_Format(PyExc_ValueError, "%s must be an fp32 device tensor of %lld values", what, (long long)count);
         throw Failed{};
     }
-    return (float*)device(t, what);
+    return t;
 }
+const float* cells(PyObject* o, const char* what, int64_t count) { return (const float*)device(cells_tensor(o, what, count), what); }
+float* cells_out(PyObject* o, const char* what, int64_t count) { return (float*)written(cells_tensor(o, what, count), what); }
 
 bool is_bytes(const at::Tensor& t) { return t.scalar_type() == at::kByte; }
 
@@ -138,7 +148,7 @@ uint8_t* bytes_for(PyObject* o, const at::Tensor& x)
 {
     const at::Tensor& q = tensor(o, "q_out");
     if (!is_bytes(q) || q.numel() != x.numel()) raise(PyExc_ValueError, "q_out must be uint8 with as many elements as x");
-    return (uint8_t*)(x.numel() ? device(q, "q_out") : nullptr);
+    return (uint8_t*)(x.numel() ? written(q, "q_out") : nullptr);
 }
 
 void workspace_holds(const at::Tensor& ws, int tensors, const char* text)
@@ -188,7 +198,7 @@ ENTRY(fp8_amax, 2, "x", "amax_out", "stream")
     const at::Tensor& x = tensor(a[0], "x");
     const void* p = device_or_null(x, "x");
     const int dt = dtype_of(x);
-    float* out = (float*)device(a[1], "amax_out");
+    float* out = (float*)written(a[1], "amax_out");
     void* s = stream_of(a[2]);
     const size_t n = (size_t)x.numel();
     return checked([&] { return ::fp8_amax(p, n, dt, out, s); });
@@ -201,8 +211,8 @@ ENTRY(fp8_amax_scale, 5, "x", "fmt", "amax_out", "scale_out", "workspace", "stre
     const at::Tensor& x = tensor(a[0], "x");
     const void* p = device_or_null(x, "x");
     const int dt = dtype_of(x), fmt = small(a[1]);
-    float *amax = (float*)device(a[2], "amax_out"), *scale = (float*)device_or_none(a[3], "scale_out");
-    void *w = device(ws, "workspace"), *s = stream_of(a[5]);
+    float *amax = (float*)written(a[2], "amax_out"), *scale = (float*)written_or_none(a[3], "scale_out");
+    void *w = written(ws, "workspace"), *s = stream_of(a[5]);
     const size_t n = (size_t)x.numel();
     return checked([&] { return ::fp8_amax_scale(p, n, dt, fmt, amax, scale, w, s); });
 }
@@ -248,8 +258,8 @@ ENTRY(fp8_amax_scale_multi, 5, "xs", "fmts", "amax_out", "scale_out", "workspace
     const Tensors t(xs, a[1], "fp8_amax_scale_multi");
     const at::Tensor& ws = tensor(a[4], "workspace");
     workspace_holds(ws, t.count, "workspace must hold FP8_AMAX_WORKSPACE_BYTES bytes per tensor");
-    float *amax = cells(a[2], "amax_out", t.count), *scale = is_none(a[3]) ? nullptr : cells(a[3], "scale_out", t.count);
-    void *w = device(ws, "workspace"), *s = stream_of(a[5]);
+    float *amax = cells_out(a[2], "amax_out", t.count), *scale = is_none(a[3]) ? nullptr : cells_out(a[3], "scale_out", t.count);
+    void *w = written(ws, "workspace"), *s = stream_of(a[5]);
     return checked([&] { return ::fp8_amax_scale_multi(t.count, t.x, t.n, t.dtype, t.fmt, amax, scale, w, s); });
 }
 
@@ -262,10 +272,10 @@ ENTRY(fp8_quantize_multi, 4, "xs", "fmts", "scale", "q_outs", "stream")
     for (int i = 0; fine && i < t.count; ++i) {
         const at::Tensor& o = tensor(qs[i], "q_out");
         fine = is_bytes(o) && (size_t)o.numel() == t.n[i];
-        if (fine) q[i] = (uint8_t*)device_or_null(o, "q_out");
+        if (fine) q[i] = (uint8_t*)written_or_null(o, "q_out");
     }
     if (!fine) raise(PyExc_ValueError, "q_outs must be uint8 tensors with as many elements as their inputs");
-    float* scale = cells(a[2], "scale", t.count);
+    const float* scale = cells(a[2], "scale", t.count);
     void* s = stream_of(a[4]);
     return checked([&] { return ::fp8_quantize_multi(t.count, t.x, t.n, t.dtype, t.fmt, scale, q, s); });
 }
@@ -273,7 +283,7 @@ ENTRY(fp8_quantize_multi, 4, "xs", "fmts", "scale", "q_outs", "stream")
 ENTRY(fp8_scale_from_amax, 3, "amax", "fmt", "scale_out", "stream")
 {
     const float* amax = (const float*)device(a[0], "amax");
-    float* out = (float*)device(a[2], "scale_out");
+    float* out = (float*)written(a[2], "scale_out");
     const int fmt = small(a[1]);
     void* s = stream_of(a[3]);
     return checked([&] { return ::fp8_scale_from_amax(amax, fmt, out, s); });
@@ -333,7 +343,7 @@ ENTRY(fp8_dequantize, 4, "q", "fmt", "scale", "out", "stream")
     const uint8_t* p = (const uint8_t*)device_or_null(q, "q");
     const Factor f(a[2], "scale");
     const int dt = dtype_of(out), fmt = small(a[1]);
-    void *o = q.numel() ? device(out, "out") : nullptr, *s = stream_of(a[4]);
+    void *o = q.numel() ? written(out, "out") : nullptr, *s = stream_of(a[4]);
     const size_t n = (size_t)q.numel();
     return checked([&] { return ::fp8_dequantize(p, n, fmt, f.host, f.dev, dt, o, s); });
 }
@@ -344,7 +354,8 @@ ENTRY(fp8_quantize_amax, 5, "x", "fmt", "scale", "q_out", "amax_out", "stream")
     uint8_t* q = bytes_for(a[3], x);
     const void* p = device_or_null(x, "x");
     const int dt = dtype_of(x), fmt = small(a[1]);
-    float *scale = cells(a[2], "scale", 1), *amax = cells(a[4], "amax_out", 1);
+    const float* scale = cells(a[2], "scale", 1);
+    float* amax = cells_out(a[4], "amax_out", 1);
     void* s = stream_of(a[5]);
     const size_t n = (size_t)x.numel();
     return checked([&] { return ::fp8_quantize_amax(p, n, dt, fmt, scale, q, amax, s); });
@@ -369,7 +380,7 @@ ENTRY(fp8_scale_from_amax_history, 3, "amax_history", "fmt", "scale_out", "strea
 {
     const at::Tensor& h = tensor(a[0], "amax_history");
     const float* p = h.numel() ? cells(a[0], "amax_history", -1) : nullptr;
-    float* out = cells(a[2], "scale_out", 1);
+    float* out = cells_out(a[2], "scale_out", 1);
     const int fmt = small(a[1]);
     void* s = stream_of(a[3]);
     const size_t n = (size_t)h.numel();
@@ -380,7 +391,7 @@ ENTRY(fp8_scale_from_amax_n, 3, "amax", "fmt", "scale_out", "stream")
 {
     const int64_t n = tensor(a[0], "amax").numel();
     const float* p = n ? cells(a[0], "amax", -1) : nullptr;
-    float* out = n ? cells(a[2], "scale_out", n) : nullptr;
+    float* out = n ? cells_out(a[2], "scale_out", n) : nullptr;
     const int fmt = small(a[1]);
     void* s = stream_of(a[3]);
     return checked([&] { return ::fp8_scale_from_amax_n(p, (size_t)n, fmt, out, s); });
@@ -400,7 +411,7 @@ ENTRY(fp8_amax_rows, 2, "x", "amax_out", "stream")
     const int64_t rows = x.size(0), cols = x.size(1);
     const void* p = device_or_null(x, "x");
     const int dt = dtype_of(x);
-    float* amax = rows ? cells(a[1], "amax_out", rows) : nullptr;
+    float* amax = rows ? cells_out(a[1], "amax_out", rows) : nullptr;
     void* s = stream_of(a[2]);
     return checked([&] { return ::fp8_amax_rows(p, rows, cols, dt, amax, s); });
 }
@@ -415,7 +426,7 @@ ENTRY(fp8_quantize_rows, 4, "x", "fmt", "scale", "q_out", "stream")
     const void* p = device_or_null(x, "x");
     const int dt = dtype_of(x), fmt = small(a[1]);
     const float* scale = work ? cells(a[2], "scale", rows) : nullptr;
-    uint8_t* o = (uint8_t*)device_or_null(q, "q_out");
+    uint8_t* o = (uint8_t*)written_or_null(q, "q_out");
     void* s = stream_of(a[4]);
     return checked([&] { return ::fp8_quantize_rows(p, rows, cols, dt, fmt, scale, o, s); });
 }
@@ -431,12 +442,12 @@ ENTRY(fp8_quantize_transpose, 5, "x", "fmt", "scale", "q_out", "qt_out", "stream
     if (!is_none(a[3])) {
         const at::Tensor& t = tensor(a[3], "q_out");
         if (!is_bytes(t) || !has_shape(t, rows, cols)) raise(PyExc_ValueError, "q_out must be None or a uint8 tensor of the shape of x");
-        q = (uint8_t*)device_or_null(t, "q_out");
+        q = (uint8_t*)written_or_null(t, "q_out");
     }
     const void* p = device_or_null(x, "x");
     const int dt = dtype_of(x), fmt = small(a[1]);
     const float* scale = work ? cells(a[2], "scale", 1) : nullptr;
-    uint8_t* t = (uint8_t*)device_or_null(qt, "qt_out");
+    uint8_t* t = (uint8_t*)written_or_null(qt, "qt_out");
     void* s = stream_of(a[5]);
     return checked([&] { return ::fp8_quantize_transpose(p, rows, cols, dt, fmt, scale, q, t, s); });
 }
@@ -455,7 +466,7 @@ struct Product {
         if (tb.size(transB ? 1 : 0) != K || !has_shape(tc, M, N)) raise(PyExc_ValueError, "%s", shapes);
         A = (const uint8_t*)device_or_null(ta, "A");
         B = (const uint8_t*)device_or_null(tb, "B");
-        C = device_or_null(tc, "C");
+        C = written_or_null(tc, "C");
     }
 };
 const char* const kBytes2d = "A and B must be 2-D uint8 tensors of FP8 bytes";
@@ -512,7 +523,7 @@ ENTRY(fp8_gemm_splitk, 10, "A", "fmtA", "transA", "B", "fmtB", "transB", "C", "s
     const Product p(tensor(a[0], "A"), tA, tensor(a[3], "B"), tB, c, kBytes2d, kShapesEx);
     const Factors f(a[7], a[8]);
     const int fa = small(a[1]), fb = small(a[4]), dt = dtype_of(c), flags = small(a[10]), splits = small(a[11]);
-    void *ws = device_or_none(a[9], "workspace"), *s = stream_of(a[12]);
+    void *ws = written_or_none(a[9], "workspace"), *s = stream_of(a[12]);
     const size_t bytes = is_none(a[9]) ? 0 : (size_t)tensor(a[9], "workspace").numel() * tensor(a[9], "workspace").element_size();
     return checked([&] { return ::fp8_gemm_splitk(p.A, fa, tA, p.B, fb, tB, p.C, p.M, p.N, p.K, dt, f.A.host, f.B.host, f.A.dev, f.B.dev, flags, splits,
                                                   ws, bytes, s); });
@@ -544,7 +555,7 @@ ENTRY(fp8_gemm_fused, 10, "A", "fmtA", "transA", "B", "fmtB", "transB", "D", "ou
     for (int i = 0; i < 4; ++i)
         if (!is_none(a[8 + i]) && tensor(a[8 + i], names[i]).scalar_type() != at::kFloat) raise(PyExc_ValueError, "%s must be an fp32 device tensor", names[i]);
     const float *pA = (const float*)device(sA, "sA"), *pB = (const float*)device(sB, "sB"), *pD = (const float*)device_or_none(a[10], "sD");
-    float* amax = (float*)device_or_none(a[11], "amax_out");
+    float* amax = (float*)written_or_none(a[11], "amax_out");
     const int fa = small(a[1]), fb = small(a[4]), flags = small(a[12]);
     const int64_t nA = sA.numel(), nB = sB.numel();
     void* s = stream_of(a[13]);
@@ -563,9 +574,9 @@ ENTRY(fp8_scaled_gemm, 12, "a", "fmtA", "transA", "b", "fmtB", "transB", "qa_out
         raise(PyExc_ValueError, "qa_out / qb_out must be uint8 tensors of the operands' shapes");
     workspace_holds(ws, 2, "workspace must hold 2 * FP8_AMAX_WORKSPACE_BYTES bytes");
     const int dt = dtype_of(x), odt = dtype_of(c), fa = small(a[1]), fb = small(a[4]), flags = small(a[12]);
-    uint8_t *qa = (uint8_t*)device_or_null(qx, "qa_out"), *qb = (uint8_t*)device_or_null(qy, "qb_out");
-    float *amax = cells(a[8], "amax_out", 2), *scale = cells(a[9], "scale_out", 2);
-    void *w = device(ws, "workspace"), *s = stream_of(a[13]);
+    uint8_t *qa = (uint8_t*)written_or_null(qx, "qa_out"), *qb = (uint8_t*)written_or_null(qy, "qb_out");
+    float *amax = cells_out(a[8], "amax_out", 2), *scale = cells_out(a[9], "scale_out", 2);
+    void *w = written(ws, "workspace"), *s = stream_of(a[13]);
     return checked([&] { return ::fp8_scaled_gemm(p.A, p.B, dt, tA, tB, p.M, p.N, p.K, fa, fb, qa, qb, amax, scale, w, p.C, odt, flags, s); });
 }
 
