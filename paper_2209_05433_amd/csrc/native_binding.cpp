@@ -65,15 +65,28 @@ const at::Tensor& tensor(PyObject* o, const char* what)
     return THPVariable_Unpack(o);
 }
 
-long long integer(PyObject* o)
+// The low 64 bits of an integer (or of what stands for one by __index__).
+unsigned long long low_bits(PyObject* o)
 {
-    const long long x = PyLong_AsLongLong(o);
-    if (x == -1 && PyErr_Occurred()) throw Failed{};
+    const unsigned long long x = PyLong_AsUnsignedLongLongMask(o);
+    if (x == ~0ull && PyErr_Occurred()) throw Failed{};
     return x;
 }
 
-// An integer argument that the C ABI takes as an int (checked there); absent: `otherwise`.
-int small(PyObject* o, int otherwise = 0) { return o ? (int)integer(o) : otherwise; }
+// The same of int(o), for arguments that anything with an integer value may be given for.
+unsigned long long low_bits_of_int(PyObject* o)
+{
+    if (PyLong_CheckExact(o)) return low_bits(o);
+    PyObject* i = PyNumber_Long(o);
+    if (!i) throw Failed{};
+    const unsigned long long x = PyLong_AsUnsignedLongLongMask(i);
+    Py_DECREF(i);
+    return x;
+}
+
+// Arguments that the C ABI takes as an int (and checks): a format; a number of slices, flags, a kind (absent: 0).
+int small(PyObject* o) { return (int)low_bits(o); }
+int small_of_int(PyObject* o) { return o ? (int)low_bits_of_int(o) : 0; }
 
 int truth(PyObject* o)
 {
@@ -82,24 +95,31 @@ int truth(PyObject* o)
     return t;
 }
 
+// float(o)
 float real(PyObject* o)
 {
-    const double d = PyFloat_AsDouble(o);
-    if (d == -1.0 && PyErr_Occurred()) throw Failed{};
+    PyObject* f = PyNumber_Float(o);
+    if (!f) throw Failed{};
+    const double d = PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
     return (float)d;
 }
 
-// None: torch's current stream; an object with a cuda_stream, or the handle itself.
+// None: torch's current stream; an object with a cuda_stream, or what int() makes the handle itself.
 void* stream_of(PyObject* o)
 {
     if (is_none(o)) return (void*)c10::hip::getCurrentHIPStream().stream();
-    if (PyLong_Check(o)) return PyLong_AsVoidPtr(o);
+    if (PyLong_CheckExact(o)) return (void*)(uintptr_t)low_bits(o);
     PyObject* h = PyObject_GetAttrString(o, "cuda_stream");
-    if (!h) throw Failed{};
-    void* p = PyLong_AsVoidPtr(h);
+    if (!h) {
+        if (!PyErr_ExceptionMatches(PyExc_AttributeError)) throw Failed{};
+        PyErr_Clear();
+        return (void*)(uintptr_t)low_bits_of_int(o);
+    }
+    const unsigned long long p = PyLong_AsUnsignedLongLongMask(h);
     Py_DECREF(h);
-    if (!p && PyErr_Occurred()) throw Failed{};
-    return p;
+    if (p == ~0ull && PyErr_Occurred()) throw Failed{};
+    return (void*)(uintptr_t)p;
 }
 
 void check_device(const at::Tensor& t, const char* what)
@@ -247,7 +267,7 @@ struct Tensors {
             dtype = dt;
             x[i] = device_or_null(t, "x");
             n[i] = (size_t)t.numel();
-            fmt[i] = small(f[i]);
+            fmt[i] = small_of_int(f[i]);
         }
     }
 };
@@ -329,7 +349,7 @@ ENTRY(fp8_quantize_ex, 5, "x", "fmt", "scale", "flags", "q_out", "stream")
     const at::Tensor& x = tensor(a[0], "x");
     uint8_t* q = bytes_for(a[4], x);
     const void* p = device_or_null(x, "x");
-    const int dt = dtype_of(x), fmt = small(a[1]), flags = small(a[3]);
+    const int dt = dtype_of(x), fmt = small(a[1]), flags = small_of_int(a[3]);
     const Factor f(a[2], "scale");
     void* s = stream_of(a[5]);
     const size_t n = (size_t)x.numel();
@@ -369,8 +389,7 @@ ENTRY(fp8_quantize_sr, 5, "x", "fmt", "scale", "seed", "q_out", "stream")
     const int dt = dtype_of(x), fmt = small(a[1]);
     Factor f(a[2], "scale", true);
     if (f.dev) f.host = 1.0f;
-    const unsigned long long seed = PyLong_AsUnsignedLongLongMask(a[3]);
-    if (seed == (unsigned long long)-1 && PyErr_Occurred()) throw Failed{};
+    const unsigned long long seed = low_bits_of_int(a[3]);
     void* s = stream_of(a[5]);
     const size_t n = (size_t)x.numel();
     return checked([&] { return ::fp8_quantize_sr(p, n, dt, fmt, f.host, f.dev, seed, q, s); });
@@ -511,7 +530,7 @@ ENTRY(fp8_gemm_ex, 9, "A", "fmtA", "transA", "B", "fmtB", "transB", "C", "sA", "
     const at::Tensor& c = tensor(a[6], "C");
     const Product p(tensor(a[0], "A"), tA, tensor(a[3], "B"), tB, c, kBytes2d, kShapesEx);
     const Factors f(a[7], a[8]);
-    const int fa = small(a[1]), fb = small(a[4]), dt = dtype_of(c), flags = small(a[9]);
+    const int fa = small(a[1]), fb = small(a[4]), dt = dtype_of(c), flags = small_of_int(a[9]);
     void* s = stream_of(a[10]);
     return checked([&] { return ::fp8_gemm_ex(p.A, fa, tA, p.B, fb, tB, p.C, p.M, p.N, p.K, dt, f.A.host, f.B.host, f.A.dev, f.B.dev, flags, s); });
 }
@@ -522,7 +541,7 @@ ENTRY(fp8_gemm_splitk, 10, "A", "fmtA", "transA", "B", "fmtB", "transB", "C", "s
     const at::Tensor& c = tensor(a[6], "C");
     const Product p(tensor(a[0], "A"), tA, tensor(a[3], "B"), tB, c, kBytes2d, kShapesEx);
     const Factors f(a[7], a[8]);
-    const int fa = small(a[1]), fb = small(a[4]), dt = dtype_of(c), flags = small(a[10]), splits = small(a[11]);
+    const int fa = small(a[1]), fb = small(a[4]), dt = dtype_of(c), flags = small_of_int(a[10]), splits = small_of_int(a[11]);
     void *ws = written_or_none(a[9], "workspace"), *s = stream_of(a[12]);
     const size_t bytes = is_none(a[9]) ? 0 : (size_t)tensor(a[9], "workspace").numel() * tensor(a[9], "workspace").element_size();
     return checked([&] { return ::fp8_gemm_splitk(p.A, fa, tA, p.B, fb, tB, p.C, p.M, p.N, p.K, dt, f.A.host, f.B.host, f.A.dev, f.B.dev, flags, splits,
@@ -535,7 +554,7 @@ ENTRY(fp8_gemm_splitk_static, 9, "A", "fmtA", "transA", "B", "fmtB", "transB", "
     const at::Tensor& c = tensor(a[6], "C");
     const Product p(tensor(a[0], "A"), tA, tensor(a[3], "B"), tB, c, kBytes2d, kShapesEx);
     const Factors f(a[7], a[8]);
-    const int fa = small(a[1]), fb = small(a[4]), dt = dtype_of(c), flags = small(a[9]), splits = small(a[10]);
+    const int fa = small(a[1]), fb = small(a[4]), dt = dtype_of(c), flags = small_of_int(a[9]), splits = small_of_int(a[10]);
     void* s = stream_of(a[11]);
     return checked([&] { return ::fp8_gemm_splitk_static(p.A, fa, tA, p.B, fb, tB, p.C, p.M, p.N, p.K, dt, f.A.host, f.B.host, f.A.dev, f.B.dev, flags,
                                                          splits, s); });
@@ -543,7 +562,7 @@ ENTRY(fp8_gemm_splitk_static, 9, "A", "fmtA", "transA", "B", "fmtB", "transB", "
 
 ENTRY(fp8_gemm_fused, 10, "A", "fmtA", "transA", "B", "fmtB", "transB", "D", "out_kind", "sA", "sB", "sD", "amax_out", "flags", "stream")
 {
-    const int tA = truth(a[2]), tB = truth(a[5]), kind = small(a[7]);
+    const int tA = truth(a[2]), tB = truth(a[5]), kind = small_of_int(a[7]);
     const at::Tensor &d = tensor(a[6], "D"), &sA = tensor(a[8], "sA"), &sB = tensor(a[9], "sB");
     const Product p(tensor(a[0], "A"), tA, tensor(a[3], "B"), tB, d, kBytes2d, "shapes do not form D[M,N] = op(A)[M,K] op(B)[K,N]");
     const at::ScalarType want = kind == FP8_OUT_F32 ? at::kFloat : kind == FP8_OUT_BF16 ? at::kBFloat16 : at::kByte;
@@ -556,7 +575,7 @@ ENTRY(fp8_gemm_fused, 10, "A", "fmtA", "transA", "B", "fmtB", "transB", "D", "ou
         if (!is_none(a[8 + i]) && tensor(a[8 + i], names[i]).scalar_type() != at::kFloat) raise(PyExc_ValueError, "%s must be an fp32 device tensor", names[i]);
     const float *pA = (const float*)device(sA, "sA"), *pB = (const float*)device(sB, "sB"), *pD = (const float*)device_or_none(a[10], "sD");
     float* amax = (float*)written_or_none(a[11], "amax_out");
-    const int fa = small(a[1]), fb = small(a[4]), flags = small(a[12]);
+    const int fa = small(a[1]), fb = small(a[4]), flags = small_of_int(a[12]);
     const int64_t nA = sA.numel(), nB = sB.numel();
     void* s = stream_of(a[13]);
     return checked([&] { return ::fp8_gemm_fused(p.A, fa, tA, p.B, fb, tB, p.C, kind, p.M, p.N, p.K, pA, nA, pB, nB, pD, amax, flags, s); });
@@ -573,7 +592,7 @@ ENTRY(fp8_scaled_gemm, 12, "a", "fmtA", "transA", "b", "fmtB", "transB", "qa_out
     if (!is_bytes(qx) || qx.sizes() != x.sizes() || !is_bytes(qy) || qy.sizes() != y.sizes())
         raise(PyExc_ValueError, "qa_out / qb_out must be uint8 tensors of the operands' shapes");
     workspace_holds(ws, 2, "workspace must hold 2 * FP8_AMAX_WORKSPACE_BYTES bytes");
-    const int dt = dtype_of(x), odt = dtype_of(c), fa = small(a[1]), fb = small(a[4]), flags = small(a[12]);
+    const int dt = dtype_of(x), odt = dtype_of(c), fa = small(a[1]), fb = small(a[4]), flags = small_of_int(a[12]);
     uint8_t *qa = (uint8_t*)written_or_null(qx, "qa_out"), *qb = (uint8_t*)written_or_null(qy, "qb_out");
     float *amax = cells_out(a[8], "amax_out", 2), *scale = cells_out(a[9], "scale_out", 2);
     void *w = written(ws, "workspace"), *s = stream_of(a[13]);

@@ -1,4 +1,5 @@
 """The binding of the entry points that take tensors: which memory it hands out, which arguments it takes."""
+import numpy as np
 import pytest
 import torch
 
@@ -56,3 +57,38 @@ def test_outputs_that_are_lazy_clones_leave_their_origin_alone():
         torch.cuda.synchronize()
         assert all(torch.equal(t, b) for t, b in zip(origins, before)), name
         assert all(torch.equal(c, p) for c, p in zip(clones, plain)), name
+
+
+def test_arguments_that_stand_for_integers_and_numbers():
+    """Whatever int() takes is taken for flags, slices, seeds, kinds, the formats of a list and stream handles, and
+    whatever float() takes for factors."""
+    x = torch.randn(300, 64, device="cuda")
+    q, r = (torch.zeros(x.shape, dtype=torch.uint8, device="cuda") for _ in range(2))
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+
+    def same():
+        torch.cuda.synchronize()
+        assert torch.equal(q, r) and bool(q.any())
+        q.zero_(), r.zero_()
+        torch.cuda.synchronize()
+
+    fp8.fp8_quantize_sr(x, E4M3, 2.0, 77, q)
+    fp8.fp8_quantize_sr(x, E4M3, np.float64(2.0), 77.0, r, np.int64(stream.cuda_stream))
+    same()
+    fp8.fp8_quantize_ex(x, E4M3, 2.0, fp8.FP8_QUANT_NOSAT, q, stream)
+    fp8.fp8_quantize_ex(x, np.int32(E4M3), "2.0", float(fp8.FP8_QUANT_NOSAT), r, stream.cuda_stream)
+    same()
+    one = torch.ones(1, device="cuda")
+    fp8.fp8_quantize_multi([x], [E5M2], one, [q])
+    fp8.fp8_quantize_multi([x], [1.0], one, [r], float(0))
+    same()
+    a, b = q[:64].view(64, 64).fill_(0x38), r[:64].view(64, 64).fill_(0x38)
+    c, d = torch.zeros(64, 64, device="cuda"), torch.zeros(64, 64, device="cuda")
+    ws = torch.zeros(1 << 20, dtype=torch.uint8, device="cuda")
+    fp8.fp8_gemm_splitk(a, E4M3, False, b, E4M3, False, c, 1.0, 1.0, ws, fp8.FP8_GEMM_MFMA8, 1)
+    fp8.fp8_gemm_splitk(a, E4M3, 0, b, E4M3, "", d, 1, True, ws, np.float32(fp8.FP8_GEMM_MFMA8), "1")
+    torch.cuda.synchronize()
+    assert torch.equal(c, d) and bool((c == 64.0).all())
+    with pytest.raises(TypeError):
+        fp8.fp8_quantize(x, 0.0, 1.0, q)                     # a format is an integer
