@@ -4,6 +4,8 @@ unscale) of arXiv 2209.05433, as hand-written HIP kernels behind a C ABI.
 The functions re-exported here have the names and argument order of include/fp8mm.h and
 only marshal arguments; the library is loaded on first use and its absence is an error.
 """
+import os
+
 from . import binding
 from .binding import (  # noqa: F401
     FP8_E4M3, FP8_E5M2, FP8_F32, FP8_BF16,
@@ -16,6 +18,11 @@ from .binding import (  # noqa: F401
     fp8_set_knob, fp8_get_knob, FP8_KNOB_CAST_PATH, FP8_KNOB_TILE_N, FP8_KNOB_GROUP_M, FP8_KNOB_GEMM_KERNEL, FP8_KNOB_SPLIT_K, FP8_KNOB_CAST_RUN, FP8_KNOB_PERSIST, FP8_KNOB_MIXED, FP8_KNOB_SMALL, FP8_KNOB_PATIENCE, FP8_PLAN_PERSISTENT,
     fp8_last_error, fp8_version,
 )
+
+# What `import *` brings: the names above and the entry points that take tensors (looked up only where they are built).
+__all__ = [n for n in globals() if not n.startswith("_") and n != "os"]
+if os.path.exists(binding.NATIVE_PATH):
+    __all__ += binding.TENSOR_CALLS
 
 
 def __getattr__(name):

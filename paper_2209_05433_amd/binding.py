@@ -6,6 +6,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
 
 import torch
 
@@ -168,7 +169,7 @@ def native():
         m = module_from_spec(spec_from_loader(name, ExtensionFileLoader(name, NATIVE_PATH)))
         m.__spec__.loader.exec_module(m)
         m.set_error(Fp8Error)
-        _native = m
+        sys.modules[name] = _native = m              # (under the name that its functions are pickled by)
     return _native
 
 

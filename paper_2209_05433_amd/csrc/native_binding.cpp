@@ -610,40 +610,40 @@ PyObject* py_set_error(PyObject*, PyObject* type)
 
 #define METHOD(NAME, DOC) {#NAME, (PyCFunction)(void (*)(void))py_##NAME, METH_FASTCALL | METH_KEYWORDS, DOC}
 PyMethodDef methods[] = {
-    METHOD(fp8_amax, "fp8_amax(x, amax_out, stream=None)"),
-    METHOD(fp8_amax_scale, "fp8_amax_scale(x, fmt, amax_out, scale_out, workspace, stream=None)\n\namax and scale = fmt_max / amax in one launch; workspace: device "
+    METHOD(fp8_amax, "fp8_amax(x, amax_out, stream=None)\n--\n\n"),
+    METHOD(fp8_amax_scale, "fp8_amax_scale(x, fmt, amax_out, scale_out, workspace, stream=None)\n--\n\namax and scale = fmt_max / amax in one launch; workspace: device "
            "tensor of at least\nFP8_AMAX_WORKSPACE_BYTES bytes, zero-filled once before its first use."),
-    METHOD(fp8_amax_scale_multi, "fp8_amax_scale_multi(xs, fmts, amax_out, scale_out, workspace, stream=None)\n\nfp8_amax_scale for up to FP8_MULTI_MAX tensors of "
+    METHOD(fp8_amax_scale_multi, "fp8_amax_scale_multi(xs, fmts, amax_out, scale_out, workspace, stream=None)\n--\n\nfp8_amax_scale for up to FP8_MULTI_MAX tensors of "
            "one element type in one launch: amax_out and\nscale_out are fp32 device tensors of len(xs) values, workspace holds len(xs) * FP8_AMAX_WORKSPACE_BYTES bytes."),
-    METHOD(fp8_quantize_multi, "fp8_quantize_multi(xs, fmts, scale, q_outs, stream=None)\n\nfp8_quantize_dscale for up to FP8_MULTI_MAX tensors of one element type in "
+    METHOD(fp8_quantize_multi, "fp8_quantize_multi(xs, fmts, scale, q_outs, stream=None)\n--\n\nfp8_quantize_dscale for up to FP8_MULTI_MAX tensors of one element type in "
            "one launch; scale is an\nfp32 device tensor of len(xs) factors, q_outs the uint8 outputs."),
-    METHOD(fp8_scale_from_amax, "fp8_scale_from_amax(amax, fmt, scale_out, stream=None)"),
-    METHOD(fp8_quantize, "fp8_quantize(x, fmt, scale, q_out, stream=None)"),
-    METHOD(fp8_quantize_dscale, "fp8_quantize_dscale(x, fmt, scale, q_out, stream=None)"),
-    METHOD(fp8_quantize_ex, "fp8_quantize_ex(x, fmt, scale, flags, q_out, stream=None)\n\n`scale` is a float or a one-element device tensor."),
-    METHOD(fp8_dequantize, "fp8_dequantize(q, fmt, scale, out, stream=None)\n\n`scale` is a float or a one-element device tensor; out is float32 or bfloat16."),
-    METHOD(fp8_quantize_amax, "fp8_quantize_amax(x, fmt, scale, q_out, amax_out, stream=None)\n\nCast x with the one-element device tensor `scale` and write max |x| into amax_out."),
-    METHOD(fp8_quantize_sr, "fp8_quantize_sr(x, fmt, scale, seed, q_out, stream=None)\n\nStochastic-rounding cast; scale is a float or a one-element fp32 device tensor."),
-    METHOD(fp8_scale_from_amax_history, "fp8_scale_from_amax_history(amax_history, fmt, scale_out, stream=None)"),
-    METHOD(fp8_scale_from_amax_n, "fp8_scale_from_amax_n(amax, fmt, scale_out, stream=None)"),
-    METHOD(fp8_amax_rows, "fp8_amax_rows(x, amax_out, stream=None)"),
-    METHOD(fp8_quantize_rows, "fp8_quantize_rows(x, fmt, scale, q_out, stream=None)"),
-    METHOD(fp8_quantize_transpose, "fp8_quantize_transpose(x, fmt, scale, q_out, qt_out, stream=None)\n\nq_out (rows x cols, may be None) and qt_out (cols x rows) "
+    METHOD(fp8_scale_from_amax, "fp8_scale_from_amax(amax, fmt, scale_out, stream=None)\n--\n\n"),
+    METHOD(fp8_quantize, "fp8_quantize(x, fmt, scale, q_out, stream=None)\n--\n\n"),
+    METHOD(fp8_quantize_dscale, "fp8_quantize_dscale(x, fmt, scale, q_out, stream=None)\n--\n\n"),
+    METHOD(fp8_quantize_ex, "fp8_quantize_ex(x, fmt, scale, flags, q_out, stream=None)\n--\n\n`scale` is a float or a one-element device tensor."),
+    METHOD(fp8_dequantize, "fp8_dequantize(q, fmt, scale, out, stream=None)\n--\n\n`scale` is a float or a one-element device tensor; out is float32 or bfloat16."),
+    METHOD(fp8_quantize_amax, "fp8_quantize_amax(x, fmt, scale, q_out, amax_out, stream=None)\n--\n\nCast x with the one-element device tensor `scale` and write max |x| into amax_out."),
+    METHOD(fp8_quantize_sr, "fp8_quantize_sr(x, fmt, scale, seed, q_out, stream=None)\n--\n\nStochastic-rounding cast; scale is a float or a one-element fp32 device tensor."),
+    METHOD(fp8_scale_from_amax_history, "fp8_scale_from_amax_history(amax_history, fmt, scale_out, stream=None)\n--\n\n"),
+    METHOD(fp8_scale_from_amax_n, "fp8_scale_from_amax_n(amax, fmt, scale_out, stream=None)\n--\n\n"),
+    METHOD(fp8_amax_rows, "fp8_amax_rows(x, amax_out, stream=None)\n--\n\n"),
+    METHOD(fp8_quantize_rows, "fp8_quantize_rows(x, fmt, scale, q_out, stream=None)\n--\n\n"),
+    METHOD(fp8_quantize_transpose, "fp8_quantize_transpose(x, fmt, scale, q_out, qt_out, stream=None)\n--\n\nq_out (rows x cols, may be None) and qt_out (cols x rows) "
            "receive the FP8 bytes of x."),
-    METHOD(fp8_gemm, "fp8_gemm(A, fmtA, sA, B, fmtB, sB, C, stream=None)"),
-    METHOD(fp8_gemm_dscale, "fp8_gemm_dscale(A, fmtA, sA, B, fmtB, sB, C, stream=None)"),
-    METHOD(fp8_gemm_mfma8, "fp8_gemm_mfma8(A, fmtA, sA, B, fmtB, sB, C, stream=None)"),
-    METHOD(fp8_gemm_mfma8_dscale, "fp8_gemm_mfma8_dscale(A, fmtA, sA, B, fmtB, sB, C, stream=None)"),
-    METHOD(fp8_gemm_ex, "fp8_gemm_ex(A, fmtA, transA, B, fmtB, transB, C, sA, sB, flags=0, stream=None)\n\nA is [M, K] (or [K, M] if transA), B is [K, N] (or [N, K] "
+    METHOD(fp8_gemm, "fp8_gemm(A, fmtA, sA, B, fmtB, sB, C, stream=None)\n--\n\n"),
+    METHOD(fp8_gemm_dscale, "fp8_gemm_dscale(A, fmtA, sA, B, fmtB, sB, C, stream=None)\n--\n\n"),
+    METHOD(fp8_gemm_mfma8, "fp8_gemm_mfma8(A, fmtA, sA, B, fmtB, sB, C, stream=None)\n--\n\n"),
+    METHOD(fp8_gemm_mfma8_dscale, "fp8_gemm_mfma8_dscale(A, fmtA, sA, B, fmtB, sB, C, stream=None)\n--\n\n"),
+    METHOD(fp8_gemm_ex, "fp8_gemm_ex(A, fmtA, transA, B, fmtB, transB, C, sA, sB, flags=0, stream=None)\n--\n\nA is [M, K] (or [K, M] if transA), B is [K, N] (or [N, K] "
            "if transB); sA and sB are both\nfloats or both one-element device tensors."),
-    METHOD(fp8_gemm_splitk, "fp8_gemm_splitk(A, fmtA, transA, B, fmtB, transB, C, sA, sB, workspace, flags=0, splits=0, stream=None)\n\nfp8_gemm_ex with K cut into "
+    METHOD(fp8_gemm_splitk, "fp8_gemm_splitk(A, fmtA, transA, B, fmtB, transB, C, sA, sB, workspace, flags=0, splits=0, stream=None)\n--\n\nfp8_gemm_ex with K cut into "
            "slices; `workspace` is a device tensor (any dtype) of at least\nfp8_gemm_splitk_workspace_size(...) bytes, or None where that is 0."),
-    METHOD(fp8_gemm_splitk_static, "fp8_gemm_splitk_static(A, fmtA, transA, B, fmtB, transB, C, sA, sB, flags=0, splits=0, stream=None)\n\nfp8_gemm_splitk with the "
+    METHOD(fp8_gemm_splitk_static, "fp8_gemm_splitk_static(A, fmtA, transA, B, fmtB, transB, C, sA, sB, flags=0, splits=0, stream=None)\n--\n\nfp8_gemm_splitk with the "
            "library's own scratch array in place of a workspace; allocates nothing."),
-    METHOD(fp8_gemm_fused, "fp8_gemm_fused(A, fmtA, transA, B, fmtB, transB, D, out_kind, sA, sB, sD=None, amax_out=None, flags=0, stream=None)\n\nA is [M, K] (or "
+    METHOD(fp8_gemm_fused, "fp8_gemm_fused(A, fmtA, transA, B, fmtB, transB, D, out_kind, sA, sB, sD=None, amax_out=None, flags=0, stream=None)\n--\n\nA is [M, K] (or "
            "[K, M] if transA), B is [K, N] (or [N, K] if transB), D is [M, N] of the\nelement type of out_kind (uint8 for the FP8 kinds).  sA: fp32 device tensor of 1 or "
            "M values,\nsB: of 1 or N values; sD: None or one value; amax_out: None or one fp32 cell."),
-    METHOD(fp8_scaled_gemm, "fp8_scaled_gemm(a, fmtA, transA, b, fmtB, transB, qa_out, qb_out, amax_out, scale_out, workspace, C, flags=0, stream=None)\n\namax + scale + "
+    METHOD(fp8_scaled_gemm, "fp8_scaled_gemm(a, fmtA, transA, b, fmtB, transB, qa_out, qb_out, amax_out, scale_out, workspace, C, flags=0, stream=None)\n--\n\namax + scale + "
            "cast of both operands and their FP8 product in one call.  a is [M, K] (or\n[K, M] if transA), b is [K, N] (or [N, K] if transB), both bf16 or both fp32; "
            "qa_out / qb_out are\nuint8 tensors of the operands' shapes; amax_out and scale_out hold two floats ([0]: a, [1]: b);\nworkspace: 2 * FP8_AMAX_WORKSPACE_BYTES "
            "bytes, zero-filled once."),

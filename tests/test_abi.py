@@ -238,3 +238,20 @@ def test_knob_of_the_small_tiles():
             assert plan() == fp8.FP8_PLAN_TILED_256x128 | (fp8.FP8_PLAN_PERSISTENT if persistent else 0)
     finally:
         fp8.fp8_set_knob(fp8.FP8_KNOB_SMALL, 0)
+
+
+def test_tensor_calls_are_ordinary_functions_to_tools():
+    """`import *` brings the entry points that take tensors, inspect gives their argument names and defaults, and
+    they can be pickled."""
+    import inspect
+    import pickle
+    names = {}
+    exec("from paper_2209_05433_amd import *", names)
+    for name in fp8.binding.TENSOR_CALLS:
+        assert names[name] is getattr(fp8, name)
+        signature = inspect.signature(names[name])
+        assert signature.parameters["stream"].default is None
+        assert pickle.loads(pickle.dumps(names[name])) is names[name]
+    assert str(inspect.signature(fp8.fp8_gemm_splitk)) == \
+        "(A, fmtA, transA, B, fmtB, transB, C, sA, sB, workspace, flags=0, splits=0, stream=None)"
+    assert "os" not in names and {"lib", "Fp8Error", "fp8_gemm_plan", "FP8_KNOB_SMALL", "binding"} <= set(names)
