@@ -266,20 +266,20 @@ __device__ __forceinline__ u32x4 load_elements(const void* src, int count)
     return v;
 }
 
-template <int DT> struct TransposeTile { static constexpr int cols = DT == FP8_BF16 ? 256 : 128; };
-
-template <int DT, int FMT>
+// TC: tile columns, 512 bytes of x, fewer where the matrix has no more (64 or 128).  PART: the matrix has no more than
+// TT / PART rows, and no pass goes beyond them (16 x 262144 fp32 14.0 -> 9.3 us; as a choice of every last tile in the one
+// kernel, its code cost 5000 x 6144 a microsecond).
+template <int DT, int FMT, int TC, int PART>
 __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const void* __restrict__ x, int64_t rows, int64_t cols,
                                                                      const float* __restrict__ scale_dev,
                                                                      uint8_t* __restrict__ q, uint8_t* __restrict__ qt,
                                                                      int tiles_r, int tiles_c, bool diagonal)
 {
-    constexpr int TC = TransposeTile<DT>::cols;          // tile columns
     constexpr int PITCH = TC + 16;                       // LDS row pitch of the tile of q
     constexpr int EPL = DT == FP8_BF16 ? 8 : 4;          // elements per lane per load (16 bytes)
     constexpr int LPR = TC / EPL;                        // lanes per tile row
     constexpr int RPP = kThreads / LPR;                  // tile rows per pass of the workgroup
-    constexpr int PASSES = TT / RPP;
+    constexpr int PASSES = TT / RPP / PART;
     constexpr int LDS_BYTES = TT * PITCH > TC * QT_PITCH ? TT * PITCH : TC * QT_PITCH;
     __shared__ __attribute__((aligned(16))) uint8_t tile[LDS_BYTES];
     const float s = *scale_dev;
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const void
             }
         }
     };
-    const bool whole = r0 + TT <= rows && c0 + TC <= cols;
+    const bool whole = PART == 1 && r0 + TT <= rows && c0 + TC <= cols;
     if (whole) convert_tile(std::true_type{}); else convert_tile(std::false_type{});
     __syncthreads();
     // q^T: the transposing reads hand a lane 16 consecutive tile rows of one tile column = 16 bytes of
@@ -390,6 +390,22 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const void
         } else if (orow < cols) {
             for (int e = 0; e < rows - ocol; ++e) dst[e] = *LDS_PTR(uint8_t, tile + tc * QT_PITCH + trc + e);
         }
+    }
+}
+
+// The same one element per lane, both outputs written directly: for matrices of a few rows or columns, of which a tile
+// holds little, and for small ones, whose time is latency and not bandwidth (see the rule at the launch).
+template <int DT, int FMT>
+__global__ __launch_bounds__(kThreads) void quantize_transpose_elements_kernel(const void* __restrict__ x, int64_t rows, int64_t cols,
+                                                                              const float* __restrict__ scale_dev,
+                                                                              uint8_t* __restrict__ q, uint8_t* __restrict__ qt)
+{
+    const float s = *scale_dev;
+    const size_t n = (size_t)rows * (size_t)cols, stride = (size_t)gridDim.x * kThreads;
+    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) {
+        const uint8_t b = (uint8_t)encode_bits<FMT>(load_scalar<DT>(x, i) * s);
+        if (q) q[i] = b;
+        qt[(i % (size_t)cols) * (size_t)rows + i / (size_t)cols] = b;
     }
 }
 
@@ -653,13 +669,37 @@ int launch_quantize_transpose(const void* x, int64_t rows, int64_t cols, int in_
                               uint8_t* q_out, uint8_t* qt_out, hipStream_t stream)
 {
     if (rows == 0 || cols == 0) return FP8_OK;
-    const int tcols = in_dtype == FP8_BF16 ? TransposeTile<FP8_BF16>::cols : TransposeTile<FP8_F32>::cols;
+    // One element per lane where a tile would hold little of the matrix, or where there are too few tiles (measured on
+    // odd sizes, tiles against elements: 4194304 x 1 bf16 277 us and 9.8, 3 x 1398101 fp32 53 and 11, 1261 x 13 bf16 16 and 4.2,
+    // 1001 x 1001 bf16 13 and 9.5; and the other way round 17 x 1973791 fp32 65 and 139, 135301 x 31 fp32 11 and 17, 1000 x 1000
+    // fp32 8.0 and 9.5).
+    const int full = in_dtype == FP8_F32 ? 128 : 256, tcols = cols <= 64 ? 64 : cols <= 128 ? 128 : full;
+    const uint64_t small = (rows % TT == 0 && cols % tcols == 0 ? 1u << 18 : 1u << 19) * (in_dtype == FP8_F32 ? 1 : 2);
+    if (cols < 14 || rows < 12 || (uint64_t)rows * (uint64_t)cols <= small) {
+        const dim3 few(grid_for((size_t)rows * (size_t)cols, 4096));
+        FP8MM_DISPATCH_DT_FMT(quantize_transpose_elements_kernel, few, x, rows, cols, scale_dev, q_out, qt_out);
+        return check_launch("quantize_transpose");
+    }
     const int64_t tiles_r = (rows + TT - 1) / TT, tiles_c = (cols + tcols - 1) / tcols;
     if (tiles_r * tiles_c >= (1ll << 31))
         return fail(FP8_ERR_UNSUPPORTED, "quantize_transpose: %lld x %lld tiles exceed the grid limit", (long long)tiles_r, (long long)tiles_c);
     const dim3 grid((unsigned)(tiles_r * tiles_c));
     const bool diagonal = rows >= 4096 && (rows & (rows - 1)) == 0;      // see "Tile order" at the kernel
-    FP8MM_DISPATCH_DT_FMT(quantize_transpose_kernel, grid, x, rows, cols, scale_dev, q_out, qt_out, (int)tiles_r, (int)tiles_c, diagonal);
+    const int part = tcols == full && rows <= TT / 2 ? rows <= TT / 4 ? 4 : 2 : 1;
+#define FP8MM_QT_(DT, FMT, TC, PART) \
+    hipLaunchKernelGGL((quantize_transpose_kernel<DT, FMT, TC, PART>), grid, dim3(kThreads), 0, stream, x, rows, cols, scale_dev, q_out, qt_out, (int)tiles_r, (int)tiles_c, diagonal)
+#define FP8MM_QT(DT, FMT, FULL)                                       \
+    do {                                                              \
+        if (part == 4) FP8MM_QT_(DT, FMT, FULL, 4);                   \
+        else if (part == 2) FP8MM_QT_(DT, FMT, FULL, 2);              \
+        else if (tcols == 64) FP8MM_QT_(DT, FMT, 64, 1);              \
+        else if (tcols == 128) FP8MM_QT_(DT, FMT, 128, 1);            \
+        else FP8MM_QT_(DT, FMT, FULL, 1);                             \
+    } while (0)
+    if (in_dtype == FP8_F32) { if (fmt == FP8_E4M3) FP8MM_QT(FP8_F32, FP8_E4M3, 128); else FP8MM_QT(FP8_F32, FP8_E5M2, 128); }
+    else { if (fmt == FP8_E4M3) FP8MM_QT(FP8_BF16, FP8_E4M3, 256); else FP8MM_QT(FP8_BF16, FP8_E5M2, 256); }
+#undef FP8MM_QT
+#undef FP8MM_QT_
     return check_launch("quantize_transpose");
 }
 
