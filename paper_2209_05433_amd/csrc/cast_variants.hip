@@ -577,10 +577,12 @@ int launch_quantize_amax(const void* x, size_t n, int in_dtype, int fmt, const f
     // ordinary stores are best (2^28 elements: 134 us, against 142 with 16384 workgroups and 148 with
     // non-temporal stores); an output beyond the memory-side cache goes out non-temporally from many
     // short runs (6.04 10^8 elements: 329 us against 367).  Up to kAloneItems a single workgroup
-    // casts the tensor, which needs no cleared cell: one launch instead of two.
+    // casts the tensor, which needs no cleared cell: one launch instead of two.  In between a lane takes
+    // several items once there are 128 workgroups: each more is an atomic on one cell, and they end together
+    // (3 10^6 bf16 elements 10.7 us with one item a lane, 8.4 with four; 3 10^5 6.2 and 8.4).
     const bool nts = n >= kStreamingStoreBytes;
     const size_t items = n / 16;
-    const size_t per_lane = items < (size_t)kThreads * 512 ? 1 : items < (size_t)kThreads * 1024 ? 2 : 4;
+    const size_t per_lane = items < (size_t)1 << 15 ? 1 : in_dtype == FP8_F32 && items < (size_t)1 << 18 ? 2 : 4;
     const dim3 grid(items <= kAloneItems ? 1 : grid_for((items + per_lane - 1) / per_lane, nts ? kCastBlocks : 512));
     if (grid.x > 1 || n == 0) hipLaunchKernelGGL(store_u32_kernel, dim3(1), dim3(1), 0, stream, bits, 0u);
     if (n == 0) return check_launch("quantize_amax init");
