@@ -172,7 +172,7 @@ def test_one_launch_casts_without_waiting(M, N, K, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("rows,cols,off", [(1, 1, 1), (37, 3, 0), (5, 8, 1), (18, 121, 0), (70, 515, 1), (9, 2053, 0), (6, 3001, 3), (3, 4099, 0), (2, 20001, 1), (4, 8192, 0), (65, 256, 0)])
+@pytest.mark.parametrize("rows,cols,off", [(1, 1, 1), (37, 3, 0), (5, 8, 1), (18, 121, 0), (70, 515, 1), (9, 2053, 0), (6, 3001, 3), (3, 4099, 0), (2, 20001, 1), (4, 8192, 0), (65, 256, 0), (5, 2048, 1), (7, 4096, 0), (3, 2052, 0)])
 def test_rows_of_every_length(rows, cols, off, dtype):
     """Row maxima, factors and cast in each form (lanes per row), rows that start anywhere and end inside a
     vector; the largest value of a row is its last one."""
