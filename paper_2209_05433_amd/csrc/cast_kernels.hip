@@ -18,11 +18,13 @@ namespace {
 // nvec whole vectors, at any address, then n - nvec*per_vec tail elements.  Every workgroup takes
 // chunks of 32 KB (8 vectors per lane, all loaded before the first compare), four workgroups per
 // compute unit; one atomic per workgroup at the end (with one chunk per workgroup the thousands of
-// atomics on one cell cost a quarter of the run time).  Tensors that give fewer than 512 chunks are cut
-// into chunks of 8 KB: their time is the latency of a few loads, not bandwidth.
+// atomics on one cell cost a quarter of the run time).  The one-launch form cuts tensors of less than 1 MB into
+// chunks of 8 KB: their time is the latency of a few loads (64 KB of bf16 4.1 -> 3.8 us; 4 MB of fp32 5.1 -> 5.5 and
+// 10 MB of bf16 5.8 -> 6.6, all in chunks of 8 KB).  With one atomic per workgroup more workgroups only cost: 4 MB
+// of fp32 6.0 -> 9.8 us.
 constexpr int kAmaxVecs = 8;                                         // per lane and chunk
 constexpr int kAmaxVecsSmall = 2;
-constexpr size_t kAmaxSmallBelow = (size_t)512 * kThreads * kAmaxVecs;   // vectors
+constexpr size_t kAmaxSmallBelow = (size_t)32 * kThreads * kAmaxVecs;    // vectors
 
 // Last step of the amax kernels in their one-launch form (fp8_amax_scale): no cell has to be
 // cleared beforehand and the scale comes out of the same launch.  Every workgroup leaves its
@@ -119,9 +121,9 @@ __device__ __forceinline__ void amax_chunks(const u32x4_any* xv, size_t nvec, un
 }
 
 // Workgroups for a tensor of nvec vectors.
-inline unsigned amax_grid(size_t nvec)
+inline unsigned amax_grid(size_t nvec, bool ticket)
 {
-    const size_t chunk = (size_t)kThreads * (nvec < kAmaxSmallBelow ? kAmaxVecsSmall : kAmaxVecs), chunks = (nvec + chunk - 1) / chunk;
+    const size_t chunk = (size_t)kThreads * (ticket && nvec < kAmaxSmallBelow ? kAmaxVecsSmall : kAmaxVecs), chunks = (nvec + chunk - 1) / chunk;
     return (unsigned)(chunks < 1 ? 1 : chunks > (size_t)kAmaxBlocks ? (size_t)kAmaxBlocks : chunks);
 }
 
@@ -135,7 +137,7 @@ __device__ __forceinline__ void amax_vec_body(const void* __restrict__ x, size_t
     const u32x4_any* xv = (const u32x4_any*)x;
     const size_t nvec = n / PV;
     unsigned run[4] = {0u, 0u, 0u, 0u};
-    if (nvec < kAmaxSmallBelow) amax_chunks<DT, kAmaxVecsSmall>(xv, nvec, bid, grid, run);
+    if (TICKET && nvec < kAmaxSmallBelow) amax_chunks<DT, kAmaxVecsSmall>(xv, nvec, bid, grid, run);
     else amax_chunks<DT, kAmaxVecs>(xv, nvec, bid, grid, run);
     unsigned r;
     if (DT == FP8_F32) {
@@ -405,7 +407,7 @@ template <bool TICKET>
 void launch_amax_kernels(const void* x, size_t n, int in_dtype, unsigned* out, unsigned* ws, int fmt, float* scale_out,
                          hipStream_t stream)
 {
-    const unsigned grid = amax_grid(n / (in_dtype == FP8_F32 ? 4 : 8));
+    const unsigned grid = amax_grid(n / (in_dtype == FP8_F32 ? 4 : 8), TICKET);
     if (in_dtype == FP8_F32)
         hipLaunchKernelGGL((amax_vec_kernel<FP8_F32, TICKET>), dim3(grid), dim3(kThreads), 0, stream, x, n, out, ws, fmt, scale_out);
     else
@@ -450,7 +452,7 @@ int launch_amax_scale_multi(int count, const void* const* x, const size_t* n, in
     const size_t per_vec = in_dtype == FP8_F32 ? 4 : 8;
     for (int i = 0; i < count; ++i) {
         m.x[i] = x[i]; m.n[i] = n[i]; m.fmt[i] = fmt[i]; m.first[i] = total;
-        total += amax_grid(n[i] / per_vec);
+        total += amax_grid(n[i] / per_vec, true);
     }
     for (int i = count; i <= kMultiMax; ++i) m.first[i] = total;
     if (in_dtype == FP8_F32)
