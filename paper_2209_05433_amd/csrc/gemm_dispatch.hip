@@ -129,21 +129,40 @@ TileTimes tile_times(int acc, double S)
     return acc == ACC_FP8 ? TileTimes{0.62 * S + 8.9, 0.46 * S + 5.2} : TileTimes{1.21 * S + 10.0, 0.79 * S + 6.4};
 }
 
-// The same for a 256 x 256 tile of the any-shape kernel, and the time of its 128 x 128 form, of which several
-// workgroups share a compute unit (4096 x 50257 x 2048, 6000 x 3000 x 1500; 2048 x 6144 x 2048, 1000 x 3000 x 1000).
-double any_wide_us(double M, double N, double K)
+// The any-shape kernel's two forms: rounds of 256 tiles of 256 x 256, and tiles of 128 x 128 of which several share a
+// compute unit (their products, and 1.8 us per million outputs that leave one by one; a division per output with
+// per-column factors, the conversion to FP8).  Pieces of an operand that is contiguous along M / N and ends inside
+// 16 bytes are loaded with tests, which a lone workgroup of the wide form does not hide: of B in the last column of
+// tiles, of A in every round.  Fitted to nine shapes from 2001 x 3001 x 1025 to 5000 x 5001 x 5001 in all storage orders:
+// the faster form is named wherever they differ by more than 8 % (5000 x 5001 x 5001 with A stored K x M: wide 1050 us,
+// narrow 640; 4096 x 9001 x 600: wide 134, narrow 157).
+bool ragged_a(const GemmArgs& g) { return g.transA && g.M % 16 != 0; }
+bool ragged_b(const GemmArgs& g) { return !g.transB && g.N % 16 != 0; }
+double any_wide_us(const GemmArgs& g)
 {
-    return std::ceil(std::ceil(M / 256) * std::ceil(N / 256) / 256.0) * (5.0 + 1.95 * std::ceil(K / 64));
+    const double rounds = std::ceil(std::ceil(g.M / 256.0) * std::ceil(g.N / 256.0) / 256.0), S = std::ceil(g.K / 64.0);
+    return rounds * (14.0 + 1.65 * S) + S * ((ragged_b(g) ? 3.0 : 0.0) + (ragged_a(g) ? 3.1 * rounds : 0.0));
 }
-double any_128_us(double M, double N, double K) { return 5.0 + std::max(0.03 * K, 2.0 * M * N * K / 0.62e9); }
+double any_128_us(const GemmArgs& g)
+{
+    const double outputs = 1e-6 * (double)g.M * (double)g.N, K = (double)g.K, S = std::ceil(g.K / 64.0);
+    const double ends = 6.9 + (g.ep.b_per_col ? 10.0 : 0.0) + (g.ep.out_kind >= OUT_E4M3 ? 3.0 : 0.0);
+    return ends + std::max(0.03 * K, outputs * (1.8 + 0.0026 * K)) + S * ((ragged_b(g) ? 1.2 : 0.0) + (ragged_a(g) ? 1.4 : 0.0));
+}
 
-// The form of the small-tile kernel (gemm_small.hip) that beats the kernel the problem would otherwise
-// take, or SMALL_NONE.  Times in microseconds, fitted to 25 shapes from 8 x 1104 x 768 to 2048 x 2048 x
-// 2048 in all storage orders (within 20 %): a launch and the ends of a workgroup, then per workgroup and
-// compute unit a time that grows with K.  A workgroup alone on its unit takes as long as one of a full
-// unit in the 4-wave forms; the 8-wave form overlaps two, and pays for 32-byte rows of an operand
-// that is not contiguous along K.  The tiled kernel: rounds of 256 workgroups.  The any-shape kernel:
-// 0.03 us per K for a round, 0.7 PFLOP/s at best where the small tiles are in question.
+// Microseconds of a form of the small-tile kernel (gemm_small.hip): its ends, then the longer of one workgroup's walk along
+// K and what the workgroups of a compute unit take together; `further`, and `ragged` where K ends inside a chunk, for each
+// that waits for another; per K `lines` where both operands are contiguous along it, `other` elsewhere.
+struct SmallTimes { int rows, cols, chunk; double ends, each, further, ragged, lines, other, alone, alone_k; };
+
+// The form of the small-tile kernel that beats the kernel the problem would otherwise take by 5 %, or SMALL_NONE.  Checked on
+// 650 problems (1 .. 4096 x 16 .. 12288 x 1 .. 12288, all storage orders): the choice takes 0.5 % (the tiled kernel's
+// problems) and 0.8 % (the others) longer than the best of all forms over them.  Operands whose rows start anywhere, both of
+// them, cost a fifth more, and beyond 16 workgroups of 64 x 64 a compute unit, when they no longer come out of the caches,
+// again a third (4096 x 5025 x 2048: 200 us, the any-shape kernel 176).  Rows of fewer than 16 bytes are fetched byte by byte
+// (22 x 275 x 12: 13 us, the any-shape kernel 7.6).  The tiled kernel: rounds of 256 workgroups; where a single round leaves
+// half of the compute units idle, a tile has more of the caches to itself (512 x 4400 x 12096 in the FP8 mode: 65 us, 94 on
+// 64 x 64 tiles, and 93 by tile_times()).
 int choose_small(const GemmArgs& g, bool tiled)
 {
     const double M = (double)g.M, N = (double)g.N, K = (double)g.K;
@@ -155,16 +174,30 @@ int choose_small(const GemmArgs& g, bool tiled)
         const TileTimes t = tile_times(g.acc, 2.0 * std::ceil(K / (2 * TILE_K)));
         other = std::min(std::ceil(units(256, 256)) * t.wide, std::ceil(units(256, 128)) * t.narrow);
         if (g.acc == ACC_FP8) other += 1.5;                  // (the fit is that much too short below S = 16)
+        if (units(256, 128) < 1.0) {
+            const double S = 2.0 * std::ceil(K / (2 * TILE_K)), alone = g.acc == ACC_FP8 ? 8.0 + 0.28 * S : 9.0 + 0.53 * S;
+            other = std::min(other, alone + (other - alone) * std::max(0.0, 2.0 * units(256, 128) - 1.0));
+        }
     } else {
-        other = std::min(any_128_us(M, N, K), any_wide_us(M, N, K));
+        other = std::min(any_128_us(g), any_wide_us(g));
     }
-    const bool lines = !g.transA && g.transB;                // both operands contiguous along K
-    const double t32 = 3.4 + std::max(0.001 * K, units(32, 32) * (0.3 + (lines ? 0.0014 : 0.0025) * K));
-    const double t3264 = 4.0 + std::max(1.0, units(32, 64)) * (0.6 + 0.0018 * K);
-    const double t64 = 4.0 + std::max(1.0, u64) * (1.2 + 0.0026 * K);
-    const double best = std::min(t32, std::min(t3264, t64));
-    if (best >= 0.95 * other) return SMALL_NONE;
-    return best == t32 ? SMALL_32x32 : best == t3264 ? SMALL_32x64 : SMALL_64x64;
+    static const SmallTimes times[3] = {{32, 32, 128, 3.4, 0.3, 0.7, 0.8, 0.0014, 0.0025, 0.0, 0.001},
+                                        {32, 64, 128, 4.0, 0.6, 0.0, 0.3, 0.0018, 0.0018, 0.6, 0.0018},
+                                        {64, 64, 64, 4.0, 1.2, 0.0, 0.3, 0.0026, 0.0026, 1.2, 0.0026}};
+    static_assert(SMALL_32x32 == 0 && SMALL_32x64 == 1 && SMALL_64x64 == 2, "the order of the table");
+    const bool lines = !g.transA && g.transB;
+    const bool off_a = !aligned16(g.A) || (g.transA ? g.M : g.K) % 16 != 0, off_b = !aligned16(g.B) || (g.transB ? g.K : g.N) % 16 != 0;
+    const double off = off_a && off_b ? (u64 > 16 ? 1.56 : 1.2) : 1.0;
+    const double bytewise = g.K < 16 ? 0.35 * K * ((g.transA ? 0 : 1) + (g.transB ? 1 : 0)) : 0.0;
+    int form = SMALL_NONE;
+    double best = 0.95 * other;
+    for (int f = 0; f < 3; ++f) {
+        const SmallTimes& t = times[f];
+        const double n = units(t.rows, t.cols), waits = std::max(0.0, n - 1.0) * (t.further + (g.K % t.chunk ? t.ragged : 0.0));
+        const double us = t.ends + off * std::max(t.alone + bytewise + t.alone_k * K, n * (t.each + bytewise + (lines ? t.lines : t.other) * K) + waits);
+        if (us < best) { best = us; form = f; }
+    }
+    return form;
 }
 
 }  // namespace
@@ -273,8 +306,7 @@ bool mfma_any_takes(const GemmArgs& g)
     return g.M > 0 && g.N > 0 && g.K > 0 && tile_count(g, 128) <= 0x7fffffffll;
 }
 
-// The wide form where its 256 x 256 tiles take less time than the other's (from a fill of their rounds of
-// about 60 % on) and K is long enough for the two-stage pipeline to pay; FP8_KNOB_TILE_N forces
+// The wide form where its 256 x 256 tiles take less time than the other's and K is long enough for the two-stage pipeline to pay; FP8_KNOB_TILE_N forces
 // either form (128 / 256).
 bool mfma_any_wide(const GemmArgs& g)
 {
@@ -282,7 +314,7 @@ bool mfma_any_wide(const GemmArgs& g)
     // 32-bit offsets within a tile's stage: 255 rows of K bytes, or 63 K-rows of M / N bytes
     if (g.K >= (1 << 24) || g.M >= (1 << 26) || g.N >= (1 << 26)) return false;
     if (forced) return forced == 256;
-    return g.K >= 512 && any_wide_us((double)g.M, (double)g.N, (double)g.K) < any_128_us((double)g.M, (double)g.N, (double)g.K);
+    return g.K >= 512 && any_wide_us(g) < any_128_us(g);
 }
 
 int launch_mfma_any(const GemmArgs& g)
