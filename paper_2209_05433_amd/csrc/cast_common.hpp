@@ -62,6 +62,15 @@ __device__ __forceinline__ unsigned scalar_mag(const void* x, size_t i)
     return ((unsigned)(((const unsigned short*)x)[i] & 0x7fffu)) << 16;
 }
 
+// Packed running maximum (see vec_mag_max) -> sign-stripped fp32 bits.
+template <int DT>
+__device__ __forceinline__ unsigned run_to_bits(unsigned run)
+{
+    if (DT == FP8_F32) return run;
+    const u16x2 p = __builtin_bit_cast(u16x2, run);
+    return (unsigned)(p.x > p.y ? p.x : p.y) << 16;
+}
+
 template <int THREADS = kThreads>
 __device__ __forceinline__ unsigned block_max_u32(unsigned v)
 {
@@ -202,7 +211,6 @@ inline int grid_for(size_t work_items, int max_blocks)
     return (int)b;
 }
 
-inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 }  // namespace
 }  // namespace fp8mm

@@ -291,15 +291,6 @@ constexpr unsigned kCastSlots = kCastDone + 32;                      // ... and 
 constexpr unsigned kPatience = 20000;                                // ticks of the 100 MHz clock: 200 us
 static_assert(kOneLaunchBytes / (16 * kCastChunk) + 1 <= 64 && (kCastSlots + 64) * sizeof(unsigned) <= FP8_AMAX_WORKSPACE_BYTES, "a slot per lane");
 
-// Packed running maximum of vectors (vec_mag_max) -> fp32 bits.
-template <int DT>
-__device__ __forceinline__ unsigned packed_to_bits(unsigned run)
-{
-    if (DT == FP8_F32) return run;
-    const u16x2 p = __builtin_bit_cast(u16x2, run);
-    return (unsigned)(p.x > p.y ? p.x : p.y) << 16;
-}
-
 // The vectors of chunk b that the thread holds (zeros where there are none), and its tail element if it has one
 // (the elements behind the last whole vector belong to the last chunk): their largest magnitude.
 template <int DT>
@@ -317,7 +308,7 @@ __device__ __forceinline__ unsigned load_chunk(const void* x, size_t n, size_t b
 #pragma unroll
     for (int k = 0; k < kCastVecs; ++k) run = vec_mag_max<DT>(v[k], run);
     const size_t t = nvec * Elem<DT>::per_vec + threadIdx.x;
-    const unsigned r = packed_to_bits<DT>(run);
+    const unsigned r = run_to_bits<DT>(run);
     return tail && t < n ? max(r, scalar_mag<DT>(x, t)) : r;
 }
 
@@ -402,7 +393,7 @@ __global__ __launch_bounds__(kCastThreads) void amax_cast_kernel(MultiTensors m,
 
 namespace {
 // ws == nullptr: amax_out was cleared by the caller, workgroups raise it with atomics.
-// ws != nullptr: the one-launch form (see amax_finish_ticket); grids stay within kAmaxWorkgroupsMax.
+// ws != nullptr: the one-launch form (see amax_finish_ticket); grids stay within kAmaxBlocks.
 template <bool TICKET>
 void launch_amax_kernels(const void* x, size_t n, int in_dtype, unsigned* out, unsigned* ws, int fmt, float* scale_out,
                          hipStream_t stream)

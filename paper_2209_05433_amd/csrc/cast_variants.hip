@@ -20,15 +20,6 @@
 namespace fp8mm {
 namespace {
 
-// Packed running maximum (see vec_mag_max) -> sign-stripped fp32 bits.
-template <int DT>
-__device__ __forceinline__ unsigned run_to_bits(unsigned run)
-{
-    if (DT == FP8_F32) return run;
-    const u16x2 p = __builtin_bit_cast(u16x2, run);
-    return (unsigned)(p.x > p.y ? p.x : p.y) << 16;
-}
-
 // Raises *cell to at least `bits`.  Most workgroups find the cell already large enough and skip
 // the atomic, so thousands of workgroups do not queue on one address.
 __device__ __forceinline__ void raise_cell(unsigned* cell, unsigned bits)
@@ -253,19 +244,6 @@ __device__ __forceinline__ u32x4 drop_elements(u32x4 v, int k)
     return v;
 }
 
-// The `count` (1 .. per_vec - 1) elements of a row too short for a vector, one by one.
-template <int DT>
-__device__ __forceinline__ u32x4 load_elements(const void* src, int count)
-{
-    u32x4 v = {0u, 0u, 0u, 0u};
-    for (int e = 0; e < count; ++e) {
-        const unsigned x = DT == FP8_F32 ? ((const unsigned*)src)[e] : (unsigned)((const unsigned short*)src)[e] << (16 * (e & 1));
-        const int d = DT == FP8_F32 ? e : e >> 1;
-        v = (u32x4){v.x | (d == 0 ? x : 0u), v.y | (d == 1 ? x : 0u), v.z | (d == 2 ? x : 0u), v.w | (d == 3 ? x : 0u)};
-    }
-    return v;
-}
-
 // TC: tile columns, 512 bytes of x, fewer where the matrix has no more (64 or 128).  PART: the matrix has no more than
 // TT / PART rows, and no pass goes beyond them (16 x 262144 fp32 14.0 -> 9.3 us; as a choice of every last tile in the one
 // kernel, its code cost 5000 x 6144 a microsecond).
@@ -312,7 +290,7 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const void
         } else {
 #pragma unroll
             for (int p = 0; p < PASSES; ++p) v[p] = (u32x4){0u, 0u, 0u, 0u};
-            if (left > 0 && cols >= EPL) {
+            if (left > 0) {
                 const int64_t from = left == EPL ? c : cols - EPL;
 #pragma unroll
                 for (int p = 0; p < PASSES; ++p) v[p] = __builtin_nontemporal_load((const u32x4_any*)row_at(p, from));
@@ -320,9 +298,6 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const void
 #pragma unroll
                     for (int p = 0; p < PASSES; ++p) v[p] = drop_elements<DT>(v[p], EPL - left);
                 }
-            } else if (left > 0) {
-#pragma unroll
-                for (int p = 0; p < PASSES; ++p) v[p] = load_elements<DT>(row_at(p, c), left);
             }
         }
 #pragma unroll

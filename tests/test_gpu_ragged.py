@@ -38,7 +38,8 @@ def guards_hold(buf, n, off):
                                            # the line between tiles and one element per lane: few rows, few columns, few elements
                                            (11, 96001, 1), (12, 96001, 1), (81000, 13, 3), (81000, 14, 0), (1024, 256, 1), (1024, 257, 0), (1024, 1024, 0), (1025, 1025, 1),
                                            # tiles of 64, 128 and 256 columns, their last row of tiles a quarter, a half and nearly full
-                                           (16384 + 30, 64, 0), (16384 + 33, 65, 1), (8192 + 64, 128, 0), (8192 + 100, 129, 1), (32, 40000, 0), (33, 40001, 3), (64, 20000, 1), (65, 20003, 0)])
+                                           (16384 + 30, 64, 0), (16384 + 33, 65, 1), (8192 + 64, 128, 0), (8192 + 100, 129, 1), (32, 40000, 0), (33, 40001, 3), (64, 20000, 1), (65, 20003, 0),
+                                           (1100, 1003, 1), (1030, 1022, 0), (1027, 1029, 3)])
 def test_transposing_cast_at_the_edges_of_its_tiles(rows, cols, off, dtype):
     n = rows * cols
     x, host = source(n, dtype, off)
