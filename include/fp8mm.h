@@ -241,11 +241,10 @@ int fp8_quantize_transpose(const void* x, int64_t rows, int64_t cols, int in_dty
  * zeros).  Any shape is accepted.  The tiled matrix-core kernel takes those with K a
  * multiple of 16 and 16-byte aligned A and B whose operand rows start on 16-byte
  * boundaries: N a multiple of 16 where B is given as K x N, M a multiple of 16 where A is
- * given as K x M (see fp8_gemm_ex); with B given as N x K any N goes.  A C that is not
- * 16-byte aligned, or whose rows are not (N not a multiple of 16), is stored element by
- * element.  The other shapes and alignments take a second matrix-core kernel (register-staged
- * loads, 256 x 256 or 128 x 128 tiles, the same arithmetic and bound, 0.5 - 0.8 of the rate; see
- * fp8_gemm_plan).  fp8_gemm_dscale reads the two scales from device memory instead.
+ * given as K x M (see fp8_gemm_ex); with B given as N x K any N goes, and C may lie
+ * anywhere.  The other shapes and alignments take a second matrix-core kernel (register-staged
+ * loads, 256 x 256 or 128 x 128 tiles, the same arithmetic and bound, 0.5 - 0.8 of the rate),
+ * and small problems of either kind a third (32 x 32 to 64 x 64 tiles); see fp8_gemm_plan.  fp8_gemm_dscale reads the two scales from device memory instead.
  */
 int fp8_gemm(const uint8_t* A, int fmtA, float sA,
              const uint8_t* B, int fmtB, float sB,
@@ -395,11 +394,11 @@ int fp8_scaled_gemm(const void* a, const void* b, int in_dtype, int transA, int 
                     void* C, int out_dtype, int flags, void* stream);
 
 /*
- * Which kernel the GEMM entry points would run for a problem (diagnostics; nothing is launched and
+ * Which kernel the GEMM entry points would run for a problem, small ones apart (diagnostics; nothing is launched and
  * no pointer is dereferenced: only shapes, storage orders and pointer alignment decide).  Pass the
  * pointers of the intended call; sB_per_column is the per-column factor vector of fp8_gemm_fused or
  * NULL.  Returns FP8_PLAN_NO_GEMM if M, N or K is 0, otherwise one of FP8_PLAN_TILED_256x256,
- * FP8_PLAN_TILED_256x128 (the tiled matrix-core kernel, tile chosen for how well it fills the chip),
+ * FP8_PLAN_TILED_256x128 (the tiled matrix-core kernel, the tile whose rounds take less time),
  * FP8_PLAN_TILED_MIXED (the same kernel with both tile widths in one launch: 256-wide tiles for the
  * first columns of the output, 128-wide ones for the rest, where that fills the rounds of workgroups
  * better than either width alone),
@@ -408,13 +407,14 @@ int fp8_scaled_gemm(const void* a, const void* b, int in_dtype, int transA, int 
  * kernel's rate, fifteen to twenty-five times that of plain FMAs; it computes in the default accumulation mode also under FP8_GEMM_MFMA8, which
  * meets that flag's bound a fortiori) or FP8_PLAN_FMA_KERNEL (plain FMAs: only when forced by
  * FP8_KNOB_GEMM_KERNEL or for outputs of more than 2^31 - 1 tiles of 128 x 128), ORed with
- * FP8_PLAN_ELEMENTWISE_STORES where the rows of the output do not start on 16-byte boundaries, and
+ * FP8_PLAN_ELEMENTWISE_STORES where the rows of the output (or the per-column factors) do not start on
+ * 16-byte boundaries (they are stored in vectors all the same; the name is from when they were not), and
  * with FP8_PLAN_PERSISTENT where the 256 x 128 kernel runs in its persistent form (answered for
  * per-tensor factors, an fp32 output and the default accumulation mode; with a bf16 output or
  * FP8_GEMM_MFMA8 the form is used over a narrower range of K, see FP8_KNOB_PERSIST).  Problems of few
  * tiles run on a kernel of smaller ones (32 x 32 to 64 x 64, the waves of a workgroup sharing K; the same
  * instructions, accumulation mode and bound); the answer is then still the one above that describes
- * their shape and alignment.
+ * their shape and alignment (FP8_KNOB_SMALL = 1 keeps them on the kernel that the answer names).
  * A negative value is minus an fp8_status_t (bad arguments).  Section 2 fixes the arithmetic,
  * not the kernel: every plan computes the same product within the stated bounds.
  */

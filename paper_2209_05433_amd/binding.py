@@ -125,8 +125,8 @@ def fp8_get_knob(knob: int) -> int:
 
 
 def fp8_gemm_plan(A: torch.Tensor, transA: bool, B: torch.Tensor, transB: bool, C: torch.Tensor, sB_per_column=None) -> int:
-    """Which kernel the GEMM entry points would run for these tensors (an fp8_plan_t, possibly ORed
-    with FP8_PLAN_ELEMENTWISE_STORES); nothing is launched."""
+    """Which kernel the GEMM entry points would run for these tensors, the kernel of small tiles apart (an
+    fp8_plan_t, possibly ORed with FP8_PLAN_ELEMENTWISE_STORES and FP8_PLAN_PERSISTENT); nothing is launched."""
     M, K = (A.shape[1], A.shape[0]) if transA else A.shape
     N = B.shape[0] if transB else B.shape[1]
     plan = lib().fp8_gemm_plan(A.data_ptr(), int(bool(transA)), B.data_ptr(), int(bool(transB)), C.data_ptr(), M, N, K,

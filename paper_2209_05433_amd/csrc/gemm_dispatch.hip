@@ -2,7 +2,8 @@
 //
 // Shapes and pointers that meet the tiled kernel's conditions (K a multiple of 16, 16-byte aligned
 // operands whose rows start on 16-byte boundaries) go to one of its instances; everything else to the
-// matrix-core kernel for any shape (gemm_mfma_any.hip).  The generic kernel below (plain FMAs: any
+// matrix-core kernel for any shape (gemm_mfma_any.hip); small problems of either kind to the kernel of small
+// tiles (gemm_small.hip) where a model of the run times says it is the faster one.  The generic kernel below (plain FMAs: any
 // shape, any alignment, every storage order, the same epilogue) remains as the independent
 // cross-check the tests force through a knob, and for outputs with more tiles than a grid holds
 // (arXiv 2209.05433, Section 2: FP8 operands, fp32 accumulation, scales taken out once per output).

@@ -19,7 +19,8 @@
 //     accumulation: the arithmetic of the tiled kernel's default mode, so the same error bound
 //     holds (arXiv 2209.05433, Section 2: FP8 operands, single-precision accumulation, factors
 //     taken out once per output);
-//   - the epilogue is that of the generic kernel, element by element (any N, any output alignment).
+//   - the epilogue of the 128 x 128 form is that of the generic kernel, element by element (any N, any output
+//     alignment).
 // 32 KB of LDS and about 100 registers per lane: several workgroups share a compute unit and hide
 // each other's barriers and load latencies; nothing in this form is pipelined by hand.  Problems of
 // many tiles take the wide form further down (256 x 256 tiles, one workgroup per compute unit, the tiled

@@ -9,7 +9,7 @@
 //   - a few hundred workgroups exist where the tiled kernel has ten, and K is walked NW times faster;
 //   - every byte is read once per workgroup, by the one wave that multiplies it: nothing is shared
 //     between waves until the end, and there is no barrier in the K loop;
-//   - D chunks of both operands are in flight per wave, in registers.
+//   - D chunks of both operands (two; one with 64 x 64 tiles) are in flight per wave, in registers.
 // A chunk is fetched as it lies in memory, neighbouring lanes on neighbouring 16 bytes of a row (loads
 // at any address; pieces that reach over an edge load the last 16 bytes of their row and shift), and
 // goes into a slab of LDS that belongs to the wave, out of which the fragments of the matrix

@@ -360,7 +360,7 @@ def test_edge_tiles_agree_with_the_generic_kernel_exactly_on_integers(tile_n):
 def test_any_n_with_b_stored_n_by_k_and_unaligned_outputs(mode, tile_n):
     """With B stored N x K (weights kept [out, in]) the tiled kernel takes any N, e.g. a vocabulary
     size, and an output or a per-column factor vector that does not start on a 16-byte boundary: its
-    epilogue then stores element by element.  Every output kind, factors per row and per column, the
+    epilogue then stores vectors at any address.  Every output kind, factors per row and per column, the
     output amax; nothing may be written outside D."""
     rng = np.random.default_rng(77)
     for (M, N, K, transA, off) in [(300, 1001, 256, 0, 0), (64, 17, 128, 0, 0), (257, 1, 128, 0, 0),
