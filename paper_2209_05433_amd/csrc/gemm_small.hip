@@ -356,7 +356,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) amax_bits = max(amax_bits, (unsigned)__shfl_xor((int)amax_bits, d, 64));
         if (l == 0) *LDS_PTR(unsigned, cells + w) = amax_bits;
-        __syncthreads();
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);            // (the compiler keeps the LDS accesses on their sides)
+        __builtin_amdgcn_s_waitcnt(0xC07F);                 // lgkmcnt(0) only: nobody waits for the outputs' stores
+        __builtin_amdgcn_s_barrier();
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
         if (w == 0) {
             unsigned m = l < NW ? *LDS_PTR(unsigned, cells + l) : 0u;
 #pragma unroll
