@@ -414,7 +414,9 @@ int fp8_scaled_gemm(const void* a, const void* b, int in_dtype, int transA, int 
  * FP8_GEMM_MFMA8 the form is used over a narrower range of K, see FP8_KNOB_PERSIST).  Problems of few
  * tiles run on a kernel of smaller ones (32 x 32 to 64 x 64, the waves of a workgroup sharing K; the same
  * instructions, accumulation mode and bound); the answer is then still the one above that describes
- * their shape and alignment (FP8_KNOB_SMALL = 1 keeps them on the kernel that the answer names).
+ * their shape and alignment (FP8_KNOB_SMALL = 1 keeps them on the kernel that the answer names).  Where 256 x 192
+ * tiles of the tiled kernel fill the rounds of workgroups better they are taken, alone or with 256 x 128 ones; the answer
+ * is then the best choice without them (FP8_KNOB_TILE_192 = 1 makes it the kernel that runs).
  * A negative value is minus an fp8_status_t (bad arguments).  Section 2 fixes the arithmetic,
  * not the kernel: every plan computes the same product within the stated bounds.
  */
@@ -454,10 +456,13 @@ int fp8_gemm_plan(const uint8_t* A, int transA, const uint8_t* B, int transB, co
  *   FP8_KNOB_PATIENCE     the one-launch amax + cast of fp8_scaled_gemm: 0 a workgroup waits 200 us for the other
  *                         workgroups' maxima before it computes the missing ones itself, 1 it does not wait
  *                         (FP8MM_PATIENCE)
+ *   FP8_KNOB_TILE_192     the tiled kernel's tile of 256 x 192: 0 where the dispatcher's model of the run time
+ *                         prefers it (and no other knob asks for a kernel, tile width or form), 1 never
+ *                         (fp8_gemm_plan then names the kernel that runs), 2 wherever the tiled kernel runs (FP8MM_TILE_192)
  */
 typedef enum { FP8_KNOB_CAST_PATH = 0, FP8_KNOB_TILE_N = 1, FP8_KNOB_GROUP_M = 2, FP8_KNOB_GEMM_KERNEL = 3,
                FP8_KNOB_SPLIT_K = 4, FP8_KNOB_CAST_RUN = 5, FP8_KNOB_PERSIST = 6, FP8_KNOB_MIXED = 7,
-               FP8_KNOB_SMALL = 8, FP8_KNOB_PATIENCE = 9, FP8_KNOB_COUNT = 10 } fp8_knob_t;
+               FP8_KNOB_SMALL = 8, FP8_KNOB_PATIENCE = 9, FP8_KNOB_TILE_192 = 10, FP8_KNOB_COUNT = 11 } fp8_knob_t;
 int fp8_set_knob(int knob, int value);
 int fp8_get_knob(int knob);
 

@@ -22,7 +22,7 @@ FP8_PLAN_NO_GEMM, FP8_PLAN_FMA_KERNEL, FP8_PLAN_TILED_256x256, FP8_PLAN_TILED_25
 FP8_PLAN_ELEMENTWISE_STORES = 16
 FP8_MULTI_MAX = 4
 FP8_PLAN_PERSISTENT = 32
-FP8_KNOB_CAST_PATH, FP8_KNOB_TILE_N, FP8_KNOB_GROUP_M, FP8_KNOB_GEMM_KERNEL, FP8_KNOB_SPLIT_K, FP8_KNOB_CAST_RUN, FP8_KNOB_PERSIST, FP8_KNOB_MIXED, FP8_KNOB_SMALL, FP8_KNOB_PATIENCE = range(10)
+FP8_KNOB_CAST_PATH, FP8_KNOB_TILE_N, FP8_KNOB_GROUP_M, FP8_KNOB_GEMM_KERNEL, FP8_KNOB_SPLIT_K, FP8_KNOB_CAST_RUN, FP8_KNOB_PERSIST, FP8_KNOB_MIXED, FP8_KNOB_SMALL, FP8_KNOB_PATIENCE, FP8_KNOB_TILE_192 = range(11)
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libfp8mm.so")
 NATIVE_PATH = os.path.join(os.path.dirname(LIB_PATH), "_native.so")

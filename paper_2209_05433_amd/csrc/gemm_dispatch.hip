@@ -123,11 +123,12 @@ inline int64_t tile_count(const GemmArgs& g, int64_t edge) { return ((g.M + edge
 namespace {
 
 // Microseconds for one tile of the tiled kernel, S stages of 64 along K, as one of several rounds of 256 that
-// run at a time (fitted to 4096 x 6144 over K = 512 .. 2048 and to 3294 x 11648 x 4288; within 5 %).
-struct TileTimes { double wide, narrow; };
+// run at a time (fitted to 4096 x 6144 over K = 512 .. 2048 and to 3294 x 11648 x 4288; within 5 %).  middle: the
+// 256 x 192 tile, fitted to 70 products so that it is taken where it is the faster one.
+struct TileTimes { double wide, middle, narrow; };
 TileTimes tile_times(int acc, double S)
 {
-    return acc == ACC_FP8 ? TileTimes{0.62 * S + 8.9, 0.46 * S + 5.2} : TileTimes{1.21 * S + 10.0, 0.79 * S + 6.4};
+    return acc == ACC_FP8 ? TileTimes{0.62 * S + 8.9, 0.58 * S + 7.5, 0.46 * S + 5.2} : TileTimes{1.21 * S + 10.0, 1.03 * S + 7.6, 0.79 * S + 6.4};
 }
 
 // The any-shape kernel's two forms: rounds of 256 tiles of 256 x 256, and tiles of 128 x 128 of which several share a
@@ -207,10 +208,10 @@ int choose_small(const GemmArgs& g, bool tiled)
 GemmPlan plan_gemm(const GemmArgs& g)
 {
     const int64_t M = g.M, N = g.N, K = g.K;
-    GemmPlan plan{!force_generic() && mfma_any_takes(g) ? GEMM_MFMA_ANY : GEMM_GENERIC, false, false, 0, SMALL_NONE};
+    GemmPlan plan{!force_generic() && mfma_any_takes(g) ? GEMM_MFMA_ANY : GEMM_GENERIC, false, false, 0, SMALL_NONE, false, 0};
     // a knob that asks for another form of the kernels keeps the small one out, unless FP8_KNOB_SMALL names a form of it
     const int small = g.splits <= 1 && !force_generic() ? knob(FP8_KNOB_SMALL) : 1;
-    const bool small_allowed = small == 0 && !knob(FP8_KNOB_TILE_N) && !knob(FP8_KNOB_GEMM_KERNEL) && !knob(FP8_KNOB_MIXED) && !knob(FP8_KNOB_PERSIST);
+    const bool small_allowed = small == 0 && !knob(FP8_KNOB_TILE_N) && !knob(FP8_KNOB_GEMM_KERNEL) && !knob(FP8_KNOB_MIXED) && !knob(FP8_KNOB_PERSIST) && knob(FP8_KNOB_TILE_192) != 2;
     const uint64_t ldmax = (uint64_t)(M > N ? (M > K ? M : K) : (N > K ? N : K));
     const bool fits32 = 256 * ldmax < (1ull << 32) && M < (1ll << 31) - TILE_M && N < (1ll << 31) - TILE_N &&
                         K < (1ll << 31) &&
@@ -248,38 +249,42 @@ GemmPlan plan_gemm(const GemmArgs& g)
     // the wide tiles fill little of their last round (3001 x 6144 x 2048: 3 - 7 %).  Problems of
     // more than 64 rounds are left alone (the last round is then under 2 %).
     // Knob FP8_KNOB_MIXED: 0 = by the model, 1 = never, 2 = wherever it is possible.
-    const int mk = knob(FP8_KNOB_MIXED);
-    if (!tn && mk != 1 && plan.small == SMALL_NONE && g.splits <= 1 && N > TILE_N && tiles_m * wide_cols_all <= 64 * 256) {
-        const double S = 2.0 * (double)((K + 2 * TILE_K - 1) / (2 * TILE_K));
-        const double tw = tile.wide, tnar = tile.narrow;
-        // time until the last of Tw wide and then Tn narrow tiles ends on 256 units
-        auto makespan = [&](int64_t Tw, int64_t Tn) {
-            const int64_t q = Tw / 256, k = Tw % 256;          // k units get q + 1 wide tiles, the others q
-            if (Tn == 0) return (double)(q + (k > 0)) * tw;
-            double best = 1e300;
-            for (int64_t r = 0; r <= Tn; ++r) {                // r narrow tiles on the units that are free first
-                const int64_t late = r * tnar >= tw ? (int64_t)((r * tnar - tw) / tnar) : 0;     // and as many as fit on the others
-                if ((256 - k) * r + k * late >= Tn) { best = std::max((double)(q + (k > 0)) * tw, (double)q * tw + (double)r * tnar); break; }
-            }
-            for (int64_t r = 1; r <= Tn; ++r) {                // or the last one ends on a unit that had q + 1 wide tiles
-                const int64_t early = (int64_t)((tw + r * tnar) / tnar);
-                if (k * r + (256 - k) * early >= Tn) { best = std::min(best, (double)(q + 1) * tw + (double)r * tnar); break; }
-                if ((double)(q + 1) * tw + (double)r * tnar >= best) break;
-            }
-            return best;
-        };
-        const double uniform = std::min(makespan(tiles_m * wide_cols_all, 0), makespan(0, tiles_m * ((N + 127) / 128)));
+    const int mk = knob(FP8_KNOB_MIXED), pk = knob(FP8_KNOB_PERSIST), middle_knob = knob(FP8_KNOB_TILE_192);
+    const double S = 2.0 * (double)((K + 2 * TILE_K - 1) / (2 * TILE_K));
+    double chosen_us = 1e300;
+    // time until the last of Tw wide tiles (tw us each) and then Tn narrow ones ends on 256 units
+    const double tnar = tile.narrow;
+    auto makespan = [&](int64_t Tw, int64_t Tn, double tw) {
+        const int64_t q = Tw / 256, k = Tw % 256;          // k units get q + 1 wide tiles, the others q
+        if (Tn == 0) return (double)(q + (k > 0)) * tw;
+        double best = 1e300;
+        for (int64_t r = 0; r <= Tn; ++r) {                // r narrow tiles on the units that are free first
+            const int64_t late = r * tnar >= tw ? (int64_t)((r * tnar - tw) / tnar) : 0;     // and as many as fit on the others
+            if ((256 - k) * r + k * late >= Tn) { best = std::max((double)(q + (k > 0)) * tw, (double)q * tw + (double)r * tnar); break; }
+        }
+        for (int64_t r = 1; r <= Tn; ++r) {                // or the last one ends on a unit that had q + 1 wide tiles
+            const int64_t early = (int64_t)((tw + r * tnar) / tnar);
+            if (k * r + (256 - k) * early >= Tn) { best = std::min(best, (double)(q + 1) * tw + (double)r * tnar); break; }
+            if ((double)(q + 1) * tw + (double)r * tnar >= best) break;
+        }
+        return best;
+    };
+    const bool few_rounds = plan.small == SMALL_NONE && g.splits <= 1 && tiles_m * wide_cols_all <= 64 * 256;
+    if (few_rounds) chosen_us = std::min(makespan(tiles_m * wide_cols_all, 0, tile.wide), makespan(0, tiles_m * ((N + 127) / 128), tile.wide));
+    if (!tn && mk != 1 && few_rounds && N > TILE_N) {
+        const double uniform = chosen_us;
         double best = 1e300;
         int64_t best_c = 0;
         for (int64_t c = 1; c * TILE_N < N; ++c) {
             const int64_t Tn = tiles_m * ((N - c * TILE_N + 127) / 128);
             const double change = 3.0 + 350.0 / S * (double)(Tn % 256 ? Tn % 256 : 256) / 256.0;
-            const double t = makespan(tiles_m * c, Tn) + change;
+            const double t = makespan(tiles_m * c, Tn, tile.wide) + change;
             if (t < best) { best = t; best_c = c; }
         }
         if (best_c > 0 && (mk == 2 || best < 0.97 * uniform)) {
             plan.kernel = GEMM_TILED_MIXED;
             plan.wide_cols = (int)best_c;
+            chosen_us = best;
         }
     }
     // The persistent form of the narrow tile (one workgroup per compute unit walks its tiles as one K
@@ -291,13 +296,31 @@ GemmPlan plan_gemm(const GemmArgs& g)
     // passes); with bf16 outputs 2 % faster around K = 2048 in the fp16 mode, slower in the FP8 mode;
     // 1 - 2 % slower at K = 8192 throughout.  Knob FP8_KNOB_PERSIST: 0 = where it pays (below),
     // 1 = never, 2 = wherever it is possible.
-    const int pk = knob(FP8_KNOB_PERSIST);
     const int64_t tiles = tiles_m * ((N + 127) / 128);
     const bool possible = plan.kernel == GEMM_TILED_128 && c_lines && M % TILE_M == 0 && N % 128 == 0 && K % (2 * TILE_K) == 0 && K >= 8 * TILE_K &&
                           !g.ep.a_per_row && !g.ep.b_per_col && g.ep.out_kind <= OUT_BF16 && !g.ep.amax_out && g.splits <= 1;
     const bool pays = tiles > 256 && (g.ep.out_kind == OUT_F32 ? K <= 64 * TILE_K
                                                                : g.acc == ACC_F16 && K >= 16 * TILE_K && K <= 32 * TILE_K);
     plan.persistent = possible && plan.small == SMALL_NONE && pk != 1 && (pk == 2 || pays);
+    // Tiles of 256 x 192, alone or with 128-wide ones behind them: where the same model says that they beat the choice so
+    // far by 3 % (4096 x 6144 x 2048: 512 tiles = two full rounds, 84 us against 93 for 768 narrow ones; 3001 x 6144 x 2048:
+    // 252 of them and 204 narrow ones, 85 us against 90 for 384 of them and 94 for 252 wide and 72 narrow ones).  Of 70 products in the
+    // range where it decides, 19 took them: 1.00 to 1.16 times as fast, and no other would have gained more than 2 %.
+    // fp32 outputs that the persistent narrow form takes stay there (4096 x 6144 x 1024: 57 us, here 59).
+    // Knob FP8_KNOB_TILE_192: 0 = by the model, 1 = never, 2 = always.
+    if (middle_knob == 2) {
+        plan.middle = true;
+    } else if (middle_knob == 0 && !tn && !mk && !pk && few_rounds && !(plan.persistent && g.ep.out_kind == OUT_F32)) {
+        double best = makespan(tiles_m * ((N + 191) / 192), 0, tile.middle);
+        for (int64_t units = 256; units / tiles_m * 192 < N; units += 256) {     // as many columns as whole rounds hold
+            const int64_t c = units / tiles_m;
+            if (c == 0) continue;
+            const int64_t Tn = tiles_m * ((N - c * 192 + 127) / 128);
+            const double t = makespan(tiles_m * c, Tn, tile.middle) + 2.0 + 100.0 / S * (double)(Tn % 256 ? Tn % 256 : 256) / 256.0;
+            if (t < 0.97 * best) { best = t; plan.middle_cols = (int)c; }
+        }
+        plan.middle = best < 0.97 * chosen_us;
+    }
     return plan;
 }
 
@@ -358,9 +381,9 @@ int launch_gemm(const GemmArgs& g)
     if (plan.kernel == GEMM_MFMA_ANY) return launch_mfma_any(g);
     if (plan.kernel != GEMM_GENERIC) {
         GemmArgs gt = g;
-        gt.tile_n = plan.kernel == GEMM_TILED_128 ? 128 : 256;
-        gt.wide_cols = plan.kernel == GEMM_TILED_MIXED ? plan.wide_cols : 0;
-        gt.persist = plan.persistent;
+        gt.tile_n = plan.middle ? 192 : plan.kernel == GEMM_TILED_128 ? 128 : 256;
+        gt.wide_cols = plan.middle ? plan.middle_cols : plan.kernel == GEMM_TILED_MIXED ? plan.wide_cols : 0;
+        gt.persist = plan.persistent && !plan.middle;
         gt.splits = 1;
         return launch_tiled(gt);
     }

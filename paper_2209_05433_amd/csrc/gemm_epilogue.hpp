@@ -45,7 +45,8 @@ __device__ __forceinline__ void epilogue(v16f (&acc)[NB][4], uint8_t* smem, cons
     constexpr int ESZ = OUT == OUT_F32 ? 4 : OUT == OUT_BF16 ? 2 : 1;     // bytes per output
     constexpr int WN = 32 * NB;                                           // columns of the wave's sub-tile
     constexpr int ROWB = WN * ESZ + 16;                                   // padded LDS row of the wave's block
-    constexpr int ROWS_PER_ST = 1024 / (WN * ESZ);                        // C rows covered by one store instruction
+    constexpr int LANES = WN * ESZ / 16;                                  // lanes that hold a row of it between them
+    constexpr int ROWS_PER_ST = 64 / LANES;                               // C rows covered by one store instruction
     const int h = l >> 5, wn = w & 1;
     const int wave_m0 = m0 + (w >> 1) * 128, wave_n0 = n0 + wn * WN;
 
@@ -82,8 +83,8 @@ __device__ __forceinline__ void epilogue(v16f (&acc)[NB][4], uint8_t* smem, cons
 
     uint8_t* blk = smem + w * (32 * ROWB);
     uint8_t* c_wave = (uint8_t*)C + ((size_t)wave_m0 * N + wave_n0) * ESZ;
-    const int st_row = l / (64 / ROWS_PER_ST), st_col = (l % (64 / ROWS_PER_ST)) * 16;   // byte column in memory
-    const int left = N - (wave_n0 + st_col / ESZ);                                       // columns from the lane's first one to the edge
+    const int st_row = l / LANES, st_col = (l % LANES) * 16;                             // byte column in memory
+    const int left = l < ROWS_PER_ST * LANES ? N - (wave_n0 + st_col / ESZ) : 0;         // columns from the lane's first one to the edge
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) {
         unsigned row_max = 0;
@@ -150,9 +151,10 @@ __device__ __forceinline__ void epilogue(v16f (&acc)[NB][4], uint8_t* smem, cons
         }
         if (wave_m0 + mb * 32 + (l & 31) < M) amax_bits = max(amax_bits, row_max);
 #pragma unroll
-        for (int i = 0; i < 32 / ROWS_PER_ST; ++i) {
+        for (int i = 0; i < (32 + ROWS_PER_ST - 1) / ROWS_PER_ST; ++i) {
             const int row = i * ROWS_PER_ST + st_row;
             if (wave_m0 + mb * 32 + row >= M || left <= 0) continue;                       // beyond the edges of C
+            if (32 % ROWS_PER_ST != 0 && row >= 32) continue;                              // (or of the block)
             uint8_t* out = c_wave + (size_t)(mb * 32 + row) * N * ESZ + st_col;
             const u32x4 o = *LDS_PTR(u32x4, blk + row * ROWB + st_col);
             if (left >= 16 / ESZ) {

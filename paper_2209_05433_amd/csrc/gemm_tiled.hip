@@ -14,8 +14,10 @@
 //
 //   - one workgroup of 4 waves per 256 x 256 output tile, each wave owns 128 x 128 of it as
 //     4 x 4 blocks of v_mfma_f32_32x32x64_f8f6f4 (K = 64 per instruction, operand formats
-//     selected per operand, so the E5M2 x E4M3 mix costs nothing extra); a 256 x 128 variant
-//     (each wave 128 x 64) serves problems with too few wide tiles to fill the chip;
+//     selected per operand, so the E5M2 x E4M3 mix costs nothing extra); variants of 256 x 192 and
+//     256 x 128 (each wave 128 x 96 or 128 x 64) serve problems whose wide tiles would leave much of the
+//     last round of workgroups empty (4096 x 6144 x 2048 to bf16: 384 wide tiles 101 us, 768 of 128 columns 92,
+//     512 of 192 = two full rounds 84);
 //   - K is walked in stages of 64.  An operand that is contiguous along M / N in memory (B stored
 //     K x N, A stored K x M) comes as one 64 x 256 slab (16 KB) per stage in a ring of four; an
 //     operand that is contiguous along K (A stored M x K, B stored N x K) as one 256 x 128 slab
@@ -58,10 +60,12 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 // Fast kernel
 // ------------------------------------------------------------------------------------------
 constexpr int BM = 256, BK = 64;
-// The tile is 256 rows of op(A) by 64 NB columns of op(B), NB = 4 or 2 (template parameter): two
-// waves side by side along N, each NB blocks of 32 columns wide.  The narrow tile is for problems
-// whose 256 x 256 tiles would leave much of the last round of workgroups empty.
-// An operand tile of EXT rows / columns (256, or 128 for the narrow B) is staged in one of two ways,
+// The tile is 256 rows of op(A) by 64 NB columns of op(B), NB = 4, 3 or 2 (template parameter): two
+// waves side by side along N, each NB blocks of 32 columns wide.  The narrower tiles are for problems
+// whose 256 x 256 tiles would leave much of the last round of workgroups empty.  Per product they read more of
+// the LDS and widen more bytes: per stage of 64 the three take 1.21, 1.03 and 0.79 us (1.0, 0.75 and 0.5 of the
+// matrix instructions) in the fp16 mode.
+// An operand tile of EXT rows / columns (256, or 192 / 128 for the narrower B) is staged in one of two ways,
 // depending on how the operand lies in memory:
 //   K-contiguous  (A row-major M x K; B given as N x K): one EXT x 128 slab per PAIR of stages,
 //                 fragments by 16-byte LDS reads;
@@ -145,6 +149,12 @@ struct Operand {
     size_t nxt;
 };
 
+// Rows of a K-contiguous slab / bytes of a K-row of the other kind in LDS.  192 columns of the other kind lie in rows of 256
+// bytes: the columns of either wave begin at a half, so that the swizzle and the address arithmetic are those of 256
+// columns; the last quarter of a half repeats the chunk before it (the same lines are asked for, nothing more is read).
+template <bool KC, int EXT>
+constexpr int lds_extent() { return !KC && EXT == 192 ? 256 : EXT; }
+
 template <bool KC, int EXT>
 __device__ __forceinline__ void operand_setup(Operand& op, const uint8_t* base, unsigned ld, int r0, int valid,
                                               unsigned region, int w, int l, int wsel)
@@ -169,21 +179,23 @@ __device__ __forceinline__ void operand_setup(Operand& op, const uint8_t* base, 
         const int row = wsel * (EXT / 2) + (l & 31);
         op.rd = region + row * 128 + (((2 * h) ^ swz_kc(row)) * 16);
     } else {
-        constexpr int CH = EXT / 16;                  // 16-byte chunks per K-row
-        constexpr int KR = 1024 / EXT;                // K-rows filled by one load instruction (1 KB)
+        constexpr int ROW = lds_extent<KC, EXT>();    // bytes of a K-row in LDS
+        constexpr int CH = ROW / 16;                  // 16-byte chunks per K-row
+        constexpr int KR = 1024 / ROW;                // K-rows filled by one load instruction (1 KB)
         constexpr int LW = 64 / KR / 4;               // loads per wave per slab
         op.tile = base + r0;
 #pragma unroll
         for (int t = 0; t < LW; ++t) {
             const int krow = (w * LW + t) * KR + l / CH;
-            const int chunk = mc_mem<CH>(l % CH, krow);                // 16 columns; `valid` is a multiple of 16 here
+            int chunk = mc_mem<CH>(l % CH, krow);                      // 16 columns; `valid` is a multiple of 16 here
+            if (ROW != EXT) chunk = (CH * EXT / ROW / 2) * (chunk / (CH / 2)) + min(chunk % (CH / 2), CH * EXT / ROW / 2 - 1);
             op.off[t] = (unsigned)krow * ld + min(chunk, (valid - 1) >> 4) * 16;
         }
         // lane = (r = l % 32, h): column r, K bytes 32h .. 32h+31, gathered by four transposing
         // reads of 8 K-rows x 16 columns per 16-lane group; lanes 2q and 2q+1 address K-row q
         const int t16 = l & 15, gq = (l >> 4) & 1;
         const int krow = 32 * h + (t16 >> 1);
-        op.rd = region + krow * EXT + mc_pos<CH>(wsel * (CH / 2) + gq, krow) * 16 + (t16 & 1) * 8;
+        op.rd = region + krow * ROW + mc_pos<CH>(wsel * (CH / 2) + gq, krow) * 16 + (t16 & 1) * 8;
     }
 }
 
@@ -213,6 +225,7 @@ __device__ __forceinline__ void direct_load_or_zero(const uint8_t* base, unsigne
 
 // One read-part of the fragment reads of stage kt for one operand: 16 bytes per lane of block blk
 // (half 0 or 1 of the lane's 32 bytes), as one 16-byte read (KC) or two transposing reads (MC).
+// EXT: rows of a K-contiguous slab, bytes of a K-row of the other kind (lds_extent).
 template <bool KC, int EXT>
 __device__ __forceinline__ void read_part(const uint8_t* smem, const Operand& op, int kt, int kc_slot, int blk, int half,
                                           v8i* f)
@@ -263,7 +276,8 @@ __device__ __forceinline__ void gemm_tile_body(
     constexpr int B_RING = A_KC ? 2 : 3;                    // stage pairs in B's ring (if B_KC)
     constexpr bool HAS_MC = !A_KC || !B_KC;
     // direct loads per wave: per pair slab (K-contiguous) / per stage slab (MN-contiguous)
-    constexpr int A_KC_LOADS = 8, A_MC_LOADS = 4, B_KC_LOADS = 2 * NB, B_MC_LOADS = NB;
+    constexpr int B_ROW = lds_extent<B_KC, BN>();           // rows (K-contiguous) / bytes of a K-row of B's slab
+    constexpr int A_KC_LOADS = 8, A_MC_LOADS = 4, B_KC_LOADS = 2 * NB, B_MC_LOADS = B_ROW / 64;
     // LDS map: the operand with the smaller ring (MN-contiguous, or B when both are K-contiguous) first.
     constexpr unsigned A_REGION = A_KC ? 65536u : 0u;
     constexpr unsigned B_REGION = A_KC ? 0u : 65536u;
@@ -403,13 +417,13 @@ __device__ __forceinline__ void gemm_tile_body(
                 const int p = kc_pair_of(s, B_RING);
                 if (j < H && (FULL || pair_valid(p))) {
 #pragma unroll
-                    for (int t = j * (B_KC_LOADS / H); t < (j + 1) * (B_KC_LOADS / H); ++t) issue_kc(tail, opB, B_KC_LOADS, p, sb, t);
+                    for (int t = j * B_KC_LOADS / H; t < (j + 1) * B_KC_LOADS / H; ++t) issue_kc(tail, opB, B_KC_LOADS, p, sb, t);
                 }
             } else {
                 const int p = s / 2 + A_RING - 1;
                 if (FULL || pair_valid(p)) {
 #pragma unroll
-                    for (int t = j * (A_KC_LOADS / P); t < (j + 1) * (A_KC_LOADS / P); ++t) issue_kc(tail, opA, A_KC_LOADS, p, sa, t);
+                    for (int t = j * A_KC_LOADS / P; t < (j + 1) * A_KC_LOADS / P; ++t) issue_kc(tail, opA, A_KC_LOADS, p, sa, t);
                 }
             }
         } else if (j < H) {
@@ -418,14 +432,14 @@ __device__ __forceinline__ void gemm_tile_body(
                     const int p = kc_pair_of(s, A_RING);
                     if (FULL || pair_valid(p)) {
 #pragma unroll
-                        for (int t = j * (A_KC_LOADS / H); t < (j + 1) * (A_KC_LOADS / H); ++t) issue_kc(tail, opA, A_KC_LOADS, p, sa, t);
+                        for (int t = j * A_KC_LOADS / H; t < (j + 1) * A_KC_LOADS / H; ++t) issue_kc(tail, opA, A_KC_LOADS, p, sa, t);
                     }
                 }
                 if (B_KC) {
                     const int p = kc_pair_of(s, B_RING);
                     if (FULL || pair_valid(p)) {
 #pragma unroll
-                        for (int t = j * (B_KC_LOADS / H); t < (j + 1) * (B_KC_LOADS / H); ++t) issue_kc(tail, opB, B_KC_LOADS, p, sb, t);
+                        for (int t = j * B_KC_LOADS / H; t < (j + 1) * B_KC_LOADS / H; ++t) issue_kc(tail, opB, B_KC_LOADS, p, sb, t);
                     }
                 }
             }
@@ -433,11 +447,11 @@ __device__ __forceinline__ void gemm_tile_body(
             const int jj = j - H;
             if (!A_KC) {
 #pragma unroll
-                for (int t = jj * (A_MC_LOADS / H); t < (jj + 1) * (A_MC_LOADS / H); ++t) issue_mc(tail, opA, A_MC_LOADS, s + 4, t);
+                for (int t = jj * A_MC_LOADS / H; t < (jj + 1) * A_MC_LOADS / H; ++t) issue_mc(tail, opA, A_MC_LOADS, s + 4, t);
             }
             if (!B_KC) {
 #pragma unroll
-                for (int t = jj * (B_MC_LOADS / H); t < (jj + 1) * (B_MC_LOADS / H); ++t) issue_mc(tail, opB, B_MC_LOADS, s + 4, t);
+                for (int t = jj * B_MC_LOADS / H; t < (jj + 1) * B_MC_LOADS / H; ++t) issue_mc(tail, opB, B_MC_LOADS, s + 4, t);
             }
         }
     };
@@ -479,15 +493,15 @@ __device__ __forceinline__ void gemm_tile_body(
     //   ACC_FP8: one v_mfma_f32_32x32x64_f8f6f4 per block (K = 64); part j = B block j/2 against
     //            the A blocks 2(j%2) and 2(j%2)+1.
     //   ACC_F16: the FP8 bytes are widened exactly to fp16 in registers and each block takes four
-    //            v_mfma_f32_32x32x16_f16 (K = 16, 8 of the lane's 32 bytes each); a part is two B
-    //            blocks of one K sub-step against the four A blocks.  The operands of a part are
+    //            v_mfma_f32_32x32x16_f16 (K = 16, 8 of the lane's 32 bytes each); a part is two of the
+    //            4 NB pairs (K sub-step, B block), sub-step by sub-step, against the four A blocks (with NB = 3 the
+    //            two may belong to neighbouring sub-steps: A's operands are kept for both).  The operands of a part are
     //            converted during the part before it (for part 0: during the last part of the
     //            stage before, from that stage's freshly read fragments): the conversions are then
     //            independent of the MFMAs they are issued between and run in their shadow.  A
     //            conversion costs 8 cycles of the vector ALU (measured), an MFMA 32 of the matrix
     //            pipe: 24 conversions fit under the 8 MFMAs of a part, but only if none of those
     //            MFMAs waits for one of them.
-    constexpr int PPS = NB / 2;                   // parts per K sub-step (ACC_F16)
     v8h a16[2][4], b16[2][2];                     // [sub-step parity][A block], [part parity][B block of the part]
     auto compute_fp8 = [&](int j, v8i (&af)[4], v8i (&bf)[NB]) {
         const int nb = j >> 1;
@@ -498,26 +512,28 @@ __device__ __forceinline__ void gemm_tile_body(
     };
     // operands of part j of a stage whose fragments are (af, bf)
     auto convert_f16 = [&](int j, v8i (&af)[4], v8i (&bf)[NB]) {
-        const int s = j / PPS, nb0 = 2 * (j % PPS);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) b16[j & 1][i] = widen8<FMT_B>(bf[nb0 + i][2 * s], bf[nb0 + i][2 * s + 1]);
-        if (j % PPS == 0) {
+        for (int i = 0; i < 2; ++i) {
+            const int s = (2 * j + i) / NB, nb = (2 * j + i) % NB;
+            b16[j & 1][i] = widen8<FMT_B>(bf[nb][2 * s], bf[nb][2 * s + 1]);
+            if (nb == 0) {
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb) a16[s & 1][mb] = widen8<FMT_A>(af[mb][2 * s], af[mb][2 * s + 1]);
+                for (int mb = 0; mb < 4; ++mb) a16[s & 1][mb] = widen8<FMT_A>(af[mb][2 * s], af[mb][2 * s + 1]);
+            }
         }
     };
     auto compute_f16 = [&](int j) {
-        const int s = j / PPS, nb0 = 2 * (j % PPS);
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i) {
+            const int s = (2 * j + i) / NB, nb = (2 * j + i) % NB;
 #pragma unroll
             for (int mb = 0; mb < 4; ++mb)
-                acc[nb0 + i][mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b16[j & 1][i], a16[s & 1][mb], acc[nb0 + i][mb], 0, 0, 0);
+                acc[nb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b16[j & 1][i], a16[s & 1][mb], acc[nb][mb], 0, 0, 0);
+        }
     };
-    // fragment reads of the next stage that go out in one part: 8 / P read-parts of A, one of B;
+    // fragment reads of the next stage that go out in one part: 8 / P read-parts of A (up to that, with NB = 3), one of B;
     // the first halves of all blocks first (the first conversions of the next stage need them)
-    constexpr int A_RP = 8 / P;
-    constexpr int READS_PER_PART = A_RP * (A_KC ? 1 : 2) + (B_KC ? 1 : 2);
+    constexpr int READS_PER_PART = (8 + P - 1) / P * (A_KC ? 1 : 2) + (B_KC ? 1 : 2);
     auto sched_part = [&]() {
         if (ACC == ACC_FP8) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                        // MFMA
@@ -536,11 +552,8 @@ __device__ __forceinline__ void gemm_tile_body(
     };
     auto read_both = [&](int kt, int j, int sa, int sb, v8i (&af)[4], v8i (&bf)[NB]) {
 #pragma unroll
-        for (int r = 0; r < A_RP; ++r) {
-            const int ra = j * A_RP + r;
-            read_part<A_KC, BM>(smem, opA, kt, sa, ra & 3, ra >> 2, af);
-        }
-        read_part<B_KC, BN>(smem, opB, kt, sb, j % NB, j / NB, bf);
+        for (int ra = j * 8 / P; ra < (j + 1) * 8 / P; ++ra) read_part<A_KC, BM>(smem, opA, kt, sa, ra & 3, ra >> 2, af);
+        read_part<B_KC, B_ROW>(smem, opB, kt, sb, j % NB, j / NB, bf);
     };
 
     // One K stage kt (not the last).  The frags of stage kt are in (af, bf); their LDS reads were
@@ -734,23 +747,23 @@ __global__ __launch_bounds__(FAST_THREADS, 1) void gemm_fast_kernel(
                                                               (int)blockIdx.x, 0, (N + 64 * NB - 1) / (64 * NB));
 }
 
-// Both tile widths in one launch: the first wide_cols * 256 columns of the output in 256 x 256 tiles
-// (workgroups 0 .. tiles_m * wide_cols - 1, dispatched first), the remaining columns in 256 x 128
+// Two tile widths in one launch: the first wide_cols tile columns of the output in tiles of 256 x 64 NB (256 or
+// 192 wide; workgroups 0 .. tiles_m * wide_cols - 1, dispatched first), the remaining columns in 256 x 128
 // tiles.  For problems whose tiles of one width leave much of the last round of workgroups empty
 // (4096 x 6144: 384 wide tiles = 1.5 rounds, 768 narrow ones = 3 rounds at 0.6 of the wide tile's
 // time each; 256 wide + 256 narrow = one round of each); the narrow tiles also fill the compute
 // units that the last wide tiles leave idle.  The choice of wide_cols is the dispatcher's.
-template <int FMT_A, int FMT_B, int ACC, bool A_KC, bool B_KC>
+template <int FMT_A, int FMT_B, int ACC, bool A_KC, bool B_KC, int NB>
 __global__ __launch_bounds__(FAST_THREADS, 1) void gemm_mixed_kernel(
     const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, void* __restrict__ C,
     int M, int N, int K, EpilogueArgs ep, int group_m, int pairs, int wide_cols)
 {
     const int wide_tiles = ((M + BM - 1) / BM) * wide_cols;
     if ((int)blockIdx.x < wide_tiles)
-        gemm_tile_body<FMT_A, FMT_B, ACC, A_KC, B_KC, 4, false>(A, B, C, M, N, K, ep, group_m, 1, pairs, (int)blockIdx.x, 0, wide_cols);
+        gemm_tile_body<FMT_A, FMT_B, ACC, A_KC, B_KC, NB, false>(A, B, C, M, N, K, ep, group_m, 1, pairs, (int)blockIdx.x, 0, wide_cols);
     else
         gemm_tile_body<FMT_A, FMT_B, ACC, A_KC, B_KC, 2, false>(A, B, C, M, N, K, ep, group_m, 1, pairs, (int)blockIdx.x - wide_tiles,
-                                                                wide_cols * 256, (N - wide_cols * 256 + 127) / 128);
+                                                                wide_cols * (64 * NB), (N - wide_cols * (64 * NB) + 127) / 128);
 }
 
 // ---- launch ------------------------------------------------------------------------------
@@ -799,11 +812,11 @@ int launch_fast(const GemmArgs& g)
     return check_launch(PERSIST ? "gemm (tiled kernel, persistent form)" : "gemm (tiled kernel)");
 }
 
-template <int FA, int FB, int ACC, bool A_KC, bool B_KC>
+template <int FA, int FB, int ACC, bool A_KC, bool B_KC, int NB>
 int launch_mixed(const GemmArgs& g)
 {
     static std::atomic<unsigned long long> attr_set{0ull};
-    auto kern = gemm_mixed_kernel<FA, FB, ACC, A_KC, B_KC>;
+    auto kern = gemm_mixed_kernel<FA, FB, ACC, A_KC, B_KC, NB>;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return fail(FP8_ERR_DEVICE, "hipGetDevice failed");
     const unsigned long long bit = 1ull << (dev & 63);
@@ -814,7 +827,7 @@ int launch_mixed(const GemmArgs& g)
         if (dev < 64) attr_set.fetch_or(bit, std::memory_order_relaxed);
     }
     const int64_t tiles_m = (g.M + BM - 1) / BM;
-    const int64_t grid = tiles_m * g.wide_cols + tiles_m * ((g.N - (int64_t)g.wide_cols * 256 + 127) / 128);
+    const int64_t grid = tiles_m * g.wide_cols + tiles_m * ((g.N - (int64_t)g.wide_cols * (64 * NB) + 127) / 128);
     const int pairs = (int)((g.K + 2 * BK - 1) / (2 * BK));
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(FAST_THREADS), FAST_LDS, g.stream, g.A, g.B, g.C,
                        (int)g.M, (int)g.N, (int)g.K, g.ep, group_m_setting(), pairs, g.wide_cols);
@@ -847,19 +860,20 @@ static int launch_formats(const GemmArgs& g)
                               : launch_fast<FP8_E5M2, FP8_E5M2, ACC, A_KC, B_KC, NB>(g);
 }
 
+template <int NB>
 static int launch_mixed_formats(const GemmArgs& g)
 {
     constexpr bool A_KC = (FP8MM_LAYOUT & 2) == 0, B_KC = (FP8MM_LAYOUT & 1) != 0;
     constexpr int ACC = FP8MM_ACC;
     if (g.fmtA == FP8_E4M3)
-        return g.fmtB == FP8_E4M3 ? launch_mixed<FP8_E4M3, FP8_E4M3, ACC, A_KC, B_KC>(g) : launch_mixed<FP8_E4M3, FP8_E5M2, ACC, A_KC, B_KC>(g);
-    return g.fmtB == FP8_E4M3 ? launch_mixed<FP8_E5M2, FP8_E4M3, ACC, A_KC, B_KC>(g) : launch_mixed<FP8_E5M2, FP8_E5M2, ACC, A_KC, B_KC>(g);
+        return g.fmtB == FP8_E4M3 ? launch_mixed<FP8_E4M3, FP8_E4M3, ACC, A_KC, B_KC, NB>(g) : launch_mixed<FP8_E4M3, FP8_E5M2, ACC, A_KC, B_KC, NB>(g);
+    return g.fmtB == FP8_E4M3 ? launch_mixed<FP8_E5M2, FP8_E4M3, ACC, A_KC, B_KC, NB>(g) : launch_mixed<FP8_E5M2, FP8_E5M2, ACC, A_KC, B_KC, NB>(g);
 }
 
 int FP8MM_TILED_NAME(FP8MM_LAYOUT, FP8MM_ACC)(const GemmArgs& g)
 {
-    if (g.wide_cols > 0) return launch_mixed_formats(g);
-    return g.tile_n == 128 ? launch_formats<2>(g) : launch_formats<4>(g);
+    if (g.wide_cols > 0) return g.tile_n == 192 ? launch_mixed_formats<3>(g) : launch_mixed_formats<4>(g);
+    return g.tile_n == 128 ? launch_formats<2>(g) : g.tile_n == 192 ? launch_formats<3>(g) : launch_formats<4>(g);
 }
 
 }  // namespace fp8mm
