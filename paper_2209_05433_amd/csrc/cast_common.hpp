@@ -71,15 +71,29 @@ __device__ __forceinline__ unsigned run_to_bits(unsigned run)
     return (unsigned)(p.x > p.y ? p.x : p.y) << 16;
 }
 
+// Largest value over the lanes of each row of 16, in its first lane / over all 64 lanes, in every lane; all lanes active.
+// Lanes exchange within the vector registers (a shuffle goes through the LDS unit and takes about a hundred clocks
+// a step: the six steps were a quarter of a microsecond of every small kernel).
+__device__ __forceinline__ unsigned row_max_u32(unsigned v)
+{
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x101, 0xf, 0xf, false));      // row_shl:1, 2, 4, 8
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x102, 0xf, 0xf, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xf, 0xf, false));
+    return max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x108, 0xf, 0xf, false));
+}
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v)
+{
+    v = row_max_u32(v);
+    const unsigned a = (unsigned)__builtin_amdgcn_readlane((int)v, 0), b = (unsigned)__builtin_amdgcn_readlane((int)v, 16);
+    const unsigned c = (unsigned)__builtin_amdgcn_readlane((int)v, 32), d = (unsigned)__builtin_amdgcn_readlane((int)v, 48);
+    return max(max(a, b), max(c, d));
+}
+
 template <int THREADS = kThreads>
 __device__ __forceinline__ unsigned block_max_u32(unsigned v)
 {
     __shared__ unsigned part[THREADS / 64];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        unsigned o = __shfl_xor(v, off, 64);
-        v = v > o ? v : o;
-    }
+    v = wave_max_u32(v);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -150,10 +164,10 @@ template <> struct Piece<FP8_F32> {
     static __device__ __forceinline__ type of(const u32x4& o, int k) { return o[k]; }
 };
 
-// One group: the loaded vectors in[k] = xv[v + k * kThreads], k < VPI -> the pieces
-// qp[v + k * kThreads]; only the first `count` pieces are stored.  AMAX: the running packed maximum of the
+// One group: the loaded vectors in[k] = xv[v + k * THREADS], k < VPI -> the pieces
+// qp[v + k * THREADS]; only the first `count` pieces are stored.  AMAX: the running packed maximum of the
 // vectors is kept in `run` (vectors beyond `count` must be zeros).
-template <int DT, int FMT, int PATH, bool NTS, bool AMAX>
+template <int DT, int FMT, int PATH, bool NTS, bool AMAX, int THREADS = kThreads>
 __device__ __forceinline__ void cast_group(const u32x4* in, typename Piece<DT>::type* __restrict__ qp,
                                            size_t v, int count, float s, unsigned& run)
 {
@@ -170,7 +184,7 @@ __device__ __forceinline__ void cast_group(const u32x4* in, typename Piece<DT>::
 #pragma unroll
     for (int k = 0; k < VPI; ++k) {
         if (k < count) {
-            typename Piece<DT>::type* dst = &qp[v + (size_t)k * kThreads];
+            typename Piece<DT>::type* dst = &qp[v + (size_t)k * THREADS];
             if (NTS) __builtin_nontemporal_store(Piece<DT>::of(o, k), dst); else *dst = Piece<DT>::of(o, k);
         }
     }
@@ -178,28 +192,28 @@ __device__ __forceinline__ void cast_group(const u32x4* in, typename Piece<DT>::
 
 // A lane's walk over the vectors [vlo, vhi) of its workgroup: 8 vectors per step, all loads of a
 // step issued before the first conversion; then the remainder, group by group.
-template <int DT, int FMT, int PATH, bool NTS, bool AMAX>
+template <int DT, int FMT, int PATH, bool NTS, bool AMAX, int THREADS = kThreads>
 __device__ __forceinline__ void cast_run(const u32x4_any* __restrict__ xv, typename Piece<DT>::type* __restrict__ qp,
                                          size_t vlo, size_t vhi, float s, unsigned& run)
 {
     constexpr int VPI = DT == FP8_BF16 ? 2 : 4;
     size_t v = vlo + threadIdx.x;
-    for (; v + 7 * kThreads < vhi; v += 8 * kThreads) {
+    for (; v + 7 * THREADS < vhi; v += 8 * THREADS) {
         u32x4 in[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) in[k] = __builtin_nontemporal_load(&xv[v + (size_t)k * kThreads]);
+        for (int k = 0; k < 8; ++k) in[k] = __builtin_nontemporal_load(&xv[v + (size_t)k * THREADS]);
 #pragma unroll
         for (int g = 0; g < 8 / VPI; ++g)
-            cast_group<DT, FMT, PATH, NTS, AMAX>(in + g * VPI, qp, v + (size_t)g * VPI * kThreads, VPI, s, run);
+            cast_group<DT, FMT, PATH, NTS, AMAX, THREADS>(in + g * VPI, qp, v + (size_t)g * VPI * THREADS, VPI, s, run);
     }
-    for (; v < vhi; v += VPI * kThreads) {
-        const size_t left = (vhi - v + kThreads - 1) / kThreads;        // vectors of this lane still there
+    for (; v < vhi; v += VPI * THREADS) {
+        const size_t left = (vhi - v + THREADS - 1) / THREADS;        // vectors of this lane still there
         const int count = left < (size_t)VPI ? (int)left : VPI;
         u32x4 in[VPI];
 #pragma unroll
         for (int k = 0; k < VPI; ++k)
-            in[k] = k < count ? __builtin_nontemporal_load(&xv[v + (size_t)k * kThreads]) : (u32x4){0u, 0u, 0u, 0u};
-        cast_group<DT, FMT, PATH, NTS, AMAX>(in, qp, v, count, s, run);
+            in[k] = k < count ? __builtin_nontemporal_load(&xv[v + (size_t)k * THREADS]) : (u32x4){0u, 0u, 0u, 0u};
+        cast_group<DT, FMT, PATH, NTS, AMAX, THREADS>(in, qp, v, count, s, run);
     }
 }
 

@@ -20,11 +20,15 @@ namespace {
 // compute unit; one atomic per workgroup at the end (with one chunk per workgroup the thousands of
 // atomics on one cell cost a quarter of the run time).  The one-launch form cuts tensors of less than 1 MB into
 // chunks of 8 KB: their time is the latency of a few loads (64 KB of bf16 4.1 -> 3.8 us; 4 MB of fp32 5.1 -> 5.5 and
-// 10 MB of bf16 5.8 -> 6.6, all in chunks of 8 KB).  With one atomic per workgroup more workgroups only cost: 4 MB
+// 10 MB of bf16 5.8 -> 6.6, all in chunks of 8 KB); up to 128 KB one workgroup reads the tensor alone, 16 vectors per lane in
+// flight: no tickets are drawn, each of which is a round trip to memory (64 KB of bf16 3.9 -> 2.5 us, 128 KB 4.1 -> 2.9; 200 KB would
+// be as fast either way).  With one atomic per workgroup more workgroups only cost: 4 MB
 // of fp32 6.0 -> 9.8 us.
 constexpr int kAmaxVecs = 8;                                         // per lane and chunk
 constexpr int kAmaxVecsSmall = 2;
 constexpr size_t kAmaxSmallBelow = (size_t)32 * kThreads * kAmaxVecs;    // vectors
+constexpr int kAmaxVecsAlone = 16;
+constexpr size_t kAmaxAloneBelow = (size_t)2 * kThreads * kAmaxVecsAlone;  // vectors that one workgroup reads alone: 128 KB
 
 // Last step of the amax kernels in their one-launch form (fp8_amax_scale): no cell has to be
 // cleared beforehand and the scale comes out of the same launch.  Every workgroup leaves its
@@ -123,6 +127,7 @@ __device__ __forceinline__ void amax_chunks(const u32x4_any* xv, size_t nvec, un
 // Workgroups for a tensor of nvec vectors.
 inline unsigned amax_grid(size_t nvec, bool ticket)
 {
+    if (ticket && nvec <= kAmaxAloneBelow) return 1;
     const size_t chunk = (size_t)kThreads * (ticket && nvec < kAmaxSmallBelow ? kAmaxVecsSmall : kAmaxVecs), chunks = (nvec + chunk - 1) / chunk;
     return (unsigned)(chunks < 1 ? 1 : chunks > (size_t)kAmaxBlocks ? (size_t)kAmaxBlocks : chunks);
 }
@@ -137,7 +142,8 @@ __device__ __forceinline__ void amax_vec_body(const void* __restrict__ x, size_t
     const u32x4_any* xv = (const u32x4_any*)x;
     const size_t nvec = n / PV;
     unsigned run[4] = {0u, 0u, 0u, 0u};
-    if (TICKET && nvec < kAmaxSmallBelow) amax_chunks<DT, kAmaxVecsSmall>(xv, nvec, bid, grid, run);
+    if (TICKET && nvec > kThreads * kAmaxVecsSmall && nvec <= kAmaxAloneBelow) amax_chunks<DT, kAmaxVecsAlone>(xv, nvec, bid, grid, run);
+    else if (TICKET && nvec < kAmaxSmallBelow) amax_chunks<DT, kAmaxVecsSmall>(xv, nvec, bid, grid, run);
     else amax_chunks<DT, kAmaxVecs>(xv, nvec, bid, grid, run);
     unsigned r;
     if (DT == FP8_F32) {
@@ -335,9 +341,7 @@ __device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_
         __builtin_amdgcn_s_waitcnt(0x0070);                  // vmcnt(0): the own maximum has been acknowledged
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         const unsigned long long here = __ballot(p >> 31);
-        unsigned m = p & 0x7fffffffu;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, d, 64));
+        const unsigned m = wave_max_u32(p & 0x7fffffffu);
         if (l == 0) {
             largest = m;
             absent = ~here;

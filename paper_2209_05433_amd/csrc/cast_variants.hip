@@ -30,10 +30,11 @@ __device__ __forceinline__ void raise_cell(unsigned* cell, unsigned bits)
 // ------------------------------------------------------------------------------------------
 // cast + amax in one pass
 // ------------------------------------------------------------------------------------------
-constexpr size_t kAloneItems = 8 * kThreads;        // items of 16 elements that one workgroup casts alone
+constexpr int kMaxThreads = 1024;
+constexpr size_t kAloneItems = 2 * kMaxThreads;     // items of 16 elements that one workgroup casts alone
 
-template <int DT, int FMT, bool NTS>
-__global__ __launch_bounds__(kThreads) void quantize_amax_kernel(const void* __restrict__ x, size_t n,
+template <int DT, int FMT, bool NTS, int THREADS>
+__global__ __launch_bounds__(THREADS) void quantize_amax_kernel(const void* __restrict__ x, size_t n,
                                                                 const float* __restrict__ scale_dev,
                                                                 uint8_t* __restrict__ q,
                                                                 unsigned* __restrict__ amax_bits)
@@ -46,7 +47,7 @@ __global__ __launch_bounds__(kThreads) void quantize_amax_kernel(const void* __r
     const size_t lo = (size_t)blockIdx.x * per;
     const size_t hi = lo + per < nitem ? lo + per : nitem;
     if (lo < hi)
-        cast_run<DT, FMT, kCastCvt, NTS, true>((const u32x4_any*)x, (typename Piece<DT>::type*)q, VPI * lo, VPI * hi, s, run);
+        cast_run<DT, FMT, kCastCvt, NTS, true, THREADS>((const u32x4_any*)x, (typename Piece<DT>::type*)q, VPI * lo, VPI * hi, s, run);
     unsigned r = run_to_bits<DT>(run);
     const size_t t = nitem * 16 + threadIdx.x;      // fewer than 16 tail elements
     if (blockIdx.x == 0 && t < n) {
@@ -54,7 +55,7 @@ __global__ __launch_bounds__(kThreads) void quantize_amax_kernel(const void* __r
         r = r > m ? r : m;
         q[t] = (uint8_t)encode_bits<FMT>(load_scalar<DT>(x, t) * s);
     }
-    r = block_max_u32(r);
+    r = block_max_u32<THREADS>(r);
     if (threadIdx.x != 0) return;
     if (gridDim.x == 1) *amax_bits = r;             // a single workgroup: the cell was not cleared
     else raise_cell(amax_bits, r);
@@ -140,12 +141,7 @@ __global__ __launch_bounds__(kThreads) void amax_rows_kernel(const void* __restr
             }
         }
         r = max(r, run_to_bits<DT>(run));
-        if (G == kThreads) {
-            r = block_max_u32(r);
-        } else {
-#pragma unroll
-            for (int d = G / 2; d >= 1; d >>= 1) r = max(r, (unsigned)__shfl_xor((int)r, d, 64));
-        }
+        r = G == kThreads ? block_max_u32(r) : G == 64 ? wave_max_u32(r) : row_max_u32(r);
         if (lane == 0 && row < rows) amax_out[row] = as_f32(r);
         if (G == kThreads) __syncthreads();                  // the reduction's staging cells are reused by the next row
     }
@@ -548,27 +544,33 @@ int launch_quantize_amax(const void* x, size_t n, int in_dtype, int fmt, const f
                          float* amax_out, hipStream_t stream)
 {
     unsigned* bits = (unsigned*)amax_out;
-    // Measured (bf16, E4M3): up to a few hundred MB of output 512 workgroups (one atomic each) and
-    // ordinary stores are best (2^28 elements: 134 us, against 142 with 16384 workgroups and 148 with
-    // non-temporal stores); an output beyond the memory-side cache goes out non-temporally from many
-    // short runs (6.04 10^8 elements: 329 us against 367).  Up to kAloneItems a single workgroup
-    // casts the tensor, which needs no cleared cell: one launch instead of two.  In between a lane takes
-    // several items once there are 128 workgroups: each more is an atomic on one cell, and they end together
-    // (3 10^6 bf16 elements 10.7 us with one item a lane, 8.4 with four; 3 10^5 6.2 and 8.4).
+    // Every workgroup ends with an atomic on one cell, and all end together.  Up to kAloneItems a single workgroup of 1024
+    // casts the tensor, which needs no cleared cell: one launch instead of two.  Up to 2^14 items small workgroups, an item a lane.
+    // Up to 2^20 (2^21 of bf16) one workgroup of 1024 per compute unit at most: against 512 workgroups of 256 half the atomics and
+    // four times the waves where the tensor is small (10^6 bf16 elements 8.7 -> 5.8 us, 10^7 14.2 -> 10.9, 10^6 fp32 7.5 -> 6.0;
+    // but 5 10^7 fp32 49 -> 52).  Beyond, 512 workgroups of 256 and ordinary stores (2^28 elements: 134 us, against 142 with 16384
+    // and 148 with non-temporal stores); an output beyond the memory-side cache goes out non-temporally from many
+    // short runs (6.04 10^8 elements: 329 us against 367).
     const bool nts = n >= kStreamingStoreBytes;
     const size_t items = n / 16;
-    const size_t per_lane = items < (size_t)1 << 15 ? 1 : in_dtype == FP8_F32 && items < (size_t)1 << 18 ? 2 : 4;
-    const dim3 grid(items <= kAloneItems ? 1 : grid_for((items + per_lane - 1) / per_lane, nts ? kCastBlocks : 512));
+    const bool large = items <= kAloneItems || (items >= (size_t)1 << 14 && items < (in_dtype == FP8_F32 ? (size_t)1 << 20 : (size_t)1 << 21));
+    const size_t per_group = large ? kMaxThreads : (items < (size_t)1 << 14 ? 1 : 4) * (size_t)kThreads;
+    const size_t groups = (items + per_group - 1) / per_group, most = nts ? kCastBlocks : large ? 256 : 512;
+    const dim3 grid((unsigned)(items <= kAloneItems ? 1 : groups < most ? groups : most));
     if (grid.x > 1 || n == 0) hipLaunchKernelGGL(store_u32_kernel, dim3(1), dim3(1), 0, stream, bits, 0u);
     if (n == 0) return check_launch("quantize_amax init");
-#define FP8MM_QA(DT, FMT)                                                                                                   \
-    do {                                                                                                                    \
-        if (nts) hipLaunchKernelGGL((quantize_amax_kernel<DT, FMT, true>), grid, dim3(kThreads), 0, stream, x, n, scale_dev, q_out, bits); \
-        else hipLaunchKernelGGL((quantize_amax_kernel<DT, FMT, false>), grid, dim3(kThreads), 0, stream, x, n, scale_dev, q_out, bits);    \
+#define FP8MM_QA_(DT, FMT, NTS, THREADS) \
+    hipLaunchKernelGGL((quantize_amax_kernel<DT, FMT, NTS, THREADS>), grid, dim3(THREADS), 0, stream, x, n, scale_dev, q_out, bits)
+#define FP8MM_QA(DT, FMT)                                             \
+    do {                                                              \
+        if (nts) FP8MM_QA_(DT, FMT, true, kThreads);                  \
+        else if (large) FP8MM_QA_(DT, FMT, false, kMaxThreads);       \
+        else FP8MM_QA_(DT, FMT, false, kThreads);                     \
     } while (0)
     if (in_dtype == FP8_F32) { if (fmt == FP8_E4M3) FP8MM_QA(FP8_F32, FP8_E4M3); else FP8MM_QA(FP8_F32, FP8_E5M2); }
     else { if (fmt == FP8_E4M3) FP8MM_QA(FP8_BF16, FP8_E4M3); else FP8MM_QA(FP8_BF16, FP8_E5M2); }
 #undef FP8MM_QA
+#undef FP8MM_QA_
     return check_launch("quantize_amax");
 }
 

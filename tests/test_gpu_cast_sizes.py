@@ -1,0 +1,57 @@
+"""amax and cast + amax at the sizes where another number or size of workgroups takes over, and the lanes' reduction: the
+maximum is found wherever in the tensor it lies, and the bytes are those of the plain cast, which test_gpu_cast holds to the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2209_05433_amd as fp8
+
+pytestmark = pytest.mark.gpu
+
+DTYPES = {"f32": torch.float32, "bf16": torch.bfloat16}
+
+
+def edges(vec):
+    """Elements: one workgroup with 2 and with 16 vectors of `vec` a lane and beyond; items of 16 elements that one workgroup, an
+    item a lane of small workgroups, large workgroups and 512 of them take."""
+    marks = [vec * 512, vec * 4096, vec * 8192, 16 * 2048, 16 << 14, 16 << 20, 16 << 21]
+    return [1, vec - 1, vec * 64 + 1] + [m + d for m in marks for d in (-1, 0, 16, 17)]
+
+
+@pytest.mark.parametrize("dtype", sorted(DTYPES))
+def test_maxima_and_bytes_at_the_edges_of_the_grids(dtype):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    ws = torch.zeros(fp8.FP8_AMAX_WORKSPACE_BYTES // 4, dtype=torch.int32, device="cuda")
+    for n in edges(4 if dtype == "f32" else 8):
+        x = torch.randn(n, device="cuda", generator=g).to(DTYPES[dtype])
+        amax, scale, amax1, amax2 = (torch.full((1,), -3.0, device="cuda") for _ in range(4))
+        q, q_ref = (torch.full((n + 64,), 9, dtype=torch.uint8, device="cuda") for _ in range(2))
+        for k, at in enumerate((0, n - 1, n // 2, (n * 7) // 11)):
+            x[at] = -(10.0 + k)
+            fp8.fp8_amax_scale(x, fp8.FP8_E4M3, amax, scale, ws)
+            fp8.fp8_amax(x, amax1)
+            fp8.fp8_quantize_dscale(x, fp8.FP8_E4M3, scale, q_ref[32:32 + n])
+            fp8.fp8_quantize_amax(x, fp8.FP8_E4M3, scale, q[32:32 + n], amax2)
+            torch.cuda.synchronize()
+            want = float(x.abs().max())
+            assert float(amax) == float(amax1) == float(amax2) == want, (n, at)
+            assert np.float32(float(scale)) == np.float32(448.0) / np.float32(want)
+            assert torch.equal(q, q_ref), (n, at)          # (and nothing around the output is written)
+        x[n // 3] = float("nan")
+        fp8.fp8_amax_scale(x, fp8.FP8_E4M3, amax, scale, ws)
+        fp8.fp8_quantize_amax(x, fp8.FP8_E4M3, scale, q[32:32 + n], amax2)
+        torch.cuda.synchronize()
+        assert bool(torch.isnan(amax)) and bool(torch.isnan(amax2)) and float(scale) == 1.0, n
+        assert not bool(ws[:1056].any()), "a counter was left behind"
+
+
+@pytest.mark.parametrize("cols", [16, 100, 128, 300, 512, 2048, 5000])
+def test_row_maxima_in_every_lane(cols):
+    """One row per column: row r has its maximum in column r."""
+    x = torch.rand(cols, cols, device="cuda")
+    x.fill_diagonal_(-2.0)
+    for dtype in DTYPES.values():
+        amax = torch.zeros(cols, device="cuda")
+        fp8.fp8_amax_rows(x.to(dtype), amax)
+        assert bool((amax == 2.0).all()), (cols, dtype, int((amax != 2.0).sum()))
