@@ -299,7 +299,8 @@ int fp8_gemm_ex(const uint8_t* A, int fmtA, int transA, const uint8_t* B, int fm
  * compute units.  The slices' fp32 sums go to `workspace`; a second kernel adds them in slice order
  * (results are the same in every run), applies 1 / (sA sB) once per output (Section 2) and converts.
  * Arguments, bounds and error behaviour as fp8_gemm_ex, and:
- *   splits           0: the library chooses (about 256 / tiles, slices of at least 512 along K);
+ *   splits           0: the library chooses (about 256 / tiles, slices of at least 512 along K; one where
+ *                    that is the faster form);
  *                    1..64: that many slices (fewer if K is too short to give each one 128)
  *   workspace        device, 4-byte aligned (16 for the fastest stores), at least
  *                    fp8_gemm_splitk_workspace_size(M, N, K, transA, transB, splits) bytes

@@ -116,8 +116,16 @@ int fill_gemm_args(const char* who, GemmArgs& g, const uint8_t* A, int fmtA, int
 enum { GEMM_GENERIC = 1, GEMM_TILED_256 = 2, GEMM_TILED_128 = 3, GEMM_MFMA_ANY = 4, GEMM_TILED_MIXED = 5 };
 // small: the form of the small-tile kernel that takes the problem instead (SMALL_*).
 // middle: 256 x 192 tiles instead of what `kernel` names; middle_cols > 0: for that many tile columns, 128-wide ones for the rest.
-struct GemmPlan { int kernel; bool elementwise_stores; bool persistent; int wide_cols; int small; bool middle; int middle_cols; };
+// us: of a problem that the tiled kernel takes, what the model of run times gives for the small-tile form, or for the better of the
+// single tile widths.
+struct GemmPlan { int kernel; bool elementwise_stores; bool persistent; int wide_cols; int small; bool middle; int middle_cols; double us; };
 GemmPlan plan_gemm(const GemmArgs& g);
+
+// Microseconds for one tile of the tiled kernel, S stages of 64 along K, as one of several rounds of 256 that
+// run at a time (fitted to 4096 x 6144 over K = 512 .. 2048 and to 3294 x 11648 x 4288; within 5 %).  middle: the
+// 256 x 192 tile, fitted to 70 products so that it is taken where it is the faster one.
+struct TileTimes { double wide, middle, narrow; };
+TileTimes tile_times(int acc, double S);
 
 // ---- small device helpers used by the kernels -------------------------------------------------
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));

@@ -120,16 +120,12 @@ inline int64_t tile_count(const GemmArgs& g, int64_t edge) { return ((g.M + edge
 
 }  // namespace
 
-namespace {
-
-// Microseconds for one tile of the tiled kernel, S stages of 64 along K, as one of several rounds of 256 that
-// run at a time (fitted to 4096 x 6144 over K = 512 .. 2048 and to 3294 x 11648 x 4288; within 5 %).  middle: the
-// 256 x 192 tile, fitted to 70 products so that it is taken where it is the faster one.
-struct TileTimes { double wide, middle, narrow; };
 TileTimes tile_times(int acc, double S)
 {
     return acc == ACC_FP8 ? TileTimes{0.62 * S + 8.9, 0.58 * S + 7.5, 0.46 * S + 5.2} : TileTimes{1.21 * S + 10.0, 1.03 * S + 7.6, 0.79 * S + 6.4};
 }
+
+namespace {
 
 // The any-shape kernel's two forms: rounds of 256 tiles of 256 x 256, and tiles of 128 x 128 of which several share a
 // compute unit (their products, and 1.8 us per million outputs that leave one by one; a division per output with
@@ -164,13 +160,12 @@ struct SmallTimes { int rows, cols, chunk; double ends, each, further, ragged, l
 // again a third (4096 x 5025 x 2048: 200 us, the any-shape kernel 176).  Rows of fewer than 16 bytes are fetched byte by byte
 // (22 x 275 x 12: 13 us, the any-shape kernel 7.6).  The tiled kernel: rounds of 256 workgroups; where a single round leaves
 // half of the compute units idle, a tile has more of the caches to itself (512 x 4400 x 12096 in the FP8 mode: 65 us, 94 on
-// 64 x 64 tiles, and 93 by tile_times()).
-int choose_small(const GemmArgs& g, bool tiled)
+// 64 x 64 tiles, and 93 by tile_times()).  us_chosen: the time of what was chosen.
+int choose_small(const GemmArgs& g, bool tiled, double& us_chosen)
 {
     const double M = (double)g.M, N = (double)g.N, K = (double)g.K;
     auto units = [&](double tm, double tn) { return std::ceil(M / tm) * std::ceil(N / tn) / 256.0; };
     const double u64 = units(64, 64);
-    if (u64 > 32) return SMALL_NONE;
     double other;
     if (tiled) {
         const TileTimes t = tile_times(g.acc, 2.0 * std::ceil(K / (2 * TILE_K)));
@@ -183,6 +178,8 @@ int choose_small(const GemmArgs& g, bool tiled)
     } else {
         other = std::min(any_128_us(g), any_wide_us(g));
     }
+    us_chosen = other;
+    if (u64 > 32) return SMALL_NONE;
     static const SmallTimes times[3] = {{32, 32, 128, 3.4, 0.3, 0.7, 0.8, 0.0014, 0.0025, 0.0, 0.001},
                                         {32, 64, 128, 4.0, 0.6, 0.0, 0.3, 0.0018, 0.0018, 0.6, 0.0018},
                                         {64, 64, 64, 4.0, 1.2, 0.0, 0.3, 0.0026, 0.0026, 1.2, 0.0026}};
@@ -197,7 +194,7 @@ int choose_small(const GemmArgs& g, bool tiled)
         const SmallTimes& t = times[f];
         const double n = units(t.rows, t.cols), waits = std::max(0.0, n - 1.0) * (t.further + (g.K % t.chunk ? t.ragged : 0.0));
         const double us = t.ends + off * std::max(t.alone + bytewise + t.alone_k * K, n * (t.each + bytewise + (lines ? t.lines : t.other) * K) + waits);
-        if (us < best) { best = us; form = f; }
+        if (us < best) { best = us_chosen = us; form = f; }
     }
     return form;
 }
@@ -208,7 +205,7 @@ int choose_small(const GemmArgs& g, bool tiled)
 GemmPlan plan_gemm(const GemmArgs& g)
 {
     const int64_t M = g.M, N = g.N, K = g.K;
-    GemmPlan plan{!force_generic() && mfma_any_takes(g) ? GEMM_MFMA_ANY : GEMM_GENERIC, false, false, 0, SMALL_NONE, false, 0};
+    GemmPlan plan{!force_generic() && mfma_any_takes(g) ? GEMM_MFMA_ANY : GEMM_GENERIC, false, false, 0, SMALL_NONE, false, 0, 1e300};
     // a knob that asks for another form of the kernels keeps the small one out, unless FP8_KNOB_SMALL names a form of it
     const int small = g.splits <= 1 && !force_generic() ? knob(FP8_KNOB_SMALL) : 1;
     const bool small_allowed = small == 0 && !knob(FP8_KNOB_TILE_N) && !knob(FP8_KNOB_GEMM_KERNEL) && !knob(FP8_KNOB_MIXED) && !knob(FP8_KNOB_PERSIST) && knob(FP8_KNOB_TILE_192) != 2;
@@ -227,7 +224,7 @@ GemmPlan plan_gemm(const GemmArgs& g)
     const bool c_lines = N % 16 == 0 && aligned16(g.C) && (!g.ep.b_per_col || aligned16(g.ep.sB_dev));
     const bool fast = !force_generic() && !force_mfma_any() && aligned16(g.A) && aligned16(g.B) && fits32 && K % 16 == 0 &&
                       (g.transB || N % 16 == 0) && (!g.transA || M % 16 == 0);
-    if (small_allowed) plan.small = choose_small(g, fast);
+    if (small_allowed) plan.small = choose_small(g, fast, plan.us);
     else if (small >= 2 && tile_count(g, 32) <= 0x7fffffffll) plan.small = SMALL_32x32 + small - 2;
     if (!fast) return plan;
     // Tile width.  One workgroup per compute unit (256 of them) runs at a time: the width whose rounds

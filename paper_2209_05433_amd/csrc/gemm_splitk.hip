@@ -69,12 +69,25 @@ inline bool aligned_to(const void* p, uintptr_t a) { return ((uintptr_t)p & (a -
 // How a split-K call cuts a problem that the tiled kernel takes.  One round of workgroups (256
 // compute units) is the target; a slice is never shorter than 4 stage pairs (512 of K), whose
 // prologue and epilogue a shorter slice would not pay for.  requested > 0 forces the count.
+//
+// The library's own choice is one slice where the plain product takes less time: the small tiles walk a short K
+// before the slices' two launches have begun, and sums that are many next to K cost more to write and read than idle
+// compute units do.  Slices: a round of tiles, 3.5 us for the second launch, 0.32 us for each slice (its loads follow one another)
+// and 0.2 us per MB of sums.  Plain: the model of plan_gemm, no faster than 1.9 ns along K (256 x 256: 1.1 ns out of one
+// XCD's L2, 2.1 beyond it), and a tenth more for the small tiles, whose slope grows beyond K = 8192.  In the fp16 mode only the
+// small tiles may take a problem over: their waves cut K as slices do, while the tiled kernel's one chain of sums is further from
+// the 64-bit result than the slices' (2304 x 2560 x 12288: 1.5e-7 against 1.1e-7); the FP8 instructions' own error hides that.
+// Measured on 11 outputs from 256 x 256 to 3072 x 2560, nine K from 1024 to 32768, both accumulation modes, cut as before / in
+// one slice: 256 x 256 x 1024 23 / 5 us, 512 x 512 x 4096 28 / 12, 1024 x 1024 x 4096 36 / 18 (FP8 mode 30 / 16),
+// 3072 x 2560 x 4096 in the FP8 mode 50 / 34; kept: 1024 x 1024 x 16384 50 / 56, 256 x 256 x 32768 42 / 63,
+// 1536 x 1536 x 8192 56 / 71.  Where it errs by more than a tenth it cuts as before: outputs of
+// about 120 tiles at K = 8192 .. 16384 in the FP8 mode (2752 x 2752 x 8192 70 / 56).
 SplitPlan plan_splitk(const GemmArgs& g, int requested)
 {
     SplitPlan sp{1, 0, 256};
     GemmArgs probe = g;
-    const int kernel = plan_gemm(probe).kernel;
-    if (kernel != GEMM_TILED_256 && kernel != GEMM_TILED_128 && kernel != GEMM_TILED_MIXED) return sp;
+    const GemmPlan plain = plan_gemm(probe);
+    if (plain.kernel != GEMM_TILED_256 && plain.kernel != GEMM_TILED_128 && plain.kernel != GEMM_TILED_MIXED) return sp;
     const int forced_tile = knob(FP8_KNOB_TILE_N);
     sp.tile_n = forced_tile ? forced_tile : 256;             // the slices fill the chip: the wide tile is the faster one
     const int64_t tiles = ((g.M + TILE_M - 1) / TILE_M) * ((g.N + sp.tile_n - 1) / sp.tile_n);
@@ -87,6 +100,12 @@ SplitPlan plan_splitk(const GemmArgs& g, int requested)
     const int64_t per = (pairs + want - 1) / want;
     sp.pairs_per_split = (int)per;
     sp.splits = (int)((pairs + per - 1) / per);             // every slice holds at least one pair
+    if (requested <= 0 && sp.splits > 1 && (plain.small != SMALL_NONE || g.acc == ACC_FP8)) {
+        const double sums_mb = 4e-6 * sp.splits * (double)g.M * (double)g.N;
+        const double cut = tile_times(g.acc, 2.0 * (double)per).wide + 3.5 + 0.32 * sp.splits + 0.2 * sums_mb;
+        const double one = (plain.small != SMALL_NONE ? 1.1 : 1.03) * (plain.us > 4.0 + 0.0019 * (double)g.K ? plain.us : 4.0 + 0.0019 * (double)g.K);
+        if (one < cut) { sp.splits = 1; sp.pairs_per_split = (int)pairs; }
+    }
     return sp;
 }
 
@@ -171,8 +190,13 @@ size_t fp8_gemm_splitk_workspace_size(int64_t M, int64_t N, int64_t K, int trans
     if (M <= 0 || N <= 0 || K <= 0 || splits < 0 || splits > kMaxSplitK) return 0;
     GemmArgs g{};
     g.M = M; g.N = N; g.K = K; g.transA = transA != 0; g.transB = transB != 0;     // null pointers count as aligned
-    const SplitPlan sp = plan_splitk(g, splits ? splits : knob(FP8_KNOB_SPLIT_K));
-    return splitk_workspace_bytes(g, sp);
+    size_t bytes = 0;
+    for (int acc : {ACC_F16, ACC_FP8}) {                    // whichever the call will ask for
+        g.acc = acc;
+        const size_t need = splitk_workspace_bytes(g, plan_splitk(g, splits ? splits : knob(FP8_KNOB_SPLIT_K)));
+        bytes = need > bytes ? need : bytes;
+    }
+    return bytes;
 }
 
 int fp8_gemm_splitk(const uint8_t* A, int fmtA, int transA, const uint8_t* B, int fmtB, int transB,

@@ -124,6 +124,26 @@ def test_too_small_a_workspace_is_rejected_before_anything_is_launched():
     assert bool((C == 3.0).all())
 
 
+@pytest.mark.parametrize("flags", [0, fp8.FP8_GEMM_MFMA8])
+@pytest.mark.parametrize("M,N,K,cut", [(256, 256, 1024, False), (272, 528, 4112, False), (1024, 1024, 8192, False), (768, 1280, 16384, True)])
+def test_the_library_choice_on_both_sides_of_its_rule(M, N, K, cut, flags):
+    """splits = 0: one slice (no workspace, no second launch) where K is short, slices where it is long; the bound holds for
+    both, and a call without a workspace is the plain product where the query says 0."""
+    rng = np.random.default_rng(M + K)
+    dY, X = random_codes(rng, (K, M), E5M2, 0x4F), random_codes(rng, (K, N), E4M3, 0x6F)
+    C, need = splitk(to_dev(dY), E5M2, 1, to_dev(X), E4M3, 0, M, N, K, fp8.FP8_F32, 3.0, 0.5, flags, 0, fill=9.0)
+    assert (need > 0) == cut
+    rows = np.array([0, 255, M - 1])
+    S, T = oracle.gemm_rows(np.ascontiguousarray(dY.T), E5M2, X, E4M3, rows)
+    c_ref, alpha = oracle.unscale(S, 3.0, 0.5)
+    bound = REL[flags] * alpha * T + 0.5 * oracle.ulp(c_ref, oracle.F32)
+    assert np.all(np.abs(out_to_f64(C[torch.from_numpy(rows).cuda()]) - c_ref) <= bound)
+    if not cut:
+        plain = torch.empty_like(C)
+        fp8.fp8_gemm_ex(to_dev(dY), E5M2, 1, to_dev(X), E4M3, 0, plain, 3.0, 0.5, flags)
+        assert torch.equal(plain, C)
+
+
 def test_weight_gradient_regime_full_size():
     """dW[1024 x 1024] = dY^T X over K = 65536 tokens (E5M2^T x E4M3 -> fp32): 16 tiles, which the
     slices spread over the chip.  Whole rows element by element, every output through block sums,
