@@ -453,7 +453,7 @@ int fp8_gemm_plan(const uint8_t* A, int transA, const uint8_t* B, int transB, co
  *   FP8_KNOB_SMALL        the kernel of small tiles: 0 where the dispatcher's model of the run time prefers it
  *                         (and no knob asks for another kernel, tile width or form), 1 never (fp8_gemm_plan
  *                         then names the kernel that runs), 2 / 3 / 4 always, with tiles of 32 x 32 /
- *                         32 x 64 / 64 x 64 (FP8MM_SMALL)
+ *                         32 x 64 / 64 x 64 (of the last, the form the model prefers) (FP8MM_SMALL)
  *   FP8_KNOB_PATIENCE     the one-launch amax + cast of fp8_scaled_gemm: 0 a workgroup waits 200 us for the other
  *                         workgroups' maxima before it computes the missing ones itself, 1 it does not wait
  *                         (FP8MM_PATIENCE)

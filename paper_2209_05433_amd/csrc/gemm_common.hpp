@@ -90,8 +90,8 @@ int FP8MM_ANY_NAME(3)(const GemmArgs& g, bool wide);
 int launch_tiled(const GemmArgs& g);
 
 // The kernel for small problems (gemm_small.hip), one translation unit per pair of storage orders;
-// its forms are named by their output tile.
-enum { SMALL_NONE = -1, SMALL_32x32 = 0, SMALL_32x64 = 1, SMALL_64x64 = 2 };
+// its forms are named by their output tile; two more of the largest for operands that are both contiguous along K.
+enum { SMALL_NONE = -1, SMALL_32x32 = 0, SMALL_32x64 = 1, SMALL_64x64 = 2, SMALL_64x64_LINES8 = 3, SMALL_64x64_LINES4 = 4 };
 #define FP8MM_SMALL_NAME_(l) launch_small_l##l
 #define FP8MM_SMALL_NAME(l) FP8MM_SMALL_NAME_(l)
 int FP8MM_SMALL_NAME(0)(const GemmArgs& g, int form);

@@ -161,7 +161,8 @@ struct SmallTimes { int rows, cols, chunk; double ends, each, further, ragged, l
 // (22 x 275 x 12: 13 us, the any-shape kernel 7.6).  The tiled kernel: rounds of 256 workgroups; where a single round leaves
 // half of the compute units idle, a tile has more of the caches to itself (512 x 4400 x 12096 in the FP8 mode: 65 us, 94 on
 // 64 x 64 tiles, and 93 by tile_times()).  us_chosen: the time of what was chosen.
-int choose_small(const GemmArgs& g, bool tiled, double& us_chosen)
+// pinned: one of the three tile sizes, whatever it takes; the forms with 64 x 64 tiles are chosen from all the same.
+int choose_small(const GemmArgs& g, bool tiled, double& us_chosen, int pinned)
 {
     const double M = (double)g.M, N = (double)g.N, K = (double)g.K;
     auto units = [&](double tm, double tn) { return std::ceil(M / tm) * std::ceil(N / tn) / 256.0; };
@@ -179,20 +180,35 @@ int choose_small(const GemmArgs& g, bool tiled, double& us_chosen)
         other = std::min(any_128_us(g), any_wide_us(g));
     }
     us_chosen = other;
-    if (u64 > 32) return SMALL_NONE;
-    static const SmallTimes times[3] = {{32, 32, 128, 3.4, 0.3, 0.7, 0.8, 0.0014, 0.0025, 0.0, 0.001},
+    if (u64 > 32 && pinned == SMALL_NONE) return SMALL_NONE;
+    static const SmallTimes times[5] = {{32, 32, 128, 3.4, 0.3, 0.7, 0.8, 0.0014, 0.0025, 0.0, 0.001},
                                         {32, 64, 128, 4.0, 0.6, 0.0, 0.3, 0.0018, 0.0018, 0.6, 0.0018},
-                                        {64, 64, 64, 4.0, 1.2, 0.0, 0.3, 0.0026, 0.0026, 1.2, 0.0026}};
-    static_assert(SMALL_32x32 == 0 && SMALL_32x64 == 1 && SMALL_64x64 == 2, "the order of the table");
-    const bool lines = !g.transA && g.transB;
+                                        {64, 64, 64, 4.0, 1.2, 0.0, 0.3, 0.0026, 0.0026, 1.2, 0.0026},
+                                        {64, 64, 128, 4.0, 3.0, 0.0, 0.3, 0.0022, 0.0, 3.0, 0.0022},
+                                        {64, 64, 128, 4.0, 2.0, 0.0, 0.3, 0.00227, 0.0, 1.5, 0.0027}};
+    static_assert(SMALL_32x32 == 0 && SMALL_32x64 == 1 && SMALL_64x64 == 2 && SMALL_64x64_LINES8 == 3 && SMALL_64x64_LINES4 == 4, "the order of the table");
+    // ... the last three with the FP8 instructions, where both operands are contiguous along K: each, lines, alone, alone_k
+    static const double fp8_lines[3][4] = {{1.2, 0.0026, 1.2, 0.0029}, {1.4, 0.0020, 1.4, 0.0020}, {2.0, 0.00164, 1.5, 0.0023}};
+    const bool lines = !g.transA && g.transB, fp8 = g.acc == ACC_FP8;
     const bool off_a = !aligned16(g.A) || (g.transA ? g.M : g.K) % 16 != 0, off_b = !aligned16(g.B) || (g.transB ? g.K : g.N) % 16 != 0;
     const double off = off_a && off_b ? (u64 > 16 ? 1.56 : 1.2) : 1.0;
     const double bytewise = g.K < 16 ? 0.35 * K * ((g.transA ? 0 : 1) + (g.transB ? 1 : 0)) : 0.0;
     int form = SMALL_NONE;
-    double best = 0.95 * other;
-    for (int f = 0; f < 3; ++f) {
-        const SmallTimes& t = times[f];
-        const double n = units(t.rows, t.cols), waits = std::max(0.0, n - 1.0) * (t.further + (g.K % t.chunk ? t.ragged : 0.0));
+    double best = pinned == SMALL_NONE ? 0.95 * other : 1e300;
+    for (int f = 0; f < 5; ++f) {
+        const bool only_lines = f == SMALL_64x64_LINES8 || f == SMALL_64x64_LINES4;
+        if ((only_lines && !lines) || (pinned != SMALL_NONE && (only_lines ? (int)SMALL_64x64 : f) != pinned)) continue;
+        SmallTimes t = times[f];
+        double n = units(t.rows, t.cols);
+        // 64 x 64 tiles of operands that are both contiguous along K: a lone workgroup of the first form streams at half the
+        // rate of three, and up to two a compute unit the fullest one tells
+        if (lines && t.rows == 64) {
+            const double* p = fp8_lines[f - SMALL_64x64];
+            if (fp8) { t.each = p[0]; t.lines = p[1]; t.alone = p[2]; t.alone_k = p[3]; }
+            else if (f == SMALL_64x64) t.alone_k = 0.0042;
+            if (n <= 2.0 || f == SMALL_64x64_LINES8) n = std::max(n, std::ceil(n));
+        }
+        const double waits = std::max(0.0, n - 1.0) * (t.further + (g.K % t.chunk ? t.ragged : 0.0));
         const double us = t.ends + off * std::max(t.alone + bytewise + t.alone_k * K, n * (t.each + bytewise + (lines ? t.lines : t.other) * K) + waits);
         if (us < best) { best = us_chosen = us; form = f; }
     }
@@ -224,8 +240,8 @@ GemmPlan plan_gemm(const GemmArgs& g)
     const bool c_lines = N % 16 == 0 && aligned16(g.C) && (!g.ep.b_per_col || aligned16(g.ep.sB_dev));
     const bool fast = !force_generic() && !force_mfma_any() && aligned16(g.A) && aligned16(g.B) && fits32 && K % 16 == 0 &&
                       (g.transB || N % 16 == 0) && (!g.transA || M % 16 == 0);
-    if (small_allowed) plan.small = choose_small(g, fast, plan.us);
-    else if (small >= 2 && tile_count(g, 32) <= 0x7fffffffll) plan.small = SMALL_32x32 + small - 2;
+    if (small_allowed) plan.small = choose_small(g, fast, plan.us, SMALL_NONE);
+    else if (small >= 2 && tile_count(g, 32) <= 0x7fffffffll) plan.small = choose_small(g, fast, plan.us, SMALL_32x32 + small - 2);
     if (!fast) return plan;
     // Tile width.  One workgroup per compute unit (256 of them) runs at a time: the width whose rounds
     // of workgroups take less time (4096 x 6144: 384 wide tiles = two rounds, the second half empty, 768

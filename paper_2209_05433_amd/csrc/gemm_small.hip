@@ -9,7 +9,7 @@
 //   - a few hundred workgroups exist where the tiled kernel has ten, and K is walked NW times faster;
 //   - every byte is read once per workgroup, by the one wave that multiplies it: nothing is shared
 //     between waves until the end, and there is no barrier in the K loop;
-//   - D chunks of both operands (two; one with 64 x 64 tiles) are in flight per wave, in registers.
+//   - D chunks of both operands (two; one with 64 x 64 tiles, of 64 or 128) are in flight per wave, in registers.
 // A chunk is fetched as it lies in memory, neighbouring lanes on neighbouring 16 bytes of a row (loads
 // at any address; pieces that reach over an edge load the last 16 bytes of their row and shift), and
 // goes into a slab of LDS that belongs to the wave, out of which the fragments of the matrix
@@ -399,8 +399,18 @@ int launch_acc(const GemmArgs& g, int form)
     switch (form) {
         case SMALL_32x32: return launch_form<FA, FB, ACC, A_KC, B_KC, 1, 1, 2, 8, 2>(g);
         case SMALL_32x64: return launch_form<FA, FB, ACC, A_KC, B_KC, 1, 2, 2, 4, 2>(g);
-        default: return launch_form<FA, FB, ACC, A_KC, B_KC, 2, 2, 1, 4, 1>(g);
     }
+    // Both operands contiguous along K: chunks of 128 read whole lines and take half the trips.  Eight waves where a compute unit
+    // has one tile, whose four waves keep 32 KB in flight, a quarter of what the stream of a weight takes (64 x 12288 x 12288
+    // 63 -> 43 us, FP8 mode 50 -> 42; 256 x 3072 x 12288 56 -> 32, 41 -> 30; 512 x 2048 x 6144 27 -> 20; 64 x 12288 x 3072
+    // 21 -> 15); four where it has several and K is long (128 x 12288 x 12288 84 -> 63, FP8 mode 76 -> 61; 512 x 3072 x 12288
+    // 72 -> 57).  The first form stays for K up to about 2400 (512 x 6144 x 2048: 21.7, here 22.7: three workgroups a compute
+    // unit against two) and for the other orders, whose slabs of 128 x 64 leave room for one workgroup.
+    if constexpr (A_KC && B_KC) {
+        if (form == SMALL_64x64_LINES8) return launch_form<FA, FB, ACC, A_KC, B_KC, 2, 2, 2, 8, 1>(g);
+        if (form == SMALL_64x64_LINES4) return launch_form<FA, FB, ACC, A_KC, B_KC, 2, 2, 2, 4, 1>(g);
+    }
+    return launch_form<FA, FB, ACC, A_KC, B_KC, 2, 2, 1, 4, 1>(g);
 }
 
 }  // namespace

@@ -42,6 +42,14 @@ def test_small_forms_at_their_edges(M, N, K, off, transA, transB, form):
         ragged.test_small_tiles_at_their_edges(M, N, K, off, transA, transB)
 
 
+# 64 x 64 tiles of operands that are both contiguous along K have three forms: eight waves (few tiles and long K: the list
+# above has them), four waves with chunks of 128 (several tiles per compute unit and long K), four with chunks of 64 (short K)
+@pytest.mark.parametrize("M,N,K,off", [(1030, 1100, 2601, 1), (1088, 1024, 2560, 0), (1500, 1505, 200, 0), (1500, 1505, 67, 2), (61, 190, 1281, 0), (64, 128, 2048, 0)])
+def test_64x64_forms_of_k_contiguous_operands(M, N, K, off):
+    with pinned(SMALL_FORMS["64x64"]):
+        ragged.test_small_tiles_at_their_edges(M, N, K, off, 0, 1)
+
+
 @pytest.mark.parametrize("form", sorted(FORMS))
 @pytest.mark.parametrize("mode", fused.MODES)
 def test_outputs_of_every_form(mode, form):
