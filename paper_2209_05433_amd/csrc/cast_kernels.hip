@@ -20,15 +20,17 @@ namespace {
 // compute unit; one atomic per workgroup at the end (with one chunk per workgroup the thousands of
 // atomics on one cell cost a quarter of the run time).  The one-launch form cuts tensors of less than 1 MB into
 // chunks of 8 KB: their time is the latency of a few loads (64 KB of bf16 4.1 -> 3.8 us; 4 MB of fp32 5.1 -> 5.5 and
-// 10 MB of bf16 5.8 -> 6.6, all in chunks of 8 KB); up to 128 KB one workgroup reads the tensor alone, 16 vectors per lane in
-// flight: no tickets are drawn, each of which is a round trip to memory (64 KB of bf16 3.9 -> 2.5 us, 128 KB 4.1 -> 2.9; 200 KB would
-// be as fast either way).  With one atomic per workgroup more workgroups only cost: 4 MB
-// of fp32 6.0 -> 9.8 us.
+// 10 MB of bf16 5.8 -> 6.6, all in chunks of 8 KB); up to 64 KB one workgroup reads the tensor alone, 16 vectors per lane in
+// flight: no tickets are drawn, each of which is a round trip to memory.  The line lies where amax and the cast that follows
+// it, together, gain on a tensor that another kernel has just written: one workgroup fetches what lies in eight L2s, and the cast's
+// workgroups again what lies in its own (amax + cast in chunks of 8 KB / by one workgroup: 16 KB of bf16 5.1 / 4.5 us, 32 KB 5.5 / 4.75,
+// 64 KB 5.7 / 5.5, but 96 KB 5.7 / 6.45, 128 KB 5.8 / 6.6; of fp32 64 KB 6.05 / 5.4, 96 KB 6.2 / 6.7).  With one atomic per
+// workgroup more workgroups only cost: 4 MB of fp32 6.0 -> 9.8 us.
 constexpr int kAmaxVecs = 8;                                         // per lane and chunk
 constexpr int kAmaxVecsSmall = 2;
 constexpr size_t kAmaxSmallBelow = (size_t)32 * kThreads * kAmaxVecs;    // vectors
 constexpr int kAmaxVecsAlone = 16;
-constexpr size_t kAmaxAloneBelow = (size_t)2 * kThreads * kAmaxVecsAlone;  // vectors that one workgroup reads alone: 128 KB
+constexpr size_t kAmaxAloneBelow = (size_t)kThreads * kAmaxVecsAlone;      // vectors that one workgroup reads alone: 64 KB
 
 // Last step of the amax kernels in their one-launch form (fp8_amax_scale): no cell has to be
 // cleared beforehand and the scale comes out of the same launch.  Every workgroup leaves its
