@@ -417,7 +417,8 @@ int fp8_scaled_gemm(const void* a, const void* b, int in_dtype, int transA, int 
  * instructions, accumulation mode and bound); the answer is then still the one above that describes
  * their shape and alignment (FP8_KNOB_SMALL = 1 keeps them on the kernel that the answer names).  Where 256 x 192
  * tiles of the tiled kernel fill the rounds of workgroups better they are taken, alone or with 256 x 128 ones; the answer
- * is then the best choice without them (FP8_KNOB_TILE_192 = 1 makes it the kernel that runs).
+ * is then the best choice without them (FP8_KNOB_TILE_192 = 1 makes it the kernel that runs).  fp8_gemm_form names what runs in
+ * these cases too.
  * A negative value is minus an fp8_status_t (bad arguments).  Section 2 fixes the arithmetic,
  * not the kernel: every plan computes the same product within the stated bounds.
  */
@@ -427,6 +428,20 @@ typedef enum { FP8_PLAN_NO_GEMM = 0, FP8_PLAN_FMA_KERNEL = 1, FP8_PLAN_TILED_256
                FP8_PLAN_PERSISTENT = 32 } fp8_plan_t;
 int fp8_gemm_plan(const uint8_t* A, int transA, const uint8_t* B, int transB, const void* C,
                   int64_t M, int64_t N, int64_t K, const float* sB_per_column);
+
+/*
+ * The form of the kernel that a call runs, small tiles, 256 x 192 tiles, output kind (fp8_out_t) and flags included
+ * (diagnostics; as fp8_gemm_plan nothing is launched and no pointer dereferenced).  Answered for a per-tensor factor of A
+ * and no output amax: a factor per row or an amax keeps a call out of FP8_FORM_TILED_128_PERSISTENT and changes nothing else.
+ * The last two are forms of the 64 x 64 tile for operands that are both contiguous along K: chunks of 128 in eight and in four waves.
+ * A negative value is minus an fp8_status_t (bad arguments).
+ */
+typedef enum { FP8_FORM_NO_GEMM = 0, FP8_FORM_FMA = 1, FP8_FORM_TILED_256 = 2, FP8_FORM_TILED_192 = 3, FP8_FORM_TILED_128 = 4,
+               FP8_FORM_TILED_128_PERSISTENT = 5, FP8_FORM_TILED_256_128 = 6, FP8_FORM_TILED_192_128 = 7,
+               FP8_FORM_ANY_256 = 8, FP8_FORM_ANY_128 = 9, FP8_FORM_SMALL_32x32 = 10, FP8_FORM_SMALL_32x64 = 11,
+               FP8_FORM_SMALL_64x64 = 12, FP8_FORM_SMALL_64x64_LINES8 = 13, FP8_FORM_SMALL_64x64_LINES4 = 14 } fp8_form_t;
+int fp8_gemm_form(const uint8_t* A, int transA, const uint8_t* B, int transB, const void* C,
+                  int64_t M, int64_t N, int64_t K, int out_kind, const float* sB_per_column, int flags);
 
 /*
  * Tuning knobs, for diagnostics, tests and benchmarks (the paper fixes the arithmetic, not the

@@ -22,6 +22,9 @@ FP8_PLAN_NO_GEMM, FP8_PLAN_FMA_KERNEL, FP8_PLAN_TILED_256x256, FP8_PLAN_TILED_25
 FP8_PLAN_ELEMENTWISE_STORES = 16
 FP8_MULTI_MAX = 4
 FP8_PLAN_PERSISTENT = 32
+(FP8_FORM_NO_GEMM, FP8_FORM_FMA, FP8_FORM_TILED_256, FP8_FORM_TILED_192, FP8_FORM_TILED_128, FP8_FORM_TILED_128_PERSISTENT, FP8_FORM_TILED_256_128,
+ FP8_FORM_TILED_192_128, FP8_FORM_ANY_256, FP8_FORM_ANY_128, FP8_FORM_SMALL_32x32, FP8_FORM_SMALL_32x64, FP8_FORM_SMALL_64x64,
+ FP8_FORM_SMALL_64x64_LINES8, FP8_FORM_SMALL_64x64_LINES4) = range(15)
 FP8_KNOB_CAST_PATH, FP8_KNOB_TILE_N, FP8_KNOB_GROUP_M, FP8_KNOB_GEMM_KERNEL, FP8_KNOB_SPLIT_K, FP8_KNOB_CAST_RUN, FP8_KNOB_PERSIST, FP8_KNOB_MIXED, FP8_KNOB_SMALL, FP8_KNOB_PATIENCE, FP8_KNOB_TILE_192 = range(11)
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libfp8mm.so")
@@ -32,7 +35,7 @@ EXPORTS = (
     "fp8_quantize_dscale", "fp8_quantize_ex", "fp8_dequantize", "fp8_quantize_amax", "fp8_quantize_sr",
     "fp8_scale_from_amax_history", "fp8_scale_from_amax_n", "fp8_amax_rows", "fp8_quantize_rows",
     "fp8_quantize_transpose", "fp8_gemm", "fp8_gemm_dscale", "fp8_gemm_mfma8",
-    "fp8_gemm_mfma8_dscale", "fp8_gemm_ex", "fp8_gemm_splitk", "fp8_gemm_splitk_workspace_size", "fp8_gemm_splitk_static", "fp8_gemm_fused", "fp8_scaled_gemm", "fp8_gemm_plan", "fp8_set_knob", "fp8_get_knob",
+    "fp8_gemm_mfma8_dscale", "fp8_gemm_ex", "fp8_gemm_splitk", "fp8_gemm_splitk_workspace_size", "fp8_gemm_splitk_static", "fp8_gemm_fused", "fp8_scaled_gemm", "fp8_gemm_plan", "fp8_gemm_form", "fp8_set_knob", "fp8_get_knob",
     "fp8_last_error", "fp8_version",
 )
 
@@ -85,6 +88,7 @@ def lib() -> ctypes.CDLL:
     L.fp8_quantize_rows.argtypes, L.fp8_quantize_rows.restype = [vp, i64, i64, i, i, vp, vp, vp], i
     L.fp8_quantize_transpose.argtypes, L.fp8_quantize_transpose.restype = [vp, i64, i64, i, i, vp, vp, vp, vp], i
     L.fp8_gemm_plan.argtypes, L.fp8_gemm_plan.restype = [vp, i, vp, i, vp, i64, i64, i64, vp], i
+    L.fp8_gemm_form.argtypes, L.fp8_gemm_form.restype = [vp, i, vp, i, vp, i64, i64, i64, i, vp, i], i
     L.fp8_set_knob.argtypes, L.fp8_set_knob.restype = [i, i], i
     L.fp8_get_knob.argtypes, L.fp8_get_knob.restype = [i], i
     L.fp8_last_error.argtypes, L.fp8_last_error.restype = [], c.c_char_p
@@ -134,6 +138,17 @@ def fp8_gemm_plan(A: torch.Tensor, transA: bool, B: torch.Tensor, transB: bool, 
     if plan < 0:
         raise Fp8Error(-plan, lib().fp8_last_error().decode())
     return plan
+
+
+def fp8_gemm_form(A: torch.Tensor, transA: bool, B: torch.Tensor, transB: bool, C: torch.Tensor, out_kind: int, sB_per_column=None, flags: int = 0) -> int:
+    """The form of the kernel (an fp8_form_t) that a product of these tensors runs, small tiles and 256 x 192 tiles included."""
+    M, K = (A.shape[1], A.shape[0]) if transA else A.shape
+    N = B.shape[0] if transB else B.shape[1]
+    form = lib().fp8_gemm_form(A.data_ptr(), int(bool(transA)), B.data_ptr(), int(bool(transB)), C.data_ptr(), M, N, K, int(out_kind),
+                               None if sB_per_column is None else sB_per_column.data_ptr(), int(flags))
+    if form < 0:
+        raise Fp8Error(-form, lib().fp8_last_error().decode())
+    return form
 
 
 def fp8_scale_from_amax_host(amax: float, fmt: int) -> float:

@@ -504,4 +504,20 @@ int fp8_gemm_plan(const uint8_t* A, int transA, const uint8_t* B, int transB, co
     return kernel | (plan.elementwise_stores ? FP8_PLAN_ELEMENTWISE_STORES : 0) | (plan.persistent ? FP8_PLAN_PERSISTENT : 0);
 }
 
+int fp8_gemm_form(const uint8_t* A, int transA, const uint8_t* B, int transB, const void* C,
+                  int64_t M, int64_t N, int64_t K, int out_kind, const float* sB_per_column, int flags)
+{
+    clear_error();
+    if (M < 0 || N < 0 || K < 0) return -fail(FP8_ERR_INVALID_ARG, "fp8_gemm_form: negative dimension (M=%lld N=%lld K=%lld)", (long long)M, (long long)N, (long long)K);
+    if ((transA != 0 && transA != 1) || (transB != 0 && transB != 1)) return -fail(FP8_ERR_INVALID_ARG, "fp8_gemm_form: transA/transB must be 0 or 1");
+    if (out_kind < OUT_F32 || out_kind > OUT_E5M2) return -fail(FP8_ERR_INVALID_ARG, "fp8_gemm_form: out_kind %d is not an fp8_out_t", out_kind);
+    if (flags & ~FP8_GEMM_MFMA8) return -fail(FP8_ERR_INVALID_ARG, "fp8_gemm_form: unknown flag bits 0x%x", flags & ~FP8_GEMM_MFMA8);
+    if (M == 0 || N == 0 || K == 0) return FP8_FORM_NO_GEMM;
+    GemmArgs g{};
+    g.A = A; g.B = B; g.C = const_cast<void*>(C); g.M = M; g.N = N; g.K = K;
+    g.transA = transA != 0; g.transB = transB != 0; g.acc = (flags & FP8_GEMM_MFMA8) ? ACC_FP8 : ACC_F16;
+    g.ep.out_kind = out_kind; g.ep.sB_dev = sB_per_column; g.ep.b_per_col = sB_per_column != nullptr;
+    return gemm_form(g);
+}
+
 }  // extern "C"

@@ -120,6 +120,8 @@ enum { GEMM_GENERIC = 1, GEMM_TILED_256 = 2, GEMM_TILED_128 = 3, GEMM_MFMA_ANY =
 // single tile widths.
 struct GemmPlan { int kernel; bool elementwise_stores; bool persistent; int wide_cols; int small; bool middle; int middle_cols; double us; };
 GemmPlan plan_gemm(const GemmArgs& g);
+// The form (fp8_form_t) of the kernel that launch_gemm takes for it.
+int gemm_form(const GemmArgs& g);
 
 // Microseconds for one tile of the tiled kernel, S stages of 64 along K, as one of several rounds of 256 that
 // run at a time (fitted to 4096 x 6144 over K = 512 .. 2048 and to 3294 x 11648 x 4288; within 5 %).  middle: the

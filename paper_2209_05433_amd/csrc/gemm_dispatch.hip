@@ -370,6 +370,19 @@ int launch_tiled(const GemmArgs& g)
     return table[(g.transA ? 2 : 0) + (g.transB ? 1 : 0)][g.acc == ACC_FP8 ? 1 : 0](g);
 }
 
+int gemm_form(const GemmArgs& g)
+{
+    static_assert(FP8_FORM_SMALL_64x64_LINES4 - FP8_FORM_SMALL_32x32 == SMALL_64x64_LINES4, "the order of the forms");
+    const GemmPlan plan = plan_gemm(g);
+    if (plan.small != SMALL_NONE) return FP8_FORM_SMALL_32x32 + plan.small;
+    if (plan.kernel == GEMM_GENERIC) return FP8_FORM_FMA;
+    if (plan.kernel == GEMM_MFMA_ANY) return mfma_any_wide(g) ? FP8_FORM_ANY_256 : FP8_FORM_ANY_128;
+    if (plan.middle) return plan.middle_cols > 0 ? FP8_FORM_TILED_192_128 : FP8_FORM_TILED_192;
+    if (plan.kernel == GEMM_TILED_MIXED) return FP8_FORM_TILED_256_128;
+    if (plan.kernel == GEMM_TILED_256) return FP8_FORM_TILED_256;
+    return plan.persistent ? FP8_FORM_TILED_128_PERSISTENT : FP8_FORM_TILED_128;
+}
+
 int launch_gemm(const GemmArgs& g)
 {
     const int64_t M = g.M, N = g.N, K = g.K;

@@ -166,6 +166,9 @@ int main(void)
     EXPECT(fp8_gemm_plan(A, 0, B, 0, C, -1, 512, 512, NULL), -BAD);
     EXPECT(fp8_gemm_plan(A, 0, B, 3, C, 512, 512, 512, NULL), -BAD);
     EXPECT(fp8_gemm_plan(A, 0, B, 0, C, INT64_MAX / 2, 3, 5, NULL), FP8_PLAN_FMA_KERNEL);
+    EXPECT(fp8_gemm_form(A, 0, B, 0, C, 8192, 49152, 12288, FP8_OUT_BF16, NULL, 0), FP8_FORM_TILED_256);
+    EXPECT(fp8_gemm_form(A, 0, B, 0, C, 4096, 6144, 2048, FP8_OUT_BF16, NULL, 0), FP8_FORM_TILED_192);
+    EXPECT(fp8_gemm_form(A, 0, B, 0, C, 16, 16, 16, 4, NULL, 0), -BAD);
     EXPECT(fp8_gemm_splitk_workspace_size(1024, 1024, 65536, 1, 0, 0), (size_t)16 * 1024 * 1024 * 4);
     EXPECT(fp8_gemm_splitk_workspace_size(1024, 1024, 65536, 1, 0, 70), 0);
     EXPECT(fp8_gemm_splitk_workspace_size(-5, 1024, 65536, 1, 0, 0), 0);
@@ -185,6 +188,11 @@ int main(void)
             if (plan < 0 || kernel < FP8_PLAN_FMA_KERNEL || kernel > FP8_PLAN_TILED_MIXED ||
                 (plan & ~(15 | FP8_PLAN_ELEMENTWISE_STORES | FP8_PLAN_PERSISTENT))) {
                 printf("plan(%lld, %lld, %lld, %d, %d, +%d) = %d\n", (long long)dim[0], (long long)dim[1], (long long)dim[2], ta, tb, off, plan);
+                ++failures;
+            }
+            const int form = fp8_gemm_form(A + off, ta, B, tb, C, dim[0], dim[1], dim[2], (int)((s >> 24) & 3), (s >> 33) & 1 ? F : NULL, (s >> 34) & 1 ? FP8_GEMM_MFMA8 : 0);
+            if (form < FP8_FORM_FMA || form > FP8_FORM_SMALL_64x64_LINES4) {
+                printf("form(%lld, %lld, %lld, %d, %d, +%d) = %d\n", (long long)dim[0], (long long)dim[1], (long long)dim[2], ta, tb, off, form);
                 ++failures;
             }
             const size_t ws = fp8_gemm_splitk_workspace_size(dim[0], dim[1], dim[2], ta, tb, (int)((s >> 20) % 65));

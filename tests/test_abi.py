@@ -98,6 +98,43 @@ def test_gemm_plan_names_the_kernel_for_the_workload_shapes():
     assert plan(2, 0, 5, 5, 5) == -fp8.FP8_ERR_INVALID_ARG and plan(0, 0, -1, 5, 5) == -fp8.FP8_ERR_INVALID_ARG
 
 
+def test_gemm_form_names_what_runs():
+    """fp8_gemm_form is the same host logic as fp8_gemm_plan with the output kind, the flags, the small tiles and the 256 x 192
+    tiles in it."""
+    L = fp8.lib()
+    A, B, C, F = 1 << 20, 1 << 34, 1 << 40, 1 << 42
+    form = lambda ta, tb, M, N, K, out=fp8.FP8_OUT_F32, sb=None, flags=0, a=A: L.fp8_gemm_form(a, ta, B, tb, C, M, N, K, out, sb, flags)
+    M8 = fp8.FP8_GEMM_MFMA8
+    assert form(0, 0, 8192, 49152, 12288) == fp8.FP8_FORM_TILED_256
+    assert form(0, 0, 4096, 6144, 2048) == fp8.FP8_FORM_TILED_128_PERSISTENT
+    assert form(0, 0, 4096, 6144, 2048, fp8.FP8_OUT_BF16) == form(0, 0, 4096, 6144, 2048, fp8.FP8_OUT_BF16, F, M8) == fp8.FP8_FORM_TILED_192
+    assert form(0, 1, 3001, 6144, 2048, fp8.FP8_OUT_E4M3, F) == fp8.FP8_FORM_TILED_192_128
+    assert form(0, 1, 3001, 6144, 2048, fp8.FP8_OUT_E4M3, F, M8) == fp8.FP8_FORM_TILED_256_128
+    assert form(0, 0, 8192, 50257, 12288) == fp8.FP8_FORM_ANY_256 and form(0, 0, 8192, 9001, 300) == fp8.FP8_FORM_ANY_128
+    assert form(0, 1, 16, 6144, 2048, fp8.FP8_OUT_BF16, F) == fp8.FP8_FORM_SMALL_32x32
+    assert form(0, 0, 0, 5, 5) == form(0, 0, 5, 5, 0) == fp8.FP8_FORM_NO_GEMM
+    for bad in (form(2, 0, 5, 5, 5), form(0, 0, -1, 5, 5), form(0, 0, 5, 5, 5, 4), form(0, 0, 5, 5, 5, 0, None, 2)):
+        assert bad == -fp8.FP8_ERR_INVALID_ARG
+    # with the small and the 192-wide tiles forbidden it is fp8_gemm_plan's answer
+    name = {fp8.FP8_PLAN_TILED_256x256: fp8.FP8_FORM_TILED_256, fp8.FP8_PLAN_TILED_256x128: fp8.FP8_FORM_TILED_128,
+            fp8.FP8_PLAN_TILED_256x128 | fp8.FP8_PLAN_PERSISTENT: fp8.FP8_FORM_TILED_128_PERSISTENT, fp8.FP8_PLAN_TILED_MIXED: fp8.FP8_FORM_TILED_256_128}
+    rng = np.random.default_rng(4)
+    old = fp8.fp8_set_knob(fp8.FP8_KNOB_SMALL, 1), fp8.fp8_set_knob(fp8.FP8_KNOB_TILE_192, 1)
+    try:
+        seen = set()
+        for _ in range(2000):
+            M, N, K = (16 * int(np.exp(rng.uniform(0, np.log(800)))) + int(rng.integers(8) == 0) for _ in range(3))
+            ta, tb = int(rng.integers(2)), int(rng.integers(2))
+            plan = L.fp8_gemm_plan(A, ta, B, tb, C, M, N, K, None) & ~fp8.FP8_PLAN_ELEMENTWISE_STORES
+            got = form(ta, tb, M, N, K)
+            assert got == name[plan] if plan in name else got in (fp8.FP8_FORM_ANY_256, fp8.FP8_FORM_ANY_128)
+            seen.add(got)
+        assert seen >= {fp8.FP8_FORM_TILED_256, fp8.FP8_FORM_TILED_128, fp8.FP8_FORM_TILED_256_128, fp8.FP8_FORM_ANY_256, fp8.FP8_FORM_ANY_128}
+    finally:
+        fp8.fp8_set_knob(fp8.FP8_KNOB_SMALL, old[0])
+        fp8.fp8_set_knob(fp8.FP8_KNOB_TILE_192, old[1])
+
+
 def test_knobs_round_trip_and_reject_bad_values():
     assert fp8.fp8_get_knob(fp8.FP8_KNOB_TILE_N) == 0
     assert fp8.fp8_set_knob(fp8.FP8_KNOB_TILE_N, 128) == 0

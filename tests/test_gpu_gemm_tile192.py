@@ -61,17 +61,34 @@ def test_every_output_kind_at_the_edges_of_the_tile(transA, transB, mode):
                     assert np.array_equal(D.cpu().numpy(), oracle.quantize((ref * 0.25).astype(np.float32), fmt, 1.0)), (M, N, K, per_column)
 
 
-# sizes at which the dispatcher takes the tile by itself: two full rounds of it; a round of it and 128-wide tiles for the
-# rest of N; a single round, where K is short
+# sizes at which the dispatcher takes the tile by itself: two full rounds of it; a single round, where K is short; a round of it and
+# 128-wide tiles for the rest of N
+TAKEN = {(4096, 6144, 2048): fp8.FP8_FORM_TILED_192, (2816, 4416, 384): fp8.FP8_FORM_TILED_192,
+         (1984, 8576, 4112): fp8.FP8_FORM_TILED_192_128, (3296, 6192, 880): fp8.FP8_FORM_TILED_192_128}
+
+
 @pytest.mark.parametrize("mode", sorted(FLAGS))
-@pytest.mark.parametrize("M,N,K,transB", [(4096, 6144, 2048, 0), (3001, 6144, 2048, 1), (1984, 8576, 4112, 0), (2816, 4416, 384, 0)])
-def test_the_dispatchers_choice_gives_the_bits_of_the_other_tiles(M, N, K, transB, mode):
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", sorted(TAKEN))
+def test_the_dispatchers_choice_gives_the_bits_of_the_other_tiles(M, N, K, transA, transB, mode):
     g = torch.Generator(device="cuda")
     g.manual_seed(M)
-    dA, dB = (torch.randint(0, 0x78, s, dtype=torch.uint8, device="cuda", generator=g) for s in ((M, K), (N, K) if transB else (K, N)))
+    # codes up to 2^3 (E4M3) and 2^2 (E5M2) of either sign: sums around zero
+    dA, dB = (torch.randint(0, top, s, dtype=torch.uint8, device="cuda", generator=g) | torch.randint(0, 2, s, dtype=torch.uint8, device="cuda", generator=g) << 7
+              for top, s in ((0x51, (K, M) if transA else (M, K)), (0x45, (N, K) if transB else (K, N))))
     sB = torch.rand(N, device="cuda", generator=g) + 0.5
-    for kind, sD in ((fp8.FP8_OUT_BF16, None), (fp8.FP8_OUT_E4M3, torch.full((1,), 1e-3, device="cuda"))):
-        D, amax = product(dA, 0, dB, transB, (M, N), kind, sB, sD, FLAGS[mode])
+    sD = None
+    for kind in (fp8.FP8_OUT_F32, fp8.FP8_OUT_BF16, fp8.FP8_OUT_E4M3):
+        buf = torch.empty((M, N), dtype=OUT[kind], device="cuda")
+        assert fp8.fp8_gemm_form(dA, transA, dB, transB, buf, kind, sB, FLAGS[mode]) == TAKEN[M, N, K]
+        factor = sD if kind >= fp8.FP8_OUT_E4M3 else None
+        D, amax = product(dA, transA, dB, transB, (M, N), kind, sB, factor, FLAGS[mode])
         with knob(fp8.FP8_KNOB_TILE_192, 1):
-            D1, amax1 = product(dA, 0, dB, transB, (M, N), kind, sB, sD, FLAGS[mode])
+            assert fp8.fp8_gemm_form(dA, transA, dB, transB, buf, kind, sB, FLAGS[mode]) not in (fp8.FP8_FORM_TILED_192, fp8.FP8_FORM_TILED_192_128)
+            D1, amax1 = product(dA, transA, dB, transB, (M, N), kind, sB, factor, FLAGS[mode])
         assert torch.equal(D, D1) and torch.equal(amax, amax1), (kind, int((D != D1).sum()))
+        if kind == fp8.FP8_OUT_F32:
+            sD = (100.0 / D.std()).reshape(1)           # the FP8 outputs: 448 is at four and a half deviations
+        elif kind == fp8.FP8_OUT_E4M3:
+            bytes_, counts = torch.unique(D, return_counts=True)
+            assert len(bytes_) > 200 and int(counts.max()) < 0.05 * M * N, "outputs that do not tell a wrong sum from a right one"
