@@ -189,7 +189,8 @@ int choose_small(const GemmArgs& g, bool tiled, double& us_chosen, int pinned)
     static_assert(SMALL_32x32 == 0 && SMALL_32x64 == 1 && SMALL_64x64 == 2 && SMALL_64x64_LINES8 == 3 && SMALL_64x64_LINES4 == 4, "the order of the table");
     // ... the last three with the FP8 instructions, where both operands are contiguous along K: each, lines, alone, alone_k
     static const double fp8_lines[3][4] = {{1.2, 0.0026, 1.2, 0.0029}, {1.4, 0.0020, 1.4, 0.0020}, {2.0, 0.00164, 1.5, 0.0023}};
-    const bool lines = !g.transA && g.transB, fp8 = g.acc == ACC_FP8;
+    // (what the tiled kernel does not take is computed in the fp16 mode, whatever the flag says)
+    const bool lines = !g.transA && g.transB, fp8 = tiled && g.acc == ACC_FP8;
     const bool off_a = !aligned16(g.A) || (g.transA ? g.M : g.K) % 16 != 0, off_b = !aligned16(g.B) || (g.transB ? g.K : g.N) % 16 != 0;
     const double off = off_a && off_b ? (u64 > 16 ? 1.56 : 1.2) : 1.0;
     const double bytewise = g.K < 16 ? 0.35 * K * ((g.transA ? 0 : 1) + (g.transB ? 1 : 0)) : 0.0;

@@ -135,6 +135,21 @@ def test_gemm_form_names_what_runs():
         fp8.fp8_set_knob(fp8.FP8_KNOB_TILE_192, old[1])
 
 
+def test_the_flag_does_not_change_the_form_off_the_tiled_kernel():
+    """Problems that the tiled kernel does not take are computed in the default mode under FP8_GEMM_MFMA8 too: they run the
+    form that they run without the flag."""
+    L = fp8.lib()
+    A, B, C = 1 << 20, 1 << 34, 1 << 40
+    form = lambda a, ta, tb, M, N, K, flags: L.fp8_gemm_form(a, ta, B, tb, C, M, N, K, fp8.FP8_OUT_BF16, None, flags)
+    assert form(A, 0, 1, 1559, 3843, 405, fp8.FP8_GEMM_MFMA8) == form(A, 0, 1, 1559, 3843, 405, 0)
+    rng = np.random.default_rng(6)
+    for _ in range(4000):
+        M, N, K = (int(np.exp(rng.uniform(0, np.log(12000)))) for _ in range(3))
+        ta, tb, off = int(rng.integers(2)), int(rng.integers(2)), int(rng.integers(2))
+        K |= off ^ 1                                    # an odd K or an operand at an odd address
+        assert form(A + off, ta, tb, M, N, K, fp8.FP8_GEMM_MFMA8) == form(A + off, ta, tb, M, N, K, 0), (M, N, K, ta, tb, off)
+
+
 def test_knobs_round_trip_and_reject_bad_values():
     assert fp8.fp8_get_knob(fp8.FP8_KNOB_TILE_N) == 0
     assert fp8.fp8_set_knob(fp8.FP8_KNOB_TILE_N, 128) == 0
