@@ -474,7 +474,8 @@ int fp8_gemm_form(const uint8_t* A, int transA, const uint8_t* B, int transB, co
  *                         (FP8MM_PATIENCE)
  *   FP8_KNOB_TILE_192     the tiled kernel's tile of 256 x 192: 0 where the dispatcher's model of the run time
  *                         prefers it (and no other knob asks for a kernel, tile width or form), 1 never
- *                         (fp8_gemm_plan then names the kernel that runs), 2 wherever the tiled kernel runs (FP8MM_TILE_192)
+ *                         (fp8_gemm_plan then names the kernel that runs), 2 wherever the tiled kernel runs; with FP8_KNOB_MIXED = 2
+ *                         for the first half of the columns, 128-wide tiles for the rest (FP8MM_TILE_192)
  */
 typedef enum { FP8_KNOB_CAST_PATH = 0, FP8_KNOB_TILE_N = 1, FP8_KNOB_GROUP_M = 2, FP8_KNOB_GEMM_KERNEL = 3,
                FP8_KNOB_SPLIT_K = 4, FP8_KNOB_CAST_RUN = 5, FP8_KNOB_PERSIST = 6, FP8_KNOB_MIXED = 7,

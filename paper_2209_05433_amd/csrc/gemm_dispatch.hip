@@ -321,9 +321,10 @@ GemmPlan plan_gemm(const GemmArgs& g)
     // 252 of them and 204 narrow ones, 85 us against 90 for 384 of them and 94 for 252 wide and 72 narrow ones).  Of 70 products in the
     // range where it decides, 19 took them: 1.00 to 1.16 times as fast, and no other would have gained more than 2 %.
     // fp32 outputs that the persistent narrow form takes stay there (4096 x 6144 x 1024: 57 us, here 59).
-    // Knob FP8_KNOB_TILE_192: 0 = by the model, 1 = never, 2 = always.
+    // Knob FP8_KNOB_TILE_192: 0 = by the model, 1 = never, 2 = always (with FP8_KNOB_MIXED = 2: for half of the columns, 128-wide ones behind).
     if (middle_knob == 2) {
         plan.middle = true;
+        plan.middle_cols = mk == 2 && N > 192 ? (int)((N + 191) / 384) : 0;
     } else if (middle_knob == 0 && !tn && !mk && !pk && few_rounds && !(plan.persistent && g.ep.out_kind == OUT_F32)) {
         double best = makespan(tiles_m * ((N + 191) / 192), 0, tile.middle);
         for (int64_t units = 256; units / tiles_m * 192 < N; units += 256) {     // as many columns as whole rounds hold
