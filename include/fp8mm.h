@@ -468,7 +468,8 @@ int fp8_gemm_form(const uint8_t* A, int transA, const uint8_t* B, int transB, co
  *   FP8_KNOB_SMALL        the kernel of small tiles: 0 where the dispatcher's model of the run time prefers it
  *                         (and no knob asks for another kernel, tile width or form), 1 never (fp8_gemm_plan
  *                         then names the kernel that runs), 2 / 3 / 4 always, with tiles of 32 x 32 /
- *                         32 x 64 / 64 x 64 (of the last, the form the model prefers) (FP8MM_SMALL)
+ *                         32 x 64 / 64 x 64 (of the last, the form the model prefers or FP8_KNOB_SMALL_64
+ *                         names) (FP8MM_SMALL)
  *   FP8_KNOB_PATIENCE     the one-launch amax + cast of fp8_scaled_gemm: 0 a workgroup waits 200 us for the other
  *                         workgroups' maxima before it computes the missing ones itself, 1 it does not wait
  *                         (FP8MM_PATIENCE)
@@ -476,10 +477,13 @@ int fp8_gemm_form(const uint8_t* A, int transA, const uint8_t* B, int transB, co
  *                         prefers it (and no other knob asks for a kernel, tile width or form), 1 never
  *                         (fp8_gemm_plan then names the kernel that runs), 2 wherever the tiled kernel runs; with FP8_KNOB_MIXED = 2
  *                         for the first half of the columns, 128-wide tiles for the rest (FP8MM_TILE_192)
+ *   FP8_KNOB_SMALL_64     the form of 64 x 64 tiles of operands that are both contiguous along K: 0 the one the model prefers,
+ *                         1 chunks of 64, 2 / 3 chunks of 128 in eight / four waves (FP8MM_SMALL_64)
  */
 typedef enum { FP8_KNOB_CAST_PATH = 0, FP8_KNOB_TILE_N = 1, FP8_KNOB_GROUP_M = 2, FP8_KNOB_GEMM_KERNEL = 3,
                FP8_KNOB_SPLIT_K = 4, FP8_KNOB_CAST_RUN = 5, FP8_KNOB_PERSIST = 6, FP8_KNOB_MIXED = 7,
-               FP8_KNOB_SMALL = 8, FP8_KNOB_PATIENCE = 9, FP8_KNOB_TILE_192 = 10, FP8_KNOB_COUNT = 11 } fp8_knob_t;
+               FP8_KNOB_SMALL = 8, FP8_KNOB_PATIENCE = 9, FP8_KNOB_TILE_192 = 10,
+               FP8_KNOB_SMALL_64 = 11, FP8_KNOB_COUNT = 12 } fp8_knob_t;
 int fp8_set_knob(int knob, int value);
 int fp8_get_knob(int knob);
 

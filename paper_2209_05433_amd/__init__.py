@@ -15,7 +15,7 @@ from .binding import (  # noqa: F401
     fp8_gemm_splitk_workspace_size, FP8_SPLITK_STATIC_BYTES, FP8_GEMM_MFMA8,
     FP8_OUT_F32, FP8_OUT_BF16, FP8_OUT_E4M3, FP8_OUT_E5M2, fp8_gemm_plan,
     FP8_PLAN_NO_GEMM, FP8_PLAN_FMA_KERNEL, FP8_PLAN_TILED_256x256, FP8_PLAN_TILED_256x128, FP8_PLAN_MFMA_ANY, FP8_PLAN_TILED_MIXED, FP8_PLAN_ELEMENTWISE_STORES,
-    fp8_set_knob, fp8_get_knob, FP8_KNOB_CAST_PATH, FP8_KNOB_TILE_N, FP8_KNOB_GROUP_M, FP8_KNOB_GEMM_KERNEL, FP8_KNOB_SPLIT_K, FP8_KNOB_CAST_RUN, FP8_KNOB_PERSIST, FP8_KNOB_MIXED, FP8_KNOB_SMALL, FP8_KNOB_PATIENCE, FP8_KNOB_TILE_192, FP8_PLAN_PERSISTENT,
+    fp8_set_knob, fp8_get_knob, FP8_KNOB_CAST_PATH, FP8_KNOB_TILE_N, FP8_KNOB_GROUP_M, FP8_KNOB_GEMM_KERNEL, FP8_KNOB_SPLIT_K, FP8_KNOB_CAST_RUN, FP8_KNOB_PERSIST, FP8_KNOB_MIXED, FP8_KNOB_SMALL, FP8_KNOB_PATIENCE, FP8_KNOB_TILE_192, FP8_KNOB_SMALL_64, FP8_PLAN_PERSISTENT,
     fp8_gemm_form, FP8_FORM_NO_GEMM, FP8_FORM_FMA, FP8_FORM_TILED_256, FP8_FORM_TILED_192, FP8_FORM_TILED_128, FP8_FORM_TILED_128_PERSISTENT,
     FP8_FORM_TILED_256_128, FP8_FORM_TILED_192_128, FP8_FORM_ANY_256, FP8_FORM_ANY_128, FP8_FORM_SMALL_32x32, FP8_FORM_SMALL_32x64,
     FP8_FORM_SMALL_64x64, FP8_FORM_SMALL_64x64_LINES8, FP8_FORM_SMALL_64x64_LINES4,

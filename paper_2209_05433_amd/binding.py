@@ -25,7 +25,7 @@ FP8_PLAN_PERSISTENT = 32
 (FP8_FORM_NO_GEMM, FP8_FORM_FMA, FP8_FORM_TILED_256, FP8_FORM_TILED_192, FP8_FORM_TILED_128, FP8_FORM_TILED_128_PERSISTENT, FP8_FORM_TILED_256_128,
  FP8_FORM_TILED_192_128, FP8_FORM_ANY_256, FP8_FORM_ANY_128, FP8_FORM_SMALL_32x32, FP8_FORM_SMALL_32x64, FP8_FORM_SMALL_64x64,
  FP8_FORM_SMALL_64x64_LINES8, FP8_FORM_SMALL_64x64_LINES4) = range(15)
-FP8_KNOB_CAST_PATH, FP8_KNOB_TILE_N, FP8_KNOB_GROUP_M, FP8_KNOB_GEMM_KERNEL, FP8_KNOB_SPLIT_K, FP8_KNOB_CAST_RUN, FP8_KNOB_PERSIST, FP8_KNOB_MIXED, FP8_KNOB_SMALL, FP8_KNOB_PATIENCE, FP8_KNOB_TILE_192 = range(11)
+FP8_KNOB_CAST_PATH, FP8_KNOB_TILE_N, FP8_KNOB_GROUP_M, FP8_KNOB_GEMM_KERNEL, FP8_KNOB_SPLIT_K, FP8_KNOB_CAST_RUN, FP8_KNOB_PERSIST, FP8_KNOB_MIXED, FP8_KNOB_SMALL, FP8_KNOB_PATIENCE, FP8_KNOB_TILE_192, FP8_KNOB_SMALL_64 = range(12)
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libfp8mm.so")
 NATIVE_PATH = os.path.join(os.path.dirname(LIB_PATH), "_native.so")

@@ -48,6 +48,7 @@ static void seed_knobs()
     if ((e = getenv("FP8MM_SMALL")) && atoi(e) >= 0 && atoi(e) <= 4) g_knob[FP8_KNOB_SMALL] = atoi(e);
     if ((e = getenv("FP8MM_PATIENCE")) && atoi(e) == 1) g_knob[FP8_KNOB_PATIENCE] = 1;
     if ((e = getenv("FP8MM_TILE_192")) && atoi(e) >= 0 && atoi(e) <= 2) g_knob[FP8_KNOB_TILE_192] = atoi(e);
+    if ((e = getenv("FP8MM_SMALL_64")) && atoi(e) >= 0 && atoi(e) <= 3) g_knob[FP8_KNOB_SMALL_64] = atoi(e);
     if ((e = getenv("FP8MM_MIXED")) && atoi(e) >= 0 && atoi(e) <= 2) g_knob[FP8_KNOB_MIXED] = atoi(e);
 }
 
@@ -122,6 +123,7 @@ int fp8_set_knob(int which, int value)
         case FP8_KNOB_SMALL: ok = value >= 0 && value <= 4; break;
         case FP8_KNOB_PATIENCE: ok = value == 0 || value == 1; break;
         case FP8_KNOB_TILE_192: ok = value >= 0 && value <= 2; break;
+        case FP8_KNOB_SMALL_64: ok = value >= 0 && value <= 3; break;
     }
     if (!ok) return -fail(FP8_ERR_INVALID_ARG, "fp8_set_knob: value %d is not valid for knob %d", value, which);
     const int old = knob(which);                    // seeds from the environment first

@@ -161,7 +161,8 @@ struct SmallTimes { int rows, cols, chunk; double ends, each, further, ragged, l
 // (22 x 275 x 12: 13 us, the any-shape kernel 7.6).  The tiled kernel: rounds of 256 workgroups; where a single round leaves
 // half of the compute units idle, a tile has more of the caches to itself (512 x 4400 x 12096 in the FP8 mode: 65 us, 94 on
 // 64 x 64 tiles, and 93 by tile_times()).  us_chosen: the time of what was chosen.
-// pinned: one of the three tile sizes, whatever it takes; the forms with 64 x 64 tiles are chosen from all the same.
+// pinned: one of the three tile sizes, whatever it takes; the forms with 64 x 64 tiles are chosen from all the same, or named by
+// FP8_KNOB_SMALL_64.
 int choose_small(const GemmArgs& g, bool tiled, double& us_chosen, int pinned)
 {
     const double M = (double)g.M, N = (double)g.N, K = (double)g.K;
@@ -194,11 +195,13 @@ int choose_small(const GemmArgs& g, bool tiled, double& us_chosen, int pinned)
     const bool off_a = !aligned16(g.A) || (g.transA ? g.M : g.K) % 16 != 0, off_b = !aligned16(g.B) || (g.transB ? g.K : g.N) % 16 != 0;
     const double off = off_a && off_b ? (u64 > 16 ? 1.56 : 1.2) : 1.0;
     const double bytewise = g.K < 16 ? 0.35 * K * ((g.transA ? 0 : 1) + (g.transB ? 1 : 0)) : 0.0;
+    const int form64 = lines ? knob(FP8_KNOB_SMALL_64) : 0;
     int form = SMALL_NONE;
     double best = pinned == SMALL_NONE ? 0.95 * other : 1e300;
     for (int f = 0; f < 5; ++f) {
         const bool only_lines = f == SMALL_64x64_LINES8 || f == SMALL_64x64_LINES4;
         if ((only_lines && !lines) || (pinned != SMALL_NONE && (only_lines ? (int)SMALL_64x64 : f) != pinned)) continue;
+        if (form64 && f >= SMALL_64x64 && f != SMALL_64x64 + form64 - 1) continue;
         SmallTimes t = times[f];
         double n = units(t.rows, t.cols);
         // 64 x 64 tiles of operands that are both contiguous along K: a lone workgroup of the first form streams at half the

@@ -292,6 +292,24 @@ def test_knob_of_the_small_tiles():
         fp8.fp8_set_knob(fp8.FP8_KNOB_SMALL, 0)
 
 
+def test_knob_of_the_64x64_forms():
+    """FP8_KNOB_SMALL_64 names the form of 64 x 64 tiles, where both operands are contiguous along K."""
+    A, B, C = 1 << 20, 1 << 30, 1 << 34
+    form = lambda ta, tb: fp8.lib().fp8_gemm_form(A, ta, B, tb, C, 500, 3000, 1000, fp8.FP8_OUT_F32, None, 0)
+    for bad in (-1, 4):
+        with pytest.raises(fp8.Fp8Error):
+            fp8.fp8_set_knob(fp8.FP8_KNOB_SMALL_64, bad)
+    try:
+        fp8.fp8_set_knob(fp8.FP8_KNOB_SMALL, 4)
+        for value, want in ((1, fp8.FP8_FORM_SMALL_64x64), (2, fp8.FP8_FORM_SMALL_64x64_LINES8), (3, fp8.FP8_FORM_SMALL_64x64_LINES4)):
+            fp8.fp8_set_knob(fp8.FP8_KNOB_SMALL_64, value)
+            assert form(0, 1) == want
+            assert form(0, 0) == form(1, 1) == form(1, 0) == fp8.FP8_FORM_SMALL_64x64
+    finally:
+        fp8.fp8_set_knob(fp8.FP8_KNOB_SMALL_64, 0)
+        fp8.fp8_set_knob(fp8.FP8_KNOB_SMALL, 0)
+
+
 def test_tensor_calls_are_ordinary_functions_to_tools():
     """`import *` brings the entry points that take tensors, inspect gives their argument names and defaults, and
     they can be pickled."""

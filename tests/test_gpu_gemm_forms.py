@@ -42,11 +42,15 @@ def test_small_forms_at_their_edges(M, N, K, off, transA, transB, form):
         ragged.test_small_tiles_at_their_edges(M, N, K, off, transA, transB)
 
 
-# 64 x 64 tiles of operands that are both contiguous along K have three forms: eight waves (few tiles and long K: the list
-# above has them), four waves with chunks of 128 (several tiles per compute unit and long K), four with chunks of 64 (short K)
-@pytest.mark.parametrize("M,N,K,off", [(1030, 1100, 2601, 1), (1088, 1024, 2560, 0), (1500, 1505, 200, 0), (1500, 1505, 67, 2), (61, 190, 1281, 0), (64, 128, 2048, 0)])
-def test_64x64_forms_of_k_contiguous_operands(M, N, K, off):
-    with pinned(SMALL_FORMS["64x64"]):
+# 64 x 64 tiles of operands that are both contiguous along K have three forms: chunks of 64 and of 128 in four waves, of 128 in eight
+FORMS_64 = {1: fp8.FP8_FORM_SMALL_64x64, 2: fp8.FP8_FORM_SMALL_64x64_LINES8, 3: fp8.FP8_FORM_SMALL_64x64_LINES4}
+
+
+@pytest.mark.parametrize("which", sorted(FORMS_64))
+@pytest.mark.parametrize("M,N,K,off", EDGES + [(1030, 1100, 2601, 1), (1088, 1024, 2560, 0), (1500, 1505, 200, 0), (1500, 1505, 67, 2), (61, 190, 1281, 0), (64, 128, 2048, 0)])
+def test_64x64_forms_of_k_contiguous_operands(M, N, K, off, which):
+    with pinned({**SMALL_FORMS["64x64"], fp8.FP8_KNOB_SMALL_64: which}):
+        assert fp8.lib().fp8_gemm_form(1 << 20, 0, 1 << 24, 1, 1 << 28, M, N, K, fp8.FP8_OUT_F32, None, 0) == FORMS_64[which]
         ragged.test_small_tiles_at_their_edges(M, N, K, off, 0, 1)
 
 
