@@ -144,6 +144,35 @@ def test_the_library_choice_on_both_sides_of_its_rule(M, N, K, cut, flags):
         assert torch.equal(plain, C)
 
 
+@pytest.mark.parametrize("M,N,K", [(2304, 2560, 12288), (3072, 2560, 4096)])
+def test_a_size_that_only_the_default_mode_cuts(M, N, K):
+    """Two slices by default, one tiled product with the FP8 instructions: the query's size serves both, the default mode needs
+    all of it, the other none, and both meet their bounds."""
+    rng = np.random.default_rng(K)
+    dY, X = random_codes(rng, (K, M), E5M2, 0x4F), random_codes(rng, (K, N), E4M3, 0x6F)
+    ddY, dX = to_dev(dY), to_dev(X)
+    need = fp8.fp8_gemm_splitk_workspace_size(M, N, K, 1, 0, 0)
+    assert need == 2 * M * N * 4
+    rows = np.array([0, 255, 256, M - 1])
+    S, T = oracle.gemm_rows(np.ascontiguousarray(dY.T), E5M2, X, E4M3, rows)
+    c_ref, alpha = oracle.unscale(S, 3.0, 0.5)
+    got = {}
+    for flags, bytes_ in ((0, need), (fp8.FP8_GEMM_MFMA8, 0), (fp8.FP8_GEMM_MFMA8, need)):
+        C = torch.full((M, N), 9.0, device="cuda")
+        ws = torch.full((bytes_,), 0xFF, dtype=torch.uint8, device="cuda") if bytes_ else None
+        fp8.fp8_gemm_splitk(ddY, E5M2, 1, dX, E4M3, 0, C, 3.0, 0.5, ws, flags)
+        torch.cuda.synchronize()
+        bound = REL[flags] * alpha * T + 0.5 * oracle.ulp(c_ref, oracle.F32)
+        assert np.all(np.abs(out_to_f64(C[torch.from_numpy(rows).cuda()]) - c_ref) <= bound)
+        assert flags not in got or torch.equal(got[flags], C)
+        got[flags] = C
+    plain = torch.empty_like(got[0])
+    fp8.fp8_gemm_ex(ddY, E5M2, 1, dX, E4M3, 0, plain, 3.0, 0.5, fp8.FP8_GEMM_MFMA8)
+    assert torch.equal(plain, got[fp8.FP8_GEMM_MFMA8])
+    with pytest.raises(fp8.Fp8Error):
+        fp8.fp8_gemm_splitk(ddY, E5M2, 1, dX, E4M3, 0, plain, 3.0, 0.5, torch.empty(need - 4, dtype=torch.uint8, device="cuda"), 0)
+
+
 def test_weight_gradient_regime_full_size():
     """dW[1024 x 1024] = dY^T X over K = 65536 tokens (E5M2^T x E4M3 -> fp32): 16 tiles, which the
     slices spread over the chip.  Whole rows element by element, every output through block sums,
