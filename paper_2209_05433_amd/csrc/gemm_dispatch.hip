@@ -149,18 +149,38 @@ double any_128_us(const GemmArgs& g)
 }
 
 // Microseconds of a form of the small-tile kernel (gemm_small.hip): its ends, then the longer of one workgroup's walk along
-// K and what the workgroups of a compute unit take together; `further`, and `ragged` where K ends inside a chunk, for each
-// that waits for another; per K `lines` where both operands are contiguous along it, `other` elsewhere.
-struct SmallTimes { int rows, cols, chunk; double ends, each, further, ragged, lines, other, alone, alone_k; };
+// K (alone + alone_k K) and what the workgroups of a compute unit take together (each + per_k K, and, for each that waits for
+// another, `further`, `ragged` where K ends inside a chunk).  fullest: how far the compute units that have one workgroup more than the
+// average decide, up to four a unit.
+struct SmallTimes { double ends, each, per_k, alone, alone_k, further, ragged, fullest; };
+constexpr int kSmallTile[5][3] = {{32, 32, 128}, {32, 64, 128}, {64, 64, 64}, {64, 64, 128}, {64, 64, 128}};     // rows, columns, chunk of K
+constexpr SmallTimes kSmallTimes[3] = {{3.4, 0.3, 0.0025, 0.0, 0.001, 0.7, 0.8, 0.0}, {4.0, 0.6, 0.0018, 0.6, 0.0018, 0.0, 0.3, 0.0},
+                                       {4.0, 1.2, 0.0026, 1.2, 0.0026, 0.0, 0.3, 0.0}};
+constexpr double kPerK32Lines = 0.0014;      // per_k of the first, both operands contiguous along K
+// Both operands contiguous along K, all forms but the first, in the two modes.
+constexpr SmallTimes kSmallTimesLines[2][5] = {
+    {{}, {1.62, 1.53, 0.00137, 3.1, 0.00146, 0.0, 0.88, 0.89}, {2.91, 1.5, 0.00231, 2.17, 0.00282, 0.0, 0.11, 0.75},
+     {1.96, 4.58, 0.00216, 3.46, 0.00191, 0.0, 0.0, 0.73}, {1.93, 2.45, 0.00218, 4.14, 0.00258, 0.0, 0.5, 0.72}},
+    {{}, {1.76, 1.37, 0.00104, 2.7, 0.00125, 0.0, 1.15, 0.93}, {3.66, 1.19, 0.00194, 1.2, 0.00193, 0.0, 0.62, 0.62},
+     {2.25, 3.95, 0.00164, 2.83, 0.00161, 0.0, 3.0, 0.75}, {1.0, 2.69, 0.00157, 4.13, 0.00249, 0.0, 2.07, 0.83}}};
+static_assert(SMALL_32x32 == 0 && SMALL_32x64 == 1 && SMALL_64x64 == 2 && SMALL_64x64_LINES8 == 3 && SMALL_64x64_LINES4 == 4, "the order of the tables");
 
-// The form of the small-tile kernel that beats the kernel the problem would otherwise take by 5 %, or SMALL_NONE.  Checked on
-// 650 problems (1 .. 4096 x 16 .. 12288 x 1 .. 12288, all storage orders): the choice takes 0.5 % (the tiled kernel's
-// problems) and 0.8 % (the others) longer than the best of all forms over them.  Operands whose rows start anywhere, both of
-// them, cost a fifth more, and beyond 16 workgroups of 64 x 64 a compute unit, when they no longer come out of the caches,
-// again a third (4096 x 5025 x 2048: 200 us, the any-shape kernel 176).  Rows of fewer than 16 bytes are fetched byte by byte
+// The form of the small-tile kernel that beats the kernel the problem would otherwise take by 5 %, or SMALL_NONE.  On 900
+// random problems of the storage orders but one it takes 1.5 % (the tiled kernel's problems) and 2.5 % (the others) longer than the best of
+// all forms.  Operands whose rows start anywhere, both of them, cost a fifth more, and beyond 16 workgroups of 64 x 64 a compute unit, when
+// they no longer come out of the caches, again a third
+// (4096 x 5025 x 2048: 200 us, the any-shape kernel 176).  Rows of fewer than 16 bytes are fetched byte by byte
 // (22 x 275 x 12: 13 us, the any-shape kernel 7.6).  The tiled kernel: rounds of 256 workgroups; where a single round leaves
 // half of the compute units idle, a tile has more of the caches to itself (512 x 4400 x 12096 in the FP8 mode: 65 us, 94 on
-// 64 x 64 tiles, and 93 by tile_times()).  us_chosen: the time of what was chosen.
+// 64 x 64 tiles, and 93 by tile_times()).
+// Where both operands are contiguous along K that answer stands if it is 32 x 32 (eight waves, the shortest chains of sums); the other
+// forms, five in all, are told apart by a table of their own, fitted to every form's time on 2500 random problems (1 .. 4096 x 64 .. 12288
+// x 48 .. 12288, ragged ones among them, all output kinds; rows at any place cost a half more, 1.35 beyond 16 workgroups) and on 256 of 32
+// to 512 tokens through layers 2048 to 12288 wide: 1.4 % (2.6 % off the tiled kernel) and 0.8 % longer than the best of all, where the
+// general table with its three forms takes 2.0 (3.0) and 5.5 %.
+// What went to small tiles stays with them (the tiled kernel's one chain of sums is further from the 64-bit result), what did not
+// goes over for 8 % (`other` is up to a third too long where 192-wide or mixed tiles are taken).
+// us_chosen: the time of what was chosen.
 // pinned: one of the three tile sizes, whatever it takes; the forms with 64 x 64 tiles are chosen from all the same, or named by
 // FP8_KNOB_SMALL_64.
 int choose_small(const GemmArgs& g, bool tiled, double& us_chosen, int pinned)
@@ -182,38 +202,33 @@ int choose_small(const GemmArgs& g, bool tiled, double& us_chosen, int pinned)
     }
     us_chosen = other;
     if (u64 > 32 && pinned == SMALL_NONE) return SMALL_NONE;
-    static const SmallTimes times[5] = {{32, 32, 128, 3.4, 0.3, 0.7, 0.8, 0.0014, 0.0025, 0.0, 0.001},
-                                        {32, 64, 128, 4.0, 0.6, 0.0, 0.3, 0.0018, 0.0018, 0.6, 0.0018},
-                                        {64, 64, 64, 4.0, 1.2, 0.0, 0.3, 0.0026, 0.0026, 1.2, 0.0026},
-                                        {64, 64, 128, 4.0, 3.0, 0.0, 0.3, 0.0022, 0.0, 3.0, 0.0022},
-                                        {64, 64, 128, 4.0, 2.0, 0.0, 0.3, 0.00227, 0.0, 1.5, 0.0027}};
-    static_assert(SMALL_32x32 == 0 && SMALL_32x64 == 1 && SMALL_64x64 == 2 && SMALL_64x64_LINES8 == 3 && SMALL_64x64_LINES4 == 4, "the order of the table");
-    // ... the last three with the FP8 instructions, where both operands are contiguous along K: each, lines, alone, alone_k
-    static const double fp8_lines[3][4] = {{1.2, 0.0026, 1.2, 0.0029}, {1.4, 0.0020, 1.4, 0.0020}, {2.0, 0.00164, 1.5, 0.0023}};
     // (what the tiled kernel does not take is computed in the fp16 mode, whatever the flag says)
     const bool lines = !g.transA && g.transB, fp8 = tiled && g.acc == ACC_FP8;
     const bool off_a = !aligned16(g.A) || (g.transA ? g.M : g.K) % 16 != 0, off_b = !aligned16(g.B) || (g.transB ? g.K : g.N) % 16 != 0;
     const double off = off_a && off_b ? (u64 > 16 ? 1.56 : 1.2) : 1.0;
     const double bytewise = g.K < 16 ? 0.35 * K * ((g.transA ? 0 : 1) + (g.transB ? 1 : 0)) : 0.0;
-    const int form64 = lines ? knob(FP8_KNOB_SMALL_64) : 0;
+    auto us_of = [&](int f, const SmallTimes& t, double per_k, double places) {
+        const double n = units(kSmallTile[f][0], kSmallTile[f][1]), full = n <= 4.0 ? n + t.fullest * (std::ceil(n) - n) : n;
+        const double waits = std::max(0.0, n - 1.0) * (t.further + (g.K % kSmallTile[f][2] ? t.ragged : 0.0));
+        return t.ends + places * std::max(t.alone + bytewise + t.alone_k * K, full * (t.each + bytewise + per_k * K) + waits);
+    };
     int form = SMALL_NONE;
     double best = pinned == SMALL_NONE ? 0.95 * other : 1e300;
-    for (int f = 0; f < 5; ++f) {
-        const bool only_lines = f == SMALL_64x64_LINES8 || f == SMALL_64x64_LINES4;
-        if ((only_lines && !lines) || (pinned != SMALL_NONE && (only_lines ? (int)SMALL_64x64 : f) != pinned)) continue;
+    for (int f = SMALL_32x32; f <= SMALL_64x64; ++f) {
+        if (pinned != SMALL_NONE && f != pinned) continue;
+        const double us = us_of(f, kSmallTimes[f], lines && f == SMALL_32x32 ? kPerK32Lines : kSmallTimes[f].per_k, off);
+        if (us < best) { best = us_chosen = us; form = f; }
+    }
+    if (!lines || form == SMALL_32x32) return form;
+    const double off_lines = off_a && off_b ? (u64 > 16 ? 1.35 : 1.5) : 1.0;
+    const int form64 = knob(FP8_KNOB_SMALL_64);
+    best = form == SMALL_NONE && pinned == SMALL_NONE ? 0.92 * other : 1e300;
+    form = SMALL_NONE;
+    for (int f = SMALL_32x64; f <= SMALL_64x64_LINES4; ++f) {
+        if (pinned != SMALL_NONE && std::min(f, (int)SMALL_64x64) != pinned) continue;
         if (form64 && f >= SMALL_64x64 && f != SMALL_64x64 + form64 - 1) continue;
-        SmallTimes t = times[f];
-        double n = units(t.rows, t.cols);
-        // 64 x 64 tiles of operands that are both contiguous along K: a lone workgroup of the first form streams at half the
-        // rate of three, and up to two a compute unit the fullest one tells
-        if (lines && t.rows == 64) {
-            const double* p = fp8_lines[f - SMALL_64x64];
-            if (fp8) { t.each = p[0]; t.lines = p[1]; t.alone = p[2]; t.alone_k = p[3]; }
-            else if (f == SMALL_64x64) t.alone_k = 0.0042;
-            if (n <= 2.0 || f == SMALL_64x64_LINES8) n = std::max(n, std::ceil(n));
-        }
-        const double waits = std::max(0.0, n - 1.0) * (t.further + (g.K % t.chunk ? t.ragged : 0.0));
-        const double us = t.ends + off * std::max(t.alone + bytewise + t.alone_k * K, n * (t.each + bytewise + (lines ? t.lines : t.other) * K) + waits);
+        const SmallTimes& t = kSmallTimesLines[fp8 ? 1 : 0][f];
+        const double us = us_of(f, t, t.per_k, off_lines);
         if (us < best) { best = us_chosen = us; form = f; }
     }
     return form;

@@ -150,6 +150,28 @@ def test_the_flag_does_not_change_the_form_off_the_tiled_kernel():
         assert form(A + off, ta, tb, M, N, K, fp8.FP8_GEMM_MFMA8) == form(A + off, ta, tb, M, N, K, 0), (M, N, K, ta, tb, off)
 
 
+# Both operands contiguous along K, bf16 out: (M, N, K, FP8 instructions), the form and the microseconds that it and another one took
+MEASURED_FORMS = [
+    ((111, 8928, 576, 0), "SMALL_64x64", 7.6),              # 32 x 64: 10.4
+    ((179, 6400, 1216, 0), "SMALL_64x64", 10.2),            # 32 x 64: 13.2
+    ((1072, 1600, 1024, 1), "SMALL_64x64_LINES4", 9.4),     # eight waves: 12.3
+    ((1869, 704, 1088, 1), "SMALL_64x64", 10.4),            # 32 x 64: 12.8
+    ((271, 7424, 3584, 0), "SMALL_32x64", 28.6),            # 64 x 64, four waves, chunks of 128: 31.2
+    ((64, 12288, 12288, 0), "SMALL_64x64_LINES8", 43.0),    # chunks of 64: 63
+    ((128, 12288, 12288, 0), "SMALL_64x64_LINES4", 61.0),   # chunks of 64: 77.6
+    ((512, 3072, 12288, 1), "SMALL_64x64_LINES4", 39.9),    # chunks of 64: 48.7
+    ((512, 6144, 2048, 0), "SMALL_64x64", 21.7),            # eight waves: 22.7
+    ((16, 6144, 2048, 0), "SMALL_32x32", 5.7),
+]
+
+
+@pytest.mark.parametrize("problem,form,us", MEASURED_FORMS)
+def test_small_forms_are_ranked_as_measured(problem, form, us):
+    M, N, K, flags = problem
+    got = fp8.lib().fp8_gemm_form(1 << 20, 0, 1 << 34, 1, 1 << 40, M, N, K, fp8.FP8_OUT_BF16, None, flags)
+    assert got == getattr(fp8, "FP8_FORM_" + form)
+
+
 def test_knobs_round_trip_and_reject_bad_values():
     assert fp8.fp8_get_knob(fp8.FP8_KNOB_TILE_N) == 0
     assert fp8.fp8_set_knob(fp8.FP8_KNOB_TILE_N, 128) == 0
