@@ -33,6 +33,7 @@ int check_launch(const char* what)
 // ---- tuning knobs -------------------------------------------------------------------------------
 static std::atomic<int> g_knob[FP8_KNOB_COUNT];
 static std::once_flag g_knob_once;
+static std::atomic<bool> g_knobs_seeded{false};
 
 static void seed_knobs()
 {
@@ -54,7 +55,11 @@ static void seed_knobs()
 
 int knob(int which)
 {
-    std::call_once(g_knob_once, seed_knobs);
+    // (call_once takes 10 ns each time, and a product asks for ten knobs)
+    if (!g_knobs_seeded.load(std::memory_order_acquire)) {
+        std::call_once(g_knob_once, seed_knobs);
+        g_knobs_seeded.store(true, std::memory_order_release);
+    }
     return g_knob[which].load(std::memory_order_relaxed);
 }
 

@@ -119,7 +119,7 @@ enum { GEMM_GENERIC = 1, GEMM_TILED_256 = 2, GEMM_TILED_128 = 3, GEMM_MFMA_ANY =
 // us: of a problem that the tiled kernel takes, what the model of run times gives for the small-tile form, or for the better of the
 // single tile widths.
 struct GemmPlan { int kernel; bool elementwise_stores; bool persistent; int wide_cols; int small; bool middle; int middle_cols; double us; };
-GemmPlan plan_gemm(const GemmArgs& g);
+GemmPlan plan_gemm(const GemmArgs& g, bool whole = true);
 // The form (fp8_form_t) of the kernel that launch_gemm takes for it.
 int gemm_form(const GemmArgs& g);
 

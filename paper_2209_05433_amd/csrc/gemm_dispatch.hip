@@ -152,8 +152,8 @@ double any_128_us(const GemmArgs& g)
 // K (alone + alone_k K) and what the workgroups of a compute unit take together (each + per_k K, and, for each that waits for
 // another, `further`, `ragged` where K ends inside a chunk).  fullest: how far the compute units that have one workgroup more than the
 // average decide, up to four a unit.
+// (32 x 32, 32 x 64 and 64 x 64 rows and columns; chunks of 128, of 64 the first 64 x 64 form.)
 struct SmallTimes { double ends, each, per_k, alone, alone_k, further, ragged, fullest; };
-constexpr int kSmallTile[5][3] = {{32, 32, 128}, {32, 64, 128}, {64, 64, 64}, {64, 64, 128}, {64, 64, 128}};     // rows, columns, chunk of K
 constexpr SmallTimes kSmallTimes[3] = {{3.4, 0.3, 0.0025, 0.0, 0.001, 0.7, 0.8, 0.0}, {4.0, 0.6, 0.0018, 0.6, 0.0018, 0.0, 0.3, 0.0},
                                        {4.0, 1.2, 0.0026, 1.2, 0.0026, 0.0, 0.3, 0.0}};
 constexpr double kPerK32Lines = 0.0014;      // per_k of the first, both operands contiguous along K
@@ -186,7 +186,7 @@ static_assert(SMALL_32x32 == 0 && SMALL_32x64 == 1 && SMALL_64x64 == 2 && SMALL_
 int choose_small(const GemmArgs& g, bool tiled, double& us_chosen, int pinned)
 {
     const double M = (double)g.M, N = (double)g.N, K = (double)g.K;
-    auto units = [&](double tm, double tn) { return std::ceil(M / tm) * std::ceil(N / tn) / 256.0; };
+    auto units = [&](int64_t tm, int64_t tn) { return (double)((g.M + tm - 1) / tm) * (double)((g.N + tn - 1) / tn) / 256.0; };
     const double u64 = units(64, 64);
     double other;
     if (tiled) {
@@ -208,8 +208,8 @@ int choose_small(const GemmArgs& g, bool tiled, double& us_chosen, int pinned)
     const double off = off_a && off_b ? (u64 > 16 ? 1.56 : 1.2) : 1.0;
     const double bytewise = g.K < 16 ? 0.35 * K * ((g.transA ? 0 : 1) + (g.transB ? 1 : 0)) : 0.0;
     auto us_of = [&](int f, const SmallTimes& t, double per_k, double places) {
-        const double n = units(kSmallTile[f][0], kSmallTile[f][1]), full = n <= 4.0 ? n + t.fullest * (std::ceil(n) - n) : n;
-        const double waits = std::max(0.0, n - 1.0) * (t.further + (g.K % kSmallTile[f][2] ? t.ragged : 0.0));
+        const double n = f == SMALL_32x32 ? units(32, 32) : f == SMALL_32x64 ? units(32, 64) : u64, full = t.fullest > 0.0 && n <= 4.0 ? n + t.fullest * (std::ceil(n) - n) : n;
+        const double waits = std::max(0.0, n - 1.0) * (t.further + ((f == SMALL_64x64 ? g.K % 64 : g.K % 128) ? t.ragged : 0.0));
         return t.ends + places * std::max(t.alone + bytewise + t.alone_k * K, full * (t.each + bytewise + per_k * K) + waits);
     };
     int form = SMALL_NONE;
@@ -236,8 +236,9 @@ int choose_small(const GemmArgs& g, bool tiled, double& us_chosen, int pinned)
 
 }  // namespace
 
-// Which kernel a (non-empty, K > 0) problem takes.
-GemmPlan plan_gemm(const GemmArgs& g)
+// Which kernel a (non-empty, K > 0) problem takes.  whole: also what it would take without the small tiles (a launch does without: a
+// quarter of the host time of the choice).
+GemmPlan plan_gemm(const GemmArgs& g, bool whole)
 {
     const int64_t M = g.M, N = g.N, K = g.K;
     GemmPlan plan{!force_generic() && mfma_any_takes(g) ? GEMM_MFMA_ANY : GEMM_GENERIC, false, false, 0, SMALL_NONE, false, 0, 1e300};
@@ -262,6 +263,10 @@ GemmPlan plan_gemm(const GemmArgs& g)
     if (small_allowed) plan.small = choose_small(g, fast, plan.us, SMALL_NONE);
     else if (small >= 2 && tile_count(g, 32) <= 0x7fffffffll) plan.small = choose_small(g, fast, plan.us, SMALL_32x32 + small - 2);
     if (!fast) return plan;
+    if (!whole && plan.small != SMALL_NONE) {
+        plan.kernel = GEMM_TILED_256;
+        return plan;
+    }
     // Tile width.  One workgroup per compute unit (256 of them) runs at a time: the width whose rounds
     // of workgroups take less time (4096 x 6144: 384 wide tiles = two rounds, the second half empty, 768
     // narrow ones = three).  The knob FP8_KNOB_TILE_N = 128 | 256 overrides the choice.
@@ -393,7 +398,7 @@ int launch_tiled(const GemmArgs& g)
 int gemm_form(const GemmArgs& g)
 {
     static_assert(FP8_FORM_SMALL_64x64_LINES4 - FP8_FORM_SMALL_32x32 == SMALL_64x64_LINES4, "the order of the forms");
-    const GemmPlan plan = plan_gemm(g);
+    const GemmPlan plan = plan_gemm(g, false);
     if (plan.small != SMALL_NONE) return FP8_FORM_SMALL_32x32 + plan.small;
     if (plan.kernel == GEMM_GENERIC) return FP8_FORM_FMA;
     if (plan.kernel == GEMM_MFMA_ANY) return mfma_any_wide(g) ? FP8_FORM_ANY_256 : FP8_FORM_ANY_128;
@@ -416,7 +421,7 @@ int launch_gemm(const GemmArgs& g)
         hipLaunchKernelGGL(zero_fill_kernel, dim3(1024), dim3(256), 0, g.stream, (unsigned char*)g.C, nbytes);
         return check_launch("gemm (K = 0 fill)");
     }
-    const GemmPlan plan = plan_gemm(g);
+    const GemmPlan plan = plan_gemm(g, false);
     if (plan.small != SMALL_NONE) {
         typedef int (*small_fn)(const GemmArgs&, int);
         static const small_fn table[4] = {FP8MM_SMALL_NAME(0), FP8MM_SMALL_NAME(1), FP8MM_SMALL_NAME(2), FP8MM_SMALL_NAME(3)};
