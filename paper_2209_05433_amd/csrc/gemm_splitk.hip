@@ -7,6 +7,7 @@
 // unscaling is applied once per dot product) and converts to the output type.
 #include "gemm_common.hpp"
 
+#include <cmath>
 #include <mutex>
 
 namespace fp8mm {
@@ -73,17 +74,18 @@ inline bool aligned_to(const void* p, uintptr_t a) { return ((uintptr_t)p & (a -
 // The library's own choice is one slice where the plain product takes less time: the small tiles walk a short K
 // before the slices' two launches have begun, and sums that are many next to K cost more to write and read than idle
 // compute units do.  Slices: a round of tiles, 3.5 us for the second launch, 0.32 us for each slice (its loads follow one another)
-// and 0.2 us per MB of sums.  Plain: the model of plan_gemm, no faster than 1.9 ns along K (256 x 256: 1.1 ns out of one
-// XCD's L2, 2.1 beyond it), and a tenth more for the small tiles, whose slope grows beyond K = 8192.  In the fp16 mode only the
+// and 0.2 us per MB of sums.  Plain: the model of plan_gemm, which these problems exceed the more the longer K is (up to 16384) and, small
+// tiles, the further the fullest compute units are above the average: `slower`; no faster than 1.9 ns along K (256 x 256:
+// 1.1 ns out of one XCD's L2, 2.1 beyond it).  Fitted to both forms' times on 1600 random problems (256 .. 6144 both ways, K = 1024 ..
+// 65536, all storage orders, both modes): 0.6 % longer than the better of the two where the fp16 mode may choose, 0.6 % in the FP8
+// mode (always cut 37 and 27 %); 7 of them take over 3 % longer than cut, at most 17 %.
+// In the fp16 mode only the
 // small tiles may take a problem over: their waves cut K as slices do, while the tiled kernel's one chain of sums is further from
 // the 64-bit result than the slices' (2304 x 2560 x 12288: 1.5e-7 against 1.1e-7; the small tiles' error is 0.985 to 1.012 of the
 // slices', eight products of 256 x 256 x 1024 to 512 x 512 x 4096 with twelve inputs each).  The FP8 instructions' own error hides
 // that: 1.6e-5 either way, the two within 1e-5 of each other (30 products up to 2304 x 2560 x 12288, gradients and activations).
-// Measured on 11 outputs from 256 x 256 to 3072 x 2560, nine K from 1024 to 32768, both accumulation modes, cut as before / in
-// one slice: 256 x 256 x 1024 23 / 5 us, 512 x 512 x 4096 28 / 12, 1024 x 1024 x 4096 36 / 18 (FP8 mode 30 / 16),
-// 3072 x 2560 x 4096 in the FP8 mode 50 / 34; kept: 1024 x 1024 x 16384 50 / 56, 256 x 256 x 32768 42 / 63,
-// 1536 x 1536 x 8192 56 / 71.  Where it errs by more than a tenth it cuts as before: outputs of
-// about 120 tiles at K = 8192 .. 16384 in the FP8 mode (2752 x 2752 x 8192 70 / 56).
+// Cut / in one slice: 256 x 256 x 1024 23 / 5 us, 1024 x 1024 x 4096 36 / 18 (FP8 mode 30 / 16), 1024 x 1024 x 8192 41 / 36 (33 / 27),
+// 1024 x 1024 x 12288 44 / 45 (34 / 38), 816 x 704 x 17408 42 / 90, 768 x 768 x 8192 34 / 39 (28 / 34), 3072 x 768 x 8192 54 / 86.
 SplitPlan plan_splitk(const GemmArgs& g, int requested)
 {
     SplitPlan sp{1, 0, 256};
@@ -105,8 +107,15 @@ SplitPlan plan_splitk(const GemmArgs& g, int requested)
     if (requested <= 0 && sp.splits > 1 && (plain.small != SMALL_NONE || g.acc == ACC_FP8)) {
         const double sums_mb = 4e-6 * sp.splits * (double)g.M * (double)g.N;
         const double cut = tile_times(g.acc, 2.0 * (double)per).wide + 3.5 + 0.32 * sp.splits + 0.2 * sums_mb;
-        const double one = (plain.small != SMALL_NONE ? 1.1 : 1.03) * (plain.us > 4.0 + 0.0019 * (double)g.K ? plain.us : 4.0 + 0.0019 * (double)g.K);
-        if (one < cut) { sp.splits = 1; sp.pairs_per_split = (int)pairs; }
+        const double long_k = g.K < 16384 ? (double)g.K / 16384.0 : 1.0;
+        double slower = 1.2 + 0.2 * long_k;
+        if (plain.small != SMALL_NONE) {
+            const int64_t rows = plain.small >= SMALL_64x64 ? 64 : 32, cols = plain.small == SMALL_32x32 ? 32 : 64;
+            const double units = (double)((g.M + rows - 1) / rows) * (double)((g.N + cols - 1) / cols) / 256.0;
+            const double fullest = units > 1.0 && units <= 4.0 ? std::ceil(units) / units - 1.0 : 0.0;
+            slower = (g.acc == ACC_FP8 ? 0.9 + 0.6 * long_k : 1.05 + 0.4 * long_k) + 0.8 * fullest;
+        }
+        if (plain.us * slower < cut && 4.0 + 0.0019 * (double)g.K < cut) { sp.splits = 1; sp.pairs_per_split = (int)pairs; }
     }
     return sp;
 }
