@@ -16,19 +16,20 @@ namespace fp8mm {
 namespace {
 
 // nvec whole vectors, at any address, then n - nvec*per_vec tail elements.  Every workgroup takes
-// chunks of 32 KB (8 vectors per lane, all loaded before the first compare), four workgroups per
-// compute unit; one atomic per workgroup at the end (with one chunk per workgroup the thousands of
-// atomics on one cell cost a quarter of the run time).  The one-launch form cuts tensors of less than 1 MB into
+// chunks of 32 KB (8 vectors per lane, all loaded before the first compare).  In the one-launch form there are up to four workgroups per
+// compute unit; with an atomic on one cell, one: they end together, and the more there are the longer they queue (24 MB of bf16 256 /
+// 512 / 1024 workgroups 8.1 / 9.3 / 12.4 us, 32 MB 9.1 / 11.0 / 22.0, 128 MB 22.1 / 22.4 / 30.4, 600 MB 86.7 / 89.0 / 88.2).
+// The one-launch form cuts tensors of less than 1 MB into
 // chunks of 8 KB: their time is the latency of a few loads (64 KB of bf16 4.1 -> 3.8 us; 4 MB of fp32 5.1 -> 5.5 and
 // 10 MB of bf16 5.8 -> 6.6, all in chunks of 8 KB); up to 64 KB one workgroup reads the tensor alone, 16 vectors per lane in
 // flight: no tickets are drawn, each of which is a round trip to memory.  The line lies where amax and the cast that follows
 // it, together, gain on a tensor that another kernel has just written: one workgroup fetches what lies in eight L2s, and the cast's
 // workgroups again what lies in its own (amax + cast in chunks of 8 KB / by one workgroup: 16 KB of bf16 5.1 / 4.5 us, 32 KB 5.5 / 4.75,
-// 64 KB 5.7 / 5.5, but 96 KB 5.7 / 6.45, 128 KB 5.8 / 6.6; of fp32 64 KB 6.05 / 5.4, 96 KB 6.2 / 6.7).  With one atomic per
-// workgroup more workgroups only cost: 4 MB of fp32 6.0 -> 9.8 us.
+// 64 KB 5.7 / 5.5, but 96 KB 5.7 / 6.45, 128 KB 5.8 / 6.6; of fp32 64 KB 6.05 / 5.4, 96 KB 6.2 / 6.7).
 constexpr int kAmaxVecs = 8;                                         // per lane and chunk
 constexpr int kAmaxVecsSmall = 2;
 constexpr size_t kAmaxSmallBelow = (size_t)32 * kThreads * kAmaxVecs;    // vectors
+constexpr size_t kAmaxAtomics = 256;                                 // workgroups that share a cell
 constexpr int kAmaxVecsAlone = 16;
 constexpr size_t kAmaxAloneBelow = (size_t)kThreads * kAmaxVecsAlone;      // vectors that one workgroup reads alone: 64 KB
 
@@ -131,7 +132,8 @@ inline unsigned amax_grid(size_t nvec, bool ticket)
 {
     if (ticket && nvec <= kAmaxAloneBelow) return 1;
     const size_t chunk = (size_t)kThreads * (ticket && nvec < kAmaxSmallBelow ? kAmaxVecsSmall : kAmaxVecs), chunks = (nvec + chunk - 1) / chunk;
-    return (unsigned)(chunks < 1 ? 1 : chunks > (size_t)kAmaxBlocks ? (size_t)kAmaxBlocks : chunks);
+    const size_t most = ticket ? kAmaxBlocks : kAmaxAtomics;
+    return (unsigned)(chunks < 1 ? 1 : chunks > most ? most : chunks);
 }
 
 // The work of workgroup `bid` of `grid` on one tensor.
