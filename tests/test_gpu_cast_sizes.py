@@ -13,8 +13,8 @@ DTYPES = {"f32": torch.float32, "bf16": torch.bfloat16}
 
 def edges(vec):
     """Elements: one workgroup with 2 and with 16 vectors of `vec` a lane and beyond; items of 16 elements that one workgroup, an
-    item a lane of small workgroups, large workgroups and 512 of them take."""
-    marks = [vec * 512, vec * 4096, vec * 8192, 16 * 2048, 16 << 14, 16 << 20, 16 << 21]
+    item a lane of small workgroups, large workgroups and 512 of them take; chunks that 256 workgroups take once."""
+    marks = [vec * 512, vec * 4096, vec * 8192, 16 * 256, 16 * 512, 16 * 2048, 16 << 14, 16 << 20, 16 << 21, vec * 2048 * 256]
     return [1, vec - 1, vec * 64 + 1] + [m + d for m in marks for d in (-1, 0, 16, 17)]
 
 
