@@ -342,7 +342,9 @@ GemmPlan plan_gemm(const GemmArgs& g, bool whole)
     // Tiles of 256 x 192, alone or with 128-wide ones behind them: where the same model says that they beat the choice so
     // far by 3 % (4096 x 6144 x 2048: 512 tiles = two full rounds, 84 us against 93 for 768 narrow ones; 3001 x 6144 x 2048:
     // 252 of them and 204 narrow ones, 85 us against 90 for 384 of them and 94 for 252 wide and 72 narrow ones).  Of 70 products in the
-    // range where it decides, 19 took them: 1.00 to 1.16 times as fast, and no other would have gained more than 2 %.
+    // range where it decides, 19 took them, and no other would have gained more than 2 %.  240 random products that take them, all
+    // storage orders and outputs: 1.10 times as fast in the mean (1.05 to 1.13 by order and mode), 0.93 to 1.29; two of them more than 3 %
+    // slower, FP8 mode with fp32 outputs.
     // fp32 outputs that the persistent narrow form takes stay there (4096 x 6144 x 1024: 57 us, here 59).
     // Knob FP8_KNOB_TILE_192: 0 = by the model, 1 = never, 2 = always (with FP8_KNOB_MIXED = 2: for half of the columns, 128-wide ones behind).
     if (middle_knob == 2) {

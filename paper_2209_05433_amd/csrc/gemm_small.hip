@@ -404,8 +404,8 @@ int launch_acc(const GemmArgs& g, int form)
     // has one tile, whose four waves keep 32 KB in flight, a quarter of what the stream of a weight takes (64 x 12288 x 12288
     // 63 -> 43 us, FP8 mode 50 -> 42; 256 x 3072 x 12288 56 -> 32, 41 -> 30; 512 x 2048 x 6144 27 -> 20; 64 x 12288 x 3072
     // 21 -> 15); four where it has several and K is long (128 x 12288 x 12288 84 -> 63, FP8 mode 76 -> 61; 512 x 3072 x 12288
-    // 72 -> 57).  The first form stays for K up to about 2400 (512 x 6144 x 2048: 21.7, here 22.7: three workgroups a compute
-    // unit against two) and for the other orders, whose slabs of 128 x 64 leave room for one workgroup.
+    // 72 -> 57).  The first form stays where K is short (512 x 6144 x 2048: 21.7, here 22.7: three workgroups a compute
+    // unit against two; the dispatcher's table tells them apart) and for the other orders, whose slabs of 128 x 64 leave room for one workgroup.
     if constexpr (A_KC && B_KC) {
         if (form == SMALL_64x64_LINES8) return launch_form<FA, FB, ACC, A_KC, B_KC, 2, 2, 2, 8, 1>(g);
         if (form == SMALL_64x64_LINES4) return launch_form<FA, FB, ACC, A_KC, B_KC, 2, 2, 2, 4, 1>(g);
