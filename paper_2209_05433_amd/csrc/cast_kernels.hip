@@ -408,16 +408,16 @@ void launch_amax_kernels(const void* x, size_t n, int in_dtype, unsigned* out, u
 {
     const unsigned grid = amax_grid(n / (in_dtype == FP8_F32 ? 4 : 8), TICKET);
     if (in_dtype == FP8_F32)
-        hipLaunchKernelGGL((amax_vec_kernel<FP8_F32, TICKET>), dim3(grid), dim3(kThreads), 0, stream, x, n, out, ws, fmt, scale_out);
+        enqueue((amax_vec_kernel<FP8_F32, TICKET>), dim3(grid), dim3(kThreads), 0, stream, x, n, out, ws, fmt, scale_out);
     else
-        hipLaunchKernelGGL((amax_vec_kernel<FP8_BF16, TICKET>), dim3(grid), dim3(kThreads), 0, stream, x, n, out, ws, fmt, scale_out);
+        enqueue((amax_vec_kernel<FP8_BF16, TICKET>), dim3(grid), dim3(kThreads), 0, stream, x, n, out, ws, fmt, scale_out);
 }
 }  // namespace
 
 int launch_amax(const void* x, size_t n, int in_dtype, float* amax_out, hipStream_t stream)
 {
     unsigned* out = (unsigned*)amax_out;
-    hipLaunchKernelGGL(store_u32_kernel, dim3(1), dim3(1), 0, stream, out, 0u);
+    enqueue(store_u32_kernel, dim3(1), dim3(1), 0, stream, out, 0u);
     if (n == 0) return check_launch("amax init");
     launch_amax_kernels<false>(x, n, in_dtype, out, nullptr, 0, nullptr, stream);
     return check_launch("amax");
@@ -427,7 +427,7 @@ int launch_amax_scale(const void* x, size_t n, int in_dtype, int fmt, float* ama
                       hipStream_t stream)
 {
     static_assert((kTicketPartials + kAmaxBlocks) * sizeof(unsigned) <= FP8_AMAX_WORKSPACE_BYTES, "counters + one partial per workgroup");
-    if (n == 0) hipLaunchKernelGGL(amax_empty_kernel, dim3(1), dim3(1), 0, stream, fmt, amax_out, scale_out);
+    if (n == 0) enqueue(amax_empty_kernel, dim3(1), dim3(1), 0, stream, fmt, amax_out, scale_out);
     else launch_amax_kernels<true>(x, n, in_dtype, (unsigned*)amax_out, (unsigned*)workspace, fmt, scale_out, stream);
     return check_launch("amax_scale");
 }
@@ -455,9 +455,9 @@ int launch_amax_scale_multi(int count, const void* const* x, const size_t* n, in
     }
     for (int i = count; i <= kMultiMax; ++i) m.first[i] = total;
     if (in_dtype == FP8_F32)
-        hipLaunchKernelGGL(amax_multi_kernel<FP8_F32>, dim3(total), dim3(kThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace);
+        enqueue(amax_multi_kernel<FP8_F32>, dim3(total), dim3(kThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace);
     else
-        hipLaunchKernelGGL(amax_multi_kernel<FP8_BF16>, dim3(total), dim3(kThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace);
+        enqueue(amax_multi_kernel<FP8_BF16>, dim3(total), dim3(kThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace);
     return check_launch("amax_scale_multi");
 }
 
@@ -465,7 +465,7 @@ float scale_from_amax_host(float amax, int fmt) { return scale_rule(amax, fmt); 
 
 int launch_scale_from_amax(const float* amax, int fmt, float* scale_out, hipStream_t stream)
 {
-    hipLaunchKernelGGL(scale_kernel, dim3(1), dim3(1), 0, stream, amax, fmt, scale_out);
+    enqueue(scale_kernel, dim3(1), dim3(1), 0, stream, amax, fmt, scale_out);
     return check_launch("scale_from_amax");
 }
 
@@ -489,9 +489,9 @@ void launch_quantize_typed(const void* x, size_t n, float scale, const float* sc
     const bool nts = n >= kStreamingStoreBytes;
 #define FP8MM_LAUNCH_QV(PATH)                                                                                      \
     do {                                                                                                           \
-        if (nts) hipLaunchKernelGGL((quantize_vec_kernel<DT, FMT, PATH, true>), dim3(grid), dim3(kThreads), 0,     \
+        if (nts) enqueue((quantize_vec_kernel<DT, FMT, PATH, true>), dim3(grid), dim3(kThreads), 0,     \
                                     stream, x, n, scale, scale_dev, q);                                            \
-        else hipLaunchKernelGGL((quantize_vec_kernel<DT, FMT, PATH, false>), dim3(grid), dim3(kThreads), 0,        \
+        else enqueue((quantize_vec_kernel<DT, FMT, PATH, false>), dim3(grid), dim3(kThreads), 0,        \
                                 stream, x, n, scale, scale_dev, q);                                                \
     } while (0)
     if (!saturate) FP8MM_LAUNCH_QV(kCastBitsStrict);
@@ -590,11 +590,11 @@ int launch_dequantize(const uint8_t* q, size_t n, int fmt, float scale, const fl
     if (n == 0) return FP8_OK;
     const int grid = grid_for(n / 16 + 1, 256 * 256);     // many short runs measured best (write-heavy stream)
     if (fmt == FP8_E4M3) {
-        if (out_dtype == FP8_F32) hipLaunchKernelGGL((dequantize_kernel<FP8_E4M3, FP8_F32>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out);
-        else hipLaunchKernelGGL((dequantize_kernel<FP8_E4M3, FP8_BF16>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out);
+        if (out_dtype == FP8_F32) enqueue((dequantize_kernel<FP8_E4M3, FP8_F32>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out);
+        else enqueue((dequantize_kernel<FP8_E4M3, FP8_BF16>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out);
     } else {
-        if (out_dtype == FP8_F32) hipLaunchKernelGGL((dequantize_kernel<FP8_E5M2, FP8_F32>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out);
-        else hipLaunchKernelGGL((dequantize_kernel<FP8_E5M2, FP8_BF16>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out);
+        if (out_dtype == FP8_F32) enqueue((dequantize_kernel<FP8_E5M2, FP8_F32>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out);
+        else enqueue((dequantize_kernel<FP8_E5M2, FP8_BF16>), dim3(grid), dim3(kThreads), 0, stream, q, n, scale, scale_dev, out);
     }
     return check_launch("dequantize");
 }
@@ -620,11 +620,11 @@ int launch_quantize_multi(int count, const void* const* x, const size_t* n, int 
     for (int i = count; i <= kMultiMax; ++i) m.first[i] = total;
     const bool cvt = cast_path() == kCastCvt;
     if (in_dtype == FP8_F32) {
-        if (cvt) hipLaunchKernelGGL((quantize_multi_kernel<FP8_F32, kCastCvt>), dim3(total), dim3(kThreads), 0, stream, m, scale_dev);
-        else hipLaunchKernelGGL((quantize_multi_kernel<FP8_F32, kCastBits>), dim3(total), dim3(kThreads), 0, stream, m, scale_dev);
+        if (cvt) enqueue((quantize_multi_kernel<FP8_F32, kCastCvt>), dim3(total), dim3(kThreads), 0, stream, m, scale_dev);
+        else enqueue((quantize_multi_kernel<FP8_F32, kCastBits>), dim3(total), dim3(kThreads), 0, stream, m, scale_dev);
     } else {
-        if (cvt) hipLaunchKernelGGL((quantize_multi_kernel<FP8_BF16, kCastCvt>), dim3(total), dim3(kThreads), 0, stream, m, scale_dev);
-        else hipLaunchKernelGGL((quantize_multi_kernel<FP8_BF16, kCastBits>), dim3(total), dim3(kThreads), 0, stream, m, scale_dev);
+        if (cvt) enqueue((quantize_multi_kernel<FP8_BF16, kCastCvt>), dim3(total), dim3(kThreads), 0, stream, m, scale_dev);
+        else enqueue((quantize_multi_kernel<FP8_BF16, kCastBits>), dim3(total), dim3(kThreads), 0, stream, m, scale_dev);
     }
     return check_launch("quantize_multi");
 }
@@ -655,9 +655,9 @@ int launch_amax_cast(int count, const void* const* x, const size_t* n, int in_dt
     for (int i = count; i <= kMultiMax; ++i) m.first[i] = total;
     const unsigned patience = knob(FP8_KNOB_PATIENCE) ? 0 : kPatience;
     if (in_dtype == FP8_F32)
-        hipLaunchKernelGGL(amax_cast_kernel<FP8_F32>, dim3(total), dim3(kCastThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace, patience);
+        enqueue(amax_cast_kernel<FP8_F32>, dim3(total), dim3(kCastThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace, patience);
     else
-        hipLaunchKernelGGL(amax_cast_kernel<FP8_BF16>, dim3(total), dim3(kCastThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace, patience);
+        enqueue(amax_cast_kernel<FP8_BF16>, dim3(total), dim3(kCastThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace, patience);
     return check_launch("amax_cast");
 }
 

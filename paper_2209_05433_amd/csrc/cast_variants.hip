@@ -530,11 +530,11 @@ __global__ __launch_bounds__(kThreads) void quantize_sr_kernel(const void* __res
 #define FP8MM_DISPATCH_DT_FMT(KERNEL, grid, ...)                                                           \
     do {                                                                                                   \
         if (in_dtype == FP8_F32) {                                                                         \
-            if (fmt == FP8_E4M3) hipLaunchKernelGGL((KERNEL<FP8_F32, FP8_E4M3>), grid, dim3(kThreads), 0, stream, __VA_ARGS__); \
-            else hipLaunchKernelGGL((KERNEL<FP8_F32, FP8_E5M2>), grid, dim3(kThreads), 0, stream, __VA_ARGS__);                 \
+            if (fmt == FP8_E4M3) enqueue((KERNEL<FP8_F32, FP8_E4M3>), grid, dim3(kThreads), 0, stream, __VA_ARGS__); \
+            else enqueue((KERNEL<FP8_F32, FP8_E5M2>), grid, dim3(kThreads), 0, stream, __VA_ARGS__);                 \
         } else {                                                                                           \
-            if (fmt == FP8_E4M3) hipLaunchKernelGGL((KERNEL<FP8_BF16, FP8_E4M3>), grid, dim3(kThreads), 0, stream, __VA_ARGS__); \
-            else hipLaunchKernelGGL((KERNEL<FP8_BF16, FP8_E5M2>), grid, dim3(kThreads), 0, stream, __VA_ARGS__);                \
+            if (fmt == FP8_E4M3) enqueue((KERNEL<FP8_BF16, FP8_E4M3>), grid, dim3(kThreads), 0, stream, __VA_ARGS__); \
+            else enqueue((KERNEL<FP8_BF16, FP8_E5M2>), grid, dim3(kThreads), 0, stream, __VA_ARGS__);                \
         }                                                                                                  \
     } while (0)
 
@@ -560,10 +560,10 @@ int launch_quantize_amax(const void* x, size_t n, int in_dtype, int fmt, const f
     const size_t per_group = large ? kMaxThreads : (items < (size_t)1 << 14 ? 1 : 4) * (size_t)kThreads;
     const size_t groups = (items + per_group - 1) / per_group, most = nts ? kCastBlocks : large ? 256 : 512;
     const dim3 grid((unsigned)(items <= kAloneItems ? 1 : groups < most ? groups : most));
-    if (grid.x > 1 || n == 0) hipLaunchKernelGGL(store_u32_kernel, dim3(1), dim3(1), 0, stream, bits, 0u);
+    if (grid.x > 1 || n == 0) enqueue(store_u32_kernel, dim3(1), dim3(1), 0, stream, bits, 0u);
     if (n == 0) return check_launch("quantize_amax init");
 #define FP8MM_QA_(DT, FMT, NTS, THREADS) \
-    hipLaunchKernelGGL((quantize_amax_kernel<DT, FMT, NTS, THREADS>), grid, dim3(THREADS), 0, stream, x, n, scale_dev, q_out, bits)
+    enqueue((quantize_amax_kernel<DT, FMT, NTS, THREADS>), grid, dim3(THREADS), 0, stream, x, n, scale_dev, q_out, bits)
 #define FP8MM_QA(DT, FMT)                                             \
     do {                                                              \
         if (nts) FP8MM_QA_(DT, FMT, true, kThreads);                  \
@@ -591,14 +591,14 @@ int launch_quantize_sr(const void* x, size_t n, int in_dtype, int fmt, float sca
 
 int launch_scale_from_history(const float* hist, size_t len, int fmt, float* scale_out, hipStream_t stream)
 {
-    hipLaunchKernelGGL(scale_from_history_kernel, dim3(1), dim3(kThreads), 0, stream, hist, len, fmt, scale_out);
+    enqueue(scale_from_history_kernel, dim3(1), dim3(kThreads), 0, stream, hist, len, fmt, scale_out);
     return check_launch("scale_from_amax_history");
 }
 
 int launch_scale_n(const float* amax, size_t n, int fmt, float* scale_out, hipStream_t stream)
 {
     if (n == 0) return FP8_OK;
-    hipLaunchKernelGGL(scale_n_kernel, dim3(grid_for(n, 1024)), dim3(kThreads), 0, stream, amax, n, fmt, scale_out);
+    enqueue(scale_n_kernel, dim3(grid_for(n, 1024)), dim3(kThreads), 0, stream, amax, n, fmt, scale_out);
     return check_launch("scale_from_amax_n");
 }
 
@@ -626,9 +626,9 @@ int launch_amax_rows(const void* x, int64_t rows, int64_t cols, int in_dtype, fl
     const dim3 grid = rows_grid(rows, group);
 #define FP8MM_AR(DT)                                                                                                                        \
     do {                                                                                                                                    \
-        if (group == 16) hipLaunchKernelGGL((amax_rows_kernel<DT, 16>), grid, dim3(kThreads), 0, stream, x, rows, cols, amax_out);       \
-        else if (group == 64) hipLaunchKernelGGL((amax_rows_kernel<DT, 64>), grid, dim3(kThreads), 0, stream, x, rows, cols, amax_out);  \
-        else hipLaunchKernelGGL((amax_rows_kernel<DT, kThreads>), grid, dim3(kThreads), 0, stream, x, rows, cols, amax_out);             \
+        if (group == 16) enqueue((amax_rows_kernel<DT, 16>), grid, dim3(kThreads), 0, stream, x, rows, cols, amax_out);       \
+        else if (group == 64) enqueue((amax_rows_kernel<DT, 64>), grid, dim3(kThreads), 0, stream, x, rows, cols, amax_out);  \
+        else enqueue((amax_rows_kernel<DT, kThreads>), grid, dim3(kThreads), 0, stream, x, rows, cols, amax_out);             \
     } while (0)
     if (in_dtype == FP8_F32) FP8MM_AR(FP8_F32); else FP8MM_AR(FP8_BF16);
 #undef FP8MM_AR
@@ -643,9 +643,9 @@ int launch_quantize_rows(const void* x, int64_t rows, int64_t cols, int in_dtype
     const dim3 grid = rows_grid(rows, group);
 #define FP8MM_QR(DT, FMT)                                                                                                                                 \
     do {                                                                                                                                                  \
-        if (group == 16) hipLaunchKernelGGL((quantize_rows_kernel<DT, FMT, 16>), grid, dim3(kThreads), 0, stream, x, rows, cols, scale_dev, q_out);       \
-        else if (group == 64) hipLaunchKernelGGL((quantize_rows_kernel<DT, FMT, 64>), grid, dim3(kThreads), 0, stream, x, rows, cols, scale_dev, q_out);  \
-        else hipLaunchKernelGGL((quantize_rows_kernel<DT, FMT, kThreads>), grid, dim3(kThreads), 0, stream, x, rows, cols, scale_dev, q_out);             \
+        if (group == 16) enqueue((quantize_rows_kernel<DT, FMT, 16>), grid, dim3(kThreads), 0, stream, x, rows, cols, scale_dev, q_out);       \
+        else if (group == 64) enqueue((quantize_rows_kernel<DT, FMT, 64>), grid, dim3(kThreads), 0, stream, x, rows, cols, scale_dev, q_out);  \
+        else enqueue((quantize_rows_kernel<DT, FMT, kThreads>), grid, dim3(kThreads), 0, stream, x, rows, cols, scale_dev, q_out);             \
     } while (0)
     if (in_dtype == FP8_F32) { if (fmt == FP8_E4M3) FP8MM_QR(FP8_F32, FP8_E4M3); else FP8MM_QR(FP8_F32, FP8_E5M2); }
     else { if (fmt == FP8_E4M3) FP8MM_QR(FP8_BF16, FP8_E4M3); else FP8MM_QR(FP8_BF16, FP8_E5M2); }
@@ -675,7 +675,7 @@ int launch_quantize_transpose(const void* x, int64_t rows, int64_t cols, int in_
     const bool diagonal = rows >= 4096 && (rows & (rows - 1)) == 0;      // see "Tile order" at the kernel
     const int part = tcols == full && rows <= TT / 2 ? rows <= TT / 4 ? 4 : 2 : 1;
 #define FP8MM_QT_(DT, FMT, TC, PART) \
-    hipLaunchKernelGGL((quantize_transpose_kernel<DT, FMT, TC, PART>), grid, dim3(kThreads), 0, stream, x, rows, cols, scale_dev, q_out, qt_out, (int)tiles_r, (int)tiles_c, diagonal)
+    enqueue((quantize_transpose_kernel<DT, FMT, TC, PART>), grid, dim3(kThreads), 0, stream, x, rows, cols, scale_dev, q_out, qt_out, (int)tiles_r, (int)tiles_c, diagonal)
 #define FP8MM_QT(DT, FMT, FULL)                                       \
     do {                                                              \
         if (part == 4) FP8MM_QT_(DT, FMT, FULL, 4);                   \

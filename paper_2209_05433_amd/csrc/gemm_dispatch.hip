@@ -98,7 +98,7 @@ int launch_generic(const GemmArgs& g)
     if (tiles > 0x7fffffffll)
         return fail(FP8_ERR_UNSUPPORTED, "gemm (generic kernel): %lld tiles of 64 x 64 exceed the grid limit", (long long)tiles);
     const dim3 grid((unsigned)tiles);
-    hipLaunchKernelGGL((gemm_generic_kernel<FA, FB>), grid, dim3(256), 0, g.stream, g.A, g.B, g.C, g.M, g.N, g.K,
+    enqueue((gemm_generic_kernel<FA, FB>), grid, dim3(256), 0, g.stream, g.A, g.B, g.C, g.M, g.N, g.K,
                        g.ep, g.transA, g.transB);
     return check_launch("gemm (generic kernel)");
 }
@@ -414,13 +414,13 @@ int launch_gemm(const GemmArgs& g)
 {
     const int64_t M = g.M, N = g.N, K = g.K;
     if (g.ep.amax_out) {                                     // written, not accumulated
-        hipLaunchKernelGGL(zero_cell_kernel, dim3(1), dim3(1), 0, g.stream, (unsigned*)g.ep.amax_out);
+        enqueue(zero_cell_kernel, dim3(1), dim3(1), 0, g.stream, (unsigned*)g.ep.amax_out);
         if (M == 0 || N == 0) return check_launch("gemm (amax init)");
     }
     if (M == 0 || N == 0) return FP8_OK;
     if (K == 0) {                                            // empty sums: every output is +0
         const size_t nbytes = (size_t)M * (size_t)N * (size_t)out_elem_size(g.ep.out_kind);
-        hipLaunchKernelGGL(zero_fill_kernel, dim3(1024), dim3(256), 0, g.stream, (unsigned char*)g.C, nbytes);
+        enqueue(zero_fill_kernel, dim3(1024), dim3(256), 0, g.stream, (unsigned char*)g.C, nbytes);
         return check_launch("gemm (K = 0 fill)");
     }
     const GemmPlan plan = plan_gemm(g, false);

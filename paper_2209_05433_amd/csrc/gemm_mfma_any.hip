@@ -517,7 +517,7 @@ template <int FA, int FB, bool A_KC, bool B_KC>
 int launch_one(const GemmArgs& g, bool wide)
 {
     if (!wide) {
-        hipLaunchKernelGGL((gemm_mfma_any_kernel<FA, FB, A_KC, B_KC>), dim3((unsigned)tile_count(g, FT)), dim3(256), 0, g.stream,
+        enqueue((gemm_mfma_any_kernel<FA, FB, A_KC, B_KC>), dim3((unsigned)tile_count(g, FT)), dim3(256), 0, g.stream,
                            g.A, g.B, g.C, g.M, g.N, g.K, g.ep);
         return check_launch("gemm (matrix-core kernel for any shape)");
     }
@@ -533,7 +533,7 @@ int launch_one(const GemmArgs& g, bool wide)
             return fail(FP8_ERR_DEVICE, "hipFuncSetAttribute(LDS=%d): %s", W_LDS, hipGetErrorString(e));
         if (dev < 64) attr_set.fetch_or(bit, std::memory_order_relaxed);
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)tile_count(g, WT)), dim3(256), W_LDS, g.stream, g.A, g.B, g.C, g.M, g.N, g.K, g.ep);
+    enqueue(kern, dim3((unsigned)tile_count(g, WT)), dim3(256), W_LDS, g.stream, g.A, g.B, g.C, g.M, g.N, g.K, g.ep);
     return check_launch("gemm (matrix-core kernel for any shape, wide form)");
 }
 

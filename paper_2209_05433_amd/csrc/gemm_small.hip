@@ -387,7 +387,7 @@ int launch_form(const GemmArgs& g)
         }
     }
     const int64_t tiles = ((g.M + 32 * RM - 1) / (32 * RM)) * ((g.N + 32 * RN - 1) / (32 * RN));
-    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(64 * NW), LDS, g.stream, g.A, g.B, g.C, g.M, g.N, g.K, g.ep);
+    enqueue(kern, dim3((unsigned)tiles), dim3(64 * NW), LDS, g.stream, g.A, g.B, g.C, g.M, g.N, g.K, g.ep);
     return check_launch("gemm (small tiles)");
 }
 

@@ -148,7 +148,7 @@ int launch_gemm_splitk(const GemmArgs& g, const SplitPlan& sp, void* ws)
     if (blocks > 65536) blocks = 65536;
     const dim3 grid((unsigned)blocks), block(kReduceThreads);
 #define FP8MM_LAUNCH_REDUCE(OUT, VEC)                                                                     \
-    hipLaunchKernelGGL((splitk_reduce_kernel<OUT, VEC>), grid, block, 0, g.stream, (const float*)ws, mn,  \
+    enqueue((splitk_reduce_kernel<OUT, VEC>), grid, block, 0, g.stream, (const float*)ws, mn,  \
                        sp.splits, g.ep.sA, g.ep.sB, g.ep.sA_dev, g.ep.sB_dev, g.C)
     if (bf16) { if (vec) FP8MM_LAUNCH_REDUCE(OUT_BF16, true); else FP8MM_LAUNCH_REDUCE(OUT_BF16, false); }
     else      { if (vec) FP8MM_LAUNCH_REDUCE(OUT_F32, true);  else FP8MM_LAUNCH_REDUCE(OUT_F32, false); }

@@ -811,7 +811,7 @@ int launch_fast(const GemmArgs& g)
     const int pairs = (int)((g.K + 2 * BK - 1) / (2 * BK));
     const int splits = !PERSIST && g.splits > 1 ? g.splits : 1;
     const int grid = PERSIST ? min(tiles, compute_units()) : tiles * splits;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(FAST_THREADS), FAST_LDS, g.stream, g.A, g.B, g.C,
+    enqueue(kern, dim3(grid), dim3(FAST_THREADS), FAST_LDS, g.stream, g.A, g.B, g.C,
                        (int)g.M, (int)g.N, (int)g.K, g.ep, group_m_setting(), splits,
                        splits > 1 ? g.pairs_per_split : pairs);
     return check_launch(PERSIST ? "gemm (tiled kernel, persistent form)" : "gemm (tiled kernel)");
@@ -834,7 +834,7 @@ int launch_mixed(const GemmArgs& g)
     const int64_t tiles_m = (g.M + BM - 1) / BM;
     const int64_t grid = tiles_m * g.wide_cols + tiles_m * ((g.N - (int64_t)g.wide_cols * (64 * NB) + 127) / 128);
     const int pairs = (int)((g.K + 2 * BK - 1) / (2 * BK));
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(FAST_THREADS), FAST_LDS, g.stream, g.A, g.B, g.C,
+    enqueue(kern, dim3((unsigned)grid), dim3(FAST_THREADS), FAST_LDS, g.stream, g.A, g.B, g.C,
                        (int)g.M, (int)g.N, (int)g.K, g.ep, group_m_setting(), pairs, g.wide_cols);
     return check_launch("gemm (tiled kernel, both tile widths)");
 }
