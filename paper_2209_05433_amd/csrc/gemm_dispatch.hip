@@ -252,29 +252,40 @@ GemmPlan plan_gemm(const GemmArgs& g, bool whole)
                         ((M + TILE_M - 1) / TILE_M) * ((N + TILE_N / 2 - 1) / (TILE_N / 2)) < (1ll << 31);
     // The tiled kernel works on 256 x 256 tiles and clips the last ones: loads of rows / columns
     // beyond the edge are redirected to existing ones and their outputs are not stored.  What it
-    // needs: K a multiple of 16 (it walks K in pairs of stages of 64 and fills a last, partial pair
-    // up with zeros; rows of a K-contiguous operand start every K bytes); 16-byte aligned operands;
+    // needs: K a multiple of 16 if an operand is contiguous along K (its rows start every K bytes; K is walked in pairs of
+    // stages of 64 and a last, partial pair filled up with zeros); 16-byte aligned operands;
     // rows of an N-contiguous B and of an M-contiguous A that start on 16-byte boundaries (N % 16, M % 16).  Rows of C (and a
     // per-column factor vector) may start anywhere (the epilogue's stores go to any address): with
     // B stored N x K any N goes (a vocabulary-sized output layer, weights stored [out, in]).
+    // Any K goes where neither operand is contiguous along it (a weight gradient over any number of tokens): what the last stage
+    // lacks are whole K-rows, each one load's.  In the fp16 mode, whatever the flag says, and with one factor per operand (those
+    // of rows and columns are rounded more often here), so that nothing is less accurate than on the any-shape kernel; what
+    // the small tiles, with their shorter chains of sums, took beside that kernel they keep.  Against the any-shape kernel: 4096 x 4096 x 33 43.7 ->
+    // 16.8 us, 3648 x 6272 x 100 61.9 -> 25.1, 896 x 12224 x 7259 192 -> 134, 2432 x 8256 x 4489 258 -> 166, 8192 x 12288 x 3333 580 -> 532; taken where
+    // the models of both say so, no product of 47 more than 3 % slower.
+    const bool ragged = K % 16 != 0;
+    const int acc = ragged ? (int)ACC_F16 : g.acc;
     const bool c_lines = N % 16 == 0 && aligned16(g.C) && (!g.ep.b_per_col || aligned16(g.ep.sB_dev));
-    const bool fast = !force_generic() && !force_mfma_any() && aligned16(g.A) && aligned16(g.B) && fits32 && K % 16 == 0 &&
+    const bool fast = !force_generic() && !force_mfma_any() && aligned16(g.A) && aligned16(g.B) && fits32 && (!ragged || (g.transA && !g.transB && !g.ep.a_per_row && !g.ep.b_per_col)) &&
                       (g.transB || N % 16 == 0) && (!g.transA || M % 16 == 0);
-    if (small_allowed) plan.small = choose_small(g, fast, plan.us, SMALL_NONE);
-    else if (small >= 2 && tile_count(g, 32) <= 0x7fffffffll) plan.small = choose_small(g, fast, plan.us, SMALL_32x32 + small - 2);
+    if (small_allowed) plan.small = choose_small(g, fast && !ragged, plan.us, SMALL_NONE);
+    else if (small >= 2 && tile_count(g, 32) <= 0x7fffffffll) plan.small = choose_small(g, fast && !ragged, plan.us, SMALL_32x32 + small - 2);
     if (!fast) return plan;
     if (!whole && plan.small != SMALL_NONE) {
-        plan.kernel = GEMM_TILED_256;
+        plan.kernel = ragged ? GEMM_MFMA_ANY : GEMM_TILED_256;
         return plan;
     }
     // Tile width.  One workgroup per compute unit (256 of them) runs at a time: the width whose rounds
     // of workgroups take less time (4096 x 6144: 384 wide tiles = two rounds, the second half empty, 768
     // narrow ones = three).  The knob FP8_KNOB_TILE_N = 128 | 256 overrides the choice.
-    const TileTimes tile = tile_times(g.acc, 2.0 * (double)((K + 2 * TILE_K - 1) / (2 * TILE_K)));
+    const TileTimes tile = tile_times(acc, 2.0 * (double)((K + 2 * TILE_K - 1) / (2 * TILE_K)));
     const int64_t tiles_m = (M + TILE_M - 1) / TILE_M, wide_cols_all = (N + TILE_N - 1) / TILE_N;
     auto rounds = [&](int64_t tiles) { return (double)((tiles + 255) / 256); };
-    const int tn = knob(FP8_KNOB_TILE_N);
+    const int tn = knob(FP8_KNOB_TILE_N), mk = knob(FP8_KNOB_MIXED), pk = knob(FP8_KNOB_PERSIST), middle_knob = knob(FP8_KNOB_TILE_192);
     const bool narrow = tn ? tn == 128 : rounds(tiles_m * ((N + 127) / 128)) * tile.narrow < rounds(tiles_m * wide_cols_all) * tile.wide;
+    if (ragged && !tn && !mk && middle_knob != 2 &&
+        std::min(any_128_us(g), any_wide_us(g)) < std::min(rounds(tiles_m * wide_cols_all) * tile.wide, rounds(tiles_m * ((N + 127) / 128)) * tile.narrow))
+        return plan;
     plan.kernel = narrow ? GEMM_TILED_128 : GEMM_TILED_256;
     plan.elementwise_stores = !c_lines;
     // Both widths in one launch (gemm_mixed_kernel): the first c tile columns of 256, the rest of N in
@@ -286,7 +297,6 @@ GemmPlan plan_gemm(const GemmArgs& g, bool whole)
     // the wide tiles fill little of their last round (3001 x 6144 x 2048: 3 - 7 %).  Problems of
     // more than 64 rounds are left alone (the last round is then under 2 %).
     // Knob FP8_KNOB_MIXED: 0 = by the model, 1 = never, 2 = wherever it is possible.
-    const int mk = knob(FP8_KNOB_MIXED), pk = knob(FP8_KNOB_PERSIST), middle_knob = knob(FP8_KNOB_TILE_192);
     const double S = 2.0 * (double)((K + 2 * TILE_K - 1) / (2 * TILE_K));
     double chosen_us = 1e300;
     // time until the last of Tw wide tiles (tw us each) and then Tn narrow ones ends on 256 units
@@ -337,7 +347,7 @@ GemmPlan plan_gemm(const GemmArgs& g, bool whole)
     const bool possible = plan.kernel == GEMM_TILED_128 && c_lines && M % TILE_M == 0 && N % 128 == 0 && K % (2 * TILE_K) == 0 && K >= 8 * TILE_K &&
                           !g.ep.a_per_row && !g.ep.b_per_col && g.ep.out_kind <= OUT_BF16 && !g.ep.amax_out && g.splits <= 1;
     const bool pays = tiles > 256 && (g.ep.out_kind == OUT_F32 ? K <= 64 * TILE_K
-                                                               : g.acc == ACC_F16 && K >= 16 * TILE_K && K <= 32 * TILE_K);
+                                                               : acc == ACC_F16 && K >= 16 * TILE_K && K <= 32 * TILE_K);
     plan.persistent = possible && plan.small == SMALL_NONE && pk != 1 && (pk == 2 || pays);
     // Tiles of 256 x 192, alone or with 128-wide ones behind them: where the same model says that they beat the choice so
     // far by 3 % (4096 x 6144 x 2048: 512 tiles = two full rounds, 84 us against 93 for 768 narrow ones; 3001 x 6144 x 2048:
@@ -434,6 +444,7 @@ int launch_gemm(const GemmArgs& g)
     if (plan.kernel == GEMM_MFMA_ANY) return launch_mfma_any(g);
     if (plan.kernel != GEMM_GENERIC) {
         GemmArgs gt = g;
+        if (K % 16 != 0) gt.acc = ACC_F16;                   // see plan_gemm
         gt.tile_n = plan.middle ? 192 : plan.kernel == GEMM_TILED_128 ? 128 : 256;
         gt.wide_cols = plan.middle ? plan.middle_cols : plan.kernel == GEMM_TILED_MIXED ? plan.wide_cols : 0;
         gt.persist = plan.persistent && !plan.middle;

@@ -91,6 +91,7 @@ SplitPlan plan_splitk(const GemmArgs& g, int requested)
     SplitPlan sp{1, 0, 256};
     GemmArgs probe = g;
     const GemmPlan plain = plan_gemm(probe);
+    if (g.K % 16 != 0) return sp;                            // (never cut: callers keep no workspace for it)
     if (plain.kernel != GEMM_TILED_256 && plain.kernel != GEMM_TILED_128 && plain.kernel != GEMM_TILED_MIXED) return sp;
     const int forced_tile = knob(FP8_KNOB_TILE_N);
     sp.tile_n = forced_tile ? forced_tile : 256;             // the slices fill the chip: the wide tile is the faster one

@@ -6,6 +6,7 @@ import contextlib
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2209_05433_amd as fp8
 import test_gpu_gemm as gemm
@@ -93,3 +94,30 @@ def test_factors_per_column_are_rounded_once(form):
             assert np.all(np.isfinite(want))
             got = fused.run_fused(A, fused.E4M3, B, fused.E4M3, fp8.FP8_OUT_F32, sA, col)[0].cpu().numpy()
             assert np.array_equal(got, want), "%d of %d outputs differ" % (np.count_nonzero(got != want), want.size)
+
+
+# K of one row, of less than a stage, one less and one more than a pair of stages, several pairs and a remainder
+@pytest.mark.parametrize("K", [1, 63, 127, 129, 1000, 2305])
+@pytest.mark.parametrize("knobs", [{TILE_N: 256}, {TILE_N: 128}, {fp8.FP8_KNOB_TILE_192: 2}, {fp8.FP8_KNOB_TILE_192: 2, fp8.FP8_KNOB_MIXED: 2}],
+                         ids=["256", "128", "192", "192 and 128"])
+def test_tiled_kernel_over_any_k_of_operands_contiguous_along_m_and_n(knobs, K):
+    """Sums of integers, exact; guard bytes of NaN behind the operands and around the output."""
+    rng = np.random.default_rng(K)
+    M, N = 272, 592
+    for fmtA, fmtB, flags in ((fused.E4M3, fused.E4M3, 0), (fused.E5M2, fused.E4M3, fp8.FP8_GEMM_MFMA8)):
+        A = fused.oracle.quantize(rng.integers(-3, 4, (M, K)).astype(np.float32), fmtA, 1.0)
+        B = fused.oracle.quantize(rng.integers(-3, 4, (K, N)).astype(np.float32), fmtB, 1.0)
+        want = fused.oracle.gemm_rows(A, fmtA, B, fmtB)[0]
+        dA, dB = (torch.full((x.size + 512,), 0x7F, dtype=torch.uint8, device="cuda") for x in (A, B))
+        dA, dB = dA[:A.size].view(K, M), dB[:B.size].view(K, N)
+        dA.copy_(torch.from_numpy(np.ascontiguousarray(A.T)))
+        dB.copy_(torch.from_numpy(B))
+        buf = torch.full((M * N + 128,), 9.0, device="cuda")
+        C = buf[64:64 + M * N].view(M, N)
+        with pinned(knobs):
+            assert fp8.fp8_gemm_form(dA, True, dB, False, C, fp8.FP8_OUT_F32, None, flags) in (
+                fp8.FP8_FORM_TILED_256, fp8.FP8_FORM_TILED_128, fp8.FP8_FORM_TILED_192, fp8.FP8_FORM_TILED_192_128)
+            fp8.fp8_gemm_ex(dA, fmtA, True, dB, fmtB, False, C, 1.0, 1.0, flags=flags)
+        torch.cuda.synchronize()
+        assert np.array_equal(C.cpu().numpy().astype(np.float64), want)
+        assert bool((buf[:64] == 9).all()) and bool((buf[64 + M * N:] == 9).all())
