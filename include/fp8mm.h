@@ -243,7 +243,7 @@ int fp8_quantize_transpose(const void* x, int64_t rows, int64_t cols, int in_dty
  * boundaries: N a multiple of 16 where B is given as K x N, M a multiple of 16 where A is
  * given as K x M (see fp8_gemm_ex); with B given as N x K any N goes, and C may lie
  * anywhere.  The other shapes and alignments take a second matrix-core kernel (register-staged
- * loads, 256 x 256 or 128 x 128 tiles, the same arithmetic and bound, 0.5 - 0.8 of the rate),
+ * loads, 256 x 256 or 256 x 128 tiles, the same arithmetic and bound, about 0.9 of the rate),
  * and small problems of either kind a third (32 x 32 to 64 x 64 tiles); see fp8_gemm_plan.  fp8_gemm_dscale reads the two scales from device memory instead.
  */
 int fp8_gemm(const uint8_t* A, int fmtA, float sA,
@@ -404,7 +404,7 @@ int fp8_scaled_gemm(const void* a, const void* b, int in_dtype, int transA, int 
  * first columns of the output, 128-wide ones for the rest, where that fills the rounds of workgroups
  * better than either width alone),
  * FP8_PLAN_MFMA_ANY (the matrix-core kernel for every other shape and alignment: an odd K, operand
- * rows that do not start on 16-byte boundaries, unaligned pointers; 0.5 - 0.8 of the tiled
+ * rows that do not start on 16-byte boundaries, unaligned pointers; about 0.9 of the tiled
  * kernel's rate, fifteen to twenty-five times that of plain FMAs; it computes in the default accumulation mode also under FP8_GEMM_MFMA8, which
  * meets that flag's bound a fortiori) or FP8_PLAN_FMA_KERNEL (plain FMAs: only when forced by
  * FP8_KNOB_GEMM_KERNEL or for outputs of more than 2^31 - 1 tiles of 128 x 128), ORed with
@@ -453,7 +453,7 @@ int fp8_gemm_form(const uint8_t* A, int transA, const uint8_t* B, int transB, co
  *                         rounding written from Table 1 (FP8MM_CAST_PATH=bits); both are bit-equal
  *   FP8_KNOB_TILE_N       0 the dispatcher chooses, 128 or 256 forces the tile width of the
  *                         tiled kernel and the form of the any-shape matrix-core kernel
- *                         (128 x 128 / 256 x 256 tiles) (FP8MM_TILE_N)
+ *                         (256 x 128 / 256 x 256 tiles) (FP8MM_TILE_N)
  *   FP8_KNOB_GROUP_M      tile rows per band of the tile order, 0 = default 8 (FP8MM_GROUP_M)
  *   FP8_KNOB_GEMM_KERNEL  0 the dispatcher chooses, 1 always the plain FMA kernel (FP8MM_GEMM=generic),
  *                         2 always the any-shape matrix-core kernel (FP8MM_GEMM=any)

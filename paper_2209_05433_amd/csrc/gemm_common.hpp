@@ -72,17 +72,17 @@ constexpr int TILE_M = 256, TILE_N = 256, TILE_K = 64;
 int launch_gemm(const GemmArgs& g);
 
 // The matrix-core kernel for any shape and alignment (gemm_mfma_any.hip): operands staged through
-// registers; 128 x 128 tiles, or 256 x 256 tiles where those fill the chip (mfma_any_wide).  Takes
-// every problem with M, N, K > 0 whose tile count fits the grid.
+// registers; tiles of 256 x 256 or 256 x 128.  Takes every problem with M, N, K > 0 whose tile count fits the grid; the few that its tiles
+// do not (see mfma_any_width) run on 64 x 64 tiles of the small-tile kernel.
 bool mfma_any_takes(const GemmArgs& g);
-bool mfma_any_wide(const GemmArgs& g);
+int mfma_any_width(const GemmArgs& g);       // 256 or 128 columns; 0: the small-tile kernel
 int launch_mfma_any(const GemmArgs& g);
 #define FP8MM_ANY_NAME_(l) launch_mfma_any_l##l
 #define FP8MM_ANY_NAME(l) FP8MM_ANY_NAME_(l)
-int FP8MM_ANY_NAME(0)(const GemmArgs& g, bool wide);         // one translation unit per pair of storage orders
-int FP8MM_ANY_NAME(1)(const GemmArgs& g, bool wide);
-int FP8MM_ANY_NAME(2)(const GemmArgs& g, bool wide);
-int FP8MM_ANY_NAME(3)(const GemmArgs& g, bool wide);
+int FP8MM_ANY_NAME(0)(const GemmArgs& g, int width);        // one translation unit per pair of storage orders
+int FP8MM_ANY_NAME(1)(const GemmArgs& g, int width);
+int FP8MM_ANY_NAME(2)(const GemmArgs& g, int width);
+int FP8MM_ANY_NAME(3)(const GemmArgs& g, int width);
 
 // The tiled kernel instance for g's storage orders and accumulation mode, with g.tile_n, g.splits,
 // g.pairs_per_split as given (the caller has checked that the tiled kernel takes
@@ -130,6 +130,40 @@ struct TileTimes { double wide, middle, narrow; };
 TileTimes tile_times(int acc, double S);
 
 // ---- small device helpers used by the kernels -------------------------------------------------
+typedef u32x4 u32x4_any __attribute__((aligned(1)));     // 16 bytes at any address: one load or store on this target
+
+// The vector without its first k bytes (0 <= k < 16), zeros behind the rest.
+__device__ __forceinline__ u32x4 drop_bytes(u32x4 v, int k)
+{
+    if (k & 8) v = (u32x4){v.z, v.w, 0u, 0u};
+    if (k & 4) v = (u32x4){v.y, v.z, v.w, 0u};
+    const int b = k & 3;
+    return (u32x4){__builtin_amdgcn_alignbyte(v.y, v.x, b), __builtin_amdgcn_alignbyte(v.z, v.y, b),
+                   __builtin_amdgcn_alignbyte(v.w, v.z, b), __builtin_amdgcn_alignbyte(0u, v.w, b)};
+}
+
+// A whole row of fewer than 16 bytes, at the end of the vector.
+__device__ __forceinline__ u32x4 load_short(const uint8_t* row, int len)
+{
+    u32x4 v = {0u, 0u, 0u, 0u};
+    for (int j = 0; j < len; ++j) {
+        const int at = 16 - len + j;
+        const unsigned b = (unsigned)row[j] << (8 * (at & 3));
+        v = (u32x4){v.x | (at >> 2 == 0 ? b : 0u), v.y | (at >> 2 == 1 ? b : 0u), v.z | (at >> 2 == 2 ? b : 0u), v.w | (at >> 2 == 3 ? b : 0u)};
+    }
+    return v;
+}
+
+// 16 bytes of a row of `len` bytes, from byte `at` on; zeros beyond the row's end (nothing outside the
+// row is read).
+__device__ __forceinline__ u32x4 load_guarded(const uint8_t* row, int64_t at, int64_t len)
+{
+    const int64_t count = len - at;
+    if (count >= 16) return *(const u32x4_any*)(row + at);
+    if (count <= 0) return (u32x4){0u, 0u, 0u, 0u};
+    return drop_bytes(len >= 16 ? *(const u32x4_any*)(row + len - 16) : load_short(row, (int)len), (int)(16 - count));
+}
+
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 

@@ -127,25 +127,29 @@ TileTimes tile_times(int acc, double S)
 
 namespace {
 
-// The any-shape kernel's two forms: rounds of 256 tiles of 256 x 256, and tiles of 128 x 128 of which several share a
-// compute unit (their products, and 1.8 us per million outputs that leave one by one; a division per output with
-// per-column factors, the conversion to FP8).  Pieces of an operand that is contiguous along M / N and ends inside
-// 16 bytes are loaded with tests, which a lone workgroup of the wide form does not hide: of B in the last column of
-// tiles, of A in every round.  Fitted to nine shapes from 2001 x 3001 x 1025 to 5000 x 5001 x 5001 in all storage orders:
-// the faster form is named wherever they differ by more than 8 % (5000 x 5001 x 5001 with A stored K x M: wide 1050 us,
-// narrow 640; 4096 x 9001 x 600: wide 134, narrow 157).
-bool ragged_a(const GemmArgs& g) { return g.transA && g.M % 16 != 0; }
-bool ragged_b(const GemmArgs& g) { return !g.transB && g.N % 16 != 0; }
-double any_wide_us(const GemmArgs& g)
+// Microseconds of the any-shape kernel in tiles of 256 x `width`: rounds of 256 tiles, each its ends (by output kind: fp32, bf16, FP8
+// with factors per column and the maximum) and S stages.  Fitted to both widths' times on 110 random problems (256 .. 8192 x 256 .. 12288 x
+// 16 .. 8192, all storage orders and output kinds), within 6 %; the width that it names takes 0.04 % longer than the better of the two in the mean, 4 % at
+// most (always 256: 39 %).
+double any_us(const GemmArgs& g, int width)
 {
-    const double rounds = std::ceil(std::ceil(g.M / 256.0) * std::ceil(g.N / 256.0) / 256.0), S = std::ceil(g.K / 64.0);
-    return rounds * (14.0 + 1.65 * S) + S * ((ragged_b(g) ? 3.0 : 0.0) + (ragged_a(g) ? 3.1 * rounds : 0.0));
+    const double rounds = std::ceil(std::ceil(g.M / 256.0) * std::ceil((double)g.N / width) / 256.0), S = 2.0 * std::ceil(g.K / 128.0);
+    const int kind = g.ep.out_kind == OUT_F32 ? 0 : g.ep.out_kind == OUT_BF16 ? 1 : 2;
+    constexpr double wide[3] = {11.7, 8.5, 19.8}, narrow[3] = {6.3, 4.9, 10.8};
+    return width == 256 ? 2.5 + rounds * (wide[kind] + 1.54 * S) : 2.8 + rounds * (narrow[kind] + 0.98 * S);
 }
-double any_128_us(const GemmArgs& g)
+
+// Off the tiled kernel, fp32 outputs stay on small tiles up to the times below (of any-shape kernels that took longer: rounds of 256 x 256
+// tiles, and of 128 x 128 ones of which several shared a compute unit): the waves of a small tile share K, and its shorter chains
+// of sums are nearer to the 64-bit result (1.1e-7 against 1.5e-7 over K = 12288).  The rounding of a 16-bit or FP8 output hides that,
+// and those go by what the kernels take: 1718 x 3405 x 6200 147 -> 105 us, 1903 x 3712 x 1809 54 -> 39, 6435 x 2048 x 2181 129 -> 80.
+double small_line_us(const GemmArgs& g)
 {
-    const double outputs = 1e-6 * (double)g.M * (double)g.N, K = (double)g.K, S = std::ceil(g.K / 64.0);
-    const double ends = 6.9 + (g.ep.b_per_col ? 10.0 : 0.0) + (g.ep.out_kind >= OUT_E4M3 ? 3.0 : 0.0);
-    return ends + std::max(0.03 * K, outputs * (1.8 + 0.0026 * K)) + S * ((ragged_b(g) ? 1.2 : 0.0) + (ragged_a(g) ? 1.4 : 0.0));
+    const double rounds = std::ceil(std::ceil(g.M / 256.0) * std::ceil(g.N / 256.0) / 256.0), K = (double)g.K, S = std::ceil(K / 64.0);
+    const double outputs = 1e-6 * (double)g.M * (double)g.N, ragged_a = g.transA && g.M % 16 != 0, ragged_b = !g.transB && g.N % 16 != 0;
+    const double wide = rounds * (14.0 + 1.65 * S) + S * (3.0 * ragged_b + 3.1 * ragged_a * rounds);
+    const double narrow = 6.9 + (g.ep.b_per_col ? 10.0 : 0.0) + std::max(0.03 * K, outputs * (1.8 + 0.0026 * K)) + S * (1.2 * ragged_b + 1.4 * ragged_a);
+    return std::min(wide, narrow);
 }
 
 // Microseconds of a form of the small-tile kernel (gemm_small.hip): its ends, then the longer of one workgroup's walk along
@@ -198,7 +202,8 @@ int choose_small(const GemmArgs& g, bool tiled, double& us_chosen, int pinned)
             other = std::min(other, alone + (other - alone) * std::max(0.0, 2.0 * units(256, 128) - 1.0));
         }
     } else {
-        other = std::min(any_128_us(g), any_wide_us(g));
+        other = small_line_us(g);
+        if (g.ep.out_kind != OUT_F32) other = std::min(other, 1.1 * std::min(any_us(g, 256), any_us(g, 128)));     // (1.1: their error where a round is short)
     }
     us_chosen = other;
     if (u64 > 32 && pinned == SMALL_NONE) return SMALL_NONE;
@@ -261,8 +266,8 @@ GemmPlan plan_gemm(const GemmArgs& g, bool whole)
     // lacks are whole K-rows, each one load's.  In the fp16 mode, whatever the flag says, and with one factor per operand (those
     // of rows and columns are rounded more often here), so that nothing is less accurate than on the any-shape kernel; what
     // the small tiles, with their shorter chains of sums, took beside that kernel they keep.  Against the any-shape kernel: 4096 x 4096 x 33 43.7 ->
-    // 16.8 us, 3648 x 6272 x 100 61.9 -> 25.1, 896 x 12224 x 7259 192 -> 134, 2432 x 8256 x 4489 258 -> 166, 8192 x 12288 x 3333 580 -> 532; taken where
-    // the models of both say so, no product of 47 more than 3 % slower.
+    // 16.8 us, 3648 x 6272 x 100 61.9 -> 25.1, 896 x 12224 x 7259 192 -> 134, 2432 x 8256 x 4489 258 -> 166, 8192 x 12288 x 3333 580 -> 532
+    // (beside the any-shape kernel's forms of that time; no product of 47 more than 3 % slower).
     const bool ragged = K % 16 != 0;
     const int acc = ragged ? (int)ACC_F16 : g.acc;
     const bool c_lines = N % 16 == 0 && aligned16(g.C) && (!g.ep.b_per_col || aligned16(g.ep.sB_dev));
@@ -283,9 +288,6 @@ GemmPlan plan_gemm(const GemmArgs& g, bool whole)
     auto rounds = [&](int64_t tiles) { return (double)((tiles + 255) / 256); };
     const int tn = knob(FP8_KNOB_TILE_N), mk = knob(FP8_KNOB_MIXED), pk = knob(FP8_KNOB_PERSIST), middle_knob = knob(FP8_KNOB_TILE_192);
     const bool narrow = tn ? tn == 128 : rounds(tiles_m * ((N + 127) / 128)) * tile.narrow < rounds(tiles_m * wide_cols_all) * tile.wide;
-    if (ragged && !tn && !mk && middle_knob != 2 &&
-        std::min(any_128_us(g), any_wide_us(g)) < std::min(rounds(tiles_m * wide_cols_all) * tile.wide, rounds(tiles_m * ((N + 127) / 128)) * tile.narrow))
-        return plan;
     plan.kernel = narrow ? GEMM_TILED_128 : GEMM_TILED_256;
     plan.elementwise_stores = !c_lines;
     // Both widths in one launch (gemm_mixed_kernel): the first c tile columns of 256, the rest of N in
@@ -377,25 +379,38 @@ GemmPlan plan_gemm(const GemmArgs& g, bool whole)
 // ---- the matrix-core kernel for any shape (gemm_mfma_any.hip) ------------------------------------
 bool mfma_any_takes(const GemmArgs& g)
 {
-    return g.M > 0 && g.N > 0 && g.K > 0 && tile_count(g, 128) <= 0x7fffffffll;
+    return g.M > 0 && g.N > 0 && g.K > 0 && tile_count(g, 128) <= 0x7fffffffll && (mfma_any_width(g) || tile_count(g, 64) <= 0x7fffffffll);
 }
 
-// The wide form where its 256 x 256 tiles take less time than the other's and K is long enough for the two-stage pipeline to pay; FP8_KNOB_TILE_N forces
-// either form (128 / 256).
-bool mfma_any_wide(const GemmArgs& g)
+// The narrower tile unless the wider one saves 6 %, the model's error; FP8_KNOB_TILE_N forces either.  Not for the kernel's tiles: an operand
+// contiguous along M / N with rows of fewer than 16 bytes, offsets within a tile's stage beyond 32 bits.
+int mfma_any_width(const GemmArgs& g)
 {
+    if (g.M >= (1 << 26) || g.N >= (1 << 26) || (g.transA && g.M < 16) || (!g.transB && g.N < 16)) return 0;
     const int forced = knob(FP8_KNOB_TILE_N);
-    // 32-bit offsets within a tile's stage: 255 rows of K bytes, or 63 K-rows of M / N bytes
-    if (g.K >= (1 << 24) || g.M >= (1 << 26) || g.N >= (1 << 26)) return false;
-    if (forced) return forced == 256;
-    return g.K >= 512 && any_wide_us(g) < any_128_us(g);
+    if (forced) return forced;
+    return any_us(g, 256) < 0.94 * any_us(g, 128) ? 256 : 128;
 }
+
+namespace {
+
+int launch_small(const GemmArgs& g, int form)
+{
+    typedef int (*small_fn)(const GemmArgs&, int);
+    static const small_fn table[4] = {FP8MM_SMALL_NAME(0), FP8MM_SMALL_NAME(1), FP8MM_SMALL_NAME(2), FP8MM_SMALL_NAME(3)};
+    return table[(g.transA ? 2 : 0) + (g.transB ? 1 : 0)](g, form);
+}
+
+}  // namespace
 
 int launch_mfma_any(const GemmArgs& g)
 {
-    typedef int (*any_fn)(const GemmArgs&, bool);
+    typedef int (*any_fn)(const GemmArgs&, int);
     static const any_fn table[4] = {FP8MM_ANY_NAME(0), FP8MM_ANY_NAME(1), FP8MM_ANY_NAME(2), FP8MM_ANY_NAME(3)};
-    return table[(g.transA ? 2 : 0) + (g.transB ? 1 : 0)](g, mfma_any_wide(g));
+    if (const int width = mfma_any_width(g)) return table[(g.transA ? 2 : 0) + (g.transB ? 1 : 0)](g, width);
+    GemmArgs gs = g;
+    gs.acc = ACC_F16;
+    return launch_small(gs, SMALL_64x64);
 }
 
 int launch_tiled(const GemmArgs& g)
@@ -413,7 +428,10 @@ int gemm_form(const GemmArgs& g)
     const GemmPlan plan = plan_gemm(g, false);
     if (plan.small != SMALL_NONE) return FP8_FORM_SMALL_32x32 + plan.small;
     if (plan.kernel == GEMM_GENERIC) return FP8_FORM_FMA;
-    if (plan.kernel == GEMM_MFMA_ANY) return mfma_any_wide(g) ? FP8_FORM_ANY_256 : FP8_FORM_ANY_128;
+    if (plan.kernel == GEMM_MFMA_ANY) {
+        const int width = mfma_any_width(g);
+        return width == 256 ? FP8_FORM_ANY_256 : width ? FP8_FORM_ANY_128 : FP8_FORM_SMALL_64x64;
+    }
     if (plan.middle) return plan.middle_cols > 0 ? FP8_FORM_TILED_192_128 : FP8_FORM_TILED_192;
     if (plan.kernel == GEMM_TILED_MIXED) return FP8_FORM_TILED_256_128;
     if (plan.kernel == GEMM_TILED_256) return FP8_FORM_TILED_256;
@@ -435,11 +453,9 @@ int launch_gemm(const GemmArgs& g)
     }
     const GemmPlan plan = plan_gemm(g, false);
     if (plan.small != SMALL_NONE) {
-        typedef int (*small_fn)(const GemmArgs&, int);
-        static const small_fn table[4] = {FP8MM_SMALL_NAME(0), FP8MM_SMALL_NAME(1), FP8MM_SMALL_NAME(2), FP8MM_SMALL_NAME(3)};
         GemmArgs gs = g;
         if (plan.kernel == GEMM_MFMA_ANY) gs.acc = ACC_F16;  // as the any-shape kernel computes these problems
-        return table[(g.transA ? 2 : 0) + (g.transB ? 1 : 0)](gs, plan.small);
+        return launch_small(gs, plan.small);
     }
     if (plan.kernel == GEMM_MFMA_ANY) return launch_mfma_any(g);
     if (plan.kernel != GEMM_GENERIC) {

@@ -14,7 +14,6 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-typedef u32x4 u32x4_any __attribute__((aligned(1)));     // 16 bytes at any address: one store on this target
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 

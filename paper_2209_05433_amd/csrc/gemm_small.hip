@@ -39,43 +39,10 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-typedef u32x4 u32x4_any __attribute__((aligned(1)));     // 16 bytes at any address: one load on this target
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 
 constexpr int SK = 64;                                    // K per sub-chunk; a chunk has S of them
-
-// The vector without its first k bytes (0 <= k < 16), zeros behind the rest.
-__device__ __forceinline__ u32x4 drop_bytes(u32x4 v, int k)
-{
-    if (k & 8) v = (u32x4){v.z, v.w, 0u, 0u};
-    if (k & 4) v = (u32x4){v.y, v.z, v.w, 0u};
-    const int b = k & 3;
-    return (u32x4){__builtin_amdgcn_alignbyte(v.y, v.x, b), __builtin_amdgcn_alignbyte(v.z, v.y, b),
-                   __builtin_amdgcn_alignbyte(v.w, v.z, b), __builtin_amdgcn_alignbyte(0u, v.w, b)};
-}
-
-// A whole row of fewer than 16 bytes, at the end of the vector.
-__device__ __forceinline__ u32x4 load_short(const uint8_t* row, int len)
-{
-    u32x4 v = {0u, 0u, 0u, 0u};
-    for (int j = 0; j < len; ++j) {
-        const int at = 16 - len + j;
-        const unsigned b = (unsigned)row[j] << (8 * (at & 3));
-        v = (u32x4){v.x | (at >> 2 == 0 ? b : 0u), v.y | (at >> 2 == 1 ? b : 0u), v.z | (at >> 2 == 2 ? b : 0u), v.w | (at >> 2 == 3 ? b : 0u)};
-    }
-    return v;
-}
-
-// 16 bytes of a row of `len` bytes, from byte `at` on; zeros beyond the row's end (nothing outside the
-// row is read).
-__device__ __forceinline__ u32x4 load_guarded(const uint8_t* row, int64_t at, int64_t len)
-{
-    const int64_t count = len - at;
-    if (count >= 16) return *(const u32x4_any*)(row + at);
-    if (count <= 0) return (u32x4){0u, 0u, 0u, 0u};
-    return drop_bytes(len >= 16 ? *(const u32x4_any*)(row + len - 16) : load_short(row, (int)len), (int)(16 - count));
-}
 
 // One operand of the tile: R blocks of 32 rows of op(A) / columns of op(B) from t0 on, `ext` of them in
 // all; chunks of CK = 64 S along K.  KC: element (r, k) at base[r K + k]; else at base[k ext + r].

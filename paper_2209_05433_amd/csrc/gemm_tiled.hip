@@ -46,15 +46,13 @@
 //
 // This file is compiled once per (storage orders, accumulation mode): -DFP8MM_LAYOUT, -DFP8MM_ACC.
 #include "gemm_epilogue.hpp"
+#include "gemm_slabs.hpp"
 
 #include <atomic>
 #include <type_traits>
 
 namespace fp8mm {
 namespace {
-
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef int v4i __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------------------------------
 // Fast kernel
@@ -76,31 +74,6 @@ constexpr int FAST_LDS = 160 * 1024;         // all of the LDS of a compute unit
 constexpr int FAST_THREADS = 256;
 constexpr int GROUP_M = 8;                   // tile rows per band of the tile order
 constexpr int NUM_XCD = 8;
-
-// Chunk swizzles.  K-contiguous slab: rows of 128 B = 8 chunks; MN-contiguous slab: rows of
-// EXT bytes = 16 or 8 chunks (the swizzle value is reduced to the chunk count).  Measured on gfx950: with these a 16-byte fragment read costs 5 clocks per
-// wave instruction (the conflict-free rate, 64 banks of 4 bytes) and a transposing 8-byte read
-// 7.3 clocks.
-__device__ __forceinline__ int swz_kc(int row) { return (row >> 1) & 7; }
-// MN-contiguous slab: mc_pos = position in its K-row of the chunk whose index in memory is c; mc_mem
-// = the memory chunk that sits at position p (the inverse map, used on the global side of the direct
-// loads, whose LDS placement is fixed).  The XOR with the K-row spreads the 8 K-rows that one 16-lane
-// group of a transposing read touches over 8 chunk positions.  In a 256-byte row (16 chunks, all 64
-// banks) the odd memory chunks also change halves: the two 16-lane groups that are served
-// together read neighbouring chunks (columns 0-15 and 16-31 of a block), which then lie in
-// different halves of the banks instead of sharing 32 of them.
-template <int CH>
-__device__ __forceinline__ int mc_pos(int c, int krow)
-{
-    const int p = c ^ (krow & 7 & (CH - 1));
-    return CH == 16 ? p ^ ((c & 1) << 3) : p;
-}
-template <int CH>
-__device__ __forceinline__ int mc_mem(int p, int krow)
-{
-    const int c = p ^ (krow & 7 & (CH - 1));               // right but for bit 3, which does not enter bit 0
-    return CH == 16 ? c ^ ((c & 1) << 3) : c;
-}
 
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding:
 // vmcnt = bits 3:0 and 15:14, expcnt = 6:4, lgkmcnt = 11:8).
@@ -149,12 +122,6 @@ struct Operand {
     size_t nxt;
 };
 
-// Rows of a K-contiguous slab / bytes of a K-row of the other kind in LDS.  192 columns of the other kind lie in rows of 256
-// bytes: the columns of either wave begin at a half, so that the swizzle and the address arithmetic are those of 256
-// columns; the last quarter of a half repeats the chunk before it (the same lines are asked for, nothing more is read).
-template <bool KC, int EXT>
-constexpr int lds_extent() { return !KC && EXT == 192 ? 256 : EXT; }
-
 template <bool KC, int EXT>
 __device__ __forceinline__ void operand_setup(Operand& op, const uint8_t* base, unsigned ld, int r0, int valid,
                                               unsigned region, int w, int l, int wsel)
@@ -163,7 +130,7 @@ __device__ __forceinline__ void operand_setup(Operand& op, const uint8_t* base, 
     // existing one (their products only reach outputs that are never stored).
     op.ld = ld;
     op.region = region;
-    const int h = l >> 5;
+    op.rd = fragment_start<KC, lds_extent<KC, EXT>()>(region, wsel, l);
 #pragma unroll
     for (int t = 0; t < 8; ++t) op.off[t] = 0;
     if (KC) {
@@ -174,10 +141,6 @@ __device__ __forceinline__ void operand_setup(Operand& op, const uint8_t* base, 
             const int row = (w * LW + t) * 8 + (l >> 3);
             op.off[t] = (unsigned)min(row, valid - 1) * ld + (((l & 7) ^ swz_kc(row)) * 16);
         }
-        // lane = (r = l % 32, h = l / 32) reads K bytes 32h .. 32h+31 of row r of its stage:
-        // chunks 4 par + 2h and + 1 of the 128-byte row (par = stage parity)
-        const int row = wsel * (EXT / 2) + (l & 31);
-        op.rd = region + row * 128 + (((2 * h) ^ swz_kc(row)) * 16);
     } else {
         constexpr int ROW = lds_extent<KC, EXT>();    // bytes of a K-row in LDS
         constexpr int CH = ROW / 16;                  // 16-byte chunks per K-row
@@ -191,11 +154,6 @@ __device__ __forceinline__ void operand_setup(Operand& op, const uint8_t* base, 
             if (ROW != EXT) chunk = (CH * EXT / ROW / 2) * (chunk / (CH / 2)) + min(chunk % (CH / 2), CH * EXT / ROW / 2 - 1);
             op.off[t] = (unsigned)krow * ld + min(chunk, (valid - 1) >> 4) * 16;
         }
-        // lane = (r = l % 32, h): column r, K bytes 32h .. 32h+31, gathered by four transposing
-        // reads of 8 K-rows x 16 columns per 16-lane group; lanes 2q and 2q+1 address K-row q
-        const int t16 = l & 15, gq = (l >> 4) & 1;
-        const int krow = 32 * h + (t16 >> 1);
-        op.rd = region + krow * ROW + mc_pos<CH>(wsel * (CH / 2) + gq, krow) * 16 + (t16 & 1) * 8;
     }
 }
 
@@ -221,27 +179,6 @@ __device__ __forceinline__ void direct_load_or_zero(const uint8_t* base, unsigne
 {
     const uint8_t* p = valid ? base + off : g_zero_chunk;
     asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(p), "{m0}"(lds_addr) : "memory");
-}
-
-// One read-part of the fragment reads of stage kt for one operand: 16 bytes per lane of block blk
-// (half 0 or 1 of the lane's 32 bytes), as one 16-byte read (KC) or two transposing reads (MC).
-// EXT: rows of a K-contiguous slab, bytes of a K-row of the other kind (lds_extent).
-template <bool KC, int EXT>
-__device__ __forceinline__ void read_part(const uint8_t* smem, const Operand& op, int kt, int kc_slot, int blk, int half,
-                                          v8i* f)
-{
-    if (KC) {
-        const unsigned addr = (op.rd ^ (unsigned)((kt & 1) * 64 + half * 16)) + kc_slot * (EXT * 128) + blk * 32 * 128;
-        const v4i a = *LDS_PTR(v4i, smem + addr);
-        f[blk][4 * half + 0] = a.x; f[blk][4 * half + 1] = a.y; f[blk][4 * half + 2] = a.z; f[blk][4 * half + 3] = a.w;
-    } else {
-        const unsigned base = (unsigned)(kt & (MC_SLOTS - 1)) * (64 * EXT) + (op.rd ^ (unsigned)(blk * 32));
-#pragma unroll
-        for (int s = 2 * half; s < 2 * half + 2; ++s) {
-            const v2i p = __builtin_amdgcn_ds_read_tr8_b64_v2i32(LDS_PTR(v2i, smem + base + s * 8 * EXT));
-            f[blk][2 * s] = p.x; f[blk][2 * s + 1] = p.y;
-        }
-    }
 }
 
 // A_KC / B_KC: how the operand lies in memory (see Operand); NB: width of the tile in blocks of 32
@@ -557,8 +494,8 @@ __device__ __forceinline__ void gemm_tile_body(
     };
     auto read_both = [&](int kt, int j, int sa, int sb, v8i (&af)[4], v8i (&bf)[NB]) {
 #pragma unroll
-        for (int ra = j * 8 / P; ra < (j + 1) * 8 / P; ++ra) read_part<A_KC, BM>(smem, opA, kt, sa, ra & 3, ra >> 2, af);
-        read_part<B_KC, B_ROW>(smem, opB, kt, sb, j % NB, j / NB, bf);
+        for (int ra = j * 8 / P; ra < (j + 1) * 8 / P; ++ra) read_part<A_KC, BM, MC_SLOTS>(smem, opA.rd, kt, sa, ra & 3, ra >> 2, af);
+        read_part<B_KC, B_ROW, MC_SLOTS>(smem, opB.rd, kt, sb, j % NB, j / NB, bf);
     };
 
     // One K stage kt (not the last).  The frags of stage kt are in (af, bf); their LDS reads were

@@ -192,3 +192,31 @@ def test_fused_epilogue_on_a_ragged_problem(form):
     torch.cuda.synchronize()
     assert np.array_equal(D.cpu().numpy(), want)
     assert float(amax.item()) == float(np.max(np.abs(c)))
+
+
+# K: shorter than a vector, one vector, one byte beside the ends of a stage, of a pair, of three and of five pairs; N and M one vector and
+# one column beside the tiles' edges
+@pytest.mark.parametrize("K", [1, 15, 16, 17, 63, 65, 127, 128, 129, 383, 385, 641])
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_edges_of_tiles_and_stages_between_guards(transA, transB, K, form):
+    """Exact sums of integers, with NaN codes around the operands and guard values around the output: a piece taken from
+    beside its row, or a stage from beyond K, shows."""
+    rng = np.random.default_rng(1000 * K + 2 * transA + transB)
+    for M, N in ((16, 129), (255, 143), (257, 272), (272, 255), (513, 17)):
+        A = oracle.quantize(rng.integers(-3, 4, (M, K)).astype(np.float32), E4M3, 1.0)
+        B = oracle.quantize(rng.integers(-3, 4, (K, N)).astype(np.float32), E5M2, 1.0)
+        want = oracle.gemm_rows(A, E4M3, B, E5M2)[0]
+        off, dev = 1 + K % 15, []
+        for x in (stored(A, transA), stored(B, transB)):
+            buf = torch.full((x.size + 1024,), 0x7F, dtype=torch.uint8, device="cuda")
+            t = buf[off + 496:off + 496 + x.size].view(x.shape)
+            t.copy_(torch.from_numpy(x))
+            dev.append(t)
+        flat = torch.full((M * N + 128,), 77.0, device="cuda")
+        C = flat[64:64 + M * N].view(M, N)
+        with knob(fp8.FP8_KNOB_GEMM_KERNEL, 2):
+            assert fp8.fp8_gemm_form(dev[0], transA, dev[1], transB, C, fp8.FP8_OUT_F32) == (fp8.FP8_FORM_ANY_256 if form == 256 else fp8.FP8_FORM_ANY_128)
+            fp8.fp8_gemm_ex(dev[0], E4M3, transA, dev[1], E5M2, transB, C, 1.0, 1.0)
+        torch.cuda.synchronize()
+        assert np.array_equal(out_to_f64(C), want), (M, N, K, transA, transB)
+        assert torch.all(flat[:64] == 77.0) and torch.all(flat[64 + M * N:] == 77.0), "wrote outside C"
