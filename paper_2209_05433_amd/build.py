@@ -24,6 +24,7 @@ UNITS = [("gemm_tiled.hip", ["-DFP8MM_LAYOUT=%d" % k, "-DFP8MM_ACC=%d" % a], "ge
          for k in range(4) for a in range(2)] + \
         [("gemm_mfma_any.hip", ["-DFP8MM_LAYOUT=%d" % k], "gemm_mfma_any_l%d.o" % k) for k in range(4)] + \
         [("gemm_small.hip", ["-DFP8MM_LAYOUT=%d" % k], "gemm_small_l%d.o" % k) for k in range(4)] + \
+        [("scaled_gemm_small.hip", ["-DFP8MM_LAYOUT=%d" % k], "scaled_gemm_small_l%d.o" % k) for k in range(4)] + \
         [("gemm_dispatch.hip", [], "gemm_dispatch.o"), ("gemm_splitk.hip", [], "gemm_splitk.o"),
          ("cast_kernels.hip", [], "cast_kernels.o"),
          ("cast_variants.hip", [], "cast_variants.o"),

@@ -488,6 +488,8 @@ int fp8_scaled_gemm(const void* a, const void* b, int in_dtype, int transA, int 
         if (n[i] > 0 && (!x[i] || !q[i])) return fail(FP8_ERR_INVALID_ARG, "%s: NULL operand or FP8 output %d with %zu elements", who, i, n[i]);
         if ((uintptr_t)x[i] % (in_dtype == FP8_F32 ? 4 : 2)) return fail(FP8_ERR_INVALID_ARG, "%s: operand %d is not aligned to its element size", who, i);
     }
+    bool took = false;
+    if (int e = launch_scaled_gemm_small(g, a, b, in_dtype, amax_out, scale_out, workspace, took); e || took) return e;
     if (int e = launch_amax_cast(2, x, n, in_dtype, fmt, amax_out, scale_out, workspace, q, (hipStream_t)stream)) return e;
     return launch_gemm(g);
 }

@@ -17,6 +17,14 @@ constexpr int kCastBlocks = 1 << 20;
 constexpr int kMultiMax = FP8_MULTI_MAX;  // tensors per launch of the multi-tensor forms
 constexpr size_t kStreamingStoreBytes = (size_t)384 << 20;   // outputs from this size on are stored non-temporally
 
+// Words of the amax workspace (4096 a tensor): tickets and partial maxima of the one-launch amax (amax_finish_ticket), then those of
+// the launches in which the maxima of a tensor's parts meet in slots (amax_cast_kernel, scaled_gemm_small_kernel).
+constexpr unsigned kTicketGroup = 32;
+constexpr unsigned kTicketPartials = 32 * (1 + kAmaxBlocks / kTicketGroup);
+constexpr unsigned kCastDone = kTicketPartials + kAmaxBlocks;        // workgroups that have read all slots
+constexpr unsigned kCastSlots = kCastDone + 32;                      // ... and the slots (nothing else uses these words)
+constexpr unsigned kPatience = 20000;                                // how long a workgroup waits for them, ticks of the 100 MHz clock: 200 us
+
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 // Vectors at any address: the target's global loads and stores take them as one instruction.
 typedef u32x4 u32x4_any __attribute__((aligned(1)));

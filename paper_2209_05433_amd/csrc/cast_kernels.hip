@@ -47,8 +47,6 @@ constexpr size_t kAmaxAloneBelow = (size_t)kThreads * kAmaxVecsAlone;      // ve
 // reader draws the last ticket before it loads, again with agent-scope atomic loads.  No other
 // data is exchanged, so no cache-wide write-back or invalidate is needed.
 // r: the workgroup's maximum, valid in thread 0.
-constexpr unsigned kTicketGroup = 32;
-constexpr unsigned kTicketPartials = 32 * (1 + kAmaxBlocks / kTicketGroup);
 
 __device__ __forceinline__ unsigned draw_ticket(unsigned* counter)
 {
@@ -296,9 +294,6 @@ __global__ __launch_bounds__(kThreads) void quantize_multi_kernel(MultiTensors m
 constexpr int kCastThreads = 512, kCastVecs = 8;                     // a chunk: 8 vectors per lane
 constexpr size_t kCastChunk = (size_t)kCastThreads * kCastVecs;      // vectors
 constexpr size_t kOneLaunchBytes = (size_t)5 << 19;                  // input up to which one launch is the better form: 2.5 MB
-constexpr unsigned kCastDone = kTicketPartials + kAmaxBlocks;        // workspace word: workgroups that have read all slots
-constexpr unsigned kCastSlots = kCastDone + 32;                      // ... and the slots (nothing else uses these words)
-constexpr unsigned kPatience = 20000;                                // ticks of the 100 MHz clock: 200 us
 static_assert(kOneLaunchBytes / (16 * kCastChunk) + 1 <= 64 && (kCastSlots + 64) * sizeof(unsigned) <= FP8_AMAX_WORKSPACE_BYTES, "a slot per lane");
 
 // The vectors of chunk b that the thread holds (zeros where there are none), and its tail element if it has one
@@ -331,7 +326,7 @@ __device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_
     const unsigned own = block_max_u32<kCastThreads>(load_chunk<DT>(x, n, bid, bid == grid - 1, v));
     __shared__ unsigned largest;
     __shared__ unsigned long long absent;                    // chunks whose maximum has not come
-    __shared__ bool last;
+    unsigned ticket = 0;                                     // of the workgroup among the readers of the slots (first lane)
     if (threadIdx.x < 64) {
         const unsigned l = threadIdx.x;
         if (l == 0 && grid > 1) __hip_atomic_store(&ws[kCastSlots + bid], own | 0x80000000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -349,7 +344,8 @@ __device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_
         if (l == 0) {
             largest = m;
             absent = ~here;
-            last = grid > 1 && __hip_atomic_fetch_add(&ws[kCastDone], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == grid - 1;
+            // (nobody waits for the answer before the end: waited for here it was 0.8 us of every workgroup's time)
+            if (grid > 1) ticket = __hip_atomic_fetch_add(&ws[kCastDone], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     __syncthreads();
@@ -380,7 +376,7 @@ __device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_
     }
     const size_t t = nvec * Elem<DT>::per_vec + threadIdx.x;
     if (bid == grid - 1 && t < n) q[t] = (uint8_t)encode_bits<FMT>(load_scalar<DT>(x, t) * s);
-    if (last && threadIdx.x < 64) {
+    if (threadIdx.x < 64 && grid > 1 && (unsigned)__builtin_amdgcn_readfirstlane((int)ticket) == grid - 1) {
         if (threadIdx.x < grid) __hip_atomic_store(&ws[kCastSlots + threadIdx.x], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (threadIdx.x == 0) __hip_atomic_store(&ws[kCastDone], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

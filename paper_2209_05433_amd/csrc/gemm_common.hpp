@@ -99,6 +99,23 @@ int FP8MM_SMALL_NAME(1)(const GemmArgs& g, int form);
 int FP8MM_SMALL_NAME(2)(const GemmArgs& g, int form);
 int FP8MM_SMALL_NAME(3)(const GemmArgs& g, int form);
 
+// The whole scaled product of a small problem in one launch (scaled_gemm_small.hip), one translation unit per pair of storage orders.  g: the
+// product of fp8_scaled_gemm (g.A, g.B: where the operands' FP8 bytes go; factors from scale_out).  launch_scaled_gemm_small sets `took` to
+// whether it took the problem (scaled_gemm_small_takes); nothing has been launched where it did not.
+constexpr int kScaledSmallLds = 160 * 1024 - 1024;         // dynamic LDS at most (the kernel has a few static words)
+constexpr int kScaledSmallRow = 2048;                      // K elements of this many bytes at most
+int scaled_gemm_small_lds(const GemmArgs& g);
+int launch_scaled_gemm_small(const GemmArgs& g, const void* a, const void* b, int in_dtype, float* amax_out, float* scale_out, void* workspace, bool& took);
+#define FP8MM_SCALED_NAME_(l) launch_scaled_gemm_small_l##l
+#define FP8MM_SCALED_NAME(l) FP8MM_SCALED_NAME_(l)
+#define FP8MM_DECLARE_SCALED(l) \
+    int FP8MM_SCALED_NAME(l)(const GemmArgs& g, const void* a, const void* b, int in_dtype, float* amax_out, float* scale_out, void* workspace);
+FP8MM_DECLARE_SCALED(0)
+FP8MM_DECLARE_SCALED(1)
+FP8MM_DECLARE_SCALED(2)
+FP8MM_DECLARE_SCALED(3)
+#undef FP8MM_DECLARE_SCALED
+
 // Split-K (gemm_splitk.hip): K cut into `splits` slices of pairs_per_split stage pairs.
 constexpr int kMaxSplitK = 64;
 struct SplitPlan { int splits, pairs_per_split, tile_n; };

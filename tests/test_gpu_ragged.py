@@ -33,6 +33,55 @@ def guards_hold(buf, n, off):
     return bool((b[:off] == 0xAA).all() and (b[off + n:] == 0xAA).all())
 
 
+# one tile; tiles and chunks with one vector more and less than a whole one; the smallest and the longest K; tiles that share their chunks unevenly
+SCALED = [(8, 8, 8), (32, 32, 128), (40, 24, 136), (256, 256, 256), (24, 1000, 120), (1000, 40, 264), (72, 200, 1024), (8, 64, 512), (33, 65, 520)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", SCALED)
+def test_scaled_product_in_one_launch_equals_the_separate_calls(M, N, K, transA, transB, dtype):
+    """fp8_scaled_gemm of a few small tiles is one launch: every result bit for bit that of the separate calls, with and
+    without waiting for the other workgroups, both modes, between guards, again and again on one workspace; an output that
+    shares memory with an operand (which keeps the launches apart) too."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    a = torch.randn((K, M) if transA else (M, K), device="cuda", generator=g).mul_(7.0).to(DTYPES[dtype])
+    b = torch.randn((N, K) if transB else (K, N), device="cuda", generator=g).to(DTYPES[dtype])
+    a.view(-1)[-1], b.view(-1)[-1] = 900.0, -300.0
+    if M > 8:
+        a.view(-1)[3] = float("nan") if K == 120 else 0.0
+    ws = torch.zeros(2 * fp8.FP8_AMAX_WORKSPACE_BYTES // 4, dtype=torch.int32, device="cuda")
+    new = lambda n, dt: torch.full((n + 128,), 3, dtype=dt, device="cuda")
+    cut = lambda t, *shape: t[64:t.numel() - 64].view(*shape)
+    for out, flags in ((torch.float32, 0), (torch.bfloat16, fp8.FP8_GEMM_MFMA8)):
+        def buffers():
+            return [new(a.numel(), torch.uint8), new(b.numel(), torch.uint8), new(M * N, out), torch.zeros(2, device="cuda"), torch.zeros(2, device="cuda")]
+        def views(t):
+            return cut(t[0], *a.shape), cut(t[1], *b.shape), cut(t[2], M, N), t[3], t[4]
+        qa, qb, c, amax, scale = views(buffers())
+        fp8.fp8_amax_scale_multi((a, b), (E5M2, E4M3), amax, scale, torch.zeros_like(ws))
+        fp8.fp8_quantize_multi((a, b), (E5M2, E4M3), scale, (qa, qb))
+        fp8.fp8_gemm_ex(qa, E5M2, transA, qb, E4M3, transB, c, scale[0:1], scale[1:2], flags=flags)
+        want = [t.clone() for t in (qa, qb, c, amax, scale)]
+        for patience in (0, 1, 0):
+            bufs = buffers()
+            got = views(bufs)
+            with knob(fp8.FP8_KNOB_PATIENCE, patience):
+                fp8.fp8_scaled_gemm(a, E5M2, transA, b, E4M3, transB, got[0], got[1], got[3], got[4], ws, got[2], flags)
+            torch.cuda.synchronize()
+            assert not bool(ws.any())
+            for x, y in zip(got, want):
+                assert torch.equal(x.contiguous().view(torch.uint8), y.view(torch.uint8)), (out, patience)
+            for t in bufs[:3]:
+                assert bool((t[:64] == 3).all()) and bool((t[-64:] == 3).all())
+    if M * N * 4 <= a.numel() * a.element_size():
+        c_in_a = a.view(-1).view(torch.uint8)[:M * N * 4].view(torch.float32).view(M, N)
+        qa, qb, c, amax, scale = views([new(a.numel(), torch.uint8), new(b.numel(), torch.uint8), new(M * N, torch.float32), torch.zeros(2, device="cuda"), torch.zeros(2, device="cuda")])
+        fp8.fp8_scaled_gemm(a, E5M2, transA, b, E4M3, transB, qa, qb, amax, scale, ws, c)
+        fp8.fp8_scaled_gemm(a, E5M2, transA, b, E4M3, transB, qa, qb, amax, scale, ws, c_in_a)
+        assert torch.equal(c.contiguous().view(torch.uint8), c_in_a.contiguous().view(torch.uint8))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("rows,cols,off", [(127, 255, 0), (129, 257, 1), (136, 264, 0), (8, 3, 1), (3, 8, 0), (257, 513, 3), (140, 126, 0), (128, 256, 1),
                                            # the line between tiles and one element per lane: few rows, few columns, few elements
