@@ -376,7 +376,7 @@ int fp8_gemm_fused(const uint8_t* A, int fmtA, int transA, const uint8_t* B, int
  * single-precision accumulation, and the factors taken out once per output.  It does on `stream` what
  * fp8_amax_scale_multi, fp8_quantize_multi and fp8_gemm_ex (factors read from scale_out) do in that
  * order, and every result is theirs bit for bit; what it saves is the host time between short dependent
- * launches, for operands of up to 2.5 MB together one of the launches (amax and cast read them once), and for a few
+ * launches, for operands of up to about 40 MB together one of the launches (amax and cast read them once), and for a few
  * small tiles two (one launch does it all: 256 x 256 x 256 from fp32 18 us in separate calls, 7.2 in this one).
  *   a, b        the operands in the wide type in_dtype, stored as fp8_gemm_ex stores A and B
  *               (a: M x K, or K x M if transA; b: K x N, or N x K if transB); alignment as for fp8_amax
@@ -470,7 +470,7 @@ int fp8_gemm_form(const uint8_t* A, int transA, const uint8_t* B, int transB, co
  *                         then names the kernel that runs), 2 / 3 / 4 always, with tiles of 32 x 32 /
  *                         32 x 64 / 64 x 64 (of the last, the form the model prefers or FP8_KNOB_SMALL_64
  *                         names) (FP8MM_SMALL)
- *   FP8_KNOB_PATIENCE     the one-launch amax + cast (+ product) of fp8_scaled_gemm: 0 a workgroup waits 200 us for the other
+ *   FP8_KNOB_PATIENCE     the one-launch amax + cast (+ product) of fp8_scaled_gemm: 0 a workgroup waits 200 us (2 ms where more than 64 take part) for the other
  *                         workgroups' maxima before it computes the missing ones itself, 1 it does not wait
  *                         (FP8MM_PATIENCE)
  *   FP8_KNOB_TILE_192     the tiled kernel's tile of 256 x 192: 0 where the dispatcher's model of the run time

@@ -274,9 +274,9 @@ __global__ __launch_bounds__(kThreads) void quantize_multi_kernel(MultiTensors m
 }
 
 // ------------------------------------------------------------------------------------------
-// amax, factor and cast of small tensors (up to kMultiMax of them) in ONE launch that reads them once
-// (fp8_scaled_gemm).  Two launches on operands of this size cost what launches cost, on the host and
-// between the kernels; here a workgroup keeps its chunk of 64 KB in registers while the maxima of all
+// amax, factor and cast of tensors that fit the chip's registers (up to kMultiMax of them) in ONE launch that reads them once
+// (fp8_scaled_gemm).  Two launches cost what launches cost, on the host and
+// between the kernels, and a second read; here a workgroup keeps its chunk in registers while the maxima of all
 // chunks of the tensor meet in the workspace, and casts it from there:
 //   - workgroup b leaves its maximum in slot b and reads the others until all are there.  A slot holds
 //     the maximum with bit 31 set (maxima have it clear), so the value is its own flag: one store and
@@ -286,82 +286,87 @@ __global__ __launch_bounds__(kThreads) void quantize_multi_kernel(MultiTensors m
 //   - the last workgroup to have read the slots clears them for the next call.  A workgroup that gave up has
 //     not seen its own maximum arrive: it is waited for before the workgroup counts itself among the readers, or it
 //     could land behind the clearing.
-// Measured, amax + cast of both operands, two launches -> one: 0.5 MB of fp32 6.9 -> 3.8 us, 1 MB of bf16 7.4
-// -> 5.0.  The exchange takes longer the more workgroups take part (4 MB: 7.9 -> 9.1; 42 MB: 20.4 -> 22 - 25 with
-// chunks of 32 ... 256 KB), where two launches are the better form: their second read comes out of the
-// memory-side cache.
+// Up to kMostChunks chunks of the size that the tensors need.  Measured, amax + cast of both operands, two launches -> one: 0.5 MB of fp32
+// 6.9 -> 3.8 us, 1 MB of bf16 7.4 -> 5.0; whole steps 630 x 1472 x 640 (2.6 MB) 17.2 -> 14.3, 387 x 960 x 1920 (5 MB) 18.4 -> 15.7, 1092 x 1856 x
+// 2624 (15 MB) 37.4 -> 35.7, 1638 x 704 x 6272 (28 MB) 50.4 -> 44.5; 90 steps from 2.5 to 39 MB all faster, by 2 to 25 %.  The longer the chunks
+// take, the longer a workgroup waits before it computes what is missing (another stream's tiles may hold compute units for a millisecond, and
+// the missing maxima of large tensors are many bytes).
 // ------------------------------------------------------------------------------------------
-constexpr int kCastThreads = 512, kCastVecs = 8;                     // a chunk: 8 vectors per lane
-constexpr size_t kCastChunk = (size_t)kCastThreads * kCastVecs;      // vectors
-constexpr size_t kOneLaunchBytes = (size_t)5 << 19;                  // input up to which one launch is the better form: 2.5 MB
-static_assert(kOneLaunchBytes / (16 * kCastChunk) + 1 <= 64 && (kCastSlots + 64) * sizeof(unsigned) <= FP8_AMAX_WORKSPACE_BYTES, "a slot per lane");
+constexpr unsigned kMostChunks = 256;                                // of a launch: one workgroup per compute unit, which all should be running
+static_assert((kCastSlots + kMostChunks) * sizeof(unsigned) <= FP8_AMAX_WORKSPACE_BYTES, "a slot per chunk");
 
 // The vectors of chunk b that the thread holds (zeros where there are none), and its tail element if it has one
 // (the elements behind the last whole vector belong to the last chunk): their largest magnitude.
-template <int DT>
-__device__ __forceinline__ unsigned load_chunk(const void* x, size_t n, size_t b, bool tail, u32x4 (&v)[kCastVecs])
+template <int DT, int THREADS, int VECS>
+__device__ __forceinline__ unsigned load_chunk(const void* x, size_t n, size_t b, bool tail, u32x4 (&v)[VECS])
 {
     const u32x4_any* xv = (const u32x4_any*)x;
     const size_t nvec = n / Elem<DT>::per_vec;
     unsigned run = 0;
 #pragma unroll
-    for (int k = 0; k < kCastVecs; ++k) {
-        const size_t i = b * kCastChunk + threadIdx.x + (size_t)k * kCastThreads;
+    for (int k = 0; k < VECS; ++k) {
+        const size_t i = b * ((size_t)THREADS * VECS) + threadIdx.x + (size_t)k * THREADS;
         v[k] = (u32x4){0u, 0u, 0u, 0u};
         if (i < nvec) v[k] = xv[i];
     }
 #pragma unroll
-    for (int k = 0; k < kCastVecs; ++k) run = vec_mag_max<DT>(v[k], run);
+    for (int k = 0; k < VECS; ++k) run = vec_mag_max<DT>(v[k], run);
     const size_t t = nvec * Elem<DT>::per_vec + threadIdx.x;
     const unsigned r = run_to_bits<DT>(run);
     return tail && t < n ? max(r, scalar_mag<DT>(x, t)) : r;
 }
 
-template <int DT, int FMT>
+template <int DT, int FMT, int THREADS, int VECS>
 __device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_t n, uint8_t* __restrict__ q, float* __restrict__ amax_out,
                                                float* __restrict__ scale_out, unsigned* __restrict__ ws, unsigned bid, unsigned grid, unsigned patience)
 {
     constexpr int VPI = DT == FP8_BF16 ? 2 : 4;              // vectors that make 16 elements
-    u32x4 v[kCastVecs];
-    const unsigned own = block_max_u32<kCastThreads>(load_chunk<DT>(x, n, bid, bid == grid - 1, v));
+    u32x4 v[VECS];
+    const unsigned own = block_max_u32<THREADS>(load_chunk<DT, THREADS, VECS>(x, n, bid, bid == grid - 1, v));
     __shared__ unsigned largest;
-    __shared__ unsigned long long absent;                    // chunks whose maximum has not come
+    __shared__ unsigned long long absent[kMostChunks / 64];  // chunks whose maximum has not come
     unsigned ticket = 0;                                     // of the workgroup among the readers of the slots (first lane)
     if (threadIdx.x < 64) {
         const unsigned l = threadIdx.x;
         if (l == 0 && grid > 1) __hip_atomic_store(&ws[kCastSlots + bid], own | 0x80000000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const unsigned long long began = wall_clock64();
-        unsigned p = l == 0 && grid == 1 ? own | 0x80000000u : l < grid ? 0u : 0x80000000u;
-        while (!(p >> 31)) {
-            p = __hip_atomic_load(&ws[kCastSlots + l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (wall_clock64() - began > patience) break;
+        unsigned m = own;
+        for (unsigned k = 0; 64 * k < grid; ++k) {
+            const unsigned slot = 64 * k + l;
+            unsigned p = slot < grid && grid > 1 ? 0u : 0x80000000u;
+            while (!(p >> 31)) {
+                p = __hip_atomic_load(&ws[kCastSlots + slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (wall_clock64() - began > patience) break;
+            }
+            m = max(m, p & 0x7fffffffu);
+            const unsigned long long here = __ballot(p >> 31);
+            if (l == 0) absent[k] = ~here;
         }
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         __builtin_amdgcn_s_waitcnt(0x0070);                  // vmcnt(0): the own maximum has been acknowledged
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        const unsigned long long here = __ballot(p >> 31);
-        const unsigned m = wave_max_u32(p & 0x7fffffffu);
+        m = wave_max_u32(m);
         if (l == 0) {
             largest = m;
-            absent = ~here;
             // (nobody waits for the answer before the end: waited for here it was 0.8 us of every workgroup's time)
             if (grid > 1) ticket = __hip_atomic_fetch_add(&ws[kCastDone], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     __syncthreads();
-    for (unsigned long long left = absent; left; left &= left - 1) {       // (never, unless the chip was busy for kPatience)
-        const unsigned b = (unsigned)__builtin_ctzll(left);
-        u32x4 other[kCastVecs];
-        const unsigned m = block_max_u32<kCastThreads>(load_chunk<DT>(x, n, b, b == grid - 1, other));
-        if (threadIdx.x == 0) largest = max(largest, m);
-        __syncthreads();
-    }
+    for (unsigned k = 0; 64 * k < grid; ++k)
+        for (unsigned long long left = absent[k]; left; left &= left - 1) {    // (never, unless the chip was busy for kPatience)
+            const unsigned b = 64 * k + (unsigned)__builtin_ctzll(left);
+            u32x4 other[VECS];
+            const unsigned m = block_max_u32<THREADS>(load_chunk<DT, THREADS, VECS>(x, n, b, b == grid - 1, other));
+            if (threadIdx.x == 0) largest = max(largest, m);
+            __syncthreads();
+        }
     const float a = as_f32(largest), s = scale_rule(a, FMT);
     if (bid == 0 && threadIdx.x == 0) { *amax_out = a; *scale_out = s; }
-    const size_t nvec = n / Elem<DT>::per_vec, first = bid * kCastChunk + threadIdx.x;
+    const size_t nvec = n / Elem<DT>::per_vec, first = bid * ((size_t)THREADS * VECS) + threadIdx.x;
     typename Piece<DT>::type* qp = (typename Piece<DT>::type*)q;
 #pragma unroll
-    for (int g = 0; g < kCastVecs / VPI; ++g) {
+    for (int g = 0; g < VECS / VPI; ++g) {
         u32x4 item[VPI];
         float y[16];
 #pragma unroll
@@ -370,27 +375,27 @@ __device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_
         const u32x4 o = encode16<FMT, kCastCvt>(y);
 #pragma unroll
         for (int k = 0; k < VPI; ++k) {
-            const size_t i = first + (size_t)(g * VPI + k) * kCastThreads;
+            const size_t i = first + (size_t)(g * VPI + k) * THREADS;
             if (i < nvec) qp[i] = Piece<DT>::of(o, k);
         }
     }
     const size_t t = nvec * Elem<DT>::per_vec + threadIdx.x;
     if (bid == grid - 1 && t < n) q[t] = (uint8_t)encode_bits<FMT>(load_scalar<DT>(x, t) * s);
     if (threadIdx.x < 64 && grid > 1 && (unsigned)__builtin_amdgcn_readfirstlane((int)ticket) == grid - 1) {
-        if (threadIdx.x < grid) __hip_atomic_store(&ws[kCastSlots + threadIdx.x], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (unsigned i = threadIdx.x; i < grid; i += 64) __hip_atomic_store(&ws[kCastSlots + i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (threadIdx.x == 0) __hip_atomic_store(&ws[kCastDone], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
-template <int DT>
-__global__ __launch_bounds__(kCastThreads) void amax_cast_kernel(MultiTensors m, float* __restrict__ amax_out, float* __restrict__ scale_out,
+template <int DT, int THREADS, int VECS>
+__global__ __launch_bounds__(THREADS) void amax_cast_kernel(MultiTensors m, float* __restrict__ amax_out, float* __restrict__ scale_out,
                                                                 unsigned* __restrict__ ws, unsigned patience)
 {
     const int t = multi_find(m, blockIdx.x);
     const unsigned bid = blockIdx.x - m.first[t], grid = m.first[t + 1] - m.first[t];
     unsigned* w = ws + (size_t)t * (FP8_AMAX_WORKSPACE_BYTES / 4);
-    if (m.fmt[t] == FP8_E4M3) amax_cast_body<DT, FP8_E4M3>(m.x[t], m.n[t], m.q[t], amax_out + t, scale_out + t, w, bid, grid, patience);
-    else amax_cast_body<DT, FP8_E5M2>(m.x[t], m.n[t], m.q[t], amax_out + t, scale_out + t, w, bid, grid, patience);
+    if (m.fmt[t] == FP8_E4M3) amax_cast_body<DT, FP8_E4M3, THREADS, VECS>(m.x[t], m.n[t], m.q[t], amax_out + t, scale_out + t, w, bid, grid, patience);
+    else amax_cast_body<DT, FP8_E5M2, THREADS, VECS>(m.x[t], m.n[t], m.q[t], amax_out + t, scale_out + t, w, bid, grid, patience);
 }
 
 }  // namespace
@@ -625,35 +630,50 @@ int launch_quantize_multi(int count, const void* const* x, const size_t* n, int 
     return check_launch("quantize_multi");
 }
 
-// amax, factors and casts of `count` tensors: one launch where the tensors are small (see amax_cast_kernel), else
+// The forms of the one-launch amax + cast: workgroup and vectors of 16 bytes per lane, which make a chunk of 64, 128 or 160 KB.  (With more
+// vectors a lane's registers went to scratch memory, and operands of 48 to 64 MB took 3 to 10 % longer than in two launches.)
+constexpr struct { int threads, vecs; } kCastForm[] = {{512, 8}, {1024, 8}, {1024, 10}};
+constexpr int kCastForms = 3;
+
+// amax, factors and casts of `count` tensors: one launch where the tensors fit (see amax_cast_kernel), else
 // the two launches of the multi-tensor forms.
 int launch_amax_cast(int count, const void* const* x, const size_t* n, int in_dtype, const int* fmt, float* amax_out, float* scale_out,
                      void* workspace, uint8_t* const* q_out, hipStream_t stream)
 {
-    const size_t esz = in_dtype == FP8_F32 ? 4 : 2;
-    size_t bytes = 0;
+    const size_t per_vec = in_dtype == FP8_F32 ? 4 : 8;
     bool one = cast_path() == kCastCvt;
-    for (int i = 0; i < count; ++i) {
-        one = one && n[i] > 0;
-        bytes += n[i] * esz;
-    }
-    if (!one || bytes > kOneLaunchBytes) {
+    for (int i = 0; i < count; ++i) one = one && n[i] > 0;
+    auto chunks_of = [&](int i, size_t vecs) { return std::max<size_t>(1, (n[i] / per_vec + vecs - 1) / vecs); };
+    auto chunks = [&](size_t vecs) { size_t c = 0; for (int i = 0; i < count; ++i) c += chunks_of(i, vecs); return c; };
+    int form = -1;
+    if (one)
+        for (int f = 0; f < kCastForms && form < 0; ++f)
+            if (kCastForm[f].vecs % (in_dtype == FP8_F32 ? 4 : 2) == 0 && chunks((size_t)kCastForm[f].threads * kCastForm[f].vecs) <= kMostChunks) form = f;
+    if (form < 0) {
         if (int e = launch_amax_scale_multi(count, x, n, in_dtype, fmt, amax_out, scale_out, workspace, stream)) return e;
         return launch_quantize_multi(count, x, n, in_dtype, fmt, scale_out, q_out, stream);
     }
     MultiTensors m{};
     m.count = count;
     unsigned total = 0;
+    const size_t chunk = (size_t)kCastForm[form].threads * kCastForm[form].vecs;
     for (int i = 0; i < count; ++i) {
         m.x[i] = x[i]; m.q[i] = q_out[i]; m.n[i] = n[i]; m.fmt[i] = fmt[i]; m.first[i] = total;
-        total += (unsigned)std::max<size_t>(1, (n[i] * esz / 16 + kCastChunk - 1) / kCastChunk);
+        total += (unsigned)chunks_of(i, chunk);
     }
     for (int i = count; i <= kMultiMax; ++i) m.first[i] = total;
-    const unsigned patience = knob(FP8_KNOB_PATIENCE) ? 0 : kPatience;
-    if (in_dtype == FP8_F32)
-        enqueue(amax_cast_kernel<FP8_F32>, dim3(total), dim3(kCastThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace, patience);
-    else
-        enqueue(amax_cast_kernel<FP8_BF16>, dim3(total), dim3(kCastThreads), 0, stream, m, amax_out, scale_out, (unsigned*)workspace, patience);
+    const unsigned patience = knob(FP8_KNOB_PATIENCE) ? 0 : total <= 64 ? kPatience : 10 * kPatience;
+    unsigned* ws = (unsigned*)workspace;
+#define FP8MM_LAUNCH_CAST(DT, THREADS, VECS) \
+    enqueue((amax_cast_kernel<DT, THREADS, VECS>), dim3(total), dim3(THREADS), 0, stream, m, amax_out, scale_out, ws, patience)
+    if (in_dtype == FP8_F32) {
+        if (form == 0) FP8MM_LAUNCH_CAST(FP8_F32, 512, 8); else FP8MM_LAUNCH_CAST(FP8_F32, 1024, 8);
+    } else {
+        if (form == 0) FP8MM_LAUNCH_CAST(FP8_BF16, 512, 8);
+        else if (form == 1) FP8MM_LAUNCH_CAST(FP8_BF16, 1024, 8);
+        else FP8MM_LAUNCH_CAST(FP8_BF16, 1024, 10);
+    }
+#undef FP8MM_LAUNCH_CAST
     return check_launch("amax_cast");
 }
 

@@ -427,14 +427,16 @@ namespace {
 bool overlap(const void* p, int64_t np, const void* q, int64_t nq) { return (const char*)p < (const char*)q + nq && (const char*)q < (const char*)p + np; }
 
 // Which problems one launch takes: those of 32 x 32 tiles, at most one a compute unit (256: a workgroup waits for the maxima of others, which
-// should be running) and rows and columns of up to 2048 bytes, which are read and rounded once per tile that needs them.  Up to there it was
-// the faster form of 35 drawn products by 1.14 to 1.56; with rows of 3 - 4 KB 39 x 512 x 1872 took 15.1 us against 13.6, 46 x 256 x 1472 12.2 against 11.5.
+// should be running), rows and columns of up to 2048 bytes (a thread's registers) and, of all tiles together, 288 KB along K: they are read and
+// rounded once per tile.  90 random products, amax + cast and product apart / together: 61 x 64 x 168 of fp32 9.9 / 6.7 us, 163 x 24 x 656 of bf16
+// 11.1 / 9.6, 693 x 304 x 408 (180 KB) 12.1 / 11.1, 120 x 1896 x 264 of fp32 (253 KB) 11.4 / 11.0, but 308 x 704 x 824 (362 KB) 12.6 / 13.3;
+// geometric mean 1.37.
 // Vectors that lie wholly inside an operand or outside; operands that share no memory with an output (a tile is written while others
 // are still being loaded).
 bool scaled_gemm_small_takes(const GemmArgs& g, const void* a, const void* b, int in_dtype, const GemmPlan& plan)
 {
     const int64_t esz = in_dtype == FP8_F32 ? 4 : 2, pv = 16 / esz;
-    if (plan.small != SMALL_32x32 || cast_path() != kCastCvt) return false;
+    if (plan.small != SMALL_32x32 || cast_path() != kCastCvt || tile_count(g, 32) * g.K * esz > (288 << 10)) return false;
     if ((g.transA ? g.M : g.K) % pv || (g.transB ? g.K : g.N) % pv || scaled_gemm_small_lds(g) > kScaledSmallLds) return false;
     const int64_t na = g.M * g.K, nb = g.K * g.N, nc = g.M * g.N * out_elem_size(g.ep.out_kind);
     for (auto [x, n] : {std::pair<const void*, int64_t>{a, na * esz}, {b, nb * esz}})
@@ -454,6 +456,7 @@ int launch_scaled_gemm_small(const GemmArgs& g, const void* a, const void* b, in
     if (!scaled_gemm_small_takes(g, a, b, in_dtype, plan)) return FP8_OK;
     took = true;
     GemmArgs gs = g;
+    gs.ep.sA_dev = gs.ep.sB_dev = nullptr;                   // (the kernel has the factors before it writes them)
     if (plan.kernel == GEMM_MFMA_ANY) gs.acc = ACC_F16;      // as launch_gemm
     return table[(g.transA ? 2 : 0) + (g.transB ? 1 : 0)](gs, a, b, in_dtype, amax_out, scale_out, workspace);
 }

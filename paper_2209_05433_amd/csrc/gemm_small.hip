@@ -58,6 +58,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(
 
     // the factor that the thread will take the reciprocal of, loaded while the products run
     const float sA_host = ep.sA, sB_host = ep.sB;         // by value: a choice between two memory locations would cost scratch
+    const bool uniform = !ep.a_per_row && !ep.b_per_col;
     float factor = 1.0f;
     if (ep.a_per_row && tid < 32 * RM) factor = ep.sA_dev[m0 + tid < M ? m0 + tid : M - 1];
     if (ep.b_per_col && tid >= 32 * RM && tid < 32 * (RM + RN)) factor = ep.sB_dev[n0 + tid - 32 * RM < N ? n0 + tid - 32 * RM : N - 1];
@@ -139,8 +140,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(
         multiply(xa, xb);
     }
 
-    const double a_all = ep.a_per_row ? 1.0 : (double)scale_value(ep.sA_dev, sA_host), b_all = ep.b_per_col ? 1.0 : (double)scale_value(ep.sB_dev, sB_host);
-    small_tile_end<RM, RN, NW, PER_WAVE>(acc, lds, C, M, N, m0, n0, ep, a_all, b_all, factor, tid, l, w);
+    small_tile_end<RM, RN, NW, PER_WAVE>(acc, lds, C, M, N, m0, n0, ep, sA_host, sB_host, uniform, factor, tid, l, w);
 }
 
 template <int FA, int FB, int ACC, bool A_KC, bool B_KC, int RM, int RN, int S, int NW, int D>

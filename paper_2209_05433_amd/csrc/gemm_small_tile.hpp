@@ -119,18 +119,17 @@ constexpr int small_lds_per_wave()
 }
 
 // The end of a tile of 32 RM x 32 RN outputs at (m0, n0) whose sums lie in the NW waves' accumulators; PER_WAVE bytes of LDS are each wave's.
-// a_all, b_all: the operands' factors (1 where there is one per row / column); factor: the row's or column's that the thread
-// will take the reciprocal of.
+// sA_host, sB_host: the operands' factors where ep names no place for them; factor: the row's or column's that the thread will take the reciprocal of.
 template <int RM, int RN, int NW, int PER_WAVE>
 __device__ __forceinline__ void small_tile_end(const v16f (&acc)[RN][RM], uint8_t* lds, void* __restrict__ C, int64_t M, int64_t N, int64_t m0, int64_t n0,
-                                               const EpilogueArgs& ep, double a_all, double b_all, float factor, int tid, int l, int w)
+                                               const EpilogueArgs& ep, float sA_host, float sB_host, bool uniform, float factor, int tid, int l, int w)
 {
     constexpr int RED = 32 * RM * RED_PITCH * 4;          // bytes of a wave's sums
-    const bool uniform = !ep.a_per_row && !ep.b_per_col;
     // The waves' sums meet in LDS, 32 columns at a time; a thread adds 4 consecutive columns of a row.  With factors
     // per row or column, their reciprocals (of the tile's rows, then of its columns; 1 for a factor that the
     // whole tensor has) lie behind the first wave's sums, in 64 bits: the product, rounded once, is as accurate as
     // dividing by the product of the factors, and finite wherever that is (1 / sA alone may leave the 32-bit range).
+    const double a_all = ep.a_per_row ? 1.0 : (double)scale_value(ep.sA_dev, sA_host), b_all = ep.b_per_col ? 1.0 : (double)scale_value(ep.sB_dev, sB_host);
     const double r_all = 1.0 / (a_all * b_all);
     const float sD = ep.out_kind >= OUT_E4M3 ? scale_value(ep.sD_dev, 1.0f) : 1.0f;
     double* row_factors = (double*)(lds + RED);

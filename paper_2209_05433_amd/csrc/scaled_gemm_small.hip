@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kTileThreads) void scaled_gemm_small_kernel(ScaledA
             }
         }
     }
-    small_tile_end<1, 1, kWaves, 32 * RED_PITCH * 4>(acc, lds, C, M, N, m0, n0, ep, (double)sa, (double)sb, 1.0f, tid, l, w);
+    small_tile_end<1, 1, kWaves, 32 * RED_PITCH * 4>(acc, lds, C, M, N, m0, n0, ep, sa, sb, true, 1.0f, tid, l, w);
     if (w == 0 && (unsigned)__builtin_amdgcn_readfirstlane((int)ticket) == total - 1) {
         for (unsigned i = l; i < tiles_m; i += 64) __hip_atomic_store(&ws_a[kCastSlots + i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (unsigned i = l; i < tiles_n; i += 64) __hip_atomic_store(&ws_b[kCastSlots + i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
