@@ -239,7 +239,7 @@ int fp8_quantize_transpose(const void* x, int64_t rows, int64_t cols, int in_dty
  * exactly to fp16 in registers and multiplied by the fp16 matrix-core instructions,
  * whose accumulation is fp32-grade.  M, N or K equal to 0 is valid (K == 0 writes
  * zeros).  Any shape is accepted.  The tiled matrix-core kernel takes those with K a
- * multiple of 16 and 16-byte aligned A and B whose operand rows start on 16-byte
+ * multiple of 16 (any K where A is given as K x M and B as K x N, with one factor each) and 16-byte aligned A and B whose operand rows start on 16-byte
  * boundaries: N a multiple of 16 where B is given as K x N, M a multiple of 16 where A is
  * given as K x M (see fp8_gemm_ex); with B given as N x K any N goes, and C may lie
  * anywhere.  The other shapes and alignments take a second matrix-core kernel (register-staged
@@ -406,7 +406,7 @@ int fp8_scaled_gemm(const void* a, const void* b, int in_dtype, int transA, int 
  * FP8_PLAN_MFMA_ANY (the matrix-core kernel for every other shape and alignment: an odd K, operand
  * rows that do not start on 16-byte boundaries, unaligned pointers; about 0.9 of the tiled
  * kernel's rate, fifteen to twenty-five times that of plain FMAs; it computes in the default accumulation mode also under FP8_GEMM_MFMA8, which
- * meets that flag's bound a fortiori) or FP8_PLAN_FMA_KERNEL (plain FMAs: only when forced by
+ * meets that flag's bound a fortiori, and so does every kernel where K is not a multiple of 16) or FP8_PLAN_FMA_KERNEL (plain FMAs: only when forced by
  * FP8_KNOB_GEMM_KERNEL or for outputs of more than 2^31 - 1 tiles of 128 x 128), ORed with
  * FP8_PLAN_ELEMENTWISE_STORES where the rows of the output (or the per-column factors) do not start on
  * 16-byte boundaries (they are stored in vectors all the same; the name is from when they were not), and

@@ -30,6 +30,18 @@ int check_launch(const char* what)
     return FP8_OK;
 }
 
+// ---- compute units ----------------------------------------------------------------------------
+int compute_units()
+{
+    static std::atomic<int> cached[64];
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 256;
+    if (dev < 64 && (n = cached[dev].load(std::memory_order_relaxed)) > 0) return n;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+    if (dev < 64) cached[dev].store(n, std::memory_order_relaxed);
+    return n;
+}
+
 // ---- tuning knobs -------------------------------------------------------------------------------
 static std::atomic<int> g_knob[FP8_KNOB_COUNT];
 static std::once_flag g_knob_once;

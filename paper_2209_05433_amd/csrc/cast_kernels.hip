@@ -292,7 +292,7 @@ __global__ __launch_bounds__(kThreads) void quantize_multi_kernel(MultiTensors m
 // take, the longer a workgroup waits before it computes what is missing (another stream's tiles may hold compute units for a millisecond, and
 // the missing maxima of large tensors are many bytes).
 // ------------------------------------------------------------------------------------------
-constexpr unsigned kMostChunks = 256;                                // of a launch: one workgroup per compute unit, which all should be running
+constexpr unsigned kMostChunks = 256;                                // of a launch, and no more than compute units: all workgroups should be running
 static_assert((kCastSlots + kMostChunks) * sizeof(unsigned) <= FP8_AMAX_WORKSPACE_BYTES, "a slot per chunk");
 
 // The vectors of chunk b that the thread holds (zeros where there are none), and its tail element if it has one
@@ -645,10 +645,11 @@ int launch_amax_cast(int count, const void* const* x, const size_t* n, int in_dt
     for (int i = 0; i < count; ++i) one = one && n[i] > 0;
     auto chunks_of = [&](int i, size_t vecs) { return std::max<size_t>(1, (n[i] / per_vec + vecs - 1) / vecs); };
     auto chunks = [&](size_t vecs) { size_t c = 0; for (int i = 0; i < count; ++i) c += chunks_of(i, vecs); return c; };
+    const size_t most = std::min<size_t>(kMostChunks, compute_units());
     int form = -1;
     if (one)
         for (int f = 0; f < kCastForms && form < 0; ++f)
-            if (kCastForm[f].vecs % (in_dtype == FP8_F32 ? 4 : 2) == 0 && chunks((size_t)kCastForm[f].threads * kCastForm[f].vecs) <= kMostChunks) form = f;
+            if (kCastForm[f].vecs % (in_dtype == FP8_F32 ? 4 : 2) == 0 && chunks((size_t)kCastForm[f].threads * kCastForm[f].vecs) <= most) form = f;
     if (form < 0) {
         if (int e = launch_amax_scale_multi(count, x, n, in_dtype, fmt, amax_out, scale_out, workspace, stream)) return e;
         return launch_quantize_multi(count, x, n, in_dtype, fmt, scale_out, q_out, stream);

@@ -43,6 +43,9 @@ inline bool valid_dtype(int d) { return d == FP8_F32 || d == FP8_BF16; }
 enum CastPath { kCastBits = 0, kCastCvt = 1, kCastBitsStrict = 2 /* non-saturating, kernels only */ };
 CastPath cast_path();
 
+// Compute units of the current device: launches whose workgroups wait for one another, and the persistent form, have at most one on each.
+int compute_units();
+
 // Current value of a tuning knob (fp8_knob_t).  The knobs are process-wide atomics, seeded once
 // from the environment (FP8MM_CAST_PATH, FP8MM_TILE_N, FP8MM_GROUP_M, FP8MM_GEMM, FP8MM_SPLIT_K)
 // and changed through fp8_set_knob(); no launch path reads the environment.

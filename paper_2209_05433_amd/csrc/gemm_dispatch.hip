@@ -451,12 +451,11 @@ int launch_scaled_gemm_small(const GemmArgs& g, const void* a, const void* b, in
     typedef int (*scaled_fn)(const GemmArgs&, const void*, const void*, int, float*, float*, void*);
     static const scaled_fn table[4] = {FP8MM_SCALED_NAME(0), FP8MM_SCALED_NAME(1), FP8MM_SCALED_NAME(2), FP8MM_SCALED_NAME(3)};
     took = false;
-    if (g.M == 0 || g.N == 0 || g.K == 0 || g.K * (in_dtype == FP8_F32 ? 4 : 2) > kScaledSmallRow || tile_count(g, 32) > 256) return FP8_OK;
+    if (g.M == 0 || g.N == 0 || g.K == 0 || g.K * (in_dtype == FP8_F32 ? 4 : 2) > kScaledSmallRow || tile_count(g, 32) > std::min(256, compute_units())) return FP8_OK;
     const GemmPlan plan = plan_gemm(g, false);
     if (!scaled_gemm_small_takes(g, a, b, in_dtype, plan)) return FP8_OK;
     took = true;
     GemmArgs gs = g;
-    gs.ep.sA_dev = gs.ep.sB_dev = nullptr;                   // (the kernel has the factors before it writes them)
     if (plan.kernel == GEMM_MFMA_ANY) gs.acc = ACC_F16;      // as launch_gemm
     return table[(g.transA ? 2 : 0) + (g.transB ? 1 : 0)](gs, a, b, in_dtype, amax_out, scale_out, workspace);
 }

@@ -716,18 +716,6 @@ int group_m_setting()
     return v > 0 ? v : GROUP_M;
 }
 
-// Compute units of the current device (the persistent form runs one workgroup on each).
-int compute_units()
-{
-    static std::atomic<int> cached[64];
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 256;
-    if (dev < 64 && (n = cached[dev].load(std::memory_order_relaxed)) > 0) return n;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-    if (dev < 64) cached[dev].store(n, std::memory_order_relaxed);
-    return n;
-}
-
 template <int FA, int FB, int ACC, bool A_KC, bool B_KC, int NB, bool PERSIST = false>
 int launch_fast(const GemmArgs& g)
 {

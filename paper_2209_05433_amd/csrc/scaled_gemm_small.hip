@@ -132,7 +132,7 @@ struct ScaledArgs {
 };
 
 template <int DT, int FMT_A, int FMT_B, int ACC, bool A_KC, bool B_KC, int NV>
-__global__ __launch_bounds__(kTileThreads) void scaled_gemm_small_kernel(ScaledArgs p, void* __restrict__ C, int M, int N, int K, EpilogueArgs ep)
+__global__ __launch_bounds__(kTileThreads) void scaled_gemm_small_kernel(ScaledArgs p, void* __restrict__ C, int M, int N, int K, int out_kind)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     typedef Operand<A_KC, 1, 2> OpA;
@@ -212,9 +212,9 @@ __global__ __launch_bounds__(kTileThreads) void scaled_gemm_small_kernel(ScaledA
     b.template cast<FMT_B>(vb, sb, slabs_b, p.qb, tm, tiles_m);
     __syncthreads();
 
-    v16f acc[1][1];
+    v16f acc;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[0][0][e] = 0.0f;
+    for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
     const OpA oa{}; const OpB ob{};
     for (int c = w; c < chunks; c += kWaves) {
 #pragma unroll
@@ -223,16 +223,45 @@ __global__ __launch_bounds__(kTileThreads) void scaled_gemm_small_kernel(ScaledA
             oa.fragments(lds + c * OpA::SLAB, sub, l, fa);
             ob.fragments(slabs_b + c * OpB::SLAB, sub, l, fb);
             if (ACC == ACC_FP8) {
-                acc[0][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[0], fa[0], acc[0][0], FMT_B, FMT_A, 0, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[0], fa[0], acc, FMT_B, FMT_A, 0, 0, 0, 0);
             } else {
 #pragma unroll
                 for (int s = 0; s < 4; ++s)
-                    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(widen8<FMT_B>(fb[0][2 * s], fb[0][2 * s + 1]), widen8<FMT_A>(fa[0][2 * s], fa[0][2 * s + 1]),
-                                                                      acc[0][0], 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(widen8<FMT_B>(fb[0][2 * s], fb[0][2 * s + 1]), widen8<FMT_A>(fa[0][2 * s], fa[0][2 * s + 1]),
+                                                                      acc, 0, 0, 0);
             }
         }
     }
-    small_tile_end<1, 1, kWaves, 32 * RED_PITCH * 4>(acc, lds, C, M, N, m0, n0, ep, sa, sb, true, 1.0f, tid, l, w);
+
+    // the waves' sums meet in LDS and are added in wave order; a thread has 4 consecutive columns of a row (as in gemm_small_kernel)
+    constexpr int RED = 32 * RED_PITCH;                   // floats of a wave's sums
+    const float r = (float)(1.0 / ((double)sa * (double)sb));
+    __syncthreads();                                      // the slabs are done with
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        *LDS_PTR(v4f, (float*)lds + w * RED + (l & 31) * RED_PITCH + 8 * q + 4 * (l >> 5)) =
+            (v4f){acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    __syncthreads();
+    const int64_t gm = m0 + (tid >> 3), gn = n0 + 4 * (tid & 7);
+    if (tid < 32 * 8 && gm < M && gn < N) {
+        const float* red = (const float*)lds + (tid >> 3) * RED_PITCH + 4 * (tid & 7);
+        v4f sum = *LDS_PTR(v4f, red);
+#pragma unroll
+        for (int v = 1; v < kWaves; ++v) sum += *LDS_PTR(v4f, red + v * RED);
+        sum *= r;
+        const int left = N - gn < 4 ? (int)(N - gn) : 4;
+        if (out_kind == OUT_F32) {
+            float* out = (float*)C + gm * N + gn;
+            if (left == 4 && ((uintptr_t)out & 15) == 0) *(v4f*)out = sum;
+            else for (int e = 0; e < left; ++e) out[e] = e == 0 ? sum.x : e == 1 ? sum.y : e == 2 ? sum.z : sum.w;
+        } else {
+            unsigned short* out = (unsigned short*)C + gm * N + gn;
+            const unsigned lo = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){sum.x, sum.y}, v2bf));
+            const unsigned hi = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){sum.z, sum.w}, v2bf));
+            if (left == 4 && ((uintptr_t)out & 7) == 0) *(v2i*)out = (v2i){(int)lo, (int)hi};
+            else for (int e = 0; e < left; ++e) out[e] = (unsigned short)((e < 2 ? lo : hi) >> (16 * (e & 1)));
+        }
+    }
     if (w == 0 && (unsigned)__builtin_amdgcn_readfirstlane((int)ticket) == total - 1) {
         for (unsigned i = l; i < tiles_m; i += 64) __hip_atomic_store(&ws_a[kCastSlots + i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (unsigned i = l; i < tiles_n; i += 64) __hip_atomic_store(&ws_b[kCastSlots + i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -258,7 +287,7 @@ int launch_typed(const GemmArgs& g, const ScaledArgs& p)
         }
     }
     const int64_t tiles = ((g.M + 31) / 32) * ((g.N + 31) / 32);
-    enqueue(kern, dim3((unsigned)tiles), dim3(kTileThreads), lds, g.stream, p, g.C, (int)g.M, (int)g.N, (int)g.K, g.ep);
+    enqueue(kern, dim3((unsigned)tiles), dim3(kTileThreads), lds, g.stream, p, g.C, (int)g.M, (int)g.N, (int)g.K, g.ep.out_kind);
     return check_launch("scaled gemm (one launch)");
 }
 
