@@ -27,11 +27,22 @@ namespace {
 constexpr int kWaves = 8, kTileThreads = 64 * kWaves;
 static_assert((kCastSlots + 256) * sizeof(unsigned) <= FP8_AMAX_WORKSPACE_BYTES, "a slot per tile row or column");
 
+// The vector without its first k elements (0 <= k < per_vec), zeros behind the rest.
+template <int DT>
+__device__ __forceinline__ u32x4 without_first(u32x4 v, int k)
+{
+    const int words = DT == FP8_F32 ? k : k >> 1;
+    if (words & 2) v = (u32x4){v.z, v.w, 0u, 0u};
+    if (words & 1) v = (u32x4){v.y, v.z, v.w, 0u};
+    if (DT == FP8_BF16 && (k & 1))
+        v = (u32x4){(v.x >> 16) | (v.y << 16), (v.y >> 16) | (v.z << 16), (v.z >> 16) | (v.w << 16), v.w >> 16};
+    return v;
+}
+
 // The 32 rows of op(A) / columns of op(B) from t0 on, in their wide type: vector j of a thread holds per_vec elements at K index
-// k(j) of a row (KC: element (r, k) at x[r K + k]) or columns at one K index (MC: at x[k ext + r]).  K (KC) or ext (MC) is a multiple of per_vec:
-// a vector lies wholly inside the tensor or outside.
-// NV: vectors per thread.
-template <int DT, bool KC, int NV>
+// k0 + j STEP of a row (KC: element (r, k) at x[r K + k]) or columns at one K index (MC: at x[k ext + r]).  NV: vectors per thread.  RAGGED: the rows in
+// memory (of K or ext elements, per_vec at least) end inside a vector: that one is loaded from the row's last elements and shifted.
+template <int DT, bool KC, int NV, bool RAGGED>
 struct Panel {
     typedef Operand<KC, 1, 2> Slab;                       // chunks of 128 along K
     static constexpr int PV = Elem<DT>::per_vec, ESZ = Elem<DT>::size;
@@ -41,6 +52,7 @@ struct Panel {
     const char* x;
     int64_t first, pitch, safe;                           // element of vector 0; elements between two vectors; a vector near by that is there
     int k0, K, to;                                        // K index of vector 0; K; where it goes in the first slab
+    int over;                                             // MC: elements of the thread's vectors beyond the end of the row
     bool row;                                             // the thread's row / columns exist
 
     __device__ __forceinline__ void setup(const void* x_, int64_t ext, int K_, int64_t t0, int tid)
@@ -48,33 +60,43 @@ struct Panel {
         x = (const char*)x_;
         K = K_;
         const int r = tid / LANES, e = (tid % LANES) * PV;
+        to = r * Slab::PITCH + e;
         if (KC) {
             row = t0 + r < ext;
             k0 = e;
+            over = 0;
             first = (t0 + r) * K + e;
             pitch = STEP;
             safe = (t0 + (row ? r : 0)) * K;
-            to = r * Slab::PITCH + e;
         } else {
             row = t0 + e < ext;
             k0 = r;
+            over = RAGGED && row && t0 + e + PV > ext ? (int)(t0 + e + PV - ext) : 0;
             first = (int64_t)r * ext + t0 + e;
             pitch = STEP * ext;
-            safe = t0 + (row ? e : 0);
-            to = r * Slab::PITCH + e;
+            safe = RAGGED ? 0 : t0 + (row ? e : 0);
         }
     }
     __device__ __forceinline__ bool here(int j) const { return row && k0 + j * STEP < K; }
+    // how many elements of vector j, which is here, lie beyond the end of its row
+    __device__ __forceinline__ int beyond(int j) const
+    {
+        if (!RAGGED) return 0;
+        if (!KC) return over;
+        const int b = k0 + j * STEP + PV - K;
+        return b > 0 ? b : 0;
+    }
     // Every vector is loaded, one near by in the place of one that is not there (with a choice whether to load, the compiler kept the registers
     // in scratch memory).
     __device__ __forceinline__ unsigned load(u32x4 (&v)[NV]) const
     {
         unsigned run = 0;
 #pragma unroll
-        for (int j = 0; j < NV; ++j) v[j] = *(const u32x4_any*)(x + (here(j) ? first + j * pitch : safe) * ESZ);
+        for (int j = 0; j < NV; ++j) v[j] = *(const u32x4_any*)(x + (here(j) ? first + j * pitch - beyond(j) : safe) * ESZ);
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
             const unsigned mask = here(j) ? ~0u : 0u;
+            if (RAGGED) v[j] = without_first<DT>(v[j], here(j) ? beyond(j) : 0);
             v[j] = (u32x4){v[j].x & mask, v[j].y & mask, v[j].z & mask, v[j].w & mask};
             run = vec_mag_max<DT>(v[j], run);
         }
@@ -103,7 +125,11 @@ struct Panel {
                     const auto piece = Piece<DT>::of(o, i);
                     uint8_t* at = slabs + c * Slab::SLAB + to + (KC ? (j % PER_CHUNK) * STEP : (j % PER_CHUNK) * STEP * Slab::PITCH);
                     if constexpr (DT == FP8_BF16) *LDS_PTR(u32x2, at) = piece; else *LDS_PTR(unsigned, at) = piece;
-                    if (turn == 0 && here(j)) *(typename Piece<DT>::type*)(q + first + j * pitch) = piece;
+                    if (turn == 0 && here(j)) {
+                        uint8_t* out = q + first + j * pitch;
+                        if (!RAGGED || beyond(j) == 0) *(typename Piece<DT>::type*)out = piece;
+                        else for (int n = 0; n < PV - beyond(j); ++n) out[n] = (uint8_t)(o[(PV / 4) * i + (n >> 2)] >> (8 * (n & 3)));
+                    }
                 }
                 if (j % PER_CHUNK == PER_CHUNK - 1) turn = turn == 0 ? sharers - 1 : turn - 1;
             }
@@ -111,14 +137,15 @@ struct Panel {
     }
 };
 
-// The largest magnitude of a tensor of n elements, n a multiple of per_vec, by one workgroup; valid in thread 0.
+// The largest magnitude of a tensor of n elements by one workgroup; valid in thread 0.
 template <int DT>
 __device__ __forceinline__ unsigned tensor_max(const void* x, size_t n)
 {
     const u32x4_any* xv = (const u32x4_any*)x;
     unsigned run = 0;
     for (size_t i = threadIdx.x; i < n / Elem<DT>::per_vec; i += kTileThreads) run = vec_mag_max<DT>(xv[i], run);
-    const unsigned r = block_max_u32<kTileThreads>(run_to_bits<DT>(run));
+    const size_t tail = n / Elem<DT>::per_vec * Elem<DT>::per_vec + threadIdx.x;
+    const unsigned r = block_max_u32<kTileThreads>(max(run_to_bits<DT>(run), tail < n ? scalar_mag<DT>(x, tail) : 0u));
     __syncthreads();                                      // (its staging cells are used again)
     return r;
 }
@@ -131,7 +158,7 @@ struct ScaledArgs {
     unsigned patience;
 };
 
-template <int DT, int FMT_A, int FMT_B, int ACC, bool A_KC, bool B_KC, int NV>
+template <int DT, int FMT_A, int FMT_B, int ACC, bool A_KC, bool B_KC, int NV, bool RAGGED>
 __global__ __launch_bounds__(kTileThreads) void scaled_gemm_small_kernel(ScaledArgs p, void* __restrict__ C, int M, int N, int K, int out_kind)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -148,7 +175,7 @@ __global__ __launch_bounds__(kTileThreads) void scaled_gemm_small_kernel(ScaledA
     unsigned* ws_a = p.ws;
     unsigned* ws_b = p.ws + FP8_AMAX_WORKSPACE_BYTES / 4;
 
-    Panel<DT, A_KC, NV> a; Panel<DT, B_KC, NV> b;
+    Panel<DT, A_KC, NV, RAGGED> a; Panel<DT, B_KC, NV, RAGGED> b;
     a.setup(p.a, M, K, m0, tid);
     b.setup(p.b, N, K, n0, tid);
     u32x4 va[NV], vb[NV];
@@ -269,10 +296,10 @@ __global__ __launch_bounds__(kTileThreads) void scaled_gemm_small_kernel(ScaledA
     }
 }
 
-template <int DT, int FA, int FB, int ACC, bool A_KC, bool B_KC, int NV>
+template <int DT, int FA, int FB, int ACC, bool A_KC, bool B_KC, int NV, bool RAGGED>
 int launch_typed(const GemmArgs& g, const ScaledArgs& p)
 {
-    auto kern = scaled_gemm_small_kernel<DT, FA, FB, ACC, A_KC, B_KC, NV>;
+    auto kern = scaled_gemm_small_kernel<DT, FA, FB, ACC, A_KC, B_KC, NV, RAGGED>;
     const int lds = scaled_gemm_small_lds(g);
     if (lds > 65536) {
         // more dynamic LDS than the default limit: raised once per device
@@ -291,18 +318,27 @@ int launch_typed(const GemmArgs& g, const ScaledArgs& p)
     return check_launch("scaled gemm (one launch)");
 }
 
-template <int DT, int FA, int FB, int ACC>
+template <int DT, int FA, int FB, int ACC, bool RAGGED>
 int launch_vecs(const GemmArgs& g, const ScaledArgs& p)
 {
     constexpr bool A_KC = (FP8MM_LAYOUT & 2) == 0, B_KC = (FP8MM_LAYOUT & 1) != 0;
     constexpr int MOST = kScaledSmallRow / 256;          // vectors per thread for the longest K
-    return g.K * Elem<DT>::size <= kScaledSmallRow / 2 ? launch_typed<DT, FA, FB, ACC, A_KC, B_KC, MOST / 2>(g, p) : launch_typed<DT, FA, FB, ACC, A_KC, B_KC, MOST>(g, p);
+    if constexpr (!RAGGED)
+        if (g.K * Elem<DT>::size > kScaledSmallRow / 2) return launch_typed<DT, FA, FB, ACC, A_KC, B_KC, MOST, false>(g, p);
+    return launch_typed<DT, FA, FB, ACC, A_KC, B_KC, MOST / 2, RAGGED>(g, p);   // (ragged rows: only so long, see scaled_gemm_small_takes)
+}
+
+template <int DT, int FA, int FB, int ACC>
+int launch_rows(const GemmArgs& g, const ScaledArgs& p)
+{
+    constexpr int PV = Elem<DT>::per_vec;
+    return (g.transA ? g.M : g.K) % PV || (g.transB ? g.K : g.N) % PV ? launch_vecs<DT, FA, FB, ACC, true>(g, p) : launch_vecs<DT, FA, FB, ACC, false>(g, p);
 }
 
 template <int DT, int FA, int FB>
 int launch_acc(const GemmArgs& g, const ScaledArgs& p)
 {
-    return g.acc == ACC_FP8 ? launch_vecs<DT, FA, FB, ACC_FP8>(g, p) : launch_vecs<DT, FA, FB, ACC_F16>(g, p);
+    return g.acc == ACC_FP8 ? launch_rows<DT, FA, FB, ACC_FP8>(g, p) : launch_rows<DT, FA, FB, ACC_F16>(g, p);
 }
 
 template <int DT>

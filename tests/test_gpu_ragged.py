@@ -55,7 +55,7 @@ def test_one_launch_casts_of_larger_tensors(M, N, K, dtype):
 
 
 # one tile; tiles and chunks with one vector more and less than a whole one; the smallest and the longest K; tiles that share their chunks unevenly
-SCALED = [(8, 8, 8), (32, 32, 128), (40, 24, 136), (256, 256, 256), (24, 1000, 120), (1000, 40, 264), (72, 200, 1024), (8, 64, 512), (33, 65, 520)]
+SCALED = [(8, 8, 8), (32, 32, 128), (40, 24, 136), (256, 256, 256), (24, 1000, 120), (1000, 40, 264), (72, 200, 1024), (8, 64, 512), (33, 65, 520), (9, 70, 127), (35, 97, 9), (257, 131, 131), (64, 33, 1021), (15, 1000, 250), (33, 65, 511)]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
