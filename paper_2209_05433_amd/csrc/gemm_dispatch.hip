@@ -431,9 +431,9 @@ bool overlap(const void* p, int64_t np, const void* q, int64_t nq) { return (con
 // rounded once per tile.  90 random products, amax + cast and product apart / together: 61 x 64 x 168 of fp32 9.9 / 6.7 us, 163 x 24 x 656 of bf16
 // 11.1 / 9.6, 693 x 304 x 408 (180 KB) 12.1 / 11.1, 120 x 1896 x 264 of fp32 (253 KB) 11.4 / 11.0, but 308 x 704 x 824 (362 KB) 12.6 / 13.3;
 // geometric mean 1.37.
-// Where rows in memory end inside a vector, K of up to 1024 bytes: 43 such products 1.35 in the geometric mean, least 1.11 (graph nodes 1.20, 0.98;
-// 34 x 260 x 87 of fp32 11.6 / 6.8, 41 x 575 x 424 of bf16 11.2 / 9.3), but of 7 with a longer K all but one lost as graph nodes
-// (78 x 54 x 579 of bf16 9.9 / 11.1, 674 x 261 x 274 of fp32 9.6 / 11.8; geometric mean 0.95).
+// Where rows in memory end inside a vector, K of up to 1024 bytes: 38 such products 1.34 in the geometric mean, least 1.11 (graph nodes 1.19, 0.98;
+// 34 x 260 x 87 of fp32 11.6 / 6.8, 41 x 575 x 424 of bf16 11.2 / 9.3), but of 6 with a longer K all but one lost as graph nodes
+// (78 x 54 x 579 of bf16 9.9 / 11.1, 674 x 261 x 274 of fp32 9.6 / 11.8; geometric mean 0.94).
 // Rows in memory of at least a vector; operands that share no memory with an output (a tile is written while others
 // are still being loaded).
 bool scaled_gemm_small_takes(const GemmArgs& g, const void* a, const void* b, int in_dtype, const GemmPlan& plan)
