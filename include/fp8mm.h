@@ -470,8 +470,9 @@ int fp8_gemm_form(const uint8_t* A, int transA, const uint8_t* B, int transB, co
  *                         then names the kernel that runs), 2 / 3 / 4 always, with tiles of 32 x 32 /
  *                         32 x 64 / 64 x 64 (of the last, the form the model prefers or FP8_KNOB_SMALL_64
  *                         names) (FP8MM_SMALL)
- *   FP8_KNOB_PATIENCE     the one-launch amax + cast (+ product) of fp8_scaled_gemm: 0 a workgroup waits 200 us (2 ms where more than 64 take part) for the other
- *                         workgroups' maxima before it computes the missing ones itself, 1 it does not wait
+ *   FP8_KNOB_PATIENCE     the launches of fp8_scaled_gemm whose workgroups wait for one another's maxima: 0 a workgroup waits
+ *                         10 us (amax + cast) or 50 us (the whole product in one launch) before it computes missing ones
+ *                         itself, sharing them with the others that have waited as long, 1 it does not wait
  *                         (FP8MM_PATIENCE)
  *   FP8_KNOB_TILE_192     the tiled kernel's tile of 256 x 192: 0 where the dispatcher's model of the run time
  *                         prefers it (and no other knob asks for a kernel, tile width or form), 1 never

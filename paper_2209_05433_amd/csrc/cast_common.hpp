@@ -23,7 +23,6 @@ constexpr unsigned kTicketGroup = 32;
 constexpr unsigned kTicketPartials = 32 * (1 + kAmaxBlocks / kTicketGroup);
 constexpr unsigned kCastDone = kTicketPartials + kAmaxBlocks;        // workgroups that have read all slots
 constexpr unsigned kCastSlots = kCastDone + 32;                      // ... and the slots (nothing else uses these words)
-constexpr unsigned kPatience = 20000;                                // how long a workgroup waits for them, ticks of the 100 MHz clock: 200 us
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 // Vectors at any address: the target's global loads and stores take them as one instruction.
@@ -109,6 +108,52 @@ __device__ __forceinline__ unsigned block_max_u32(unsigned v)
         for (int w = 1; w < THREADS / 64; ++w) v = v > part[w] ? v : part[w];
     }
     return v;   // valid in thread 0
+}
+
+// How long a workgroup waits for the slots: `ticks` of the 100 MHz clock, or not at all.
+inline unsigned patience(unsigned ticks) { return knob(FP8_KNOB_PATIENCE) ? 0u : ticks; }
+
+// For a workgroup that has waited long enough: the maxima of the parts whose slots were still empty.  absent: a bit in LDS for each of the
+// `count` parts, set where the maximum has not come.  The workgroups that get here share what is missing, so that together they read each part
+// about once: each starts at another part (`turn` is its number), leaves what it finds in that part's slot (the value is the same whoever finds it)
+// and looks at the slots again before the next.  At most `count` rounds.  slot(i): where the maximum of part i goes; part_max(i): the workgroup takes
+// it from the tensor (a barrier inside; valid in thread 0); take(i, m): the maximum of part i is m.  All threads call it.  The caller waits for the
+// stores of thread 0 before it counts the workgroup among the readers, or they could land behind the clearing of the slots.
+// (Each workgroup on its own took all missing parts: four streams of 2048 x 4096 x 2048 steps in bf16 took 2064 us a call, now 178; in
+// separate launches 160 - 180.)
+template <typename Slot, typename PartMax, typename Take>
+__device__ __forceinline__ void missing_maxima(unsigned long long* absent, unsigned count, unsigned turn, Slot slot, PartMax part_max, Take take)
+{
+    for (;;) {
+        if (threadIdx.x < 64) {
+            for (unsigned k = 0; 64 * k < count; ++k) {
+                const unsigned i = 64 * k + threadIdx.x;
+                bool missing = absent[k] >> threadIdx.x & 1;
+                if (missing) {
+                    const unsigned p = __hip_atomic_load(slot(i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (p >> 31) { take(i, p & 0x7fffffffu); missing = false; }
+                }
+                const unsigned long long left = __ballot(missing);
+                if (threadIdx.x == 0) absent[k] = left;
+            }
+        }
+        __syncthreads();
+        unsigned left = 0;
+        for (unsigned k = 0; 64 * k < count; ++k) left += (unsigned)__popcll(absent[k]);
+        if (left == 0) return;
+        unsigned skip = turn % left, k = 0;               // the part: this many missing ones from the first
+        while (skip >= (unsigned)__popcll(absent[k])) skip -= (unsigned)__popcll(absent[k++]);
+        unsigned long long bits = absent[k];
+        for (; skip > 0; --skip) bits &= bits - 1;
+        const unsigned i = 64 * k + (unsigned)__builtin_ctzll(bits);
+        const unsigned m = part_max(i);
+        if (threadIdx.x == 0) {
+            __hip_atomic_store(slot(i), m | 0x80000000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            take(i, m);
+            absent[k] &= ~(1ull << (i & 63));
+        }
+        __syncthreads();
+    }
 }
 
 __global__ void store_u32_kernel(unsigned* p, unsigned v) { *p = v; }

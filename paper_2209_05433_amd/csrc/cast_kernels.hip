@@ -281,18 +281,19 @@ __global__ __launch_bounds__(kThreads) void quantize_multi_kernel(MultiTensors m
 //   - workgroup b leaves its maximum in slot b and reads the others until all are there.  A slot holds
 //     the maximum with bit 31 set (maxima have it clear), so the value is its own flag: one store and
 //     one load per lane of a wave, agent-scope atomics both, no other data is exchanged through memory;
-//   - nobody has to be resident for anybody else to finish: a workgroup that has waited kPatience
-//     computes the maxima that are missing itself, from the tensor;
-//   - the last workgroup to have read the slots clears them for the next call.  A workgroup that gave up has
-//     not seen its own maximum arrive: it is waited for before the workgroup counts itself among the readers, or it
-//     could land behind the clearing.
+//   - nobody has to be resident for anybody else to finish: a workgroup that has waited kCastPatience
+//     sees to the maxima that are missing itself, with the others that wait (missing_maxima);
+//   - the last workgroup to have read the slots clears them for the next call.
 // Up to kMostChunks chunks of the size that the tensors need.  Measured, amax + cast of both operands, two launches -> one: 0.5 MB of fp32
 // 6.9 -> 3.8 us, 1 MB of bf16 7.4 -> 5.0; whole steps 630 x 1472 x 640 (2.6 MB) 17.2 -> 14.3, 387 x 960 x 1920 (5 MB) 18.4 -> 15.7, 1092 x 1856 x
-// 2624 (15 MB) 37.4 -> 35.7, 1638 x 704 x 6272 (28 MB) 50.4 -> 44.5; 90 steps from 2.5 to 39 MB all faster, by 2 to 25 %.  The longer the chunks
-// take, the longer a workgroup waits before it computes what is missing (another stream's tiles may hold compute units for a millisecond, and
-// the missing maxima of large tensors are many bytes).
+// 2624 (15 MB) 37.4 -> 35.7, 1638 x 704 x 6272 (28 MB) 50.4 -> 44.5; 90 steps from 2.5 to 39 MB all faster, by 2 to 25 %.
+// The 1024-thread forms take a compute unit each, so two streams' launches, or one beside a long product, do not all run at once.  10 us is about
+// twice what the maxima take on an empty chip; from 0.5 to 20 us a call took the same alone, on two and on four streams, with 70 us 5 - 25 % more on four.
+// Four streams of such steps, two launches / one: 2048 x 4096 x 2048 161 / 177 us a call, 2048 x 6144 x 2048 240 / 245, 1638 x 704 x 6272 169 / 167,
+// 2048 x 2000 x 2000 of fp32 134 / 136; two streams 89 / 80, 117 / 112, 90 / 78, 64 / 59; beside a product of a millisecond 440 / 427 (40 MB), 440 / 326 (17 MB).
 // ------------------------------------------------------------------------------------------
-constexpr unsigned kMostChunks = 256;                                // of a launch, and no more than compute units: all workgroups should be running
+constexpr unsigned kCastPatience = 1000;                             // 10 us
+constexpr unsigned kMostChunks = 256;                                // of a launch, and no more than compute units: on an empty chip all workgroups run at once
 static_assert((kCastSlots + kMostChunks) * sizeof(unsigned) <= FP8_AMAX_WORKSPACE_BYTES, "a slot per chunk");
 
 // The vectors of chunk b that the thread holds (zeros where there are none), and its tail element if it has one
@@ -325,12 +326,14 @@ __device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_
     const unsigned own = block_max_u32<THREADS>(load_chunk<DT, THREADS, VECS>(x, n, bid, bid == grid - 1, v));
     __shared__ unsigned largest;
     __shared__ unsigned long long absent[kMostChunks / 64];  // chunks whose maximum has not come
+    __shared__ bool complete;                                // there are none
     unsigned ticket = 0;                                     // of the workgroup among the readers of the slots (first lane)
     if (threadIdx.x < 64) {
         const unsigned l = threadIdx.x;
         if (l == 0 && grid > 1) __hip_atomic_store(&ws[kCastSlots + bid], own | 0x80000000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const unsigned long long began = wall_clock64();
         unsigned m = own;
+        unsigned long long any = 0;
         for (unsigned k = 0; 64 * k < grid; ++k) {
             const unsigned slot = 64 * k + l;
             unsigned p = slot < grid && grid > 1 ? 0u : 0x80000000u;
@@ -339,8 +342,9 @@ __device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_
                 if (wall_clock64() - began > patience) break;
             }
             m = max(m, p & 0x7fffffffu);
-            const unsigned long long here = __ballot(p >> 31);
-            if (l == 0) absent[k] = ~here;
+            const unsigned long long gone = ~__ballot(p >> 31);
+            any |= gone;
+            if (l == 0) absent[k] = gone;
         }
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         __builtin_amdgcn_s_waitcnt(0x0070);                  // vmcnt(0): the own maximum has been acknowledged
@@ -348,19 +352,26 @@ __device__ __forceinline__ void amax_cast_body(const void* __restrict__ x, size_
         m = wave_max_u32(m);
         if (l == 0) {
             largest = m;
+            complete = any == 0;
             // (nobody waits for the answer before the end: waited for here it was 0.8 us of every workgroup's time)
-            if (grid > 1) ticket = __hip_atomic_fetch_add(&ws[kCastDone], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (grid > 1 && any == 0) ticket = __hip_atomic_fetch_add(&ws[kCastDone], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     __syncthreads();
-    for (unsigned k = 0; 64 * k < grid; ++k)
-        for (unsigned long long left = absent[k]; left; left &= left - 1) {    // (never, unless the chip was busy for kPatience)
-            const unsigned b = 64 * k + (unsigned)__builtin_ctzll(left);
-            u32x4 other[VECS];
-            const unsigned m = block_max_u32<THREADS>(load_chunk<DT, THREADS, VECS>(x, n, b, b == grid - 1, other));
-            if (threadIdx.x == 0) largest = max(largest, m);
-            __syncthreads();
+    if (__builtin_expect(!complete, 0)) {                    // (never, unless other work held compute units for as long)
+        missing_maxima(absent, grid, bid, [&](unsigned i) { return &ws[kCastSlots + i]; },
+                       [&](unsigned i) {
+                           u32x4 other[VECS];
+                           return block_max_u32<THREADS>(load_chunk<DT, THREADS, VECS>(x, n, i, i == grid - 1, other));
+                       },
+                       [&](unsigned, unsigned m) { atomicMax(&largest, m); });
+        if (threadIdx.x == 0) {
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_s_waitcnt(0x0070);              // vmcnt(0): the maxima of others have been acknowledged
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            ticket = __hip_atomic_fetch_add(&ws[kCastDone], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+    }
     const float a = as_f32(largest), s = scale_rule(a, FMT);
     if (bid == 0 && threadIdx.x == 0) { *amax_out = a; *scale_out = s; }
     const size_t nvec = n / Elem<DT>::per_vec, first = bid * ((size_t)THREADS * VECS) + threadIdx.x;
@@ -663,10 +674,10 @@ int launch_amax_cast(int count, const void* const* x, const size_t* n, int in_dt
         total += (unsigned)chunks_of(i, chunk);
     }
     for (int i = count; i <= kMultiMax; ++i) m.first[i] = total;
-    const unsigned patience = knob(FP8_KNOB_PATIENCE) ? 0 : total <= 64 ? kPatience : 10 * kPatience;
+    const unsigned ticks = patience(kCastPatience);
     unsigned* ws = (unsigned*)workspace;
 #define FP8MM_LAUNCH_CAST(DT, THREADS, VECS) \
-    enqueue((amax_cast_kernel<DT, THREADS, VECS>), dim3(total), dim3(THREADS), 0, stream, m, amax_out, scale_out, ws, patience)
+    enqueue((amax_cast_kernel<DT, THREADS, VECS>), dim3(total), dim3(THREADS), 0, stream, m, amax_out, scale_out, ws, ticks)
     if (in_dtype == FP8_F32) {
         if (form == 0) FP8MM_LAUNCH_CAST(FP8_F32, 512, 8); else FP8MM_LAUNCH_CAST(FP8_F32, 1024, 8);
     } else {

@@ -6,7 +6,7 @@
 // columns of op(B) that it needs in their wide type, all of them at once, into registers:
 //   - the workgroups of the first tile column / row leave the maximum of their rows of A / columns of B in a slot of the workspace, everybody
 //     reads all slots (as in amax_cast_kernel: the value is its own flag, bit 31; nothing else is exchanged).  Nobody has to be resident for anybody
-//     else to finish: a workgroup that has waited kPatience takes both maxima from the tensors itself;
+//     else to finish: those that have waited kScaledPatience see to the missing maxima together (missing_maxima);
 //   - the factors known, the registers are rounded to FP8, into LDS where the fragments are read; of every row and column the
 //     workgroups that share it write one chunk of 128 to the FP8 outputs in turn;
 //   - products and sums are those of gemm_small_kernel in tiles of 32 x 32 (chunk c of 128 belongs to wave c % 8, the waves' sums are added in wave
@@ -25,6 +25,9 @@ namespace fp8mm {
 namespace {
 
 constexpr int kWaves = 8, kTileThreads = 64 * kWaves;
+// 50 us: beside a product whose tiles hold the compute units for 240 us, 256 x 256 x 256 took 106 us a call with 50 or 200 us of patience, 150 - 175 with 10 or less
+// (the units that a workgroup gives back go to the other product).
+constexpr unsigned kScaledPatience = 5000;
 static_assert((kCastSlots + 256) * sizeof(unsigned) <= FP8_AMAX_WORKSPACE_BYTES, "a slot per tile row or column");
 
 // The vector without its first k elements (0 <= k < per_vec), zeros behind the rest.
@@ -137,17 +140,32 @@ struct Panel {
     }
 };
 
-// The largest magnitude of a tensor of n elements by one workgroup; valid in thread 0.
-template <int DT>
-__device__ __forceinline__ unsigned tensor_max(const void* x, size_t n)
+// The largest magnitude of the 32 rows of op(A) / columns of op(B) from t0 on, by the workgroup; valid in thread 0.  (Small loops of their own: with
+// Panel's loads in their place the compiler kept addresses for these all through the kernel, and 256 x 256 x 256 took 0.2 us longer.)
+template <int DT, bool KC>
+__device__ __forceinline__ unsigned panel_max(const void* x, int64_t ext, int K, int64_t t0)
 {
-    const u32x4_any* xv = (const u32x4_any*)x;
-    unsigned run = 0;
-    for (size_t i = threadIdx.x; i < n / Elem<DT>::per_vec; i += kTileThreads) run = vec_mag_max<DT>(xv[i], run);
-    const size_t tail = n / Elem<DT>::per_vec * Elem<DT>::per_vec + threadIdx.x;
-    const unsigned r = block_max_u32<kTileThreads>(max(run_to_bits<DT>(run), tail < n ? scalar_mag<DT>(x, tail) : 0u));
-    __syncthreads();                                      // (its staging cells are used again)
-    return r;
+    constexpr int PV = Elem<DT>::per_vec, ESZ = Elem<DT>::size;
+    const int rows = ext - t0 < 32 ? (int)(ext - t0) : 32;
+    unsigned run = 0, r = 0;
+    if (KC) {                                             // one run of elements
+        const char* first = (const char*)x + t0 * K * ESZ;
+        const int n = rows * K, tail = n / PV * PV + threadIdx.x;
+#pragma unroll 1
+        for (int i = threadIdx.x; i < n / PV; i += kTileThreads) run = vec_mag_max<DT>(((const u32x4_any*)first)[i], run);
+        if (tail < n) r = scalar_mag<DT>(first, tail);
+    } else {                                              // a K index per thread
+#pragma unroll 1
+        for (int k = threadIdx.x; k < K; k += kTileThreads) {
+            const char* first = (const char*)x + (k * ext + t0) * ESZ;
+            int c = 0;
+#pragma unroll 1
+            for (; c + PV <= rows; c += PV) run = vec_mag_max<DT>(*(const u32x4_any*)(first + c * ESZ), run);
+#pragma unroll 1
+            for (; c < rows; ++c) r = max(r, scalar_mag<DT>(first, c));
+        }
+    }
+    return block_max_u32<kTileThreads>(max(r, run_to_bits<DT>(run)));
 }
 
 struct ScaledArgs {
@@ -182,7 +200,8 @@ __global__ __launch_bounds__(kTileThreads) void scaled_gemm_small_kernel(ScaledA
     const unsigned run_a = a.load(va), run_b = b.load(vb);
 
     __shared__ unsigned part_a[kWaves], part_b[kWaves], largest[2];
-    __shared__ bool all;
+    __shared__ unsigned long long absent[5];                 // panels whose maximum has not come, those of B behind those of A
+    __shared__ bool complete;                                // there are none
     unsigned ticket = 0;                                     // of the workgroup among those that have read all slots (first lane)
     {
         const unsigned ma = wave_max_u32(run_a), mb = wave_max_u32(run_b);
@@ -217,16 +236,26 @@ __global__ __launch_bounds__(kTileThreads) void scaled_gemm_small_kernel(ScaledA
         ma = wave_max_u32(ma); mb = wave_max_u32(mb);
         if (l == 0) {
             largest[0] = ma; largest[1] = mb;
-            all = everybody;
+            complete = everybody;
             // (nobody waits for the answer before the end: waited for here it was 0.8 us of every workgroup's time)
-            ticket = __hip_atomic_fetch_add(&ws_a[kCastDone], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (everybody) ticket = __hip_atomic_fetch_add(&ws_a[kCastDone], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     __syncthreads();
-    if (!all) {                                              // (never, unless the chip was busy for kPatience)
-        const unsigned ma = tensor_max<DT>(p.a, (size_t)M * K), mb = tensor_max<DT>(p.b, (size_t)K * N);
-        if (tid == 0) { largest[0] = ma; largest[1] = mb; }
+    if (__builtin_expect(!complete, 0)) {                                     // (never, unless other work held compute units for as long)
+        const unsigned panels = tiles_m + tiles_n;
+        if (tid == 0)
+            for (unsigned k = 0; 64 * k < panels; ++k) absent[k] = panels - 64 * k >= 64 ? ~0ull : (1ull << (panels - 64 * k)) - 1;
         __syncthreads();
+        missing_maxima(absent, panels, t, [&](unsigned i) { return p.ws + kCastSlots + (i < tiles_m ? i : FP8_AMAX_WORKSPACE_BYTES / 4 + i - tiles_m); },
+                       [&](unsigned i) { return i < tiles_m ? panel_max<DT, A_KC>(p.a, M, K, i * 32) : panel_max<DT, B_KC>(p.b, N, K, (i - tiles_m) * 32); },
+                       [&](unsigned i, unsigned m) { atomicMax(&largest[i < tiles_m ? 0 : 1], m); });
+        if (tid == 0) {
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_s_waitcnt(0x0070);              // vmcnt(0): the maxima of others have been acknowledged
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            ticket = __hip_atomic_fetch_add(&ws_a[kCastDone], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
     const float amax_a = as_f32(largest[0]), amax_b = as_f32(largest[1]);
     const float sa = scale_rule(amax_a, FMT_A), sb = scale_rule(amax_b, FMT_B);
@@ -356,7 +385,7 @@ int launch_formats(const GemmArgs& g, const ScaledArgs& p)
 
 int FP8MM_SCALED_NAME(FP8MM_LAYOUT)(const GemmArgs& g, const void* a, const void* b, int in_dtype, float* amax_out, float* scale_out, void* workspace)
 {
-    const ScaledArgs p{a, b, (uint8_t*)g.A, (uint8_t*)g.B, amax_out, scale_out, (unsigned*)workspace, knob(FP8_KNOB_PATIENCE) ? 0u : kPatience};
+    const ScaledArgs p{a, b, (uint8_t*)g.A, (uint8_t*)g.B, amax_out, scale_out, (unsigned*)workspace, patience(kScaledPatience)};
     return in_dtype == FP8_F32 ? launch_formats<FP8_F32>(g, p) : launch_formats<FP8_BF16>(g, p);
 }
 

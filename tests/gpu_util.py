@@ -1,4 +1,5 @@
 """Helpers shared by the GPU parity tests: host arrays <-> device buffers, mismatch reports."""
+import ctypes
 import os
 
 import numpy as np
@@ -39,6 +40,36 @@ class knob:
     def __exit__(self, *exc):
         import paper_2209_05433_amd as fp8
         fp8.fp8_set_knob(self.which, self.old)
+
+
+class _Dim3(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_uint) for n in "xyz"]
+
+
+class _KernelNode(ctypes.Structure):                      # hipKernelNodeParams
+    _fields_ = [("block", _Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", _Dim3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def launches(f):
+    """(workgroups, threads of each) of the kernels that f launches, in order: as a HIP graph records them, nothing runs."""
+    with open("/proc/self/maps") as maps:
+        path = next(line.split()[-1] for line in maps if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        f()
+    raw, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        node, kind, k = ctypes.c_void_p(node), ctypes.c_int(-1), _KernelNode()
+        assert hip.hipGraphNodeGetType(node, ctypes.byref(kind)) == 0 and kind.value == 0, "not a kernel node"
+        assert hip.hipGraphKernelNodeGetParams(node, ctypes.byref(k)) == 0
+        out.append((k.grid.x, k.block.x))
+    return out
 
 
 def cast_path(name):

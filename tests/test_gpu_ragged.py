@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import paper_2209_05433_amd as fp8
-from gpu_util import bf16_to_bits, knob
+from gpu_util import bf16_to_bits, knob, launches
 
 pytestmark = pytest.mark.gpu
 
@@ -33,25 +33,30 @@ def guards_hold(buf, n, off):
     return bool((b[:off] == 0xAA).all() and (b[off + n:] == 0xAA).all())
 
 
-# the forms of the one-launch amax and cast: chunks of 64 KB to their last (256 in all), of 128 KB, of 160 KB, one more element than those hold
-@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 1024, 7168, 1024), ("bf16", 1023, 7169, 1027), ("bf16", 4096, 4095, 2048), ("bf16", 4096, 5825, 2048), ("bf16", 4097, 5824, 2049),
-                                         ("f32", 1024, 3000, 2047), ("f32", 2048, 2048, 2048), ("f32", 2049, 2048, 2048)])
-def test_one_launch_casts_of_larger_tensors(M, N, K, dtype):
+# the forms of the one-launch amax and cast (workgroups, threads): chunks of 64 KB to their last (256 in all), of 128 KB, of 160 KB; one more
+# element than those hold, in three launches
+@pytest.mark.parametrize("dtype,M,N,K,form", [("bf16", 1024, 7168, 1024, (256, 512)), ("bf16", 1023, 7169, 1027, (130, 1024)), ("bf16", 4096, 4095, 2048, (256, 1024)),
+                                              ("bf16", 4096, 5825, 2048, (249, 1024)), ("bf16", 4097, 5824, 2049, (249, 1024)), ("f32", 1024, 3000, 2047, (252, 1024)),
+                                              ("f32", 2048, 2048, 2048, (256, 1024)), ("f32", 2049, 2048, 2048, None)])
+def test_one_launch_casts_of_larger_tensors(M, N, K, dtype, form):
+    """... each of them with and without waiting for the other workgroups."""
     test_one_call_equals_the_separate_calls_at_every_size_of_its_casts(M, N, K, dtype)
-    if M * K < 1 << 22:
-        a, b = (torch.randn(s, device="cuda").to(DTYPES[dtype]) for s in ((M, K), (K, N)))
-        outs = []
-        for patience in (0, 1):
-            ws = torch.zeros(2 * fp8.FP8_AMAX_WORKSPACE_BYTES // 4, dtype=torch.int32, device="cuda")
-            qa, qb, c = (torch.zeros(s, dtype=t, device="cuda") for s, t in ((a.shape, torch.uint8), (b.shape, torch.uint8), ((M, N), torch.float32)))
-            amax, scale = torch.zeros(2, device="cuda"), torch.zeros(2, device="cuda")
-            with knob(fp8.FP8_KNOB_PATIENCE, patience):
-                fp8.fp8_scaled_gemm(a, E4M3, False, b, E5M2, False, qa, qb, amax, scale, ws, c)
+    a, b = (torch.randn(s, device="cuda").to(DTYPES[dtype]) for s in ((M, K), (K, N)))
+    outs = []
+    for patience in (0, 1):
+        ws = torch.zeros(2 * fp8.FP8_AMAX_WORKSPACE_BYTES // 4, dtype=torch.int32, device="cuda")
+        qa, qb, c = (torch.zeros(s, dtype=t, device="cuda") for s, t in ((a.shape, torch.uint8), (b.shape, torch.uint8), ((M, N), torch.float32)))
+        amax, scale = torch.zeros(2, device="cuda"), torch.zeros(2, device="cuda")
+        call = lambda: fp8.fp8_scaled_gemm(a, E4M3, False, b, E5M2, False, qa, qb, amax, scale, ws, c)
+        with knob(fp8.FP8_KNOB_PATIENCE, patience):
+            call()
             torch.cuda.synchronize()
-            assert not bool(ws.any())
-            outs.append((qa, qb, c, amax, scale))
-        assert all(torch.equal(x, y) for x, y in zip(*outs))
-        assert outs[0][3].tolist() == [float(a.abs().max()), float(b.abs().max())]
+            assert form is None or not bool(ws.any())
+            ran = launches(call)
+            assert ran[0] == form and len(ran) == 2 if form else len(ran) == 3, ran
+        outs.append((qa, qb, c, amax, scale))
+    assert all(torch.equal(x, y) for x, y in zip(*outs))
+    assert outs[0][3].tolist() == [float(a.abs().max()), float(b.abs().max())]
 
 
 # one tile; tiles and chunks with one vector more and less than a whole one; the smallest and the longest K; tiles that share their chunks unevenly

@@ -2,6 +2,7 @@
 between calls (the amax cells are the callers', the error text is per thread), so every result must
 equal the one obtained alone."""
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -84,3 +85,66 @@ def test_two_streams_and_two_threads_give_the_single_stream_results(form):
                            ref_out.view(torch.int16 if out.dtype == torch.bfloat16 else torch.int32)), j
         for a, b in zip(mids, ref_mids):
             assert torch.equal(a, b), j
+
+
+# one launch for all of the step; amax + cast in one launch: chunks of 64 KB, of 128 KB (bf16, fp32), of 160 KB.  From the third on
+# four of them do not fit the chip together.
+@pytest.mark.parametrize("M,N,K,dt", [(256, 256, 256, torch.float32), (1024, 1024, 1024, torch.bfloat16), (2048, 4096, 2048, torch.bfloat16),
+                                      (2048, 2000, 2000, torch.float32), (2048, 6144, 2048, torch.bfloat16)])
+def test_steps_whose_launches_wait_within_themselves_on_four_streams(M, N, K, dt):
+    """fp8_scaled_gemm on four streams and threads at once, each with buffers and a workspace of its own: the results are
+    those of a call alone, and no launch waits long for workgroups that another one keeps from running (a call takes
+    no more than three times what the separate launches take in the same situation)."""
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    jobs, want = [], []
+    for _ in range(4):
+        a, b = (torch.randn(s, device="cuda", generator=g).to(dt) for s in ((M, K), (K, N)))
+        outs = [torch.zeros(s, dtype=t, device="cuda") for s, t in (((M, K), torch.uint8), ((K, N), torch.uint8), ((M, N), torch.float32), ((2,), torch.float32), ((2,), torch.float32))]
+        jobs.append((a, b, *outs, torch.zeros(2 * fp8.FP8_AMAX_WORKSPACE_BYTES // 4, dtype=torch.int32, device="cuda")))
+
+    def one(a, b, qa, qb, c, amax, scale, ws):
+        fp8.fp8_scaled_gemm(a, E4M3, False, b, E5M2, False, qa, qb, amax, scale, ws, c)
+
+    def apart(a, b, qa, qb, c, amax, scale, ws):
+        fp8.fp8_amax_scale_multi((a, b), (E4M3, E5M2), amax, scale, ws)
+        fp8.fp8_quantize_multi((a, b), (E4M3, E5M2), scale, (qa, qb))
+        fp8.fp8_gemm_ex(qa, E4M3, False, qb, E5M2, False, c, scale[0:1], scale[1:2])
+
+    for j in jobs:
+        apart(*j)
+        torch.cuda.synchronize()
+        want.append([t.clone() for t in j[2:7]])
+        for t in j[2:]:                                     # (the separate launches leave partial maxima in the workspace)
+            t.zero_()
+    streams, errors, calls = [torch.cuda.Stream() for _ in jobs], [], 20
+
+    def worker(i, f):
+        try:
+            with torch.cuda.stream(streams[i]):
+                for _ in range(calls):
+                    f(*jobs[i])
+        except Exception as e:                                  # pragma: no cover
+            errors.append(e)
+
+    def together(f):
+        """Seconds a call, the best of three times."""
+        best = 1e9
+        for _ in range(3):
+            torch.cuda.synchronize()
+            began = time.perf_counter()
+            threads = [threading.Thread(target=worker, args=(i, f)) for i in range(len(jobs))]
+            for t in threads:
+                t.start()
+            for t in threads:
+                t.join()
+            torch.cuda.synchronize()
+            best = min(best, (time.perf_counter() - began) / calls)
+        return best
+
+    took = together(one)
+    assert not errors, errors
+    for j, w in zip(jobs, want):
+        assert not bool(j[7].any())
+        for x, y in zip(j[2:7], w):
+            assert torch.equal(x.view(torch.uint8), y.view(torch.uint8))
+    assert took < 3.0 * together(apart) + 50e-6, "%.0f us a call" % (1e6 * took)
