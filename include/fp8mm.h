@@ -432,7 +432,8 @@ int fp8_gemm_plan(const uint8_t* A, int transA, const uint8_t* B, int transB, co
 /*
  * The form of the kernel that a call runs, small tiles, 256 x 192 tiles, output kind (fp8_out_t) and flags included
  * (diagnostics; as fp8_gemm_plan nothing is launched and no pointer dereferenced).  Answered for a per-tensor factor of A
- * and no output amax: a factor per row or an amax keeps a call out of FP8_FORM_TILED_128_PERSISTENT and changes nothing else.
+ * and no output amax: a factor per row or an amax keeps a call out of FP8_FORM_TILED_128_PERSISTENT, and an amax makes a 16-bit or FP8
+ * output off the tiled kernel take small tiles where an fp32 output does (the amax shows the sums in 32 bits); they change nothing else.
  * The last two are forms of the 64 x 64 tile for operands that are both contiguous along K: chunks of 128 in eight and in four waves.
  * A negative value is minus an fp8_status_t (bad arguments).
  */

@@ -141,10 +141,12 @@ double any_us(const GemmArgs& g, int width)
     return width == 256 ? 2.5 + rounds * (wide[kind] + 1.54 * S) : 2.8 + rounds * (narrow[kind] + 0.98 * S);
 }
 
-// Off the tiled kernel, fp32 outputs stay on small tiles up to the times below (of any-shape kernels that took longer: rounds of 256 x 256
-// tiles, and of 128 x 128 ones of which several shared a compute unit): the waves of a small tile share K, and its shorter chains
-// of sums are nearer to the 64-bit result (1.1e-7 against 1.5e-7 over K = 12288).  The rounding of a 16-bit or FP8 output hides that,
-// and those go by what the kernels take: 1718 x 3405 x 6200 147 -> 105 us, 1903 x 3712 x 1809 54 -> 39, 6435 x 2048 x 2181 129 -> 80.
+// Off the tiled kernel, calls that show their sums in 32 bits (fp32 outputs, an output maximum) stay on small tiles up to the times below (of
+// any-shape kernels that took longer: rounds of 256 x 256 tiles, and of 128 x 128 ones of which several shared a compute unit): the waves of
+// a small tile share K, and its shorter chains of sums are nearer to the 64-bit result (1.1e-7 against 1.5e-7 over K = 12288).  The line is a
+// matter of what such calls have always had, no bound on the error: no product's sums get longer chains than they did.  The rounding of a
+// 16-bit or FP8 output hides the difference, and without a maximum those go by what the
+// kernels take: 1718 x 3405 x 6200 147 -> 105 us, 1903 x 3712 x 1809 54 -> 39, 6435 x 2048 x 2181 129 -> 80.
 double small_line_us(const GemmArgs& g)
 {
     const double rounds = std::ceil(std::ceil(g.M / 256.0) * std::ceil(g.N / 256.0) / 256.0), K = (double)g.K, S = std::ceil(K / 64.0);
@@ -205,7 +207,7 @@ int choose_small(const GemmArgs& g, bool tiled, double& us_chosen, int pinned)
         }
     } else {
         other = small_line_us(g);
-        if (g.ep.out_kind != OUT_F32) other = std::min(other, 1.1 * std::min(any_us(g, 256), any_us(g, 128)));     // (1.1: their error where a round is short)
+        if (g.ep.out_kind != OUT_F32 && !g.ep.amax_out) other = std::min(other, 1.1 * std::min(any_us(g, 256), any_us(g, 128)));     // (1.1: their error where a round is short)
     }
     us_chosen = other;
     if (u64 > 32 && pinned == SMALL_NONE) return SMALL_NONE;

@@ -543,3 +543,20 @@ def test_seeded_sweep_over_plans_and_epilogues_exact_on_integers():
         assert bool((flat[:guard] == 5).all()) and bool((flat[guard + M * N:] == 5).all()), what + ": wrote outside D"
     for plan in (fp8.FP8_PLAN_TILED_256x256, fp8.FP8_PLAN_TILED_256x128, fp8.FP8_PLAN_TILED_MIXED, fp8.FP8_PLAN_MFMA_ANY):
         assert seen.get(plan, 0) >= 3, "the sweep did not reach plan %d often enough: %s" % (plan, seen)
+
+
+# off the tiled kernel (rows of op(B) that start anywhere, K odd): sizes at which an FP8 output alone leaves the small tiles
+@pytest.mark.parametrize("M,N,K,transB", [(1718, 3405, 6200, 0), (1903, 3712, 1809, 1)])
+def test_output_maximum_is_that_of_the_fp32_outputs(M, N, K, transB):
+    """amax_out is the largest of the sums before they are rounded to the output's type, and shows 24 bits of them: with an FP8
+    or bf16 output it is the largest of the outputs that an fp32 call gives, bit for bit (the same sums in the same order)."""
+    rng = np.random.default_rng(M)
+    A, B = random_codes(rng, (M, K), fp8.FP8_E4M3), random_codes(rng, (N, K) if transB else (K, N), fp8.FP8_E4M3)
+    dA, dB, one = to_dev(A), to_dev(B), torch.full((1,), 3.0, device="cuda")
+    c = torch.empty((M, N), device="cuda")
+    fp8.fp8_gemm_fused(dA, fp8.FP8_E4M3, 0, dB, fp8.FP8_E4M3, transB, c, fp8.FP8_OUT_F32, one, one, None, None)
+    for kind, dt in ((fp8.FP8_OUT_E4M3, torch.uint8), (fp8.FP8_OUT_E5M2, torch.uint8), (fp8.FP8_OUT_BF16, torch.bfloat16)):
+        d, amax = torch.empty((M, N), dtype=dt, device="cuda"), torch.zeros(1, device="cuda")
+        assert fp8.fp8_gemm_form(dA, 0, dB, transB, d, kind) in (fp8.FP8_FORM_ANY_256, fp8.FP8_FORM_ANY_128)
+        fp8.fp8_gemm_fused(dA, fp8.FP8_E4M3, 0, dB, fp8.FP8_E4M3, transB, d, kind, one, one, None, amax)
+        assert float(amax.item()) == float(c.abs().max().item()), kind
