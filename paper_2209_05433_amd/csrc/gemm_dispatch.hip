@@ -177,7 +177,7 @@ static_assert(SMALL_32x32 == 0 && SMALL_32x64 == 1 && SMALL_64x64 == 2 && SMALL_
 // random problems of the storage orders but one it takes 1.5 % (the tiled kernel's problems) and 2.5 % (the others) longer than the best of
 // all forms.  Operands whose rows start anywhere, both of them, cost a fifth more, and beyond 16 workgroups of 64 x 64 a compute unit, when
 // they no longer come out of the caches, again a third
-// (4096 x 5025 x 2048: 200 us, the any-shape kernel 176).  Rows of fewer than 16 bytes are fetched byte by byte
+// (4096 x 5025 x 2048: 200 us, the any-shape kernel 176).  Rows along K of fewer than 16 bytes are fetched byte by byte
 // (22 x 275 x 12: 13 us, the any-shape kernel 7.6).  The tiled kernel: rounds of 256 workgroups; where a single round leaves
 // half of the compute units idle, a tile has more of the caches to itself (512 x 4400 x 12096 in the FP8 mode: 65 us, 94 on
 // 64 x 64 tiles, and 93 by tile_times()).

@@ -56,12 +56,18 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(
     const int64_t p = x * share + (x < rem ? x : rem) + idx;
     const int64_t m0 = (p % tiles_m) * (32 * RM), n0 = (p / tiles_m) * (32 * RN);
 
-    // the factor that the thread will take the reciprocal of, loaded while the products run
+    // the factors that the thread will take the reciprocals of, loaded while the products run
     const float sA_host = ep.sA, sB_host = ep.sB;         // by value: a choice between two memory locations would cost scratch
     const bool uniform = !ep.a_per_row && !ep.b_per_col;
-    float factor = 1.0f;
-    if (ep.a_per_row && tid < 32 * RM) factor = ep.sA_dev[m0 + tid < M ? m0 + tid : M - 1];
-    if (ep.b_per_col && tid >= 32 * RM && tid < 32 * (RM + RN)) factor = ep.sB_dev[n0 + tid - 32 * RM < N ? n0 + tid - 32 * RM : N - 1];
+    constexpr int FACTORS = (RM + RN + 2 * NW - 1) / (2 * NW);            // per thread
+    float factor[FACTORS];
+#pragma unroll
+    for (int f = 0; f < FACTORS; ++f) {
+        const int t = tid + f * 64 * NW;
+        factor[f] = 1.0f;
+        if (ep.a_per_row && t < 32 * RM) factor[f] = ep.sA_dev[m0 + t < M ? m0 + t : M - 1];
+        if (ep.b_per_col && t >= 32 * RM && t < 32 * (RM + RN)) factor[f] = ep.sB_dev[n0 + t - 32 * RM < N ? n0 + t - 32 * RM : N - 1];
+    }
 
     OpA a; OpB b;
     a.setup(A, M, K, m0, l);
@@ -154,7 +160,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(
 #pragma unroll
     for (int i = 0; i < RN; ++i) {
         __syncthreads();                                  // the slabs, or the block before, are done with
-        if (i == 0 && !uniform && tid < 32 * (RM + RN)) *LDS_PTR(double, row_factors + tid) = 1.0 / factor;
+        if (i == 0 && !uniform) {
+#pragma unroll
+            for (int f = 0; f < FACTORS; ++f)
+                if (tid + f * 64 * NW < 32 * (RM + RN)) *LDS_PTR(double, row_factors + tid + f * 64 * NW) = 1.0 / factor[f];
+        }
         float* mine_red = (float*)(lds + w * PER_WAVE);
 #pragma unroll
         for (int j = 0; j < RM; ++j)
@@ -208,7 +218,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(
     if (ep.amax_out) {
         // One atomic per workgroup: its waves end together, and so do hundreds of workgroups (one per wave took
         // longer than the product: 256 x 1024 x 4096 20.8 us against 7.1 without the maximum).
-        unsigned* cells = (unsigned*)(lds + PER_WAVE + RED);            // behind the second wave's sums
+        unsigned* cells = (unsigned*)(lds + (NW > 1 ? PER_WAVE + RED : 0));   // behind the second wave's sums; a lone wave's have been read
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) amax_bits = max(amax_bits, (unsigned)__shfl_xor((int)amax_bits, d, 64));
         if (l == 0) *LDS_PTR(unsigned, cells + w) = amax_bits;
@@ -265,6 +275,13 @@ int launch_acc(const GemmArgs& g, int form)
     if constexpr (A_KC && B_KC) {
         if (form == SMALL_64x64_LINES8) return launch_form<FA, FB, ACC, A_KC, B_KC, 2, 2, 2, 8, 1>(g);
         if (form == SMALL_64x64_LINES4) return launch_form<FA, FB, ACC, A_KC, B_KC, 2, 2, 2, 4, 1>(g);
+    }
+    // K of one chunk, or two, and more tiles than run at once (four a compute unit): as many waves.  The others would have nothing to multiply, and their zeros
+    // would be added; the sums are the same bit for bit.  5 x 300000 x 64 stored K x M 34 -> 14 us, 1500000 x 10 x 100 186 -> 110; with fewer tiles the
+    // end of a tile is what takes long, and goes faster with four waves (2064 x 400 x 64: 5.4 us, 6.9 with one).
+    if (((g.M + 63) / 64) * ((g.N + 63) / 64) > 4 * 256) {
+        if (g.K <= SK) return launch_form<FA, FB, ACC, A_KC, B_KC, 2, 2, 1, 1, 1>(g);
+        if (g.K <= 2 * SK) return launch_form<FA, FB, ACC, A_KC, B_KC, 2, 2, 1, 2, 1>(g);
     }
     return launch_form<FA, FB, ACC, A_KC, B_KC, 2, 2, 1, 4, 1>(g);
 }

@@ -12,7 +12,7 @@ import paper_2209_05433_amd as fp8
 import test_gpu_gemm as gemm
 import test_gpu_gemm_fused as fused
 import test_gpu_ragged as ragged
-from gpu_util import knob
+from gpu_util import knob, launches
 
 pytestmark = pytest.mark.gpu
 
@@ -121,3 +121,80 @@ def test_tiled_kernel_over_any_k_of_operands_contiguous_along_m_and_n(knobs, K):
         torch.cuda.synchronize()
         assert np.array_equal(C.cpu().numpy().astype(np.float64), want)
         assert bool((buf[:64] == 9).all()) and bool((buf[64 + M * N:] == 9).all())
+
+
+# rows in memory of one byte to one less than a vector; K of one row, of rows that together are less than a vector, of several chunks and a remainder
+@pytest.mark.parametrize("K", [1, 3, 15, 65, 1000])
+@pytest.mark.parametrize("ext", [1, 2, 5, 8, 15])
+@pytest.mark.parametrize("tile", [2, 3, 4], ids=["32x32", "32x64", "64x64"])
+def test_small_tiles_of_rows_shorter_than_a_vector(tile, ext, K):
+    """Operands stored K x M / K x N with M, N < 16: sums of integers, exact; guard bytes of NaN before and behind the operands, which begin anywhere."""
+    rng = np.random.default_rng(100 * ext + K)
+    for M, N, transA, transB in ((ext, 40, 1, 1), (40, ext, 0, 0), (ext, ext, 1, 0), (ext, 100, 1, 0)):
+        A = fused.oracle.quantize(rng.integers(-3, 4, (M, K)).astype(np.float32), fused.E4M3, 1.0)
+        B = fused.oracle.quantize(rng.integers(-3, 4, (K, N)).astype(np.float32), fused.E5M2, 1.0)
+        want = fused.oracle.gemm_rows(A, fused.E4M3, B, fused.E5M2)[0]
+        dev = []
+        for x, off in ((A.T if transA else A, 33), (B.T if transB else B, 7)):
+            buf = torch.full((x.size + 128,), 0x7F, dtype=torch.uint8, device="cuda")
+            t = buf[off:off + x.size].view(x.shape)
+            t.copy_(torch.from_numpy(np.ascontiguousarray(x)))
+            dev.append(t)
+        C = torch.full((M, N), 9.0, device="cuda")
+        with pinned({fp8.FP8_KNOB_SMALL: tile}):
+            fp8.fp8_gemm_ex(dev[0], fused.E4M3, transA, dev[1], fused.E5M2, transB, C, 1.0, 1.0)
+        torch.cuda.synchronize()
+        assert np.array_equal(C.cpu().numpy().astype(np.float64), want), (M, N, transA, transB)
+
+
+def test_rows_shorter_than_a_vector_cost_no_more_than_a_vector():
+    """A product with 15 columns, stored K x 15, against the same one with 16: 30 us against 18 (byte by byte 112)."""
+    a = torch.randint(0, 100, (16384, 4096), dtype=torch.uint8, device="cuda")
+    took = []
+    for N in (15, 16):
+        b, c = torch.randint(0, 100, (4096, N), dtype=torch.uint8, device="cuda"), torch.empty((16384, N), device="cuda")
+        best, ev = 1e9, [torch.cuda.Event(True) for _ in range(2)]
+        for _ in range(5):
+            ev[0].record()
+            for _ in range(20):
+                fp8.fp8_gemm_ex(a, fused.E4M3, False, b, fused.E4M3, False, c, 1.0, 1.0)
+            ev[1].record()
+            torch.cuda.synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]) * 50.0)
+        took.append(best)
+    assert took[0] < 3.0 * took[1], took
+
+
+# one and two chunks of 64, a chunk and one element; rows of A that end inside a vector and rows shorter than one
+@pytest.mark.parametrize("K", [7, 64, 65, 128])
+@pytest.mark.parametrize("kind", [fp8.FP8_OUT_F32, fp8.FP8_OUT_BF16, fp8.FP8_OUT_E4M3])
+@pytest.mark.parametrize("M,transA,transB", [(70, 0, 1), (67, 1, 0), (5, 1, 1)])
+def test_64x64_tiles_with_as_many_waves_as_chunks(M, transA, transB, kind, K):
+    """Beyond 1024 tiles a workgroup has no waves that K leaves without a chunk: outputs and their maximum bit for bit those of
+    the same columns in products of fewer tiles, with factors per row and column."""
+    rng = np.random.default_rng(K)
+    N, part = 70003, 17500                                # 1094 columns of tiles or more, 274
+    A, B = gemm.random_codes(rng, (M, K), fused.E4M3), gemm.random_codes(rng, (N, K), fused.E5M2)
+    dA = torch.from_numpy(np.ascontiguousarray(A.T) if transA else A).cuda()
+    dB = torch.from_numpy(B).cuda()
+    sA, sB, sD = torch.rand(M, device="cuda") + 0.5, torch.rand(N, device="cuda") + 0.5, torch.full((1,), 1e-3, device="cuda")
+    out = {fp8.FP8_OUT_F32: torch.float32, fp8.FP8_OUT_BF16: torch.bfloat16}.get(kind, torch.uint8)
+
+    def run(b, factors):
+        d, amax = torch.zeros((M, b.shape[0]), dtype=out, device="cuda"), torch.zeros(1, device="cuda")
+        with pinned({fp8.FP8_KNOB_SMALL: 4, fp8.FP8_KNOB_SMALL_64: 1}):
+            ran = launches(lambda: fp8.fp8_gemm_fused(dA, fused.E4M3, transA, b if transB else b.t().contiguous(), fused.E5M2, transB, d, kind, sA, factors,
+                                                      sD if out == torch.uint8 else None, amax))[-1][1]
+            fp8.fp8_gemm_fused(dA, fused.E4M3, transA, b if transB else b.t().contiguous(), fused.E5M2, transB, d, kind, sA, factors,
+                               sD if out == torch.uint8 else None, amax)
+        return d, amax.item(), ran
+
+    whole, amax, threads = run(dB, sB)
+    assert threads == (64 if K <= 64 else 128)
+    most = 0.0
+    for at in range(0, N, part):
+        d, m, threads = run(dB[at:at + part].contiguous(), sB[at:at + part].contiguous())
+        assert threads == 256
+        most = max(most, m)
+        assert torch.equal(d.view(torch.uint8), whole[:, at:at + part].contiguous().view(torch.uint8)), at
+    assert most == amax
