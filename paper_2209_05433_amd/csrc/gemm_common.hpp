@@ -104,6 +104,7 @@ int FP8MM_SMALL_NAME(3)(const GemmArgs& g, int form);
 // whether it took the problem (scaled_gemm_small_takes); nothing has been launched where it did not.
 constexpr int kScaledSmallLds = 160 * 1024 - 1024;         // dynamic LDS at most (the kernel has a few static words)
 constexpr int kScaledSmallRow = 2048;                      // K elements of this many bytes at most
+constexpr int kScaledSmallBytes = 192 << 10;               // ... and in all tiles together of fewer than this
 int scaled_gemm_small_lds(const GemmArgs& g);
 int launch_scaled_gemm_small(const GemmArgs& g, const void* a, const void* b, int in_dtype, float* amax_out, float* scale_out, void* workspace, bool& took);
 #define FP8MM_SCALED_NAME_(l) launch_scaled_gemm_small_l##l

@@ -429,10 +429,11 @@ namespace {
 bool overlap(const void* p, int64_t np, const void* q, int64_t nq) { return (const char*)p < (const char*)q + nq && (const char*)q < (const char*)p + np; }
 
 // Which problems one launch takes: those of 32 x 32 tiles, at most one a compute unit (256: a workgroup waits for the maxima of others, which
-// should be running), rows and columns of up to 2048 bytes (a thread's registers) and, of all tiles together, 288 KB along K: they are read and
+// should be running), rows and columns of up to 2048 bytes (a thread's registers) and, of all tiles together, less than 192 KB along K: they are read and
 // rounded once per tile.  90 random products, amax + cast and product apart / together: 61 x 64 x 168 of fp32 9.9 / 6.7 us, 163 x 24 x 656 of bf16
-// 11.1 / 9.6, 693 x 304 x 408 (180 KB) 12.1 / 11.1, 120 x 1896 x 264 of fp32 (253 KB) 11.4 / 11.0, but 308 x 704 x 824 (362 KB) 12.6 / 13.3;
-// geometric mean 1.37.
+// 11.1 / 9.6, 693 x 304 x 408 (180 KB) 12.1 / 11.1, but 308 x 704 x 824 (362 KB) 12.6 / 13.3; geometric mean 1.37.  As graph nodes, which have no host time to
+// save, 187 products below the line gain 1.17 in the geometric mean (calls 1.31; least 0.91, 936 x 240 x 288 of bf16); of 11 from there to 288 KB nine lose (0.95 in the
+// mean; 512 x 480 x 512 of bf16 10.1 / 11.1, 616 x 248 x 816 11.6 / 12.6), while calls gain 1.06.
 // Where rows in memory end inside a vector, K of up to 1024 bytes: 38 such products 1.34 in the geometric mean, least 1.11 (graph nodes 1.19, 0.98;
 // 34 x 260 x 87 of fp32 11.6 / 6.8, 41 x 575 x 424 of bf16 11.2 / 9.3), but of 6 with a longer K all but one lost as graph nodes
 // (78 x 54 x 579 of bf16 9.9 / 11.1, 674 x 261 x 274 of fp32 9.6 / 11.8; geometric mean 0.94).
@@ -441,7 +442,7 @@ bool overlap(const void* p, int64_t np, const void* q, int64_t nq) { return (con
 bool scaled_gemm_small_takes(const GemmArgs& g, const void* a, const void* b, int in_dtype, const GemmPlan& plan)
 {
     const int64_t esz = in_dtype == FP8_F32 ? 4 : 2, pv = 16 / esz;
-    if (plan.small != SMALL_32x32 || cast_path() != kCastCvt || tile_count(g, 32) * g.K * esz > (288 << 10)) return false;
+    if (plan.small != SMALL_32x32 || cast_path() != kCastCvt || tile_count(g, 32) * g.K * esz >= kScaledSmallBytes) return false;
     const bool ragged = (g.transA ? g.M : g.K) % pv || (g.transB ? g.K : g.N) % pv;
     if (ragged && g.K * esz > kScaledSmallRow / 2) return false;
     if ((g.transA ? g.M : g.K) < pv || (g.transB ? g.K : g.N) < pv || scaled_gemm_small_lds(g) > kScaledSmallLds) return false;

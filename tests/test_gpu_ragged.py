@@ -59,8 +59,35 @@ def test_one_launch_casts_of_larger_tensors(M, N, K, dtype, form):
     assert outs[0][3].tolist() == [float(a.abs().max()), float(b.abs().max())]
 
 
-# one tile; tiles and chunks with one vector more and less than a whole one; the smallest and the longest K; tiles that share their chunks unevenly
-SCALED = [(8, 8, 8), (32, 32, 128), (40, 24, 136), (256, 256, 256), (24, 1000, 120), (1000, 40, 264), (72, 200, 1024), (8, 64, 512), (33, 65, 520), (9, 70, 127), (35, 97, 9), (257, 131, 131), (64, 33, 1021), (15, 1000, 250), (33, 65, 511)]
+# one tile; tiles and chunks with one vector more and less than a whole one; the smallest and the longest K, and those at which a thread gets more vectors;
+# tiles that share their chunks unevenly
+SCALED = [(8, 8, 8), (32, 32, 128), (40, 24, 136), (256, 256, 256), (24, 1000, 120), (1000, 40, 264), (72, 200, 1024), (8, 64, 512), (33, 65, 520), (9, 70, 127), (35, 97, 9), (257, 131, 131), (64, 33, 1021), (15, 1000, 250), (33, 65, 511),
+          (40, 96, 520), (72, 64, 768), (24, 56, 776)]
+# (the last below and the first at 192 KB along K in all tiles)
+LINE = [(568, 272, 600), (512, 480, 512), (512, 512, 192)]
+
+
+def one_launch(M, N, K, transA, transB, dtype, small):
+    """Whether fp8_scaled_gemm is one launch: small tiles of 32 x 32, whole rows of up to 2048 bytes, others of up to 1024, less
+    than 192 KB along K in all tiles."""
+    esz = 2 if dtype == "bf16" else 4
+    ragged = (M if transA else K) * esz % 16 or (K if transB else N) * esz % 16
+    tiles = -(-M // 32) * -(-N // 32)
+    return small and K * esz <= (1024 if ragged else 2048) and tiles <= 256 and tiles * K * esz < 192 << 10
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", SCALED + LINE)
+def test_which_scaled_products_are_one_launch(M, N, K, transA, transB, dtype):
+    a, b = (torch.ones(s, device="cuda", dtype=DTYPES[dtype]) for s in ((K, M) if transA else (M, K), (N, K) if transB else (K, N)))
+    qa, qb, c = (torch.zeros(s, dtype=t, device="cuda") for s, t in ((a.shape, torch.uint8), (b.shape, torch.uint8), ((M, N), torch.float32)))
+    amax, scale = torch.zeros(2, device="cuda"), torch.zeros(2, device="cuda")
+    ws = torch.zeros(2 * fp8.FP8_AMAX_WORKSPACE_BYTES // 4, dtype=torch.int32, device="cuda")
+    small = fp8.fp8_gemm_form(qa, transA, qb, transB, c, fp8.FP8_OUT_F32) == fp8.FP8_FORM_SMALL_32x32
+    assert small or (M, N, K) not in SCALED or K < 16          # (the tests of the one launch are tests of it)
+    ran = launches(lambda: fp8.fp8_scaled_gemm(a, E4M3, transA, b, E4M3, transB, qa, qb, amax, scale, ws, c))
+    assert len(ran) == (1 if one_launch(M, N, K, transA, transB, dtype, small) else 2), ran
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
