@@ -501,9 +501,10 @@ int fp8_scaled_gemm(const void* a, const void* b, int in_dtype, int transA, int 
         if ((uintptr_t)x[i] % (in_dtype == FP8_F32 ? 4 : 2)) return fail(FP8_ERR_INVALID_ARG, "%s: operand %d is not aligned to its element size", who, i);
     }
     bool took = false;
-    if (int e = launch_scaled_gemm_small(g, a, b, in_dtype, amax_out, scale_out, workspace, took); e || took) return e;
+    std::optional<GemmPlan> plan;
+    if (int e = launch_scaled_gemm_small(g, a, b, in_dtype, amax_out, scale_out, workspace, took, plan); e || took) return e;
     if (int e = launch_amax_cast(2, x, n, in_dtype, fmt, amax_out, scale_out, workspace, q, (hipStream_t)stream)) return e;
-    return launch_gemm(g);
+    return launch_gemm(g, plan ? &*plan : nullptr);
 }
 
 int fp8_gemm_plan(const uint8_t* A, int transA, const uint8_t* B, int transB, const void* C,

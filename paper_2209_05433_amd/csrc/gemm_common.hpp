@@ -6,6 +6,8 @@
 #include "fp8_decode.hpp"
 #include "fp8_encode.hpp"
 
+#include <optional>
+
 namespace fp8mm {
 
 // Output kinds.  The first two are fp8_dtype_t; the FP8 kinds write one byte per output.
@@ -69,7 +71,18 @@ FP8MM_DECLARE_TILED(3)
 
 constexpr int TILE_M = 256, TILE_N = 256, TILE_K = 64;
 
-int launch_gemm(const GemmArgs& g);
+// The dispatcher's decision for a problem with M, N, K > 0 (what launch_gemm acts on).
+enum { GEMM_GENERIC = 1, GEMM_TILED_256 = 2, GEMM_TILED_128 = 3, GEMM_MFMA_ANY = 4, GEMM_TILED_MIXED = 5 };
+// small: the form of the small-tile kernel that takes the problem instead (SMALL_*).
+// middle: 256 x 192 tiles instead of what `kernel` names; middle_cols > 0: for that many tile columns, 128-wide ones for the rest.
+// us: of a problem that the tiled kernel takes, what the model of run times gives for the small-tile form, or for the better of the
+// single tile widths.
+struct GemmPlan { int kernel; bool elementwise_stores; bool persistent; int wide_cols; int small; bool middle; int middle_cols; double us; };
+GemmPlan plan_gemm(const GemmArgs& g, bool whole = true);
+// The form (fp8_form_t) of the kernel that launch_gemm takes for it.
+int gemm_form(const GemmArgs& g);
+
+int launch_gemm(const GemmArgs& g, const GemmPlan* known = nullptr);      // known: plan_gemm(g, false), where the caller has it
 
 // The matrix-core kernel for any shape and alignment (gemm_mfma_any.hip): operands staged through
 // registers; tiles of 256 x 256 or 256 x 128.  Takes every problem with M, N, K > 0 whose tile count fits the grid; the few that its tiles
@@ -101,12 +114,13 @@ int FP8MM_SMALL_NAME(3)(const GemmArgs& g, int form);
 
 // The whole scaled product of a small problem in one launch (scaled_gemm_small.hip), one translation unit per pair of storage orders.  g: the
 // product of fp8_scaled_gemm (g.A, g.B: where the operands' FP8 bytes go; factors from scale_out).  launch_scaled_gemm_small sets `took` to
-// whether it took the problem (scaled_gemm_small_takes); nothing has been launched where it did not.
+// whether it took the problem (scaled_gemm_small_takes); nothing has been launched where it did not.  plan: of the product, if it was looked for.
 constexpr int kScaledSmallLds = 160 * 1024 - 1024;         // dynamic LDS at most (the kernel has a few static words)
 constexpr int kScaledSmallRow = 2048;                      // K elements of this many bytes at most
 constexpr int kScaledSmallBytes = 192 << 10;               // ... and in all tiles together of fewer than this
 int scaled_gemm_small_lds(const GemmArgs& g);
-int launch_scaled_gemm_small(const GemmArgs& g, const void* a, const void* b, int in_dtype, float* amax_out, float* scale_out, void* workspace, bool& took);
+int launch_scaled_gemm_small(const GemmArgs& g, const void* a, const void* b, int in_dtype, float* amax_out, float* scale_out, void* workspace, bool& took,
+                             std::optional<GemmPlan>& plan);
 #define FP8MM_SCALED_NAME_(l) launch_scaled_gemm_small_l##l
 #define FP8MM_SCALED_NAME(l) FP8MM_SCALED_NAME_(l)
 #define FP8MM_DECLARE_SCALED(l) \
@@ -129,17 +143,6 @@ int launch_gemm_splitk(const GemmArgs& g, const SplitPlan& sp, void* workspace);
 int fill_gemm_args(const char* who, GemmArgs& g, const uint8_t* A, int fmtA, int transA, const uint8_t* B, int fmtB,
                    int transB, void* C, int64_t M, int64_t N, int64_t K, int out_dtype, float sA, float sB,
                    const float* sA_dev, const float* sB_dev, int flags, void* stream);
-
-// The dispatcher's decision for a problem with M, N, K > 0 (what launch_gemm acts on).
-enum { GEMM_GENERIC = 1, GEMM_TILED_256 = 2, GEMM_TILED_128 = 3, GEMM_MFMA_ANY = 4, GEMM_TILED_MIXED = 5 };
-// small: the form of the small-tile kernel that takes the problem instead (SMALL_*).
-// middle: 256 x 192 tiles instead of what `kernel` names; middle_cols > 0: for that many tile columns, 128-wide ones for the rest.
-// us: of a problem that the tiled kernel takes, what the model of run times gives for the small-tile form, or for the better of the
-// single tile widths.
-struct GemmPlan { int kernel; bool elementwise_stores; bool persistent; int wide_cols; int small; bool middle; int middle_cols; double us; };
-GemmPlan plan_gemm(const GemmArgs& g, bool whole = true);
-// The form (fp8_form_t) of the kernel that launch_gemm takes for it.
-int gemm_form(const GemmArgs& g);
 
 // Microseconds for one tile of the tiled kernel, S stages of 64 along K, as one of several rounds of 256 that
 // run at a time (fitted to 4096 x 6144 over K = 512 .. 2048 and to 3294 x 11648 x 4288; within 5 %).  middle: the

@@ -439,10 +439,12 @@ bool overlap(const void* p, int64_t np, const void* q, int64_t nq) { return (con
 // (78 x 54 x 579 of bf16 9.9 / 11.1, 674 x 261 x 274 of fp32 9.6 / 11.8; geometric mean 0.94).
 // Rows in memory of at least a vector; operands that share no memory with an output (a tile is written while others
 // are still being loaded).
-bool scaled_gemm_small_takes(const GemmArgs& g, const void* a, const void* b, int in_dtype, const GemmPlan& plan)
+// (all but the tiles, which take longer to find out)
+bool scaled_gemm_small_takes(const GemmArgs& g, const void* a, const void* b, int in_dtype)
 {
     const int64_t esz = in_dtype == FP8_F32 ? 4 : 2, pv = 16 / esz;
-    if (plan.small != SMALL_32x32 || cast_path() != kCastCvt || tile_count(g, 32) * g.K * esz >= kScaledSmallBytes) return false;
+    if (g.K * esz > kScaledSmallRow || tile_count(g, 32) > std::min(256, compute_units())) return false;
+    if (cast_path() != kCastCvt || tile_count(g, 32) * g.K * esz >= kScaledSmallBytes) return false;
     const bool ragged = (g.transA ? g.M : g.K) % pv || (g.transB ? g.K : g.N) % pv;
     if (ragged && g.K * esz > kScaledSmallRow / 2) return false;
     if ((g.transA ? g.M : g.K) < pv || (g.transB ? g.K : g.N) < pv || scaled_gemm_small_lds(g) > kScaledSmallLds) return false;
@@ -454,17 +456,18 @@ bool scaled_gemm_small_takes(const GemmArgs& g, const void* a, const void* b, in
 
 }  // namespace
 
-int launch_scaled_gemm_small(const GemmArgs& g, const void* a, const void* b, int in_dtype, float* amax_out, float* scale_out, void* workspace, bool& took)
+int launch_scaled_gemm_small(const GemmArgs& g, const void* a, const void* b, int in_dtype, float* amax_out, float* scale_out, void* workspace, bool& took,
+                             std::optional<GemmPlan>& plan)
 {
     typedef int (*scaled_fn)(const GemmArgs&, const void*, const void*, int, float*, float*, void*);
     static const scaled_fn table[4] = {FP8MM_SCALED_NAME(0), FP8MM_SCALED_NAME(1), FP8MM_SCALED_NAME(2), FP8MM_SCALED_NAME(3)};
     took = false;
-    if (g.M == 0 || g.N == 0 || g.K == 0 || g.K * (in_dtype == FP8_F32 ? 4 : 2) > kScaledSmallRow || tile_count(g, 32) > std::min(256, compute_units())) return FP8_OK;
-    const GemmPlan plan = plan_gemm(g, false);
-    if (!scaled_gemm_small_takes(g, a, b, in_dtype, plan)) return FP8_OK;
+    if (g.M == 0 || g.N == 0 || g.K == 0 || !scaled_gemm_small_takes(g, a, b, in_dtype)) return FP8_OK;
+    plan = plan_gemm(g, false);
+    if (plan->small != SMALL_32x32) return FP8_OK;
     took = true;
     GemmArgs gs = g;
-    if (plan.kernel == GEMM_MFMA_ANY) gs.acc = ACC_F16;      // as launch_gemm
+    if (plan->kernel == GEMM_MFMA_ANY) gs.acc = ACC_F16;      // as launch_gemm
     return table[(g.transA ? 2 : 0) + (g.transB ? 1 : 0)](gs, a, b, in_dtype, amax_out, scale_out, workspace);
 }
 
@@ -493,7 +496,7 @@ int gemm_form(const GemmArgs& g)
     return plan.persistent ? FP8_FORM_TILED_128_PERSISTENT : FP8_FORM_TILED_128;
 }
 
-int launch_gemm(const GemmArgs& g)
+int launch_gemm(const GemmArgs& g, const GemmPlan* known)
 {
     const int64_t M = g.M, N = g.N, K = g.K;
     if (g.ep.amax_out) {                                     // written, not accumulated
@@ -506,7 +509,7 @@ int launch_gemm(const GemmArgs& g)
         enqueue(zero_fill_kernel, dim3(1024), dim3(256), 0, g.stream, (unsigned char*)g.C, nbytes);
         return check_launch("gemm (K = 0 fill)");
     }
-    const GemmPlan plan = plan_gemm(g, false);
+    const GemmPlan plan = known ? *known : plan_gemm(g, false);
     if (plan.small != SMALL_NONE) {
         GemmArgs gs = g;
         if (plan.kernel == GEMM_MFMA_ANY) gs.acc = ACC_F16;  // as the any-shape kernel computes these problems
