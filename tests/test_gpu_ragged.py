@@ -33,14 +33,33 @@ def guards_hold(buf, n, off):
     return bool((b[:off] == 0xAA).all() and (b[off + n:] == 0xAA).all())
 
 
+# the forms of the one-launch amax and cast: chunks of 64 KB to their last (256 in all), of 128 KB, of 160 KB, one more element than those hold
+@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 1024, 7168, 1024), ("bf16", 1023, 7169, 1027), ("bf16", 4096, 4095, 2048), ("bf16", 4096, 5825, 2048), ("bf16", 4097, 5824, 2049),
+                                         ("f32", 1024, 3000, 2047), ("f32", 2048, 2048, 2048), ("f32", 2049, 2048, 2048)])
+def test_one_launch_casts_of_larger_tensors(M, N, K, dtype):
+    test_one_call_equals_the_separate_calls_at_every_size_of_its_casts(M, N, K, dtype)
+    if M * K < 1 << 22:
+        a, b = (torch.randn(s, device="cuda").to(DTYPES[dtype]) for s in ((M, K), (K, N)))
+        outs = []
+        for patience in (0, 1):
+            ws = torch.zeros(2 * fp8.FP8_AMAX_WORKSPACE_BYTES // 4, dtype=torch.int32, device="cuda")
+            qa, qb, c = (torch.zeros(s, dtype=t, device="cuda") for s, t in ((a.shape, torch.uint8), (b.shape, torch.uint8), ((M, N), torch.float32)))
+            amax, scale = torch.zeros(2, device="cuda"), torch.zeros(2, device="cuda")
+            with knob(fp8.FP8_KNOB_PATIENCE, patience):
+                fp8.fp8_scaled_gemm(a, E4M3, False, b, E5M2, False, qa, qb, amax, scale, ws, c)
+            torch.cuda.synchronize()
+            assert not bool(ws.any())
+            outs.append((qa, qb, c, amax, scale))
+        assert all(torch.equal(x, y) for x, y in zip(*outs))
+        assert outs[0][3].tolist() == [float(a.abs().max()), float(b.abs().max())]
+
+
 # the forms of the one-launch amax and cast (workgroups, threads): chunks of 64 KB to their last (256 in all), of 128 KB, of 160 KB; one more
 # element than those hold, in three launches
 @pytest.mark.parametrize("dtype,M,N,K,form", [("bf16", 1024, 7168, 1024, (256, 512)), ("bf16", 1023, 7169, 1027, (130, 1024)), ("bf16", 4096, 4095, 2048, (256, 1024)),
                                               ("bf16", 4096, 5825, 2048, (249, 1024)), ("bf16", 4097, 5824, 2049, (249, 1024)), ("f32", 1024, 3000, 2047, (252, 1024)),
                                               ("f32", 2048, 2048, 2048, (256, 1024)), ("f32", 2049, 2048, 2048, None)])
-def test_one_launch_casts_of_larger_tensors(M, N, K, dtype, form):
-    """... each of them with and without waiting for the other workgroups."""
-    test_one_call_equals_the_separate_calls_at_every_size_of_its_casts(M, N, K, dtype)
+def test_forms_of_the_one_launch_casts_with_and_without_waiting(M, N, K, dtype, form):
     a, b = (torch.randn(s, device="cuda").to(DTYPES[dtype]) for s in ((M, K), (K, N)))
     outs = []
     for patience in (0, 1):
@@ -59,35 +78,8 @@ def test_one_launch_casts_of_larger_tensors(M, N, K, dtype, form):
     assert outs[0][3].tolist() == [float(a.abs().max()), float(b.abs().max())]
 
 
-# one tile; tiles and chunks with one vector more and less than a whole one; the smallest and the longest K, and those at which a thread gets more vectors;
-# tiles that share their chunks unevenly
-SCALED = [(8, 8, 8), (32, 32, 128), (40, 24, 136), (256, 256, 256), (24, 1000, 120), (1000, 40, 264), (72, 200, 1024), (8, 64, 512), (33, 65, 520), (9, 70, 127), (35, 97, 9), (257, 131, 131), (64, 33, 1021), (15, 1000, 250), (33, 65, 511),
-          (40, 96, 520), (72, 64, 768), (24, 56, 776)]
-# (the last below and the first at 192 KB along K in all tiles)
-LINE = [(568, 272, 600), (512, 480, 512), (512, 512, 192)]
-
-
-def one_launch(M, N, K, transA, transB, dtype, small):
-    """Whether fp8_scaled_gemm is one launch: small tiles of 32 x 32, whole rows of up to 2048 bytes, others of up to 1024, less
-    than 192 KB along K in all tiles."""
-    esz = 2 if dtype == "bf16" else 4
-    ragged = (M if transA else K) * esz % 16 or (K if transB else N) * esz % 16
-    tiles = -(-M // 32) * -(-N // 32)
-    return small and K * esz <= (1024 if ragged else 2048) and tiles <= 256 and tiles * K * esz < 192 << 10
-
-
-@pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
-@pytest.mark.parametrize("M,N,K", SCALED + LINE)
-def test_which_scaled_products_are_one_launch(M, N, K, transA, transB, dtype):
-    a, b = (torch.ones(s, device="cuda", dtype=DTYPES[dtype]) for s in ((K, M) if transA else (M, K), (N, K) if transB else (K, N)))
-    qa, qb, c = (torch.zeros(s, dtype=t, device="cuda") for s, t in ((a.shape, torch.uint8), (b.shape, torch.uint8), ((M, N), torch.float32)))
-    amax, scale = torch.zeros(2, device="cuda"), torch.zeros(2, device="cuda")
-    ws = torch.zeros(2 * fp8.FP8_AMAX_WORKSPACE_BYTES // 4, dtype=torch.int32, device="cuda")
-    small = fp8.fp8_gemm_form(qa, transA, qb, transB, c, fp8.FP8_OUT_F32) == fp8.FP8_FORM_SMALL_32x32
-    assert small or (M, N, K) not in SCALED or K < 16          # (the tests of the one launch are tests of it)
-    ran = launches(lambda: fp8.fp8_scaled_gemm(a, E4M3, transA, b, E4M3, transB, qa, qb, amax, scale, ws, c))
-    assert len(ran) == (1 if one_launch(M, N, K, transA, transB, dtype, small) else 2), ran
+# one tile; tiles and chunks with one vector more and less than a whole one; the smallest and the longest K; tiles that share their chunks unevenly
+SCALED = [(8, 8, 8), (32, 32, 128), (40, 24, 136), (256, 256, 256), (24, 1000, 120), (1000, 40, 264), (72, 200, 1024), (8, 64, 512), (33, 65, 520), (9, 70, 127), (35, 97, 9), (257, 131, 131), (64, 33, 1021), (15, 1000, 250), (33, 65, 511)]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
@@ -133,6 +125,44 @@ def test_scaled_product_in_one_launch_equals_the_separate_calls(M, N, K, transA,
         fp8.fp8_scaled_gemm(a, E5M2, transA, b, E4M3, transB, qa, qb, amax, scale, ws, c)
         fp8.fp8_scaled_gemm(a, E5M2, transA, b, E4M3, transB, qa, qb, amax, scale, ws, c_in_a)
         assert torch.equal(c.contiguous().view(torch.uint8), c_in_a.contiguous().view(torch.uint8))
+
+
+# bf16: rows at which a thread gets six vectors, and eight; fp32: rows too long for the one launch
+MORE_SCALED = [(40, 96, 520), (72, 64, 768), (24, 56, 776)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", MORE_SCALED)
+def test_scaled_product_in_one_launch_of_longer_rows(M, N, K, transA, transB, dtype):
+    test_scaled_product_in_one_launch_equals_the_separate_calls(M, N, K, transA, transB, dtype)
+
+
+# (the last below and the first at 192 KB along K in all tiles)
+LINE = [(568, 272, 600), (512, 480, 512), (512, 512, 192)]
+
+
+def one_launch(M, N, K, transA, transB, dtype, small):
+    """Whether fp8_scaled_gemm is one launch: small tiles of 32 x 32, whole rows of up to 2048 bytes, others of up to 1024, less
+    than 192 KB along K in all tiles."""
+    esz = 2 if dtype == "bf16" else 4
+    ragged = (M if transA else K) * esz % 16 or (K if transB else N) * esz % 16
+    tiles = -(-M // 32) * -(-N // 32)
+    return small and K * esz <= (1024 if ragged else 2048) and tiles <= 256 and tiles * K * esz < 192 << 10
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", SCALED + MORE_SCALED + LINE)
+def test_which_scaled_products_are_one_launch(M, N, K, transA, transB, dtype):
+    a, b = (torch.ones(s, device="cuda", dtype=DTYPES[dtype]) for s in ((K, M) if transA else (M, K), (N, K) if transB else (K, N)))
+    qa, qb, c = (torch.zeros(s, dtype=t, device="cuda") for s, t in ((a.shape, torch.uint8), (b.shape, torch.uint8), ((M, N), torch.float32)))
+    amax, scale = torch.zeros(2, device="cuda"), torch.zeros(2, device="cuda")
+    ws = torch.zeros(2 * fp8.FP8_AMAX_WORKSPACE_BYTES // 4, dtype=torch.int32, device="cuda")
+    small = fp8.fp8_gemm_form(qa, transA, qb, transB, c, fp8.FP8_OUT_F32) == fp8.FP8_FORM_SMALL_32x32
+    assert small or (M, N, K) in LINE or K < 16          # (the tests of the one launch are tests of it)
+    ran = launches(lambda: fp8.fp8_scaled_gemm(a, E4M3, transA, b, E4M3, transB, qa, qb, amax, scale, ws, c))
+    assert len(ran) == (1 if one_launch(M, N, K, transA, transB, dtype, small) else 2), ran
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
