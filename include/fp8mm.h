@@ -376,7 +376,7 @@ int fp8_gemm_fused(const uint8_t* A, int fmtA, int transA, const uint8_t* B, int
  * single-precision accumulation, and the factors taken out once per output.  It does on `stream` what
  * fp8_amax_scale_multi, fp8_quantize_multi and fp8_gemm_ex (factors read from scale_out) do in that
  * order, and every result is theirs bit for bit; what it saves is the host time between short dependent
- * launches, for operands of up to about 40 MB together one of the launches (amax and cast read them once), and for a few
+ * launches, for operands of up to about 40 MB (bf16) or 32 MB (fp32) together one of the launches (amax and cast read them once), and for a few
  * small tiles two (one launch does it all: 256 x 256 x 256 from fp32 18 us in separate calls, 7.2 in this one).
  *   a, b        the operands in the wide type in_dtype, stored as fp8_gemm_ex stores A and B
  *               (a: M x K, or K x M if transA; b: K x N, or N x K if transB); alignment as for fp8_amax

@@ -20,11 +20,12 @@
 //   - tiles that lie inside C walk the stages inside K with one register of offsets per operand and no tests (526 instructions
 //     for 128 matrix instructions, no register spilled or moved); at the edges a piece that is not wholly there comes
 //     from the zero chunk or is the row's last 16 bytes, shifted when it is written.
-// Bound by the matrix cores and the loads' latency: forced onto a product that the tiled kernel takes, it needs 1.06 - 1.09 of its time
-// (8192 x 50304 x 6144).  The forms before it widened on the way into LDS, which had to carry twice the bytes, and the smaller of them
+// Over a long K bound by the matrix cores at the clock they hold (8192 x 50257 x 12288: busy 73 % of the cycles, at 1.74 GHz; 9 % of the waves' time at
+// s_waitcnt, LDS busy 19 %), over a short one by the starts and ends of the tiles (4096 x 50257 x 2048: 53 % at 1.97 GHz; a tile's ends are 8.5 of 58 us, and the last of
+// 13 rounds has 80 tiles).  Forced onto a product that the tiled kernel takes, it needs 1.06 - 1.09 of its time (8192 x 50304 x 6144).  The forms before it widened on the way into LDS, which had to carry twice the bytes, and the smaller of them
 // stored its outputs one by one.  256 x 256 tile: 4096 x 50257 x 2048 882 -> 765 us, 8192 x 50257 x 12288 9083 -> 7849,
 // 8192 x 12288 x 4095 (both contiguous along K) 884 -> 694, 5000 x 5001 x 5001 with A stored K x M 624 -> 274;
-// 256 x 128: 4096 x 4096 x 33 46 -> 21, 4673 x 4573 x 1057 147 -> 72, 1307 x 12288 x 4405 to E4M3 256 -> 223.
+// 256 x 128: 4673 x 4573 x 1057 147 -> 72, 1307 x 12288 x 4405 to E4M3 256 -> 223.
 //
 // This file is compiled once per pair of storage orders: -DFP8MM_LAYOUT.
 #include "gemm_epilogue.hpp"

@@ -5,9 +5,8 @@ boundaries, unaligned pointers) against the CPU oracle, through fp8_gemm_ex / fp
 Acceptance as for fp8_gemm: |C - C_ref| <= 2^-20 * sum_k |a b| / (sA sB) + ulp_out(C_ref) / 2, and
 equality where the sums are exact.  FP8_KNOB_GEMM_KERNEL = 2 forces the kernel onto problems the
 tiled kernel would take, = 1 forces the plain FMA kernel (an independent second implementation).
-The kernel has two forms (128 x 128 tiles, several workgroups per compute unit; 256 x 256 tiles,
-pipelined by hand, for problems of many tiles); FP8_KNOB_TILE_N = 128 / 256 forces one, and the
-tests run under both."""
+The kernel has two forms (tiles of 256 x 128 and of 256 x 256); FP8_KNOB_TILE_N = 128 / 256 forces
+one, and the tests run under both."""
 
 import numpy as np
 import pytest
