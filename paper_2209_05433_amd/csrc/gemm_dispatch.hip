@@ -432,18 +432,25 @@ bool overlap(const void* p, int64_t np, const void* q, int64_t nq) { return (con
 // should be running), rows and columns of up to 2048 bytes (a thread's registers) and, of all tiles together, less than 192 KB along K: they are read and
 // rounded once per tile.  90 random products, amax + cast and product apart / together: 61 x 64 x 168 of fp32 9.9 / 6.7 us, 163 x 24 x 656 of bf16
 // 11.1 / 9.6, 693 x 304 x 408 (180 KB) 12.1 / 11.1, but 308 x 704 x 824 (362 KB) 12.6 / 13.3; geometric mean 1.37.  As graph nodes, which have no host time to
-// save, 187 products below the line gain 1.17 in the geometric mean (calls 1.31; least 0.91, 936 x 240 x 288 of bf16); of 11 from there to 288 KB nine lose (0.95 in the
+// save, 187 products below the line gain 1.17 in the geometric mean (calls 1.31); of 11 from there to 288 KB nine lose (0.95 in the
 // mean; 512 x 480 x 512 of bf16 10.1 / 11.1, 616 x 248 x 816 11.6 / 12.6), while calls gain 1.06.
 // Where rows in memory end inside a vector, K of up to 1024 bytes: 38 such products 1.34 in the geometric mean, least 1.11 (graph nodes 1.19, 0.98;
 // 34 x 260 x 87 of fp32 11.6 / 6.8, 41 x 575 x 424 of bf16 11.2 / 9.3), but of 6 with a longer K all but one lost as graph nodes
 // (78 x 54 x 579 of bf16 9.9 / 11.1, 674 x 261 x 274 of fp32 9.6 / 11.8; geometric mean 0.94).
+// And not many tiles: every workgroup reads all maxima, and the more of them there are the longer the exchange takes (20 tiles of a short K 6.5 us, 90 7.0, 140 8, 240
+// 9 - 10), while the launches apart grow by less.  68 products of 100 to 256 tiles, apart / together: beyond 200 tiles all 10 lost as graph nodes and 5 as calls (736 x 344 x 16 of fp32
+// 7.9 / 9.3 and 8.5 / 9.4 us; 0.93 and 0.99 in the mean), up to there 29 gain 1.06 and 1.13, no call lost.  An operand contiguous along K whose FP8 rows begin anywhere costs the
+// product apart 1 - 3 us: 235 tiles there (20 gain 1.25, none lost; 247 tiles 9.2 / 9.9).  K of up to 16 that neither operand is contiguous along is
+// the fastest apart: 64 tiles (20 tiles 7.7 / 6.5; 6 from 110 on all lost, 864 x 288 x 8 7.7 / 9.8).
 // Rows in memory of at least a vector; operands that share no memory with an output (a tile is written while others
 // are still being loaded).
 // (all but the tiles, which take longer to find out)
 bool scaled_gemm_small_takes(const GemmArgs& g, const void* a, const void* b, int in_dtype)
 {
     const int64_t esz = in_dtype == FP8_F32 ? 4 : 2, pv = 16 / esz;
-    if (g.K * esz > kScaledSmallRow || tile_count(g, 32) > std::min(256, compute_units())) return false;
+    const bool along_k = !g.transA || g.transB;
+    const int most = along_k && g.K % 16 != 0 ? 235 : !along_k && g.K <= 16 ? 64 : 200;
+    if (g.K * esz > kScaledSmallRow || tile_count(g, 32) > std::min(most, compute_units())) return false;
     if (cast_path() != kCastCvt || tile_count(g, 32) * g.K * esz >= kScaledSmallBytes) return false;
     const bool ragged = (g.transA ? g.M : g.K) % pv || (g.transB ? g.K : g.N) % pv;
     if (ragged && g.K * esz > kScaledSmallRow / 2) return false;

@@ -138,17 +138,20 @@ def test_scaled_product_in_one_launch_of_longer_rows(M, N, K, transA, transB, dt
     test_scaled_product_in_one_launch_equals_the_separate_calls(M, N, K, transA, transB, dtype)
 
 
-# (the last below and the first at 192 KB along K in all tiles)
-LINE = [(568, 272, 600), (512, 480, 512), (512, 512, 192)]
+# the last below and the first at 192 KB along K in all tiles; 200 tiles and 204; 230 and 240 where an operand is contiguous along a K that is no multiple of 16;
+# 64 and 72 where K is short and neither is
+LINE = [(568, 272, 600), (512, 480, 512), (512, 512, 192), (800, 256, 64), (544, 384, 64), (736, 320, 24), (960, 256, 24), (256, 256, 16), (288, 256, 16)]
 
 
 def one_launch(M, N, K, transA, transB, dtype, small):
     """Whether fp8_scaled_gemm is one launch: small tiles of 32 x 32, whole rows of up to 2048 bytes, others of up to 1024, less
-    than 192 KB along K in all tiles."""
+    than 192 KB along K in all tiles, and no more tiles than the launches apart take longer for."""
     esz = 2 if dtype == "bf16" else 4
     ragged = (M if transA else K) * esz % 16 or (K if transB else N) * esz % 16
     tiles = -(-M // 32) * -(-N // 32)
-    return small and K * esz <= (1024 if ragged else 2048) and tiles <= 256 and tiles * K * esz < 192 << 10
+    along_k = not transA or transB
+    most = 235 if along_k and K % 16 else 64 if not along_k and K <= 16 else 200
+    return small and K * esz <= (1024 if ragged else 2048) and tiles <= most and tiles * K * esz < 192 << 10
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
